@@ -230,5 +230,5 @@ def tolerance(case):
     """Four times what a float64 evaluation of the same step differs by, at worst over these ranges.  fp32: dot products
     and sums are carried in fp64, the rounding of stored exponentials, coefficients and outputs is left (9e-8, 4e-7).
     bf16: the exponentials are rounded to 8 bits as operands of the gradient contractions, which averages out over the
-    batch (3e-4 and 3e-3 at 150 pairs, 1e-5 at 10,000)."""
-    return {"rel": 1e-6, "max": 4e-6} if case["dtype"] == "f32" else {"rel": 1.2e-3, "max": 1.2e-2}
+    batch (5e-4 and 8e-3 at 100 pairs, 1e-5 at 10,000)."""
+    return {"rel": 1e-6, "max": 4e-6} if case["dtype"] == "f32" else {"rel": 2e-3, "max": 3.2e-2}
