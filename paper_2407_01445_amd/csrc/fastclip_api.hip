@@ -108,7 +108,45 @@ TauUpd make_tau_upd(const fastclip_tau_update& upd) {
   return u;
 }
 
-void make_layout(const fastclip_config& cfg, Layout* L) {
+// fp32 path: tile sizes, partial sums and the split of the gradients' depth.  lean: nothing in the workspace that only
+// speed asks for (see make_layout).
+static void plan_f32(const fastclip_config& cfg, bool lean, Layout* L) {
+  // 64 x 64 strip tiles once there is one per compute unit; below that 32 x 32, four times as many
+  const int64_t strips = L->square ? 1 : 2;
+  L->strip_tile = strips * ((cfg.b + 63) / 64) * ((cfg.B + 63) / 64) >= 256 ? 64 : 32;
+  // Partial sums: one per contrast tile, at most 64 (the state phase reads them all); a whole local batch also sums down
+  // its columns, one partial per anchor tile, and keeps one per tile on either side.
+  const int64_t nCT = (cfg.B + L->strip_tile - 1) / L->strip_tile;
+  int64_t per = L->square ? 1 : (nCT + 63) / 64;
+  if (lean) per = nCT;
+  L->per_part = (int)per;
+  L->nparts = (int)((nCT + per - 1) / per);
+  // Gradients: tile size and splits by the time of the fullest compute unit in cycles of a SIMD.  A stage is 1024 cycles of
+  // matrix products on 32 x 32 tiles (64 deep) and 2048 on 64 x 64 tiles (32 deep), 1.3 times that as measured; a tile's
+  // start and end cost 3000, the meeting of several splits 4000 + 500 per split.  Measured: 128 anchors of 1024 pairs of
+  // width 512: 38.4 us per step with one split of 32 x 32 tiles, 33.2 with two (chosen), 34.4 with four; 1024 pairs: 94 us on
+  // 32 x 32 tiles, 88 on 64 x 64 (chosen).
+  double best_cost = 0.0;
+  for (int T = 32; T <= 64; T += 32) {
+    const int64_t kd = T == 32 ? 64 : 32;
+    const int64_t stages = (cfg.B + kd - 1) / kd + (L->square ? 0 : (cfg.b + kd - 1) / kd);
+    const int64_t tiles = 2 * ((cfg.b + T - 1) / T) * ((cfg.d + T - 1) / T);
+    for (int64_t ns = 1; ns <= 16 && ns <= stages; ++ns) {
+      const int64_t slice = (stages + ns - 1) / ns;
+      if ((stages + slice - 1) / slice != ns) continue;
+      if (ns > 1 && (lean || tiles * ns > 2048)) break;
+      const double rounds = (double)((tiles * ns + 255) / 256);
+      const double cost = rounds * ((double)slice * (T == 32 ? 1330.0 : 2600.0) + 3000.0) +
+                          (ns > 1 ? 4000.0 + 500.0 * (double)ns : 0.0);
+      if (best_cost == 0.0 || cost < best_cost) {
+        best_cost = cost;
+        L->grad_tile = T; L->nsplit = (int)ns; L->kslice = slice;
+      }
+    }
+  }
+}
+
+static void make_layout(const fastclip_config& cfg, bool lean, Layout* L) {
   memset(L, 0, sizeof(*L));
   L->B = cfg.B; L->b = cfg.b; L->off = cfg.off; L->d = cfg.d; L->N = cfg.N;
   L->bf16 = cfg.emb_dtype == FASTCLIP_BF16;
@@ -118,7 +156,7 @@ void make_layout(const fastclip_config& cfg, Layout* L) {
   // forming the similarity matrix once halves the MFMA work of the strip phase but doubles the epilogue of every
   // tile: it pays once the tiles outnumber the compute units (below that one tile's latency is the phase's time)
   const int64_t bt = (cfg.B + kTileContrasts - 1) / kTileContrasts;
-  L->square = L->bf16 && cfg.b == cfg.B && (2 * bt * bt > 256 || (cfg.flags & FASTCLIP_SINGLE_PASS));
+  L->square = cfg.b == cfg.B && (L->bf16 ? 2 * bt * bt > 256 || (cfg.flags & FASTCLIP_SINGLE_PASS) : !lean);
   // Fine tiles (opt-in) where 256 x 256 tiles would leave most of the chip idle: fewer large strip tiles than three
   // quarters of the compute units (one per compute unit is what the large-tile kernels are built for).
   const int64_t big_tiles = 2 * ((cfg.b + 255) / 256) * ((cfg.B + 255) / 256);
@@ -201,10 +239,8 @@ void make_layout(const fastclip_config& cfg, Layout* L) {
     L->kslice = (stages + best - 1) / best;
     L->nsplit = (int)((stages + L->kslice - 1) / L->kslice);
   } else {
-    L->nparts = 1;
-    L->ldE = cfg.B;
-    L->nsplit = 0;
-    L->kslice = 0;
+    L->ldE = lean ? cfg.B : (int64_t)round_up((size_t)cfg.B, 4);
+    plan_f32(cfg, lean, L);
   }
   // Every 64 x 64 block of the fold needs the coefficients of 128 anchor sides.  Forming them inside the fold saves a
   // launch, but every block then sums those anchors' partial sums again (b^2 / 32 anchor sides x nparts floats in
@@ -214,9 +250,10 @@ void make_layout(const fastclip_config& cfg, Layout* L) {
   L->nstate_blocks = L->fused_state ? (int)((cfg.b + 63) / 64) : state_blocks(cfg.b, L->nparts);
   L->diag = take(fb); L->tau1 = take(fb); L->tau2 = take(fb); L->k1 = take(fb); L->k2 = take(fb);
   L->uold1 = take(fb); L->uold2 = take(fb);
-  L->sums = take(fb * 4 * (size_t)L->nparts);
+  L->sums = take(fb * 4 * (size_t)L->nparts * (!L->bf16 && L->nparts > 1 ? 2 : 1));
   L->c1 = take(fb); L->c2 = take(fb); L->dcoef = take(fb);
-  L->red = take(sizeof(double) * 2 * (size_t)L->nstate_blocks);
+  const size_t red_bytes = sizeof(double) * 2 * (size_t)L->nstate_blocks;
+  if (L->bf16) L->red = take(red_bytes);
   const size_t esz = L->bf16 ? sizeof(bf16_t) : sizeof(float);
   if (L->bf16) {
     // fragment-ordered strips: anchors padded to whole 256-row tiles
@@ -234,8 +271,15 @@ void make_layout(const fastclip_config& cfg, Layout* L) {
     }
   } else {
     for (int s = 0; s < 2; ++s) L->E[s] = take(esz * (size_t)cfg.b * (size_t)L->ldE);
+    L->red = take(red_bytes);    // behind the strips: a word of four columns that begins in their last row may end here
+    if (L->nsplit > 1) {
+      const int64_t T = L->grad_tile, tiles = 2 * ((cfg.b + T - 1) / T) * ((cfg.d + T - 1) / T);
+      L->narrived = (int)tiles;
+      L->arrived = take(sizeof(unsigned) * (size_t)tiles);
+      L->Opart[0] = take(sizeof(double) * (size_t)L->nsplit * (size_t)tiles * (size_t)(T * T));
+    }
   }
-  if (L->square) L->F[0] = take(esz * round_up((size_t)cfg.b, 256) * (size_t)L->ldE);
+  if (L->square && L->bf16) L->F[0] = take(esz * round_up((size_t)cfg.b, 256) * (size_t)L->ldE);
   if (L->gathered) {
     L->colp = take(sizeof(float) * 2 * 4 * (size_t)L->ncol);
     if (L->bf16) {
@@ -246,6 +290,17 @@ void make_layout(const fastclip_config& cfg, Layout* L) {
     }
   }
   L->total = at;
+}
+
+// The fp32 path's workspace: partial sums and splits take a few per cent on top of the stored strips.  A configuration that
+// fits the static array without them and would not fit with them goes without, so that fastclip_step_static keeps taking it.
+void make_layout(const fastclip_config& cfg, Layout* L) {
+  make_layout(cfg, false, L);
+  if (!L->bf16 && L->total > (size_t)FASTCLIP_STATIC_SCRATCH_BYTES) {
+    Layout small;
+    make_layout(cfg, true, &small);
+    if (small.total <= (size_t)FASTCLIP_STATIC_SCRATCH_BYTES) *L = small;
+  }
 }
 
 static fastclip_status run_step(const fastclip_config* cfg, const fastclip_buffers* bufs, void* workspace,
@@ -295,24 +350,25 @@ static fastclip_status run_step(const fastclip_config* cfg, const fastclip_buffe
     if (!c.L.fused_state) { launch_state(c); mark(FASTCLIP_PHASE_STATE); }
     launch_fold_bf16(c);                  mark(FASTCLIP_PHASE_LOCAL);   // with fused_state: the state phase as well
     launch_contract_t128_bf16(c);         mark(FASTCLIP_PHASE_CONTRACT);  // outputs and scalars included
-    launch_norm_backward_bf16(c);
+    launch_norm_backward(c);
   } else if (c.L.fine) {
     launch_strips_fine_bf16(c);           mark(FASTCLIP_PHASE_STRIPS);
     if (!c.L.fused_state) { launch_state(c); mark(FASTCLIP_PHASE_STATE); }
     launch_fold_bf16(c);                  mark(FASTCLIP_PHASE_LOCAL);   // with fused_state: the state phase as well
     launch_contract_fine_bf16(c);         mark(FASTCLIP_PHASE_CONTRACT);  // outputs and scalars included
-    launch_norm_backward_bf16(c);
+    launch_norm_backward(c);
   } else if (c.L.bf16) {
     launch_strips_bf16(c);                mark(FASTCLIP_PHASE_STRIPS);
     if (!c.L.fused_state) { launch_state(c); mark(FASTCLIP_PHASE_STATE); }
     launch_fold_bf16(c);                  mark(FASTCLIP_PHASE_LOCAL);   // with fused_state: the state phase as well
     launch_contract_bf16(c);              mark(FASTCLIP_PHASE_CONTRACT);
     launch_finalize_bf16(c);
-    launch_norm_backward_bf16(c);
+    launch_norm_backward(c);
   } else {
     launch_strips_f32(c);                 mark(FASTCLIP_PHASE_STRIPS);
     launch_state(c);                      mark(FASTCLIP_PHASE_STATE);
     launch_grad_f32(c);
+    launch_norm_backward(c);
   }
   // global temperature: stepped once its gradient is complete (V2 was stepped in the state phase)
   if (c.tau_upd.optimizer && c.cfg.version != FASTCLIP_V2) launch_tau_scalar(c.tau_upd, c.tau_st, c.buf.d_tau, c.s);

@@ -42,9 +42,11 @@ struct Layout {
   int bf16;          // 1: MFMA path, 0: fp32 accuracy path
   int nparts;        // partial row sums per anchor and quantity written by the strip phase
   int64_t bstride;   // anchors padded to whole tiles of 256 (stride of the per-anchor arrays)
+  int per_part;      // fp32 path: contrast tiles behind one partial sum
+  int strip_tile, grad_tile;   // fp32 path: tile sizes of k_strips_f64 / k_grad_f64 (32 or 64)
   int64_t ldE;       // contrast columns of the stored exp strips (MFMA path: multiple of 64; fp32 path: B)
   int nsplit;        // split of the contraction over its column range
-  int64_t kslice;    // 32-deep stages per split
+  int64_t kslice;    // 32-deep stages per split (fp32 path: stages of the gradient kernel's depth)
   int nstate_blocks; // scalar partials: one per block of the state kernel, or per diagonal block of the fused fold
   int fused_state;   // 1: MFMA path, few anchors and few partial sums: the fold kernel runs the state phase itself
   int gathered;      // 1: contrast-side estimator over every global anchor (FASTCLIP_GATHERED_STATE and b < B)
@@ -53,16 +55,20 @@ struct Layout {
                      //    split there are no partial results
   int t128;          // 1: MFMA path on 128 x 128 tiles (kernels_tiles128.hip); nparts counts 128-column tiles, nsplit /
                      //    kslice count 32-deep stages, and with one split there are no partial results
-  int square;        // 1: MFMA path, b == B: the similarity matrix is formed once (F[0] holds
-                     //    l2(j, p) in the layout of E[0] until the fold transposes it into E[1])
+  int square;        // 1: b == B and the similarity matrix is formed once.  MFMA path: F[0] holds l2(j, p) in the
+                     //    layout of E[0] until the fold transposes it into E[1]; fp32 path: E[1] holds it as [p][j]
   int64_t ncol;      // gathered: entries per column-parameter array (B rounded up to whole 256-column tiles)
   size_t diag, tau1, tau2, k1, k2;   // float[bstride]
   size_t uold1, uold2;               // float[bstride]: u^t of the batch's samples (gathered with the temperatures)
   size_t sums;                       // float[4][nparts][bstride]: sum e1, sum x1 e1, sum e2, sum x2 e2
+                                     // (fp32 path with nparts > 1: double)
+  size_t arrived;                    // unsigned[narrived]: arrival counters of the gradient tiles, zeroed by k_prep
+  int narrived;
   size_t c1, c2, dcoef;              // float[bstride]
   size_t red;                        // double[nstate_blocks][2]
   size_t E[2];                       // fp32 path: float [b][ldE]; MFMA path: fragment-ordered bf16 strips
   size_t Opart[2];                   // float [nsplit][partial_split_floats(b, d)]   (MFMA path)
+                                     // fp32 path with nsplit > 1: Opart[0] is double [nsplit][2][tiles][grad_tile^2]
   // gathered: per global row j (= contrast column of the strips) and side s, in tiles of 256 columns
   // [s][tile][4][256]: log2(e)/tau_j, s_jj log2(e)/tau_j, c_j (0 for local rows and beyond B), unused.
   // Side 0 describes the text anchors j (l2(j, .), weights of d_img), side 1 the image anchors (l1(j, .), d_txt).
@@ -112,7 +118,7 @@ void launch_strips_fine_bf16(const StepCtx& c);    // MFMA path, fine tiles: exp
 void launch_contract_fine_bf16(const StepCtx& c);  // MFMA path, fine tiles: contractions, outputs and scalars
 void launch_strips_t128_bf16(const StepCtx& c);    // MFMA path, 128 x 128 tiles: exp strips + row sums
 void launch_contract_t128_bf16(const StepCtx& c);  // MFMA path, 128 x 128 tiles: contractions, outputs and scalars
-void launch_norm_backward_bf16(const StepCtx& c);  // MFMA path: gradients through the L2 normalisation, if asked for
+void launch_norm_backward(const StepCtx& c);       // gradients through the L2 normalisation, if asked for
 void launch_finalize_bf16(const StepCtx& c);   // MFMA path: combine + scalars
 
 void launch_normalize_rows(const void* raw, int raw_bf16, int64_t ld_raw, int64_t b, int64_t d, void* unit, int unit_bf16,

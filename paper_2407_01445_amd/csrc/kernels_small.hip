@@ -1,6 +1,5 @@
 // Small kernels of the FCCO step: s_ii and temperature gather, the state update of Eq. 1 with
-// the per-anchor coefficients, the fp32-storage accuracy path (strips and gradients in
-// plain loops with fp64 accumulation), the scalar outputs, and the index checker.
+// the per-anchor coefficients, the finishing kernels of the MFMA path, the scalar outputs, and the index checker.
 #include <string.h>
 
 #include "fc_internal.hpp"
@@ -59,9 +58,11 @@ __global__ void __launch_bounds__(256) k_prep(const T* __restrict__ img, const T
                                               int64_t stride, int version, float* __restrict__ diag,
                                               float* __restrict__ tau1,
                                               float* __restrict__ tau2, float* __restrict__ k1, float* __restrict__ k2,
-                                              float* __restrict__ uold1, float* __restrict__ uold2) {
+                                              float* __restrict__ uold1, float* __restrict__ uold2, unsigned* __restrict__ arrived,
+                                              int narrived) {
   const int lane = threadIdx.x & 63;
   const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < narrived; i += (int)(gridDim.x * 256)) arrived[i] = 0u;
   if (r >= b) return;
   float t1 = 0.f, t2 = 0.f, u1 = 0.f, u2 = 0.f;
   if (lane == 0) {        // issue the gathers by dataset index before the dot product so that the latencies overlap:
@@ -96,17 +97,18 @@ void launch_prep(const StepCtx& c) {
   float* k2 = (float*)(c.ws + L.k2);
   float* uold1 = (float*)(c.ws + L.uold1);
   float* uold2 = (float*)(c.ws + L.uold2);
+  unsigned* arrived = (unsigned*)(c.ws + L.arrived);
   dim3 grid((unsigned)((L.b + 3) / 4)), block(256);
   if (L.bf16)
     hipLaunchKernelGGL(k_prep<bf16_t>, grid, block, 0, c.s, (const bf16_t*)c.buf.img_glob, (const bf16_t*)c.buf.txt_glob,
                        c.cfg.ld_img, c.cfg.ld_txt, L.off, L.b, L.d, c.buf.idx, c.buf.tau, c.buf.tau_img,
                        c.buf.tau_txt, c.buf.u_img, c.buf.u_txt, c.cfg.state_stride, c.cfg.version, diag, tau1, tau2, k1, k2,
-                       uold1, uold2);
+                       uold1, uold2, arrived, L.narrived);
   else
     hipLaunchKernelGGL(k_prep<float>, grid, block, 0, c.s, (const float*)c.buf.img_glob, (const float*)c.buf.txt_glob,
                        c.cfg.ld_img, c.cfg.ld_txt, L.off, L.b, L.d, c.buf.idx, c.buf.tau, c.buf.tau_img,
                        c.buf.tau_txt, c.buf.u_img, c.buf.u_txt, c.cfg.state_stride, c.cfg.version, diag, tau1, tau2, k1, k2,
-                       uold1, uold2);
+                       uold1, uold2, arrived, L.narrived);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -214,67 +216,6 @@ void launch_prep_cols(const StepCtx& c) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Accuracy path, strips (Proc. 1).  Block (r, side): anchor r against every contrast row j != p;
-// side 0: image anchor vs texts (l1), side 1: text anchor vs images (l2).  One wavefront per
-// contrast row, fp64 accumulation; stores l as fp32 and the two row sums.
-__global__ void __launch_bounds__(256) k_strips_f32(const float* __restrict__ img, const float* __restrict__ txt,
-                                                    int64_t ld_img, int64_t ld_txt, int64_t off, int64_t B,
-                                                    int64_t d, const float* __restrict__ diag,
-                                                    const float* __restrict__ tau1, const float* __restrict__ tau2,
-                                                    float* __restrict__ E1, float* __restrict__ E2, int64_t ldE,
-                                                    float* __restrict__ sums, int64_t bstride,
-                                                    const float* __restrict__ colp, int64_t ncol,
-                                                    float* __restrict__ F1, float* __restrict__ F2) {
-  const int64_t r = blockIdx.x;
-  const int side = blockIdx.y;
-  const int64_t p = off + r;
-  const float* anchor = side == 0 ? img + p * ld_img : txt + p * ld_txt;
-  const float* X = side == 0 ? txt : img;
-  const int64_t ldx = side == 0 ? ld_txt : ld_img;
-  float* E = (side == 0 ? E1 : E2) + r * ldE;
-  float* F = colp ? (side == 0 ? F1 : F2) + r * ldE : nullptr;   // gathered: c_j l(j, p) of every remote anchor j
-  const double s_pp = (double)diag[r];
-  const double tau = (double)(side == 0 ? tau1[r] : tau2[r]);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  double sg = 0.0, sh = 0.0;
-  for (int64_t j = wave; j < B; j += 4) {
-    const float* x = X + j * ldx;
-    double acc = 0.0;
-    for (int64_t k = lane; k < d; k += 64) acc += (double)anchor[k] * (double)x[k];
-    acc = wave_sum(acc);
-    const double xs = acc - s_pp;
-    const double e = j == p ? 0.0 : exp(xs / tau);
-    if (lane == 0) E[j] = (float)e;
-    if (F && lane == 0) {
-      const float* cp = colp + (((int64_t)side * (ncol >> 8) + (j >> 8)) * 4) * 256 + (j & 255);
-      const double cj = (double)cp[512];
-      F[j] = cj == 0.0 ? 0.f : (float)(cj * exp2(acc * (double)cp[0] - (double)cp[256]));
-    }
-    sg += e;
-    sh += xs * e;
-  }
-  __shared__ double red[2][4];
-  if (lane == 0) { red[0][wave] = sg; red[1][wave] = sh; }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    // quantities 0,1 belong to side 0 (sum e1, sum x1 e1), 2,3 to side 1; nparts == 1 on this path
-    sums[(size_t)(2 * side + 0) * bstride + r] = (float)(red[0][0] + red[0][1] + red[0][2] + red[0][3]);
-    sums[(size_t)(2 * side + 1) * bstride + r] = (float)(red[1][0] + red[1][1] + red[1][2] + red[1][3]);
-  }
-}
-
-void launch_strips_f32(const StepCtx& c) {
-  const Layout& L = c.L;
-  dim3 grid((unsigned)L.b, 2), block(256);
-  hipLaunchKernelGGL(k_strips_f32, grid, block, 0, c.s, (const float*)c.buf.img_glob, (const float*)c.buf.txt_glob,
-                     c.cfg.ld_img, c.cfg.ld_txt, L.off, L.B, L.d, (const float*)(c.ws + L.diag),
-                     (const float*)(c.ws + L.tau1), (const float*)(c.ws + L.tau2), (float*)(c.ws + L.E[0]),
-                     (float*)(c.ws + L.E[1]), L.ldE, (float*)(c.ws + L.sums), L.bstride,
-                     L.gathered ? (const float*)(c.ws + L.colp) : nullptr, L.ncol,
-                     L.gathered ? (float*)(c.ws + L.F[0]) : nullptr, L.gathered ? (float*)(c.ws + L.F[1]) : nullptr);
-}
-
-
 // Global temperature (V0, V3): one thread.
 __global__ void k_tau_scalar(TauUpd u, float* tau, float* m, float* v, const float* d_tau) {
   if (threadIdx.x == 0 && blockIdx.x == 0) tau_step(u, tau, m, v, d_tau[0]);
@@ -311,18 +252,23 @@ void launch_tau_sparse(const TauUpd& u, const fastclip_tau_state& st, const int6
 // lane 0 finish the anchor sides.  With canonical 8-float records a finishing thread moves its side's four fields
 // {u, tau, m, v} as one 16-byte word: a sample costs one 32-byte sector each way, read and written whole.
 // se / sx of partial-sum lane 0 plus those of lanes 1 .. LANES - 1, which sit 256 / LANES entries apart
-template <int LANES>
-__device__ __forceinline__ void add_parts(const float (*part)[256], int sa, float& se, float& sx) {
-  float e[LANES], x[LANES];
+template <int LANES, typename T>
+__device__ __forceinline__ void add_parts(const T (*part)[256], int sa, T& se, T& sx) {
+  T e[LANES], x[LANES];
 #pragma unroll
   for (int q = 1; q < LANES; ++q) { e[q] = part[0][q * (256 / LANES) + sa]; x[q] = part[1][q * (256 / LANES) + sa]; }
 #pragma unroll
   for (int q = 1; q < LANES; ++q) { se += e[q]; sx += x[q]; }
 }
 
+// the accuracy path adds its partial sums (fp64 unless there is only one) up in fp64
+template <bool PRECISE> struct SumType { typedef float type; };
+template <> struct SumType<true> { typedef double type; };
+
 template <bool PRECISE>
 __global__ void __launch_bounds__(256) k_state(StateArgs a) {
-  __shared__ float part[2][256];
+  using sum_t = typename SumType<PRECISE>::type;
+  __shared__ sum_t part[2][256];
   __shared__ double scal[2][4];
   const int SA = 256 / a.lanes;                       // anchor sides per tile of a block
   const int sa = threadIdx.x % SA, pl = threadIdx.x / SA;
@@ -349,42 +295,47 @@ __global__ void __launch_bounds__(256) k_state(StateArgs a) {
         tau = (side ? a.tau2 : a.tau1)[r];
       }
     }
-    float se = 0.f, sx = 0.f;
+    sum_t se_t = 0, sx_t = 0;
     if (r < a.b) {
-      const float* s0 = a.sums + (size_t)(2 * side) * a.nparts * a.bstride + r;
-      const float* s1 = s0 + (size_t)a.nparts * a.bstride;
       // four partial sums of each quantity per round, so that eight loads are in flight instead of two
-      int pt = pl;
-      for (; pt + 3 * a.lanes < a.nparts; pt += 4 * a.lanes) {
-        float e[4], x[4];
+      auto add_up = [&](const auto* s0) {
+        const auto* s1 = s0 + (size_t)a.nparts * a.bstride;
+        int pt = pl;
+        for (; pt + 3 * a.lanes < a.nparts; pt += 4 * a.lanes) {
+          sum_t e[4], x[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          e[q] = s0[(size_t)(pt + q * a.lanes) * a.bstride];
-          x[q] = s1[(size_t)(pt + q * a.lanes) * a.bstride];
+          for (int q = 0; q < 4; ++q) {
+            e[q] = s0[(size_t)(pt + q * a.lanes) * a.bstride];
+            x[q] = s1[(size_t)(pt + q * a.lanes) * a.bstride];
+          }
+          se_t += (e[0] + e[1]) + (e[2] + e[3]);
+          sx_t += (x[0] + x[1]) + (x[2] + x[3]);
         }
-        se += (e[0] + e[1]) + (e[2] + e[3]);
-        sx += (x[0] + x[1]) + (x[2] + x[3]);
-      }
-      for (; pt < a.nparts; pt += a.lanes) {
-        se += s0[(size_t)pt * a.bstride];
-        sx += s1[(size_t)pt * a.bstride];
-      }
+        for (; pt < a.nparts; pt += a.lanes) {
+          se_t += s0[(size_t)pt * a.bstride];
+          sx_t += s1[(size_t)pt * a.bstride];
+        }
+      };
+      const size_t first = (size_t)(2 * side) * a.nparts * a.bstride + r;
+      if (PRECISE && a.sums64) add_up(a.sums64 + first);
+      else add_up(a.sums + first);
     }
     if (a.lanes > 1) {                                   // block-uniform
-      part[0][threadIdx.x] = se;
-      part[1][threadIdx.x] = sx;
+      part[0][threadIdx.x] = se_t;
+      part[1][threadIdx.x] = sx_t;
       __syncthreads();
       if (pl == 0) {      // all LDS reads of a thread issued together (compile-time trip counts), then added in order
         switch (a.lanes) {
-          case 2: add_parts<2>(part, sa, se, sx); break;
-          case 4: add_parts<4>(part, sa, se, sx); break;
-          case 8: add_parts<8>(part, sa, se, sx); break;
-          case 16: add_parts<16>(part, sa, se, sx); break;
-          default: add_parts<32>(part, sa, se, sx); break;
+          case 2: add_parts<2>(part, sa, se_t, sx_t); break;
+          case 4: add_parts<4>(part, sa, se_t, sx_t); break;
+          case 8: add_parts<8>(part, sa, se_t, sx_t); break;
+          case 16: add_parts<16>(part, sa, se_t, sx_t); break;
+          default: add_parts<32>(part, sa, se_t, sx_t); break;
         }
       }
       __syncthreads();                                   // before the next tile overwrites part
     }
+    const float se = (float)se_t, sx = (float)sx_t;
     float ce = 0.f;
     if (finisher) {
       const SideResult o = state_side<PRECISE>(a, se, sx, u_old, tau);
@@ -439,7 +390,9 @@ StateArgs make_state_args(const StepCtx& c) {
   a.idx = c.buf.idx; a.u_img = c.buf.u_img; a.u_txt = c.buf.u_txt;
   a.tau1 = (const float*)(c.ws + L.tau1); a.tau2 = (const float*)(c.ws + L.tau2);
   a.uold1 = (const float*)(c.ws + L.uold1); a.uold2 = (const float*)(c.ws + L.uold2);
-  a.sums = (const float*)(c.ws + L.sums); a.nparts = L.nparts; a.bstride = L.bstride; a.b = L.b;
+  a.sums = (const float*)(c.ws + L.sums); a.nparts = L.nparts;
+  a.sums64 = !L.bf16 && L.nparts > 1 ? (const double*)(c.ws + L.sums) : nullptr;
+  a.bstride = L.bstride; a.b = L.b;
   a.fused = L.fused_state;
   a.stride = c.cfg.state_stride;
   a.M = (float)(L.B - 1); a.gamma = c.cfg.gamma; a.eps = c.cfg.eps; a.rho = c.cfg.rho;
@@ -534,89 +487,6 @@ __global__ void k_scalars(const double* red, int nblocks, int64_t b, int version
 }
 
 // ------------------------------------------------------------------------------------------
-// Accuracy path, gradients (Eqs. 2-7 for the local rows).  Block (r, side) writes one output row:
-//   side 0: d_img[r] = c1_r * sum_j l1(r,j) txt_j - (c1_r M g1_r + c2_r M g2_r) txt_p
-//                      + sum_{r' != r} c2_{r'} l2(r', p) txt_{p'}
-//   side 1: the mirror image.  The stored strips hold l with the anchor's own column zeroed.
-__global__ void __launch_bounds__(256) k_grad_f32(const float* __restrict__ img, const float* __restrict__ txt,
-                                                  int64_t ld_img, int64_t ld_txt, int64_t off, int64_t b, int64_t B,
-                                                  int64_t d, const float* __restrict__ E1, const float* __restrict__ E2,
-                                                  int64_t ldE, const float* __restrict__ c1, const float* __restrict__ c2,
-                                                  const float* __restrict__ dcoef, float* __restrict__ d_img,
-                                                  float* __restrict__ d_txt, const double* __restrict__ red, int nblocks,
-                                                  int version, const float* __restrict__ tau, float rho,
-                                                  float* __restrict__ loss, float* __restrict__ d_tau,
-                                                  const float* __restrict__ F1, const float* __restrict__ F2,
-                                                  const float* __restrict__ norm_img,
-                                                  const float* __restrict__ norm_txt) {
-  const int64_t r = blockIdx.x;
-  const int side = blockIdx.y;
-  const int64_t p = off + r;
-  const float* Fown = F1 ? (side == 0 ? F1 : F2) + r * ldE : nullptr;   // gathered: remote anchors' weights
-  const float* X = side == 0 ? txt : img;       // rows that the exp weights multiply
-  const int64_t ldx = side == 0 ? ld_txt : ld_img;
-  const float* Eown = (side == 0 ? E1 : E2) + r * ldE;       // l of this anchor over all contrasts
-  const float* Eoth = side == 0 ? E2 : E1;                   // l of the other local anchors at column p
-  const float* cown = side == 0 ? c1 : c2;
-  const float* coth = side == 0 ? c2 : c1;
-  float* out = (side == 0 ? d_img : d_txt) + r * d;
-  int cw = 32;
-  while (cw < 256 && cw < d) cw <<= 1;
-  const int groups = 256 / cw;
-  const int cl = threadIdx.x % cw, grp = threadIdx.x / cw;
-  __shared__ double red2[256];
-  for (int64_t c0 = 0; c0 < d; c0 += cw) {
-    const int64_t col = c0 + cl;
-    double acc = 0.0, acc6 = 0.0;
-    if (col < d) {
-      for (int64_t j = grp; j < B; j += groups) acc += (double)Eown[j] * (double)X[j * ldx + col];
-      for (int64_t q = grp; q < b; q += groups)
-        acc6 += (double)coth[q] * (double)Eoth[q * ldE + p] * (double)X[(off + q) * ldx + col];
-      if (Fown)
-        for (int64_t j = grp; j < B; j += groups) acc6 += (double)Fown[j] * (double)X[j * ldx + col];
-    }
-    red2[threadIdx.x] = (double)cown[r] * acc + acc6;
-    __syncthreads();
-    if (grp == 0 && col < d) {
-      double t = 0.0;
-      for (int g = 0; g < groups; ++g) t += red2[g * cw + cl];
-      out[col] = (float)(t - (double)dcoef[r] * (double)X[p * ldx + col]);
-    }
-    __syncthreads();
-  }
-  if (norm_img) {
-    // gradient through e^ = e / |e|: out := (out - e^ (e^ . out)) / |e|, e^ = this side's own row (see k_finalize_bf16)
-    const float* ep = side == 0 ? img + p * ld_img : txt + p * ld_txt;
-    double dot = 0.0;
-    for (int64_t col = threadIdx.x; col < d; col += 256) dot += (double)out[col] * (double)ep[col];
-    red2[threadIdx.x] = dot;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-      if ((int)threadIdx.x < w) red2[threadIdx.x] += red2[threadIdx.x + w];
-      __syncthreads();
-    }
-    dot = red2[0];
-    const double inv = 1.0 / (double)(side == 0 ? norm_img[r] : norm_txt[r]);
-    for (int64_t col = threadIdx.x; col < d; col += 256)
-      out[col] = (float)(((double)out[col] - dot * (double)ep[col]) * inv);
-  }
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 64)
-    write_scalars(red, nblocks, b, version, tau, rho, loss, d_tau);
-}
-
-void launch_grad_f32(const StepCtx& c) {
-  const Layout& L = c.L;
-  dim3 grid((unsigned)L.b, 2), block(256);
-  hipLaunchKernelGGL(k_grad_f32, grid, block, 0, c.s, (const float*)c.buf.img_glob, (const float*)c.buf.txt_glob,
-                     c.cfg.ld_img, c.cfg.ld_txt, L.off, L.b, L.B, L.d, (const float*)(c.ws + L.E[0]),
-                     (const float*)(c.ws + L.E[1]), L.ldE, (const float*)(c.ws + L.c1), (const float*)(c.ws + L.c2),
-                     (const float*)(c.ws + L.dcoef), c.buf.d_img, c.buf.d_txt, (const double*)(c.ws + L.red),
-                     L.nstate_blocks, c.cfg.version, c.buf.tau, c.cfg.rho, c.buf.loss, c.buf.d_tau,
-                     L.gathered ? (const float*)(c.ws + L.F[0]) : nullptr,
-                     L.gathered ? (const float*)(c.ws + L.F[1]) : nullptr, c.buf.norm_img, c.buf.norm_txt);
-}
-
-// ------------------------------------------------------------------------------------------
 // MFMA path, last phase.  d_img[r] = c1_r * (sum over splits of the contraction)[r] - dcoef_r txt_p, and the mirror
 // image (the contraction already carries the contrast-side terms divided by c_r); block (0,0,0) also writes the
 // scalars.  The split partials are whole 256 x 256 tiles of [64 groups of 4 rows][256 columns][4 rows] (the order in
@@ -703,26 +573,28 @@ __global__ void __launch_bounds__(256) k_finalize_bf16(const bf16_t* __restrict_
     write_scalars(red, nblocks, b, version, tau, rho, loss, d_tau);
 }
 
-// Gradient through e^ = e / |e| (cosine similarity, Sec. 3) on the MFMA path, after k_finalize_bf16:
-// out := (out - e^ (e^ . out)) / |e|, e^ = the side's own row.  One block per anchor and side.
-__global__ void __launch_bounds__(256) k_norm_backward_bf16(const bf16_t* __restrict__ img, const bf16_t* __restrict__ txt,
-                                                            int64_t ld_img, int64_t ld_txt, int64_t off, int64_t d,
-                                                            float* __restrict__ d_img, float* __restrict__ d_txt,
-                                                            const float* __restrict__ norm_img,
-                                                            const float* __restrict__ norm_txt) {
-  __shared__ float part[4];
+// Gradient through e^ = e / |e| (cosine similarity, Sec. 3), after the gradients with respect to e^ are complete:
+// out := (out - e^ (e^ . out)) / |e|, e^ = the side's own row.  One block per anchor and side; on the accuracy path
+// (T = float) in fp64.
+template <typename T, typename A>
+__global__ void __launch_bounds__(256) k_norm_backward(const T* __restrict__ img, const T* __restrict__ txt,
+                                                       int64_t ld_img, int64_t ld_txt, int64_t off, int64_t d,
+                                                       float* __restrict__ d_img, float* __restrict__ d_txt,
+                                                       const float* __restrict__ norm_img,
+                                                       const float* __restrict__ norm_txt) {
+  __shared__ A part[4];
   const int64_t r = blockIdx.x;
   const int side = blockIdx.y;
-  const bf16_t* ep = side == 0 ? img + (off + r) * ld_img : txt + (off + r) * ld_txt;
+  const T* ep = side == 0 ? img + (off + r) * ld_img : txt + (off + r) * ld_txt;
   float* out = (side == 0 ? d_img : d_txt) + r * d;
-  float dot = 0.f;
-  for (int64_t n = threadIdx.x; n < d; n += 256) dot = fmaf(out[n], load_elem(ep + n), dot);
+  A dot = 0;
+  for (int64_t n = threadIdx.x; n < d; n += 256) dot += (A)out[n] * (A)load_elem(ep + n);
   dot = wave_sum(dot);
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = dot;
   __syncthreads();
   dot = (part[0] + part[1]) + (part[2] + part[3]);
-  const float inv = 1.0f / (side == 0 ? norm_img : norm_txt)[r];
-  for (int64_t n = threadIdx.x; n < d; n += 256) out[n] = (out[n] - dot * load_elem(ep + n)) * inv;
+  const A inv = (A)1 / (A)(side == 0 ? norm_img : norm_txt)[r];
+  for (int64_t n = threadIdx.x; n < d; n += 256) out[n] = (float)(((A)out[n] - dot * (A)load_elem(ep + n)) * inv);
 }
 
 void launch_finalize_bf16(const StepCtx& c) {
@@ -740,11 +612,17 @@ void launch_finalize_bf16(const StepCtx& c) {
                      L.nstate_blocks, c.cfg.version, c.buf.tau, c.cfg.rho, c.buf.loss, c.buf.d_tau);
 }
 
-void launch_norm_backward_bf16(const StepCtx& c) {
+void launch_norm_backward(const StepCtx& c) {
   const Layout& L = c.L;
-  if (c.buf.norm_img)
-    hipLaunchKernelGGL(k_norm_backward_bf16, dim3((unsigned)L.b, 2), dim3(256), 0, c.s, (const bf16_t*)c.buf.img_glob,
+  if (!c.buf.norm_img) return;
+  const dim3 grid((unsigned)L.b, 2), block(256);
+  if (L.bf16)
+    hipLaunchKernelGGL((k_norm_backward<bf16_t, float>), grid, block, 0, c.s, (const bf16_t*)c.buf.img_glob,
                        (const bf16_t*)c.buf.txt_glob, c.cfg.ld_img, c.cfg.ld_txt, L.off, L.d, c.buf.d_img, c.buf.d_txt,
+                       c.buf.norm_img, c.buf.norm_txt);
+  else
+    hipLaunchKernelGGL((k_norm_backward<float, double>), grid, block, 0, c.s, (const float*)c.buf.img_glob,
+                       (const float*)c.buf.txt_glob, c.cfg.ld_img, c.cfg.ld_txt, L.off, L.d, c.buf.d_img, c.buf.d_txt,
                        c.buf.norm_img, c.buf.norm_txt);
 }
 

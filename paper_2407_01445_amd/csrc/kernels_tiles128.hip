@@ -39,8 +39,6 @@ __device__ __forceinline__ void wait_younger_stages(int n) {
     default: __builtin_amdgcn_s_waitcnt(0x4f7c); break;
   }
 }
-// nothing may move across: the compiler does not see the direct-to-LDS loads write the ring
-#define FC_FENCE() do { FC_PIN(); asm volatile("" ::: "memory"); FC_PIN(); } while (0)
 
 // acc += (A operand tile) x (B operand tile)^T over the stages [s0, s0 + S), S >= 1.  Tile::dma(i, stage, slot address),
 // i = 0 .. 3, issues this wave's four wave loads of a stage.  Stage s lives in slot s mod 5; its loads are issued four

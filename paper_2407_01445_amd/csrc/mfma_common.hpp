@@ -19,6 +19,8 @@ constexpr int kStageBytes = 2 * kOpBytes;    // 32 KiB
 constexpr int kRingBytes = 5 * kStageBytes;  // 160 KiB: all of the LDS of a compute unit
 
 #define FC_PIN() __builtin_amdgcn_sched_barrier(0)
+// nothing may move across: the compiler does not see the direct-to-LDS loads write the ring
+#define FC_FENCE() do { FC_PIN(); asm volatile("" ::: "memory"); FC_PIN(); } while (0)
 #define FC_WAIT_VMCNT0() __builtin_amdgcn_s_waitcnt(0x0f70)
 #define FC_WAIT_VMCNT8() __builtin_amdgcn_s_waitcnt(0x0f78)
 #define FC_WAIT_VMCNT16() __builtin_amdgcn_s_waitcnt(0x4f70)
@@ -38,6 +40,14 @@ __device__ __forceinline__ void dma16(const void* uniform_base, uint32_t lane_by
                :
                : "v"(lane_byte_off), "s"(uniform_base), "s"(__builtin_amdgcn_readfirstlane(lds_byte_addr))
                : "memory");
+}
+// An address that is the same in every lane, for code in which the compiler cannot see that it is.
+template <typename T>
+__device__ __forceinline__ const T* wave_uniform(const T* p) {
+  const uint64_t v = (uint64_t)(uintptr_t)p;
+  const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return (const T*)(uintptr_t)(lo | (hi << 32));
 }
 // Same for 4 bytes per lane (per-anchor scalars of the next tile).
 __device__ __forceinline__ void dma4(const void* uniform_base, uint32_t lane_byte_off, uint32_t lds_byte_addr) {

@@ -44,6 +44,7 @@ struct StateArgs {
   const float *tau1, *tau2;
   const float *uold1, *uold2;   // u^t at the batch positions, gathered by the prep kernel
   const float* sums;   // [4][nparts][bstride]
+  const double* sums64;         // accuracy path with several partial sums: the same in fp64 (then sums is not used)
   int nparts;
   int fused;           // fold kernels: 1 = form the coefficients and finish the anchors there, 0 = k_state has run
   int64_t bstride, b;
@@ -65,6 +66,27 @@ struct StateArgs {
   const float* tau_glob;
 };
 StateArgs make_state_args(const StepCtx& c);
+
+// Partial results that workgroups of ONE launch hand to each other.  The XCDs' L2 caches are not coherent with each other
+// inside a kernel, so both sides go around them: stores and loads at agent scope (written through, read past the caches).
+__device__ __forceinline__ void store_agent(double* p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double load_agent(const double* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Called by every thread of `n` workgroups after their store_agent's; true in the threads of the last one to arrive, which
+// may then load_agent what all of them stored.  *counter is 0 before the launch (k_prep); nobody waits for anybody: the
+// others go on and leave.  The wait is for this wave's own stores to be acknowledged at agent scope, the barrier for the
+// workgroup's other waves, and only then is the arrival counted.
+__device__ __forceinline__ bool last_to_arrive(unsigned* counter, unsigned n, int* lds_flag) {
+  __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt(0)
+  __syncthreads();
+  if (threadIdx.x == 0)
+    *lds_flag = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == n;
+  __syncthreads();
+  return *lds_flag != 0;
+}
 
 __device__ inline double wave_sum_f64(double v) {
 #pragma unroll

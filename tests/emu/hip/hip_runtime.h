@@ -29,6 +29,7 @@ struct float2 { float x, y; };
 struct uint4 { uint32_t x, y, z, w; };
 struct uint2 { uint32_t x, y; };
 static inline float4 make_float4(float x, float y, float z, float w) { return float4{x, y, z, w}; }
+static inline float2 make_float2(float x, float y) { return float2{x, y}; }
 
 typedef int hipError_t;
 enum { hipSuccess = 0, hipErrorInvalidSymbol = 13 };
@@ -93,6 +94,13 @@ static inline unsigned long long atomicCAS(unsigned long long* p, unsigned long 
   return cmp;
 }
 
+// workgroups run one after another here; the threads of one meet in barriers
+template <typename T> static inline void emu_atomic_store_any(T* p, T v) { __atomic_store(p, &v, __ATOMIC_SEQ_CST); }
+template <typename T> static inline T emu_atomic_load_any(const T* p) { T v; __atomic_load((T*)p, &v, __ATOMIC_SEQ_CST); return v; }
+#define __hip_atomic_store(p, v, order, scope) emu_atomic_store_any(p, v)
+#define __hip_atomic_load(p, order, scope) emu_atomic_load_any(p)
+#define __hip_atomic_fetch_add(p, v, order, scope) __atomic_fetch_add(p, v, __ATOMIC_SEQ_CST)
+
 template <typename T>
 static inline T __shfl_xor(T v, int mask) {
   emu::Wave* w = emu::t_wave;
@@ -131,6 +139,26 @@ static inline emu_f32x16 __builtin_amdgcn_mfma_f32_32x32x16_bf16(emu_bf16x8 a, e
       s += emu_bf2f(x) * emu_bf2f(y);
     }
     c[v] += s;
+  }
+  w->bar.wait();
+  return c;
+}
+// D = A B + C, 16 x 16 x 4 in fp64: lane l gives A[l % 16][l / 16] and B[l / 16][l % 16]; D[4 v + l / 16][l % 16] in v
+typedef double emu_f64x4 __attribute__((ext_vector_type(4)));
+static inline emu_f64x4 __builtin_amdgcn_mfma_f64_16x16x4f64(double a, double b, emu_f64x4 c, int, int, int) {
+  emu::Wave* w = emu::t_wave;
+  const int lane = emu::t_lane;
+  memcpy(w->buf[0][lane], &a, 8);
+  memcpy(w->buf[1][lane], &b, 8);
+  w->bar.wait();
+  for (int v = 0; v < 4; ++v) {
+    const int row = 4 * v + lane / 16, col = lane % 16;
+    for (int k = 0; k < 4; ++k) {
+      double x, y;
+      memcpy(&x, w->buf[0][row + 16 * k], 8);
+      memcpy(&y, w->buf[1][col + 16 * k], 8);
+      c[v] += x * y;
+    }
   }
   w->bar.wait();
   return c;

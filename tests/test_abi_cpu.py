@@ -393,3 +393,13 @@ def test_measure_strips_argument_errors():
     assert call(c=good_cfg(B=2048, b=512, off=512, d=128, flags=fc.GATHERED_STATE), nbytes=1 << 30) == fc.ERR_UNSUPPORTED
     assert lib.fastclip_measure_mfma_ceiling(0, 16, 0x1000, 1 << 20, None, C.byref(ms), stats) == fc.ERR_SHAPE
     assert lib.fastclip_measure_mfma_ceiling(16, 16, 0x1000, 64, None, C.byref(ms), stats) == fc.ERR_WORKSPACE
+
+
+def test_f32_workspace_takes_no_more_than_the_strips_where_the_static_array_asks_for_it():
+    """A fp32 configuration whose two stored strips fit the static array keeps fitting it: partial sums and splits that
+    would push it over are left out (and are there where there is room)."""
+    fits = good_cfg(emb_dtype=fc.F32, B=8192, b=1020, off=0, d=64, N=5000)
+    strips = 2 * 4 * 1020 * 8192
+    assert strips < fc.fastclip_workspace_bytes(fits) <= fc.STATIC_SCRATCH_BYTES
+    assert fc.fastclip_describe(fits)["nparts"] == 1
+    assert fc.fastclip_describe(good_cfg(emb_dtype=fc.F32, B=8192, b=512, off=0, d=64, N=5000))["nparts"] > 1

@@ -101,6 +101,53 @@ def test_f32_two_anchor_batch_and_gamma_one():
     assert np.array_equal(g.u_new_txt.cpu().numpy(), g.g_txt.cpu().numpy())
 
 
+F32_TILE_SHAPES = [
+    # B, b, off, d, padding of the image rows
+    (32, 32, 0, 8, 0),             # one whole tile, the whole batch local
+    (33, 33, 0, 36, 4),            # one more row and column of tiles; a ragged last stage
+    (66, 31, 34, 68, 0),           # two strips, tiles that end beyond the local anchors
+    (130, 130, 0, 30, 1),          # rows that are not 16-byte aligned and end inside a word of four
+    (300, 130, 170, 128, 0),       # several splits of the gradients' depth, the local range among them
+    (4500, 70, 3, 36, 0),          # several contrast tiles behind one partial sum
+    (1030, 1030, 0, 68, 0),        # 64 x 64 tiles, the whole batch local, ragged
+    (2100, 550, 1201, 40, 4),      # 64 x 64 tiles, two strips, ragged
+]
+
+
+@pytest.mark.parametrize("B,b,off,d,pad", F32_TILE_SHAPES)
+@pytest.mark.parametrize("version", [V0, V2, V3])
+def test_f32_tiles_at_their_edges(B, b, off, d, pad, version):
+    rng = np.random.default_rng(B + d + version)
+    N = 6000
+    img, txt = make_embeddings(B + 3, B, d, 0.5, "f32")
+    idx = draw_indices(B + 4, b, N)
+    u0i = np.where(rng.random(N) < 0.5, 0.0, rng.uniform(0.05, 2.0, N)).astype(np.float32)
+    u0t = np.where(rng.random(N) < 0.5, 0.0, rng.uniform(0.05, 2.0, N)).astype(np.float32)
+    t_img = rng.uniform(0.05, 0.1, N).astype(np.float32)
+    t_txt = rng.uniform(0.05, 0.1, N).astype(np.float32)
+    g = GpuStep(B=B, b=b, off=off, d=d, N=N, dtype="f32", version=version, eps=1e-6, rho=6.5, tau=0.07,
+                tau_grad_scale=1.0 / N, ld_img=d + pad, u_img0=u0i, u_txt0=u0t, tau_img0=t_img, tau_txt0=t_txt)
+    g.set_inputs(img, txt, idx)
+    g.step(0.6)
+    u_img, u_txt = u0i.astype(np.float64), u0t.astype(np.float64)
+    want = oracle_step(g, img, txt, idx, u_img, u_txt, 0.6, tau=float(np.float32(0.07)), tau_img=t_img.astype(np.float64),
+                       tau_txt=t_txt.astype(np.float64))
+    first = g.outputs()
+    compare(first, want, version, TOL_F32, "f32 tiles %s v%d" % ((B, b, off, d), version))
+    check_state(g, u0i, u0t, idx, u_img, u_txt, TOL_F32)
+    # whoever of several workgroups finishes a tile: the same bits (the state has moved on, so from the same state again)
+    again = GpuStep(B=B, b=b, off=off, d=d, N=N, dtype="f32", version=version, eps=1e-6, rho=6.5, tau=0.07,
+                    tau_grad_scale=1.0 / N, ld_img=d + pad, u_img0=u0i, u_txt0=u0t, tau_img0=t_img, tau_txt0=t_txt)
+    again.set_inputs(img, txt, idx)
+    again.step(0.6)
+    assert all(np.array_equal(first[k], again.outputs()[k]) for k in ("d_img", "d_txt", "u_new_img", "u_new_txt"))
+
+
+@pytest.mark.parametrize("version", [V0, V2])
+def test_f32_gathered_state_on_several_tiles(version):
+    run_gathered(300, 130, 170, 72, version, "f32", TOL_F32)
+
+
 # Two draws of a 400-case random sweep of the fp32 path on which the loss nearly cancels (case A: tau mean(log) = -0.911
 # against 2 rho tau = +0.910; case B: 112 logarithms of values around 1 whose mean is 0.0035 against a mean magnitude
 # of 3.2).  An error relative to the loss itself reads 700 - 900 times the error of the terms there; relative to the
