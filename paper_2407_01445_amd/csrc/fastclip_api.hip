@@ -146,6 +146,30 @@ static void plan_f32(const fastclip_config& cfg, bool lean, Layout* L) {
   }
 }
 
+// 128 x 128-tile path: output tiles of the contraction, the split of its depth over workgroups, and who runs the state phase.
+static void plan_t128(const fastclip_config& cfg, bool lean, Layout* L) {
+  const int64_t nA = (cfg.B + 15) / 16, nB = (cfg.b + 15) / 16, cols = (cfg.d + 63) / 64;
+  double best_cost = 0.0;
+  for (int64_t rows = 64; rows <= 128; rows += 64) {
+    const int64_t tiles = 2 * ((cfg.b + rows - 1) / rows) * cols;
+    for (int64_t ns = 1; ns <= 16 && ns * 32 <= L->ldE; ++ns) {
+      if (ns > 1 && (lean || tiles * ns > 2048)) break;
+      const int64_t sA = (nA + ns * 8 - 1) / (ns * 8), sB = (nB + ns * 8 - 1) / (ns * 8);
+      const int64_t nq = sB * 128 < cfg.b ? sB * 128 : cfg.b;
+      // the state phase inside the contraction: 64-row tiles have room for the sums of 256 local anchors beside the rows'
+      const bool fused = rows == 64 && nq <= 256 && L->nparts <= 64;
+      // us: start, coefficients, sum over the waves and end of a workgroup; a 16-deep stage of its eight waves (the load path of
+      // a compute unit: 32 or 48 KiB); partial results; the state phase as a launch of its own
+      const double cost = (double)((tiles * ns + 255) / 256) * (rows == 64 ? 5.5 + 0.27 * (double)(sA + sB) : 7.0 + 0.38 * (double)(sA + sB)) +
+                          (ns > 1 ? 2.3 + 0.1 * (double)ns : 0.0) + (fused ? 0.0 : 4.7);
+      if (best_cost == 0.0 || cost < best_cost) {
+        best_cost = cost;
+        L->nsplit = (int)ns; L->out_rows = (int)rows; L->fused_state = fused;
+      }
+    }
+  }
+}
+
 static void make_layout(const fastclip_config& cfg, bool lean, Layout* L) {
   memset(L, 0, sizeof(*L));
   L->B = cfg.B; L->b = cfg.b; L->off = cfg.off; L->d = cfg.d; L->N = cfg.N;
@@ -165,36 +189,17 @@ static void make_layout(const fastclip_config& cfg, bool lean, Layout* L) {
   // chosen when the large tiles would occupy at most half of the compute units (measured: b = 128 .. 1024 of
   // B = 1024 .. 8192 at width 512 are 4 - 22 % faster, b = 640 of 5120, 120 large tiles, breaks even)
   const bool small_ok = L->bf16 && !L->gathered && !L->square && !L->fine && !(cfg.flags & FASTCLIP_TILES_256);
-  L->t128 = small_ok && ((cfg.flags & FASTCLIP_TILES_128) ? big_tiles < 192 : big_tiles <= 128);
+  // (the kernels address rows by 32-bit byte offsets and hold the coefficients of a workgroup's local anchors in LDS)
+  const int64_t ld_max = cfg.ld_img > cfg.ld_txt ? cfg.ld_img : cfg.ld_txt;
+  L->t128 = small_ok && ((cfg.flags & FASTCLIP_TILES_128) ? big_tiles < 192 : big_tiles <= 128) &&
+            cfg.B * ld_max < ((int64_t)1 << 30) && cfg.b <= kMaxLocalQ - 128;
   size_t at = 0;
   auto take = [&](size_t bytes) { size_t o = at; at += round_up(bytes, 256); return o; };
   const size_t fb = sizeof(float) * (size_t)L->bstride;
   if (L->t128) {
     L->nparts = (int)((cfg.B + 127) / 128);
     L->ldE = (int64_t)round_up((size_t)cfg.B, 64);
-    // Split of the contraction over its column range, in 32-deep stages.  Cost model in units of one stage time of a
-    // workgroup that has its compute unit to itself (0.65 us: a stage is the latency of its instructions, not its MFMA
-    // time); measured on b = 128 .. 1024 of B = 1024 .. 8192 at width 512.  Up to 256 workgroups run one per compute
-    // unit; a second one on a compute unit stretches both by 1.45; beyond 512 they run in rounds.  A tile's start and end
-    // cost 4; with more than one split the finalize kernel costs 5 + 0.42 per MiB of partial results it reads.  One split
-    // needs no finalize kernel (the tile is finished in place).
-    const int64_t stages = L->ldE / 32;
-    const int64_t tiles = ((cfg.b + 127) / 128) * ((cfg.d + 127) / 128) * 2;
-    const double tile_mib = 128.0 * 128.0 * 4.0 / (1024.0 * 1024.0);
-    int64_t best = 1;
-    double best_cost = 0.0;
-    for (int64_t ns = 1; ns <= kMaxSplit && ns <= stages; ++ns) {
-      const int64_t slice = (stages + ns - 1) / ns;
-      const int64_t used = (stages + slice - 1) / slice;
-      if (used != ns) continue;                                     // every split must get at least one stage
-      const int64_t wgs = tiles * ns;
-      const double stretch = wgs <= 256 ? 1.0 : (wgs <= 512 ? 1.0 + 0.45 * (double)(wgs - 256) / 256.0
-                                                            : 1.45 * (double)((wgs + 511) / 512));
-      const double cost = stretch * (double)slice + 4.0 + (ns > 1 ? 5.0 + 0.42 * tile_mib * (double)wgs : 0.0);
-      if (ns == 1 || cost < best_cost) { best = ns; best_cost = cost; }
-    }
-    L->nsplit = (int)best;
-    L->kslice = (stages + best - 1) / best;
+    plan_t128(cfg, lean, L);
   } else if (L->fine) {
     L->nparts = (int)((cfg.B + 127) / 128);
     L->ldE = (int64_t)round_up((size_t)cfg.B, 64);
@@ -245,9 +250,11 @@ static void make_layout(const fastclip_config& cfg, bool lean, Layout* L) {
   // Every 64 x 64 block of the fold needs the coefficients of 128 anchor sides.  Forming them inside the fold saves a
   // launch, but every block then sums those anchors' partial sums again (b^2 / 32 anchor sides x nparts floats in
   // all, against 2 b x nparts once): worth it only while that stays small.
-  L->fused_state = L->bf16 && L->nparts <= 64 &&
-                   (double)cfg.b * (double)cfg.b / 32.0 * (double)L->nparts * 4.0 <= 2.0 * 1024 * 1024;
-  L->nstate_blocks = L->fused_state ? (int)((cfg.b + 63) / 64) : state_blocks(cfg.b, L->nparts);
+  if (!L->t128)
+    L->fused_state = L->bf16 && L->nparts <= 64 &&
+                     (double)cfg.b * (double)cfg.b / 32.0 * (double)L->nparts * 4.0 <= 2.0 * 1024 * 1024;
+  // scalar partials: t128 leaves the terms of every anchor side
+  L->nstate_blocks = L->fused_state ? (L->t128 ? (int)(2 * cfg.b) : (int)((cfg.b + 63) / 64)) : state_blocks(cfg.b, L->nparts);
   L->diag = take(fb); L->tau1 = take(fb); L->tau2 = take(fb); L->k1 = take(fb); L->k2 = take(fb);
   L->uold1 = take(fb); L->uold2 = take(fb);
   L->sums = take(fb * 4 * (size_t)L->nparts * (!L->bf16 && L->nparts > 1 ? 2 : 1));
@@ -259,9 +266,11 @@ static void make_layout(const fastclip_config& cfg, bool lean, Layout* L) {
     // fragment-ordered strips: anchors padded to whole 256-row tiles
     const size_t rows = round_up((size_t)cfg.b, 256);
     for (int s = 0; s < 2; ++s) L->E[s] = take(esz * rows * (size_t)L->ldE);
-    if (L->t128) {     // [nsplit][2 sides][b to 128][d to 128] floats, only with more than one split
-      if (L->nsplit > 1)
-        L->Opart[0] = take(sizeof(float) * (size_t)L->nsplit * 2 * round_up((size_t)cfg.b, 128) * round_up((size_t)cfg.d, 128));
+    if (L->t128) {     // arrival counters of the output tiles and of the scalars; [2][tiles][nsplit][64 x 64] floats
+      const int64_t tiles = 2 * (L->out_rows / 64) * ((cfg.b + L->out_rows - 1) / L->out_rows) * ((cfg.d + 63) / 64);
+      L->narrived = (int)tiles + 1;
+      L->arrived = take(sizeof(unsigned) * (size_t)L->narrived);
+      if (L->nsplit > 1) L->Opart[0] = take(sizeof(float) * (size_t)L->nsplit * (size_t)tiles * 64 * 64);
     } else if (L->fine) {     // [nsplit][2 sides][b to 64][d to 64] floats, only with more than one split
       if (L->nsplit > 1)
         L->Opart[0] = take(sizeof(float) * (size_t)L->nsplit * 2 * round_up((size_t)cfg.b, 64) * round_up((size_t)cfg.d, 64));
@@ -294,9 +303,10 @@ static void make_layout(const fastclip_config& cfg, bool lean, Layout* L) {
 
 // The fp32 path's workspace: partial sums and splits take a few per cent on top of the stored strips.  A configuration that
 // fits the static array without them and would not fit with them goes without, so that fastclip_step_static keeps taking it.
+// So does one of the 128 x 128-tile path with its splits.
 void make_layout(const fastclip_config& cfg, Layout* L) {
   make_layout(cfg, false, L);
-  if (!L->bf16 && L->total > (size_t)FASTCLIP_STATIC_SCRATCH_BYTES) {
+  if ((!L->bf16 || L->t128) && L->total > (size_t)FASTCLIP_STATIC_SCRATCH_BYTES) {
     Layout small;
     make_layout(cfg, true, &small);
     if (small.total <= (size_t)FASTCLIP_STATIC_SCRATCH_BYTES) *L = small;
@@ -348,8 +358,7 @@ static fastclip_status run_step(const fastclip_config* cfg, const fastclip_buffe
   if (c.L.t128) {
     launch_strips_t128_bf16(c);           mark(FASTCLIP_PHASE_STRIPS);
     if (!c.L.fused_state) { launch_state(c); mark(FASTCLIP_PHASE_STATE); }
-    launch_fold_bf16(c);                  mark(FASTCLIP_PHASE_LOCAL);   // with fused_state: the state phase as well
-    launch_contract_t128_bf16(c);         mark(FASTCLIP_PHASE_CONTRACT);  // outputs and scalars included
+    launch_contract_t128_bf16(c);         mark(FASTCLIP_PHASE_CONTRACT);  // outputs and scalars (and the state phase) included
     launch_norm_backward(c);
   } else if (c.L.fine) {
     launch_strips_fine_bf16(c);           mark(FASTCLIP_PHASE_STRIPS);

@@ -12,6 +12,7 @@ typedef uint16_t bf16_t;  // raw bf16 bits in memory
 
 constexpr int kTileContrasts = 256;  // contrast rows per workgroup tile of the strip kernel
 constexpr int kMaxSplit = 64;
+constexpr int kMaxLocalQ = 2560;     // 128 x 128-tile path: local anchors whose coefficients a workgroup of the contraction holds
 
 // State kernel: threads per anchor side that share the work of adding up that side's partial sums (a power of two up to
 // 32, a quarter of the partial sums at most so that every thread has four loads of each quantity in flight); a block
@@ -47,14 +48,18 @@ struct Layout {
   int64_t ldE;       // contrast columns of the stored exp strips (MFMA path: multiple of 64; fp32 path: B)
   int nsplit;        // split of the contraction over its column range
   int64_t kslice;    // 32-deep stages per split (fp32 path: stages of the gradient kernel's depth)
-  int nstate_blocks; // scalar partials: one per block of the state kernel, or per diagonal block of the fused fold
-  int fused_state;   // 1: MFMA path, few anchors and few partial sums: the fold kernel runs the state phase itself
+  int nstate_blocks; // scalar partials: one per block of the state kernel, per diagonal block of the fused fold, or (t128 with
+                     // fused_state) per anchor side
+  int fused_state;   // 1: MFMA path, few anchors and few partial sums: the fold kernel (t128: the contraction) runs the
+                     //    state phase itself
   int gathered;      // 1: contrast-side estimator over every global anchor (FASTCLIP_GATHERED_STATE and b < B)
   int fine;          // 1: MFMA path on fine tiles (kernels_fine.hip): 128 x 128 strip tiles, 64 x 64 output tiles of the
                      //    contraction; nparts counts 128-column tiles, nsplit / kslice count 64-deep stages, and with one
                      //    split there are no partial results
-  int t128;          // 1: MFMA path on 128 x 128 tiles (kernels_tiles128.hip); nparts counts 128-column tiles, nsplit /
-                     //    kslice count 32-deep stages, and with one split there are no partial results
+  int t128;          // 1: MFMA path on 128 x 128 strip tiles (kernels_tiles128.hip); nparts counts 128-column tiles, the
+                     //    contraction's depth is cut into nsplit x 8 slices of 16-deep stages, and with one split there
+                     //    are no partial results
+  int out_rows;      // t128: rows of an output tile of the contraction, 64 or 128
   int square;        // 1: b == B and the similarity matrix is formed once.  MFMA path: F[0] holds l2(j, p) in the
                      //    layout of E[0] until the fold transposes it into E[1]; fp32 path: E[1] holds it as [p][j]
   int64_t ncol;      // gathered: entries per column-parameter array (B rounded up to whole 256-column tiles)
@@ -62,13 +67,14 @@ struct Layout {
   size_t uold1, uold2;               // float[bstride]: u^t of the batch's samples (gathered with the temperatures)
   size_t sums;                       // float[4][nparts][bstride]: sum e1, sum x1 e1, sum e2, sum x2 e2
                                      // (fp32 path with nparts > 1: double)
-  size_t arrived;                    // unsigned[narrived]: arrival counters of the gradient tiles, zeroed by k_prep
+  size_t arrived;                    // unsigned[narrived]: arrival counters of the output tiles, zeroed by k_prep
   int narrived;
   size_t c1, c2, dcoef;              // float[bstride]
   size_t red;                        // double[nstate_blocks][2]
   size_t E[2];                       // fp32 path: float [b][ldE]; MFMA path: fragment-ordered bf16 strips
   size_t Opart[2];                   // float [nsplit][partial_split_floats(b, d)]   (MFMA path)
                                      // fp32 path with nsplit > 1: Opart[0] is double [nsplit][2][tiles][grad_tile^2]
+                                     // t128 with nsplit > 1: Opart[0] is float [2][tiles of 64 rows][nsplit][64 * 64]
   // gathered: per global row j (= contrast column of the strips) and side s, in tiles of 256 columns
   // [s][tile][4][256]: log2(e)/tau_j, s_jj log2(e)/tau_j, c_j (0 for local rows and beyond B), unused.
   // Side 0 describes the text anchors j (l2(j, .), weights of d_img), side 1 the image anchors (l1(j, .), d_txt).
@@ -117,7 +123,7 @@ void launch_contract_bf16(const StepCtx& c);   // MFMA path: strips x X contract
 void launch_strips_fine_bf16(const StepCtx& c);    // MFMA path, fine tiles: exp strips + row sums
 void launch_contract_fine_bf16(const StepCtx& c);  // MFMA path, fine tiles: contractions, outputs and scalars
 void launch_strips_t128_bf16(const StepCtx& c);    // MFMA path, 128 x 128 tiles: exp strips + row sums
-void launch_contract_t128_bf16(const StepCtx& c);  // MFMA path, 128 x 128 tiles: contractions, outputs and scalars
+void launch_contract_t128_bf16(const StepCtx& c);  // ... : (state phase,) contractions, outputs and scalars
 void launch_norm_backward(const StepCtx& c);       // gradients through the L2 normalisation, if asked for
 void launch_finalize_bf16(const StepCtx& c);   // MFMA path: combine + scalars
 

@@ -1,184 +1,110 @@
-// MFMA kernels of the FCCO step on 128 x 128 tiles, for batches whose 256 x 256 tiles would leave most of the chip idle
-// (the shapes the paper trains at: 128 - 640 anchors per worker of a global batch of 1024 - 5120, width 512):
+// MFMA kernels of the FCCO step for batches whose 256 x 256 tiles would leave most of the chip idle (the shapes the paper
+// trains at: 128 - 640 anchors per worker of a global batch of 1024 - 5120, width 512):
 //
-//  k_strips_t128_bf16    the similarity strips of Proc. 1: l = exp((s - s_ii) / tau), the per-anchor sums of l and
-//                        (s - s_ii) l, l stored in the fragment order of the contraction; any ragged edge;
-//  k_contract_t128_bf16  the gradient contractions of Eqs. 2 - 7 on 128 x 128 output tiles.  With one split of the column
-//                        range a workgroup owns its output tile for good and finishes it in place (coefficient,
-//                        diagonal terms, the step's scalars): no partial results, no further kernel.  With several
-//                        splits the partial tiles go to the workspace and k_finalize_t128_bf16 adds them up.
+//  k_strips_t128_bf16    the similarity strips of Proc. 1 on 128 x 128 tiles: l = exp((s - s_ii) / tau), the per-anchor
+//                        sums of l and (s - s_ii) l, l stored in the fragment order of the contraction; any ragged edge;
+//  k_contract_t128_bf16  everything behind them on 64 x 64 output tiles: the state phase (Eq. 1, coefficients, Eq. 9,
+//                        loss), the gradient contractions of Eqs. 2 - 7 with the contrast-side term of the local anchors
+//                        as further contraction depth, the outputs and the scalars.
 //
-// Both run the pipeline of the large-tile contraction in small: a ring of five LDS slots, each one 32-deep stage of
-// both operands (16 KiB), filled by direct-to-LDS loads four stages ahead, one barrier per stage; four wavefronts with
-// 2 x 2 accumulator blocks each.  Two workgroups share a compute unit (80 KiB of LDS each), which hides what the plain
-// instruction order of the loop leaves open.  Layouts (stored strips, accumulator blocks, LDS images) are those of the
-// large-tile kernels: see kernels_mfma.hip.
+// What bounds these batches is not bytes or flops but the chain of dependent launches and, inside a launch, the chain of
+// dependent instructions: a launch costs about 3 us, and so does a kernel that waits for memory twice.  So the whole
+// step behind the strips is one launch (it was a fold kernel with the state phase, a contraction and a finalize kernel),
+// and either kernel keeps as much in flight as the LDS holds: the strips two steps of 128 in k, the contraction 16 KiB
+// per wave, every wave on its own slice of the depth with its own LDS region, so that its main loop has no barrier.
+//
+// Column order.  The stored strips and the sums of this path number the contrasts from the worker's own rows on: column c is
+// global row (off + c) mod B.  The local anchors are columns 0 .. b - 1 whatever `off` is, so the transposing reads of
+// the contrast-side term are always aligned, and a row's own column is its own number.  Rows are addressed by 32-bit lane
+// offsets from the matrix (B ld < 2^30 elements, checked in make_layout).
 #include <string.h>
+
+#include <type_traits>
 
 #include "mfma_common.hpp"
 #include "state_common.hpp"
 
 namespace fc {
 
-constexpr int kT = 128;                         // rows of either operand of a strip tile; rows and columns of an output tile
-constexpr int kHalf = kT * BK * 2;              // one operand of a stage: 8 KiB
-constexpr int kSlot = 2 * kHalf;                // 16 KiB
-constexpr int kSlots = 5;                       // stages are requested four ahead (eight ahead in a ring of nine measured no faster)
-constexpr int kSmallRing = kSlots * kSlot;      // 80 KiB: two workgroups per compute unit
+constexpr int kT = 128;                         // anchors and contrasts of a strip tile
+constexpr int kD = 64;                          // depth of a strip stage: whole 128-byte lines
+constexpr int kPanel = kT * kD * 2;             // one operand of a stage: 16 KiB
+constexpr int kStage = 2 * kPanel;
+constexpr int kStep = 2 * kStage;               // a step = one stage for either group of waves
+constexpr int kStepRing = 2 * kStep;            // 128 KiB
 
-// "at most 4 n loads of this wave in flight", n = 0 .. 7 (s_waitcnt takes an immediate)
-__device__ __forceinline__ void wait_younger_stages(int n) {
-  switch (n) {
-    case 0: __builtin_amdgcn_s_waitcnt(0x0f70); break;
-    case 1: __builtin_amdgcn_s_waitcnt(0x0f74); break;
-    case 2: __builtin_amdgcn_s_waitcnt(0x0f78); break;
-    case 3: __builtin_amdgcn_s_waitcnt(0x0f7c); break;
-    case 4: __builtin_amdgcn_s_waitcnt(0x4f70); break;
-    case 5: __builtin_amdgcn_s_waitcnt(0x4f74); break;
-    case 6: __builtin_amdgcn_s_waitcnt(0x4f78); break;
-    default: __builtin_amdgcn_s_waitcnt(0x4f7c); break;
-  }
+// The wave's LDS reads have returned (lgkmcnt 0): what it read from may be written again.
+__device__ __forceinline__ void wave_reads_done() {
+  FC_FENCE();
+  __builtin_amdgcn_s_waitcnt(0xc07f);
+  __builtin_amdgcn_wave_barrier();
+  FC_FENCE();
 }
 
-// acc += (A operand tile) x (B operand tile)^T over the stages [s0, s0 + S), S >= 1.  Tile::dma(i, stage, slot address),
-// i = 0 .. 3, issues this wave's four wave loads of a stage.  Stage s lives in slot s mod 5; its loads are issued four
-// stages before it is read, right after the barrier of stage s - 4 ... which every wave passes only after its last read
-// of stage s - 5, the slot's previous tenant.  Vector memory operations complete in order, so "stage s has landed" is
-// "at most 4 x (stages requested after it) loads in flight".  On return no wave reads the ring any more.
-template <typename Tile>
-__device__ __forceinline__ void small_ring(f32x16 (&acc)[2][2], const Tile& T, char* ring, uint32_t ring_addr, int s0,
-                                           int S) {
-  constexpr int kAhead = kSlots - 1;
-#pragma unroll
-  for (int p = 0; p < kAhead; ++p)
-    if (p < S) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) T.dma(i, s0 + p, ring_addr + (uint32_t)(p * kSlot));
-    }
-  int slot = 0, fill = kAhead;                  // slot of stage s; slot that the stage kAhead on goes to
-  for (int s = 0; s < S; ++s) {
-    wait_younger_stages(S - 1 - s < kAhead - 1 ? S - 1 - s : kAhead - 1);
-    __builtin_amdgcn_s_barrier();
-    FC_FENCE();
-    if (s + kAhead < S) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) T.dma(i, s0 + s + kAhead, ring_addr + (uint32_t)(fill * kSlot));
-    }
-    const char* sl = ring + slot * kSlot;
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      bf16x8 a[2], b[2];
-#pragma unroll
-      for (int t = 0; t < 2; ++t) { a[t] = T.read_a(sl, t, kk); b[t] = T.read_b(sl, t, kk); }
-#pragma unroll
-      for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-        for (int tj = 0; tj < 2; ++tj)
-          acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ti], b[tj], acc[ti][tj], 0, 0, 0);
-    }
-    FC_FENCE();
-    slot = slot + 1 == kSlots ? 0 : slot + 1;
-    fill = fill + 1 == kSlots ? 0 : fill + 1;
-  }
-  __syncthreads();
-}
+// LDS image of a panel (128 rows x 128 bytes): 16-byte chunk c of row r at chunk position c ^ ((r >> 1) & 7), so that the 16
+// consecutive rows of an operand read cover a 256-byte bank window.
+__device__ __forceinline__ int p_swz(int row) { return (row >> 1) & 7; }
 
-// The same for stages at a ragged end: one at a time through registers, zero fill outside (Tile::fill_guarded).
-template <typename Tile>
-__device__ __forceinline__ void small_guarded(f32x16 (&acc)[2][2], const Tile& T, char* ring, int s0, int S, int tid) {
-  for (int s = 0; s < S; ++s) {
-    __syncthreads();
-    T.fill_guarded(s0 + s, ring, tid);
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      bf16x8 a[2], b[2];
-#pragma unroll
-      for (int t = 0; t < 2; ++t) { a[t] = T.read_a(ring, t, kk); b[t] = T.read_b(ring, t, kk); }
-#pragma unroll
-      for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-        for (int tj = 0; tj < 2; ++tj)
-          acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ti], b[tj], acc[ti][tj], 0, 0, 0);
-    }
-  }
-  __syncthreads();
-}
-
-// ----------------------------------------------------------------------------------------------------------------
-// Strip tile: both operands are K-contiguous row tiles of 128 rows x 32 of k (64 bytes per row, LDS image rt_off).
-// A operand of the MFMA = contrast rows, B operand = anchor rows.  A wave load takes 16 rows; wave w issues the loads
-// 2 w, 2 w + 1 of either operand.
-struct StripTile128 {
-  const bf16_t *X, *A;     // wave-uniform: first contrast row / first anchor row of the tile
-  int64_t ldx, lda, x_rows, a_rows, d;
-  uint32_t ox[2], oa[2];   // per-lane byte offsets of the wave loads (relative to X / A, stage 0)
-  uint32_t lx[2], la[2];   // LDS byte offsets inside a slot (wave-uniform)
-  int wr, wc, lr, hk;
-
-  __device__ __forceinline__ void setup(const bf16_t* Xc, int64_t ldx_, int64_t c0, int64_t B, const bf16_t* An,
-                                        int64_t lda_, int64_t a0, int64_t rows_a, int64_t d_, int tid) {
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    wr = wave >> 1; wc = wave & 1; lr = lane & 31; hk = lane >> 5;
-    X = Xc + c0 * ldx_; ldx = ldx_; x_rows = B - c0;
-    A = An + a0 * lda_; lda = lda_; a_rows = rows_a - a0;
-    d = d_;
-    // a row of the tile that does not exist is fetched as the tile's last existing row (x_rows, a_rows >= 1): what it
-    // contributes lands in elements that the guarded epilogue discards
-    const int x_last = (int)(x_rows < kT ? x_rows : kT) - 1, a_last = (int)(a_rows < kT ? a_rows : kT) - 1;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int j = wave * 2 + i;                      // wave load j covers rows 16 j .. 16 j + 15 of the tile
-      const int row = 16 * j + (lane >> 2);
-      const int chunk = (lane & 3) ^ rt_swz(row);      // logical chunk fetched into position (lane & 3)
-      ox[i] = (uint32_t)((row < x_last ? row : x_last) * (int)ldx_ + chunk * 8) * 2u;
-      oa[i] = (uint32_t)((row < a_last ? row : a_last) * (int)lda_ + chunk * 8) * 2u;
-      lx[i] = (uint32_t)(j * 1024);
-      la[i] = (uint32_t)(kHalf + j * 1024);
-    }
-  }
-  __device__ __forceinline__ void dma(int i, int stage, uint32_t slot) const {
-    if (i < 2) dma16(X + (int64_t)stage * BK, ox[i], slot + lx[i]);
-    else dma16(A + (int64_t)stage * BK, oa[i - 2], slot + la[i - 2]);
-  }
-  __device__ __forceinline__ void fill_guarded(int stage, char* slot, int tid) const {
-    const int chunk = tid & 3;
-    const int64_t k = (int64_t)stage * BK + chunk * 8;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int row = (tid >> 2) + 64 * i;
-      u32x4 vx = {0u, 0u, 0u, 0u}, va = {0u, 0u, 0u, 0u};
-      if (k < d && row < x_rows) vx = *(const u32x4*)(X + row * ldx + k);
-      if (k < d && row < a_rows) va = *(const u32x4*)(A + row * lda + k);
-      *(u32x4*)(slot + rt_off(row, chunk)) = vx;
-      *(u32x4*)(slot + kHalf + rt_off(row, chunk)) = va;
-    }
-  }
-  __device__ __forceinline__ bf16x8 read_a(const char* slot, int t, int kk) const {
-    return *(const bf16x8*)(slot + rt_off(wr * 64 + t * 32 + lr, kk * 2 + hk));
-  }
-  __device__ __forceinline__ bf16x8 read_b(const char* slot, int t, int kk) const {
-    return *(const bf16x8*)(slot + kHalf + rt_off(wc * 64 + t * 32 + lr, kk * 2 + hk));
-  }
-};
-
-__global__ void __launch_bounds__(256, 2) k_strips_t128_bf16(StripArgs a, int nAT, int nCT) {
-  __shared__ __attribute__((aligned(1024))) char ring[kSmallRing];
-  // after the main loop the ring is free and holds the epilogue's scalars and cross-wave sums
-  float* sk = (float*)ring;                                          // [128] log2(e)/tau of the tile's anchors
-  float* sdiag = sk + kT;                                            // [128] s_pp
-  float (*sred)[2][256] = (float (*)[2][256])(ring + 1024);          // [contrast half][quantity][anchor in the tile]
+// One workgroup per tile (128 anchors against 128 contrasts of one strip), eight waves = two groups of 2 x 2 waves of
+// 64 x 64: either group takes every other 64-deep stage, so that a SIMD always has a second wave to issue from, an operand
+// read serves two products, and the loop has half the barriers; afterwards the groups exchange halves of their
+// accumulators and each finishes half of the tile's columns.  Measured at 128 anchors of 1024 pairs, d = 512, against
+// four waves on 32-deep stages through a ring of five: 12.0 -> 8.5 us, of which (in-kernel counters, 2.4 GHz) 0.4 set-up, 1.1
+// until the first step is there, 2.6 in the four steps (1.7 of products), 0.7 exchange, 1.5 exponentials, 0.5 sums.
+__global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(StripArgs a) {
+  __shared__ __attribute__((aligned(1024))) char ring[kStepRing];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wr = wave >> 1, wc = wave & 1;
-  const int t = blockIdx.x, per_strip = nAT * nCT;
-  const int strip = t / per_strip, at = t % nAT, ct = (t / nAT) % nCT;
-  const int64_t a0 = (int64_t)at * kT, c0 = (int64_t)ct * kT;
-  const int S = (int)((a.d + BK - 1) / BK), S_ring = (int)(a.d / BK);
-  StripTile128 T;
-  // anchor rows exist up to the end of the global batch (rows beyond b belong to other workers; their results are
-  // discarded like those of replaced rows)
-  T.setup(a.contrasts[strip], a.ld_contrast[strip], c0, a.B, a.anchors[strip], a.ld_anchor[strip], a0, a.B - a.off, a.d,
-          tid);
+  const int kg = wave >> 2, q4 = wave & 3, wr = q4 >> 1, wc = q4 & 1, lr = lane & 31, hk = lane >> 5;
+  const int ct = blockIdx.x, at = blockIdx.y, strip = blockIdx.z;    // no divisions: they are serial instructions at the start
+  const int a0 = at * kT, c0 = ct * kT;
+  const int B = (int)a.B, b = (int)a.b, off = (int)a.off, d = (int)a.d;
+  // pointers pinned in scalar registers: left in the argument segment they are loaded again behind every memory fence
+  const bf16_t *Xm = wave_uniform(a.contrasts[strip]), *Am = wave_uniform(a.anchors[strip]);
+  const int ldx = (int)a.ld_contrast[strip], lda = (int)a.ld_anchor[strip];
+  const uint32_t ring_addr = lds_addr(ring);
+  // wave loads of a stage: 8 rows x 128 bytes each, four per wave and operand.  A row that does not exist is fetched as
+  // the last one that does; what it yields is masked in the epilogue.
+  uint32_t ox[4], oa[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int row = 8 * (4 * q4 + i) + (lane >> 3);
+    const uint32_t piece = (uint32_t)(((lane & 7) ^ p_swz(row)) * 16);
+    int g = off + (c0 + row < B ? c0 + row : B - 1);
+    g -= g >= B ? B : 0;
+    ox[i] = (uint32_t)(g * ldx) * 2u + piece;
+    oa[i] = (uint32_t)((a0 + row < b ? a0 + row : b - 1) * lda) * 2u + piece;
+  }
+  const int S = (d + kD - 1) / kD, steps = (S + 1) / 2;
+  const int tail = (d % kD) / 8;                  // 16-byte chunks of the last stage that exist (0: all eight)
+  // the epilogue's per-anchor scalars (a lane's anchors are a0 + 64 wc + 32 tj + lr), requested ahead of everything else
+  float kk[2], dk[2];
+#pragma unroll
+  for (int tj = 0; tj < 2; ++tj) {
+    const int m = a0 + wc * 64 + tj * 32 + lr;
+    kk[tj] = m < b ? a.kscale[strip][m] : 0.f;
+    dk[tj] = m < b ? a.diag[m] : 0.f;
+  }
+  // Load i (0 .. 3: contrasts, 4 .. 7: anchors) of this wave for a step.  A stage that does not exist is requested as the last
+  // one and not used: the number of loads per step is constant.
+  const uint32_t my = ring_addr + (uint32_t)(kg * kStage + q4 * 4096);
+  auto request = [&](auto edge, int step, int i) {
+    int st = step * 2 + kg;
+    uint32_t o = i < 4 ? ox[i & 3] : oa[i & 3];
+    if constexpr (decltype(edge)::value) {
+      st = st < S ? st : S - 1;
+      if (tail && st == S - 1) {                  // a chunk beyond the row is fetched as the stage's first one, and not used
+        const int row = 8 * (4 * q4 + (i & 3)) + (lane >> 3), c = (lane & 7) ^ p_swz(row);
+        if (c >= tail) o -= (uint32_t)c * 16u;
+      }
+    }
+    dma16((i < 4 ? Xm : Am) + st * kD, o, my + (uint32_t)((step & 1) * kStep + (i < 4 ? 0 : kPanel) + (i & 3) * 1024));
+  };
+#pragma unroll
+  for (int i = 0; i < 8; ++i) request(std::true_type{}, 0, i);
+  if (steps > 1) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) request(std::true_type{}, 1, i);
+  }
   f32x16 acc[2][2];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -186,23 +112,144 @@ __global__ void __launch_bounds__(256, 2) k_strips_t128_bf16(StripArgs a, int nA
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  if (S_ring > 0) small_ring(acc, T, ring, lds_addr(ring), 0, S_ring);
-  if (S_ring < S) small_guarded(acc, T, ring, S_ring, S - S_ring, tid);
-  if (tid < kT) {
-    const int64_t m = a0 + tid;
-    sk[tid] = m < a.b ? a.kscale[strip][m] : 0.f;
-    sdiag[tid] = m < a.b ? a.diag[m] : 0.f;
+
+  if (steps > 1) FC_WAIT_VMCNT8(); else FC_WAIT_VMCNT0();
+  __syncthreads();
+  FC_FENCE();
+  const int rx = wr * 64 + lr, ra = wc * 64 + lr;     // rows 32 further on share the swizzle
+  // EDGE: the step holds the last stage (which may end inside, or not exist for group 1)
+  auto read = [&](auto edge, int s, int kq, bf16x8 (&x)[2], bf16x8 (&y)[2]) {
+    const char* px = ring + (s & 1) * kStep + kg * kStage + rx * 128;
+    const char* pa = ring + (s & 1) * kStep + kg * kStage + kPanel + ra * 128;
+    const int c = 2 * kq + hk, st = s * 2 + kg;
+    const int valid = st >= S ? 0 : (tail && st == S - 1 ? tail : 8);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      u32x4 vx = *(const u32x4*)(px + i * 4096 + ((c ^ p_swz(rx)) << 4));
+      u32x4 va = *(const u32x4*)(pa + i * 4096 + ((c ^ p_swz(ra)) << 4));
+      if constexpr (decltype(edge)::value) {
+        const u32x4 z = {0u, 0u, 0u, 0u};
+        vx = c < valid ? vx : z;
+        va = c < valid ? va : z;
+      }
+      x[i] = __builtin_bit_cast(bf16x8, vx);
+      y[i] = __builtin_bit_cast(bf16x8, va);
+    }
+  };
+  // Four products on (x, y); loads r, r + 1 of step `next` are dealt out between them: a direct-to-LDS load holds its wave for
+  // about a hundred cycles when all eight waves issue, which the SIMD's other wave fills with its products.
+  auto multiply = [&](auto edge, const bf16x8 (&x)[2], const bf16x8 (&y)[2], bool more, int next, int r) {
+    acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[0], acc[0][0], 0, 0, 0);
+    acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[1], acc[0][1], 0, 0, 0);
+    FC_PIN();
+    if (more) request(edge, next, r);
+    FC_PIN();
+    acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], y[0], acc[1][0], 0, 0, 0);
+    acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], y[1], acc[1][1], 0, 0, 0);
+    FC_PIN();
+    if (more) request(edge, next, r + 1);
+    FC_PIN();
+  };
+  // Step s: loads 2 .. 7 of step s + 1 go out between its first products (0 and 1 went out behind the barrier of step s - 1);
+  // three quarters in, the step's panels have been read and the next step's have landed.
+  auto step = [&](auto edge_here, auto edge_next, int s) {
+    bf16x8 x0[2], y0[2], x1[2], y1[2];
+    const bool fill = s > 0 && s + 1 < steps;
+    read(edge_here, s, 0, x0, y0);
+    read(edge_here, s, 1, x1, y1);
+    multiply(edge_next, x0, y0, fill, s + 1, 2);
+    read(edge_here, s, 2, x0, y0);
+    multiply(edge_next, x1, y1, fill, s + 1, 4);
+    read(edge_here, s, 3, x1, y1);
+    multiply(edge_next, x0, y0, fill, s + 1, 6);
+    if (s + 1 < steps) {
+      FC_WAIT_VMCNT0();
+      __syncthreads();
+      FC_FENCE();
+    }
+    multiply(std::true_type{}, x1, y1, s + 2 < steps, s + 2, 0);
+  };
+  int s = 0;
+  for (; s + 2 < steps; ++s) step(std::false_type{}, std::false_type{}, s);
+  for (; s + 1 < steps; ++s) step(std::false_type{}, std::true_type{}, s);
+  step(std::true_type{}, std::true_type{}, s);
+  // ---- the groups exchange accumulator halves: group g finishes the columns 16 g .. 16 g + 15 of every 32 x 32 block
+  __syncthreads();
+  auto give = [&](auto group) {
+    constexpr int FROM = decltype(group)::value ? 0 : 8;        // the half that the other group finishes
+    float* mine = (float*)(ring + wave * 8192) + lane * 4;
+#pragma unroll
+    for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+      for (int tj = 0; tj < 2; ++tj)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const f32x4 w = {acc[ti][tj][FROM + 4 * h], acc[ti][tj][FROM + 4 * h + 1], acc[ti][tj][FROM + 4 * h + 2],
+                           acc[ti][tj][FROM + 4 * h + 3]};
+          *(f32x4*)(mine + ((ti * 2 + tj) * 2 + h) * 256) = w;
+        }
+  };
+  if (kg) give(std::true_type{}); else give(std::false_type{});
+  __syncthreads();
+  const float* other = (const float*)(ring + (wave ^ 4) * 8192);
+  float (*sred)[2][kT] = (float (*)[2][kT])(ring + 8 * 8192);        // [contrast half, group][quantity][anchor in the tile]
+  bf16_t* __restrict__ E = a.E[strip];
+  // MASK: the tile reaches beyond the batch or the local anchors, or holds anchors' own columns (B_{i-} excludes i)
+  auto finish = [&](auto masked, auto group) {
+    constexpr bool MASK = decltype(masked)::value;
+    constexpr int OWN = decltype(group)::value ? 8 : 0;
+#pragma unroll
+    for (int tj = 0; tj < 2; ++tj) {
+      const int al = wc * 64 + tj * 32 + lr, anchor = a0 + al;
+      const float k = kk[tj], dkk = dk[tj] * k;
+      float sg[4] = {0.f, 0.f, 0.f, 0.f}, sx[4] = {0.f, 0.f, 0.f, 0.f};   // independent chains
+#pragma unroll
+      for (int ti = 0; ti < 2; ++ti) {
+        const int c_first = c0 + wr * 64 + ti * 32 + kg * 16 + 4 * hk;
+        uint32_t pk[4];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const f32x4 o = *(const f32x4*)(other + ((ti * 2 + tj) * 2 + h) * 256 + lane * 4);
+          float e[4];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const float x = fmaf(acc[ti][tj][OWN + 4 * h + q] + o[q], k, -dkk);
+            e[q] = __builtin_amdgcn_exp2f(x);
+            if (MASK) {
+              const int c = c_first + 8 * h + q;
+              e[q] = (c < B && anchor < b && c != anchor) ? e[q] : 0.f;
+            }
+            sg[q] += e[q];
+            sx[q] = fmaf(x, e[q], sx[q]);
+          }
+          pk[2 * h] = pack_bf16x2(e[0], e[1]);
+          pk[2 * h + 1] = pack_bf16x2(e[2], e[3]);
+        }
+        const int cb = ((c0 + wr * 64) >> 4) + 2 * ti + kg;
+        const u32x4 w = {pk[0], pk[1], pk[2], pk[3]};
+        if (!MASK || 16 * cb < (int)a.ldE)
+          *(u32x4*)(E + (((int64_t)((a0 + wc * 64) / 32 + tj) * a.nCB + cb) * 64 + lane) * 8) = w;
+      }
+      const float g1 = (sg[0] + sg[1]) + (sg[2] + sg[3]), x1 = (sx[0] + sx[1]) + (sx[2] + sx[3]);
+      const float g2 = g1 + __shfl_xor(g1, 32), x2 = x1 + __shfl_xor(x1, 32);
+      if (hk == 0) {
+        sred[wr * 2 + kg][0][al] = g2;
+        sred[wr * 2 + kg][1][al] = k > 0.f ? x2 * __builtin_amdgcn_rcpf(k) : 0.f;   // sum of (s - s_pp) l
+      }
+    }
+  };
+  const bool whole = a0 + kT <= b && c0 + kT <= B && at != ct;
+  if (kg) {
+    if (whole) finish(std::false_type{}, std::true_type{}); else finish(std::true_type{}, std::true_type{});
+  } else {
+    if (whole) finish(std::false_type{}, std::false_type{}); else finish(std::true_type{}, std::false_type{});
   }
   __syncthreads();
-  strip_epilogue<true, 2, 2>(a, acc, sk, sdiag, sred[wr], strip, a0, c0, wr * 64, wc * 64, lane);
-  __syncthreads();
-  if (tid < kT) {
-    const int64_t m = a0 + tid;
-    if (m < a.b) {
-#pragma unroll
-      for (int q = 0; q < 2; ++q)
-        a.sums[((size_t)(2 * strip + q) * a.nparts + ct) * a.bstride + m] = sred[0][q][tid] + sred[1][q][tid];
-    }
+  if (tid < 2 * kT) {
+    const int q = tid >> 7, m = tid & (kT - 1);
+    if (a0 + m < b)
+      a.sums[((size_t)(2 * strip + q) * a.nparts + ct) * a.bstride + a0 + m] =
+          (sred[0][q][m] + sred[1][q][m]) + (sred[2][q][m] + sred[3][q][m]);
   }
 }
 
@@ -225,183 +272,415 @@ void launch_strips_t128_bf16(const StepCtx& c) {
   a.ldE = L.ldE;
   a.sums = (float*)(c.ws + L.sums);
   a.nparts = L.nparts; a.bstride = L.bstride; a.b = L.b; a.B = L.B; a.d = L.d; a.off = L.off;
-  const int nAT = (int)((L.b + kT - 1) / kT), nCT = (int)((L.B + kT - 1) / kT);
-  hipLaunchKernelGGL(k_strips_t128_bf16, dim3((unsigned)(2 * nAT * nCT)), dim3(256), 0, c.s, a, nAT, nCT);
+  a.nAT = (int)((L.b + kT - 1) / kT);
+  a.nCT = (int)((L.B + kT - 1) / kT);
+  hipLaunchKernelGGL(k_strips_t128_bf16, dim3((unsigned)a.nCT, (unsigned)a.nAT, 2), dim3(512), 0, c.s, a);
 }
 
 // ----------------------------------------------------------------------------------------------------------------
-// Contraction on 128 x 128 output tiles: C[m][n] = sum_c Efrag[m][c] X[c][n] over the contrast columns of one split.
-// A operand of a stage = 4 anchor blocks x 2 column blocks of the stored strip (8 fragments of 1 KiB, copied as they
-// are); B operand = 32 rows x 128 columns of X in its natural layout (256-byte rows; 16-byte piece p of row k at piece
-// position p ^ ((k & 3) << 2), so that the 4 rows x 64 bytes a transposing read touches per cycle cover a bank window).
-struct ContractTile128 {
-  const bf16_t* Efr;       // wave-uniform: fragment (first anchor block of the tile, column block 0)
-  const bf16_t* Xn;        // wave-uniform: X + n0
-  int64_t ldx, n0, N, B;
-  uint32_t oa[2], ob[2], la[2], lb[2];
-  int wm, wn, lane;
-
-  __device__ __forceinline__ static int swz(int k) { return (k & 3) << 2; }
-  __device__ __forceinline__ void setup(const bf16_t* E, int64_t nCB, int64_t ab0, const bf16_t* X_, int64_t ldx_,
-                                        int64_t n0_, int64_t N_, int64_t B_, int tid) {
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    lane = tid & 63; wm = wave >> 1; wn = wave & 1;
-    Efr = E + ab0 * nCB * 512; Xn = X_ + n0_; ldx = ldx_; n0 = n0_; N = N_; B = B_;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int f = wave * 2 + i;                       // A: fragment (anchor block f / 2, column block f % 2 of the stage)
-      oa[i] = (uint32_t)(((f >> 1) * (int)nCB + (f & 1)) * 512 + lane * 8) * 2u;
-      la[i] = (uint32_t)(f * 1024);
-      const int k = 4 * f + (lane >> 4);                // B: wave load f covers the stage's rows 4 f .. 4 f + 3
-      const int piece = (lane & 15) ^ swz(k);           // logical piece fetched into position (lane & 15)
-      ob[i] = (uint32_t)(k * (int)ldx_ + piece * 8) * 2u;
-      lb[i] = (uint32_t)(kHalf + f * 1024);
-    }
-  }
-  __device__ __forceinline__ const bf16_t* stage_rows(int stage) const { return Xn + (int64_t)stage * BK * ldx; }
-  __device__ __forceinline__ void dma(int i, int stage, uint32_t slot) const {
-    if (i < 2) dma16(Efr + (int64_t)stage * 1024, oa[i], slot + la[i]);
-    else dma16(stage_rows(stage), ob[i - 2], slot + lb[i - 2]);
-  }
-  __device__ __forceinline__ void fill_guarded(int stage, char* slot, int tid) const {
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int f = wave * 2 + i;
-      *(u32x4*)(slot + f * 1024 + lane * 16) = *(const u32x4*)((const char*)(Efr + (int64_t)stage * 1024) + oa[i]);
-      const int k = 4 * f + (lane >> 4);
-      const int piece = (lane & 15) ^ swz(k);
-      const int64_t c = (int64_t)stage * BK + k;        // contrast column = row of X
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (c < B && n0 + piece * 8 < N) v = *(const u32x4*)((const char*)stage_rows(stage) + ob[i]);
-      *(u32x4*)(slot + kHalf + f * 1024 + lane * 16) = v;
-    }
-  }
-  __device__ __forceinline__ bf16x8 read_a(const char* slot, int t, int kk) const {
-    return *(const bf16x8*)(slot + (((wm * 2 + t) * 2 + kk) * 1024 + lane * 16));
-  }
-  // slots e = 0..3 <-> rows 16 kk + 4 h + e, slots 4..7 <-> rows 16 kk + 8 + 4 h + (e - 4): two transposing reads, each
-  // taking 4 rows x 16 columns per group of 16 lanes (source lane s: row s / 4, columns 4 (s % 4) ..)
-  __device__ __forceinline__ bf16x8 read_b(const char* slot, int t, int kk) const {
-    const int h = lane >> 5, s = lane & 15;
-    const int n = wn * 64 + t * 32 + ((lane >> 4) & 1) * 16 + 4 * (s & 3);   // first of the 4 columns this lane reads
-    u32x2 half2[2];
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      const int k = 16 * kk + 8 * half + 4 * h + (s >> 2);
-      const char* p = slot + kHalf + k * 256 + (((n >> 3) ^ swz(k)) << 4) + ((n & 7) << 1);
-      half2[half] = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(uintptr_t)lds_addr(p)));
-    }
-    return join_halves(half2[0], half2[1]);
-  }
-};
+constexpr int kO = 64;                          // columns of an output tile; its rows: 64 MB
+constexpr int kGroups = 8;                      // state phase inside: 4 groups of 64 sums for the rows, 4 for the local anchors q
+// a wave's stage: 16 deep, 2 MB KiB of the strip and 2 KiB of X; what fits 160 KiB beside the coefficients
+template <int MB> constexpr int kWStage = 2048 * (MB + 1);
+template <int MB> constexpr int kWSlots = MB == 1 ? 4 : 3;
+template <int MB> constexpr int kWRing = 8 * kWSlots<MB> * kWStage<MB>;   // 128 / 144 KiB
 
 struct T128Job {
-  const bf16_t* E;     // fragment-ordered strip of this side
-  const bf16_t* X;     // the matrix whose rows the strip weights (texts for side 0, images for side 1): also the rows of
-                       // the diagonal terms, d_img[r] -= dcoef[r] txt[off + r]
-  const float* c_own;  // c1 (side 0) / c2 (side 1)
-  float* out;          // d_img / d_txt
+  const bf16_t* E;       // fragment-ordered strip of this side
+  const bf16_t* Eo;      // ... of the other side, whose columns 0 .. b - 1 are the contrast-side term's weights
+  const bf16_t* X;       // the matrix whose rows the strips weight (texts for side 0, images for side 1): also the rows of
+                         // the diagonal terms, d_img[r] -= dcoef[r] txt[off + r]
+  float* out;            // d_img / d_txt
   int64_t ldx;
 };
 struct T128Args {
   T128Job job[2];
-  int64_t b, d, B, off, nCB;
-  int tiles_m, tiles_n, nsplit, slice, stages;   // 32-deep stages per split and in all
-  float* part;         // nsplit > 1: [nsplit][2][b128][d128] partial results
-  int64_t b128, d128;
-  const float* dcoef;
-  const double* red; int nred; int version; const float* tau; float rho; float* loss; float* d_tau;
+  int b, d, B, off;
+  int64_t nCB;
+  int tiles_m, tiles_n, nsplit;
+  int nA, nB;            // 16-deep stages over the contrasts / over the local anchors
+  int sliceA, sliceB;    // ... per wave
+  double* part;          // nsplit > 1: [tile][split][64 x 64 floats as pairs]
+  unsigned* arrived;     // per 64 rows of an output tile, then one for the scalars (64-row tiles); 0 before the launch (k_prep)
+  float rho;
+  const float* tau;
+  float *loss, *d_tau;
 };
 
-__global__ void __launch_bounds__(256, 2) k_contract_t128_bf16(T128Args g) {
-  __shared__ __attribute__((aligned(1024))) char ring[kSmallRing];
+// Output tile (m0 .. + 63, n0 .. + 63) of one side: C = sum_c c_own E[r][c] X[c] + sum_q c_other[q] E_other[q][r] X[q] over
+// the contrasts c and the local anchors q (Eq. 2 / 4 / 6 and the local part of Eqs. 3 / 5 / 7; column q is the row X[q] in
+// both sums), minus the diagonal term.  The depth is cut into nsplit x 8 slices, one per wave of every workgroup of the
+// tile; a wave adds up its part of the first sum, multiplies by the rows' coefficients and goes on with its part of the
+// second.  Its operands go through LDS of its own, four 16-deep stages in flight, and nothing but its own waits is in the
+// loop.  Then the eight waves' tiles are added up through LDS, and with several splits by the last workgroup to arrive.
+//
+// The state phase rides along: every workgroup forms the coefficients that it needs from the partial sums (same
+// instructions, same order, hence the same bits everywhere) while its first stages are on their way, the workgroups of
+// side 0, split 0 and the first columns finish their 64 anchors.  When that is too much to read again and again
+// (plan_t128), k_state has run before and the coefficients are read.
+//
+// What bounds it: operands come at 64 bytes per clock and compute unit, so eight 16-deep stages of 64 x 64 tiles (32 KiB) take
+// 512 cycles against 256 of products (650 - 880 measured), and about 5 us go into the start, the coefficients, the sum over
+// the waves and the outputs.  128-row tiles (MB = 2) move a quarter less per product and are taken where 64-row ones need
+// a second round of workgroups; the cost model is in plan_t128.  Steps before and after (fold + contraction + finalize
+// kernels before): 128 of 1024 pairs, d = 512: 34.2 -> 22.9 us, 256 of 8192: 48.6 -> 34.5, 1024 of 1024: 37.7 -> 30.0,
+// 1000 of 4000, d = 760 (128-row tiles): 71.5 -> 64.1.
+template <int MB>
+__global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, StateArgs a) {
+  constexpr int kM = 64 * MB, kStageB = kWStage<MB>, kSlotsW = kWSlots<MB>, kX = 2048 * MB;
+  __shared__ __attribute__((aligned(1024))) char ring[kWRing<MB>];
+  __shared__ float psum[MB == 1 ? 8 * kGroups * 64 : 1];  // [wave][group][anchor]: partial sums of the coefficients' inputs
+  __shared__ __attribute__((aligned(16))) float crow[kM], drow[kM], cq[kMaxLocalQ];
+  __shared__ int flag;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1, lr = lane & 31, hk = lane >> 5;
-  const int per_side = g.nsplit * g.tiles_m * g.tiles_n;
-  const int side = (int)blockIdx.x / per_side, local = (int)blockIdx.x % per_side;
-  const int split = local % g.nsplit, tile = local / g.nsplit;
-  const int64_t m0 = (int64_t)(tile % g.tiles_m) * kT, n0 = (int64_t)(tile / g.tiles_m) * kT;
+  const int lr = lane & 31, hk = lane >> 5;
+  const int split = blockIdx.x, tm = blockIdx.y, side = blockIdx.z & 1, tn = blockIdx.z >> 1;
+  const int tile = (tn * 2 + side) * g.tiles_m + tm;
+  const int m0 = tm * kM, n0 = tn * kO;
   const T128Job& J = g.job[side];
-  const int s0 = split * g.slice;
-  const int S = s0 + g.slice <= g.stages ? g.slice : g.stages - s0;      // >= 1 by construction
-  ContractTile128 T;
-  T.setup(J.E, g.nCB, m0 >> 5, J.X, J.ldx, n0, g.d, g.B, tid);
-  f32x16 acc[2][2];
+  // pinned in scalar registers: left in the argument segment they are loaded again behind every memory fence
+  const int B = __builtin_amdgcn_readfirstlane(g.B), ldx = __builtin_amdgcn_readfirstlane((int)J.ldx);
+  const bf16_t* X = wave_uniform(J.X);
+  const int qbase = split * 8 * g.sliceB * 16;       // this workgroup's local anchors q
+  int nq = g.b - qbase < 8 * g.sliceB * 16 ? g.b - qbase : 8 * g.sliceB * 16;
+  nq = nq < 0 ? 0 : nq;
+  const bool fused = MB == 1 && a.fused;
+  const bool finisher = fused && side == 0 && tn == 0 && split == 0;
+  const int nqg = (nq + 63) >> 6;
+
+  // ---- inputs of the coefficients: of the 64 rows (both sides, for the diagonal factor too) and of the q's (the other side).
+  // They are requested and waited for ahead of the operands: vector memory operations complete in order.
+  const bool finishing = finisher && wave >= 6 && m0 + lane < g.b;       // wave 6: image side, wave 7: text side
+  int64_t fn = 0;
+  float fu = 0.f, ft = 1.f, u1 = 0.f, t1 = 1.f, u2 = 0.f, t2 = 1.f;
+  if (fused) {
+    if (finishing) {
+      fn = a.idx[m0 + lane] * a.stride;
+      fu = (wave == 6 ? a.uold1 : a.uold2)[m0 + lane];
+      ft = (wave == 6 ? a.tau1 : a.tau2)[m0 + lane];
+    }
+    const int m = tid < 64 ? m0 + tid : qbase + tid - 64;
+    if (m < g.b && tid < 64 + nqg * 64) { u1 = a.uold1[m]; t1 = a.tau1[m]; u2 = a.uold2[m]; t2 = a.tau2[m]; }
+    // group 0, 1: sum of l of the rows, image / text side; 2, 3: of (s - s_ii) l (finishers); then the q's
+    const float* p[kGroups];
+    float s[kGroups];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+    for (int j = 0; j < kGroups; ++j) {
+      const int quantity = j < 4 ? (j & 1) * 2 + (j >> 1) : 2 * (1 - side);
+      const int m1 = (j < 4 ? m0 : qbase + (j - 4) * 64) + lane;          // what a lane beyond the anchors adds up is not used
+      p[j] = a.sums + (size_t)quantity * a.nparts * a.bstride + (m1 < g.b ? m1 : g.b - 1);
+      s[j] = 0.f;
+    }
+#pragma unroll 8
+    for (int pt = wave; pt < a.nparts; pt += 8) {
+      const size_t o = (size_t)pt * a.bstride;
+      float v[kGroups];
+#pragma unroll
+      for (int j = 0; j < kGroups; ++j)
+        if (j < 2 || (j < 4 ? finisher : j - 4 < nqg)) v[j] = p[j][o]; else v[j] = 0.f;
+#pragma unroll
+      for (int j = 0; j < kGroups; ++j) s[j] += v[j];
+    }
+#pragma unroll
+    for (int j = 0; j < kGroups; ++j) psum[(wave * kGroups + j) * 64 + lane] = s[j];
+  } else {
+    for (int i = tid; i < kM + nqg * 64; i += 512) {
+      if (i < kM) {
+        crow[i] = m0 + i < g.b ? (side == 0 ? a.c1 : a.c2)[m0 + i] : 0.f;
+        drow[i] = m0 + i < g.b ? a.dcoef[m0 + i] : 0.f;
+      } else {
+        const int q = qbase + i - kM;
+        cq[i - kM] = q < g.b ? (side == 0 ? a.c2 : a.c1)[q] : 0.f;
+      }
+    }
+  }
+  FC_FENCE();
+
+  // ---- operand requests
+  const int unit = split * 8 + wave;
+  const int A0 = unit * g.sliceA, nAw = A0 >= g.nA ? 0 : (A0 + g.sliceA <= g.nA ? g.sliceA : g.nA - A0);
+  const int Q0 = unit * g.sliceB, nBw = Q0 >= g.nB ? 0 : (Q0 + g.sliceB <= g.nB ? g.sliceB : g.nB - Q0);
+  const int nst = nAw + nBw;
+  const uint32_t wring = lds_addr(ring) + (uint32_t)(wave * kSlotsW * kStageB);
+  const char* wslot = ring + wave * kSlotsW * kStageB;
+  // X: two wave loads of 8 rows x 128 bytes; 16-byte piece p of stage row k at piece p ^ (4 ((k >> 1) & 1)), so that the 4 rows x
+  // 64 bytes that a transposing read touches cover a bank window.  Rows wrap at B; pieces beyond the width are fetched as the
+  // row's first of the tile and reach no output.
+  int grow[2];
+  uint32_t xoff[2];
+  const uint32_t wrap = (uint32_t)(B * ldx) * 2u, next_rows = (uint32_t)(16 * ldx) * 2u;
+  auto open_rows = [&](int col) {              // columns col .. col + 15
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int k = 8 * i + (lane >> 3), pc = (lane & 7) ^ (((k >> 1) & 1) << 2);
+      int r = g.off + col + k;                 // below 2 B + 16: a division would take longer
+      while (r >= B) r -= B;
+      grow[i] = r;
+      xoff[i] = (uint32_t)(r * ldx + (n0 + pc * 8 < g.d ? n0 + pc * 8 : n0)) * 2u;
+    }
+  };
+  // Strip operand of the first sum: the fragments (m0 / 32 + i, stage), 1 KiB each.  Of the second: 16 anchors q x 64 columns r as
+  // 128 chunks of 16 bytes, [column block][half][q] with q at q ^ (4 half) ^ (8 (column block & 1)), again for the transposing
+  // reads' bank windows.
+  const char* src = nullptr;                   // uniform; stage `at` comes from src + woff[i]
+  uint32_t woff[2 * MB];
+  const uint32_t row_block = (uint32_t)g.nCB * 1024u;
+  int at = 0;                                  // next stage to request
+  auto open_own = [&]() {
+    src = wave_uniform((const char*)J.E + ((int64_t)(m0 >> 5) * g.nCB + A0) * 1024);
+#pragma unroll
+    for (int i = 0; i < 2 * MB; ++i) woff[i] = (uint32_t)(lane * 16) + (uint32_t)i * row_block;
+    open_rows(A0 * 16);
+  };
+  auto open_other = [&]() {
+    src = wave_uniform((const char*)J.Eo + ((int64_t)(Q0 >> 1) * g.nCB + (m0 >> 4)) * 1024 + (Q0 & 1) * 256);
+#pragma unroll
+    for (int i = 0; i < 2 * MB; ++i) {
+      const int cb = 2 * i + (lane >> 5), h = (lane >> 4) & 1, q = (lane & 15) ^ (4 * h) ^ (8 * (cb & 1));
+      woff[i] = (uint32_t)((cb * 64 + q + 32 * h) * 16);
+    }
+    open_rows(Q0 * 16);
+  };
+  uint32_t fill = wring;                       // slot of stage `at`
+  auto request = [&]() {
+#pragma unroll
+    for (int i = 0; i < 2 * MB; ++i) dma16(src, woff[i], fill + (uint32_t)(i * 1024));
+    dma16(X, xoff[0], fill + (uint32_t)kX);
+    dma16(X, xoff[1], fill + (uint32_t)(kX + 1024));
+    fill = fill + kStageB == wring + kSlotsW * kStageB ? wring : fill + kStageB;
+    ++at;
+    if (at == nAw) {
+      open_other();
+    } else {
+      src += at < nAw ? 1024u : (((Q0 + at - nAw) & 1) ? 256u : row_block - 256u);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        grow[j] += 16; xoff[j] += next_rows;
+        if (grow[j] >= B) { grow[j] -= B; xoff[j] -= wrap; }
+      }
+    }
+  };
+  if (nAw > 0) open_own(); else open_other();
+  for (int s = 0; s < kSlotsW - 1 && s < nst; ++s) request();
+
+  // ---- the coefficients
+  __syncthreads();
+  FC_FENCE();
+  if (fused) {
+    auto total = [&](int j, int al) {
+      float s = psum[j * 64 + al];
+#pragma unroll
+      for (int w = 1; w < 8; ++w) s += psum[(w * kGroups + j) * 64 + al];
+      return s;
+    };
+    float u;
+    if (tid < 64) {
+      float c1 = 0.f, c2 = 0.f, dc = 0.f;
+      if (m0 + tid < g.b) {
+        const float s1 = total(0, tid), s2 = total(1, tid);
+        c1 = anchor_coefficient(a, s1, u1, t1, &u);
+        c2 = anchor_coefficient(a, s2, u2, t2, &u);
+        dc = __fmul_rn(c1, s1) + __fmul_rn(c2, s2);
+      }
+      crow[tid] = side == 0 ? c1 : c2;
+      drow[tid] = dc;
+    } else if (tid < 64 + nqg * 64) {
+      const int j = tid - 64;
+      cq[j] = qbase + j < g.b
+                  ? anchor_coefficient(a, total(4 + (j >> 6), j & 63), side == 0 ? u2 : u1, side == 0 ? t2 : t1, &u) : 0.f;
+    }
+    __syncthreads();
+    FC_FENCE();
+    if (finishing) {
+      // 64 anchors: scatter, outputs, Eq. 9, their terms of the scalars.  Nobody in this launch waits for them but the wave that
+      // adds the terms up at the very end.
+      const int fside = wave - 6;
+      double lterm, hterm;
+      state_finish_side<false>(a, fside, m0 + lane, fn, total(fside, lane), total(2 + fside, lane), fu, ft, &lterm, &hterm);
+      double* red = a.red + 2 * ((int64_t)fside * g.b + m0 + lane);
+      store_agent(red, lterm);
+      store_agent(red + 1, hterm);
+    }
+  }
+
+  // ---- main loop
+  f32x16 acc[2 * MB][2];
+#pragma unroll
+  for (int i = 0; i < 2 * MB; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  // Unguarded loads of a stage take 32 whole rows of X and 128 columns from n0 on: they stay inside the matrix (B rows of
-  // ldx elements, the last one of d) for the stages below `safe`; words past a row's end are the next rows', and what
-  // they put into the columns from d on reaches no output.  The rest goes one stage at a time with guards.
-  int64_t rows_ok = g.B;
-  if (n0 + kT > g.d) rows_ok -= (n0 + kT - g.d + J.ldx - 1) / J.ldx;
-  const int safe = rows_ok > 0 ? (int)(rows_ok / BK) : 0;
-  const int S_ring = s0 + S <= safe ? S : (safe > s0 ? safe - s0 : 0);
-  if (S_ring > 0) small_ring(acc, T, ring, lds_addr(ring), s0, S_ring);
-  if (S_ring < S) small_guarded(acc, T, ring, s0 + S_ring, S - S_ring, tid);
-  // accumulator (ti, tj, v) of lane (lr, hk): row m0 + 64 wm + 32 ti + 8 (v >> 2) + 4 hk + (v & 3), column n0 + 64 wn + 32 tj + lr
-  if (g.nsplit == 1) {
-    // the tile is complete: d[r][n] = c_own[r] C[r][n] - (c1 M g1 + c2 M g2)[r] x_partner[off + r][n]
+  // lane offsets of the operand reads inside a slot: transposing reads take 4 rows x 16 columns per group of 16 lanes, source
+  // lane s row s / 4, columns 4 (s % 4) ..; the halves h = 0, 1 of a read are 8 rows apart
+  const int s16 = lane & 15, c16 = (lane >> 4) & 1;
+  uint32_t rx[2], rq[2 * MB][2];
+  const int k0 = 4 * hk + (s16 >> 2);                 // 8 rows further on: the same swizzles
 #pragma unroll
-    for (int ti = 0; ti < 2; ++ti)
+  for (int t = 0; t < 2; ++t) {
+    const int nl = t * 32 + c16 * 16 + 4 * (s16 & 3);
+    rx[t] = (uint32_t)(kX + k0 * 128 + (((nl >> 3) ^ (((k0 >> 1) & 1) << 2)) << 4) + ((nl & 7) << 1));
+  }
 #pragma unroll
-      for (int tj = 0; tj < 2; ++tj) {
-        const int64_t n = n0 + wn * 64 + tj * 32 + lr;
-        if (n < g.d) {
+  for (int t = 0; t < 2 * MB; ++t) {
+    const int cb = 2 * t + c16, r4 = s16 & 3, hh = r4 & 1;
 #pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int64_t m = m0 + wm * 64 + ti * 32 + 8 * (v >> 2) + 4 * hk + (v & 3);
-            if (m < g.b)
-              J.out[m * g.d + n] = J.c_own[m] * acc[ti][tj][v] - g.dcoef[m] * bf2f(J.X[(g.off + m) * J.ldx + n]);
+    for (int h = 0; h < 2; ++h)
+      rq[t][h] = (uint32_t)(cb * 512 + hh * 256 + ((8 * h + k0) ^ (4 * hh) ^ (8 * (cb & 1))) * 16 + (r4 >> 1) * 8);
+  }
+  auto tr = [](uint32_t addr) {
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(uintptr_t)addr));
+  };
+  uint32_t slot = wring;
+  // Stages [i0, i1): read stage i, request the next into the slot that stage i - 1 was read from, multiply.  The requests
+  // hide the reads' latency, and the products run on into the next stage's wait.
+  auto run = [&](auto other_side, int i0, int i1) {
+    constexpr bool OTHER = decltype(other_side)::value;
+    const float* c = cq + (Q0 * 16 - qbase) + 4 * hk;      // c_other[q], two runs of four q per lane and stage
+    for (int i = i0; i < i1; ++i) {
+      // stage i has landed: at most the younger ones, 2 MB + 2 loads each, may be in flight
+      if (MB == 1 && at - i == 3) __builtin_amdgcn_s_waitcnt(0x0f78);
+      else if (at - i == 2) __builtin_amdgcn_s_waitcnt(MB == 1 ? 0x0f74 : 0x0f76);
+      else __builtin_amdgcn_s_waitcnt(0x0f70);
+      __builtin_amdgcn_wave_barrier();
+      FC_FENCE();
+      u32x4 w[2 * MB];
+      u32x2 xl[2], xh[2];
+#pragma unroll
+      for (int t = 0; t < 2 * MB; ++t) {
+        if constexpr (!OTHER) {
+          w[t] = *(const u32x4*)(wslot + (slot - wring) + t * 1024 + lane * 16);
+        } else {
+          const u32x2 lo = tr(slot + rq[t][0]), hi = tr(slot + rq[t][1]);
+          w[t] = (u32x4){lo[0], lo[1], hi[0], hi[1]};
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        xl[t] = tr(slot + rx[t]);
+        xh[t] = tr(slot + rx[t] + 1024u);
+      }
+      f32x4 cl, ch;
+      if constexpr (OTHER) { cl = *(const f32x4*)c; ch = *(const f32x4*)(c + 8); c += 16; }
+      slot = slot + kStageB == wring + kSlotsW * kStageB ? wring : slot + kStageB;
+      FC_PIN();
+      if (at < nst) request();
+      wave_reads_done();                          // the stage's slot may be filled again
+      if constexpr (OTHER) {
+#pragma unroll
+        for (int t = 0; t < 2 * MB; ++t)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float c0 = e < 2 ? cl[2 * e] : ch[2 * e - 4], c1 = e < 2 ? cl[2 * e + 1] : ch[2 * e - 3];
+            w[t][e] = pack_bf16x2(__uint_as_float(w[t][e] << 16) * c0, __uint_as_float(w[t][e] & 0xffff0000u) * c1);
           }
-        }
       }
-    if (blockIdx.x == 0 && tid < 64) write_scalars(g.red, g.nred, g.b, g.version, g.tau, g.rho, g.loss, g.d_tau);
-  } else {
-    float* P = g.part + ((size_t)(split * 2 + side) * g.b128) * g.d128;   // whole 128 x 128 tiles exist in the buffer
 #pragma unroll
-    for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-      for (int tj = 0; tj < 2; ++tj) {
-        const int64_t n = n0 + wn * 64 + tj * 32 + lr;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int64_t m = m0 + wm * 64 + ti * 32 + 8 * (v >> 2) + 4 * hk + (v & 3);
-          P[m * g.d128 + n] = acc[ti][tj][v];
-        }
-      }
-  }
-}
-
-// Several splits: d[r][n] = c_own[r] (sum over the splits, in their order) - dcoef[r] x_partner[off + r][n].
-// A thread takes four consecutive columns of one row (d % 8 == 0 on this path).
-__global__ void __launch_bounds__(256) k_finalize_t128_bf16(T128Args g) {
-  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t per_row = g.d / 4;
-  const int side = blockIdx.y;
-  const T128Job& J = g.job[side];
-  if (q < g.b * per_row) {
-    const int64_t m = q / per_row, n = (q % per_row) * 4;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int s = 0; s < g.nsplit; ++s) {
-      const float4 v = *(const float4*)(g.part + ((size_t)(s * 2 + side) * g.b128 + m) * g.d128 + n);
-      acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+      for (int t = 0; t < 4 * MB; ++t)
+        acc[t >> 1][t & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w[t >> 1]),
+                                                                      join_halves(xl[t & 1], xh[t & 1]), acc[t >> 1][t & 1], 0, 0, 0);
     }
-    const uint2 xr = *(const uint2*)(J.X + (g.off + m) * J.ldx + n);
-    const float c = J.c_own[m], dc = g.dcoef[m];
-    float4 o;
-    o.x = c * acc.x - dc * __uint_as_float(xr.x << 16);
-    o.y = c * acc.y - dc * __uint_as_float(xr.x & 0xffff0000u);
-    o.z = c * acc.z - dc * __uint_as_float(xr.y << 16);
-    o.w = c * acc.w - dc * __uint_as_float(xr.y & 0xffff0000u);
-    *(float4*)(J.out + m * g.d + n) = o;
+  };
+  run(std::false_type{}, 0, nAw);
+#pragma unroll
+  for (int ti = 0; ti < 2 * MB; ++ti)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 c = *(const f32x4*)(crow + ti * 32 + 8 * q + 4 * hk);
+#pragma unroll
+      for (int tj = 0; tj < 2; ++tj)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[ti][tj][4 * q + v] *= c[v];
+    }
+  run(std::true_type{}, nAw, nst);
+
+  // Either finishing wave counts itself once its stores are acknowledged at agent scope (they are long since); the answer is
+  // looked at behind the outputs.
+  unsigned scalars_before = 0;
+  if (finisher && wave >= 6) {
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+    FC_FENCE();
+    if (lane == 0)
+      scalars_before = __hip_atomic_fetch_add(g.arrived + 2 * g.tiles_m * g.tiles_n, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 64)
-    write_scalars(g.red, g.nred, g.b, g.version, g.tau, g.rho, g.loss, g.d_tau);
+  // ---- the eight waves' tiles are added up, 64 rows at a time: wave w finishes block w / 2 of them, its rows 16 (w % 2) .. + 15
+  const int rl = (wave >> 2) * 32 + (wave & 1) * 16 + 4 * hk;          // row of e = 0; e = 4: 8 further on
+  const int n = n0 + ((wave >> 1) & 1) * 32 + lr;
+  float* out = J.out;
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    const int row0 = mb * 64 + rl;
+    bf16_t xd[8];                              // the diagonal terms' rows, requested ahead of the sums
+    f32x4 dc[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) dc[h] = *(const f32x4*)(drow + row0 + 8 * h);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      int m = m0 + row0 + 8 * (e >> 2) + (e & 3);
+      m = m < g.b ? m : g.b - 1;
+      xd[e] = X[(uint32_t)((g.off + m) * ldx + (n < g.d ? n : 0))];
+    }
+    __syncthreads();
+    FC_FENCE();
+    {
+      float* o = (float*)(ring + wave * 16384) + lane * 4;
+#pragma unroll
+      for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+        for (int tj = 0; tj < 2; ++tj)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const f32x16& v = acc[mb * 2 + ti][tj];
+            *(f32x4*)(o + ((ti * 2 + tj) * 4 + q) * 256) = (f32x4){v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+          }
+    }
+    __syncthreads();
+    f32x4 sum[2];
+    {
+      const float* p = (const float*)ring + wave * 512 + lane * 4;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        sum[h] = *(const f32x4*)(p + h * 256);
+#pragma unroll
+        for (int w = 1; w < 8; ++w) sum[h] += *(const f32x4*)(p + w * 4096 + h * 256);
+      }
+    }
+    bool writer = true;
+    if (g.nsplit > 1) {
+      const size_t slab = (size_t)g.nsplit * (kO * kO / 2);
+      double* all = g.part + (size_t)(tile * MB + mb) * slab + wave * 256 + lane;
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const u32x2 w = {__float_as_uint(sum[p >> 1][2 * (p & 1)]), __float_as_uint(sum[p >> 1][2 * (p & 1) + 1])};
+        store_agent(all + (size_t)split * (kO * kO / 2) + p * 64, __builtin_bit_cast(double, w));
+      }
+      writer = last_to_arrive(g.arrived + tile * MB + mb, (unsigned)g.nsplit, &flag);
+      if (writer) {
+        sum[0] = sum[1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+        for (int s = 0; s < g.nsplit; ++s)
+#pragma unroll
+          for (int p = 0; p < 4; ++p) {
+            const u32x2 w = __builtin_bit_cast(u32x2, load_agent(all + (size_t)s * (kO * kO / 2) + p * 64));
+            sum[p >> 1][2 * (p & 1)] += __uint_as_float(w[0]);
+            sum[p >> 1][2 * (p & 1) + 1] += __uint_as_float(w[1]);
+          }
+      }
+    }
+    if (writer) {
+      float* o = out + (int64_t)(m0 + row0) * g.d + n;
+      const int rows = n < g.d ? g.b - m0 - row0 : 0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int m = 8 * (e >> 2) + (e & 3);
+        if (m < rows) o[m * g.d] = sum[e >> 2][e & 3] - dc[e >> 2][e & 3] * bf2f(xd[e]);
+      }
+    }
+  }
+  // ---- scalars, by the wave that finished the last anchors
+  bool last = side == 0 && tn == 0 && tm == 0 && split == 0 && wave == 7;
+  if (fused) last = finisher && wave >= 6 && (unsigned)__shfl((int)scalars_before, 0) + 1u == 2u * (unsigned)g.tiles_m;
+  if (last) write_scalars<true>(a.red, fused ? 2 * g.b : (int)a.ntiles, g.b, a.version, g.tau, g.rho, g.loss, g.d_tau);
 }
 
 void launch_contract_t128_bf16(const StepCtx& c) {
@@ -411,25 +690,23 @@ void launch_contract_t128_bf16(const StepCtx& c) {
   for (int s = 0; s < 2; ++s) {
     T128Job& J = g.job[s];
     J.E = (const bf16_t*)(c.ws + L.E[s]);
+    J.Eo = (const bf16_t*)(c.ws + L.E[1 - s]);
     J.X = (const bf16_t*)(s == 0 ? c.buf.txt_glob : c.buf.img_glob);
     J.ldx = s == 0 ? c.cfg.ld_txt : c.cfg.ld_img;
-    J.c_own = (const float*)(c.ws + (s == 0 ? L.c1 : L.c2));
     J.out = s == 0 ? c.buf.d_img : c.buf.d_txt;
   }
-  g.b = L.b; g.d = L.d; g.B = L.B; g.off = L.off; g.nCB = L.ldE / 16;
-  g.tiles_m = (int)((L.b + kT - 1) / kT); g.tiles_n = (int)((L.d + kT - 1) / kT);
-  g.nsplit = L.nsplit; g.slice = (int)L.kslice; g.stages = (int)(L.ldE / BK);
-  g.part = L.nsplit > 1 ? (float*)(c.ws + L.Opart[0]) : nullptr;
-  g.b128 = (int64_t)round_up((size_t)L.b, kT); g.d128 = (int64_t)round_up((size_t)L.d, kT);
-  g.dcoef = (const float*)(c.ws + L.dcoef);
-  g.red = (const double*)(c.ws + L.red); g.nred = L.nstate_blocks; g.version = c.cfg.version; g.tau = c.buf.tau;
-  g.rho = c.cfg.rho; g.loss = c.buf.loss; g.d_tau = c.buf.d_tau;
-  const unsigned grid = 2u * (unsigned)(g.nsplit * g.tiles_m * g.tiles_n);
-  hipLaunchKernelGGL(k_contract_t128_bf16, dim3(grid), dim3(256), 0, c.s, g);
-  if (g.nsplit > 1) {
-    const int64_t quads = L.b * (L.d / 4);
-    hipLaunchKernelGGL(k_finalize_t128_bf16, dim3((unsigned)((quads + 255) / 256), 2), dim3(256), 0, c.s, g);
-  }
+  g.b = (int)L.b; g.d = (int)L.d; g.B = (int)L.B; g.off = (int)L.off; g.nCB = L.ldE / 16;
+  g.tiles_m = (int)((L.b + L.out_rows - 1) / L.out_rows); g.tiles_n = (int)((L.d + kO - 1) / kO);
+  g.nsplit = L.nsplit;
+  g.nA = (int)((L.B + 15) / 16); g.nB = (int)((L.b + 15) / 16);
+  g.sliceA = (g.nA + L.nsplit * 8 - 1) / (L.nsplit * 8);
+  g.sliceB = (g.nB + L.nsplit * 8 - 1) / (L.nsplit * 8);
+  g.part = L.nsplit > 1 ? (double*)(c.ws + L.Opart[0]) : nullptr;
+  g.arrived = (unsigned*)(c.ws + L.arrived);
+  g.tau = c.buf.tau; g.rho = c.cfg.rho; g.loss = c.buf.loss; g.d_tau = c.buf.d_tau;
+  auto* kernel = L.out_rows == 64 ? k_contract_t128_bf16<1> : k_contract_t128_bf16<2>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)g.nsplit, (unsigned)g.tiles_m, 2u * (unsigned)g.tiles_n), dim3(512), 0, c.s, g,
+                     make_state_args(c));
 }
 
 }  // namespace fc

@@ -95,16 +95,21 @@ __device__ inline double wave_sum_f64(double v) {
 }
 
 // Scalars (called by one whole wavefront): loss of the local batch with g replaced by u^{t+1}; Eq. 8 (V0), Eq. 10 (V3).
-// red: the state phase's per-block sums of the anchors' loss terms and h terms.
+// red: the state phase's per-block sums of the anchors' loss terms and h terms.  AGENT: they were left by other workgroups
+// of the same launch (store_agent).
 // Written as values chosen per version and then ONE store per output through the pointer it was given: with a return
 // per version, each ending in its own stores, the compiler merged the versions' last stores into one whose address
 // register the V3 path never set (it held the flag output of a v_div_scale_f64), so that V3 stored d_tau to a stray
 // address wherever this function was inlined behind other code.
+template <bool AGENT = false>
 __device__ inline void write_scalars(const double* red, int nblocks, int64_t b, int version, const float* tau, float rho,
                                      float* loss, float* d_tau) {
   const int lane = threadIdx.x & 63;
   double A = 0.0, H = 0.0;
-  for (int i = lane; i < nblocks; i += 64) { A += red[2 * i]; H += red[2 * i + 1]; }
+  for (int i = lane; i < nblocks; i += 64) {
+    A += AGENT ? load_agent(red + 2 * i) : red[2 * i];
+    H += AGENT ? load_agent(red + 2 * i + 1) : red[2 * i + 1];
+  }
   A = wave_sum_f64(A) / (double)b;
   H = wave_sum_f64(H) / (double)b;
   const bool has_tau = version != FASTCLIP_V2;                         // V2 has no global temperature (tau may be NULL)
@@ -209,6 +214,28 @@ __device__ inline void state_finish_anchor(const StateArgs& a, int64_t r, const 
   *hsum = o1.hterm + o2.hterm;
   *c1_out = o1.c;
   *c2_out = o2.c;
+}
+
+// One side (0: image, 1: text) of local anchor r, whose record is n = idx[r] stride: scatter of u^{t+1}, Eq. 9 (and the
+// temperature step if asked for), optional outputs, the side's terms of the scalars.  The coefficients stay with the caller.
+template <bool PRECISE>
+__device__ inline void state_finish_side(const StateArgs& a, int side, int64_t r, int64_t n, float sum_e, float sum_xe,
+                                         float u_old, float tau, double* lterm, double* hterm) {
+  const SideResult o = state_side<PRECISE>(a, sum_e, sum_xe, u_old, tau);
+  (side ? a.u_txt : a.u_img)[n] = o.u;
+  if (a.version == FASTCLIP_V2) {
+    (side ? a.d_tau_txt : a.d_tau_img)[r] = o.gt;
+    if (a.tau_upd.optimizer) {
+      float* pv = side ? a.v_txt : a.v_img;
+      tau_step(a.tau_upd, (side ? a.tau_txt : a.tau_img) + n, (side ? a.m_txt : a.m_img) + n, pv ? pv + n : nullptr, o.gt);
+    }
+  }
+  float* g_out = side ? a.g_txt : a.g_img;
+  if (g_out) g_out[r] = sum_e * (1.0f / a.M);
+  float* u_out = side ? a.u_new_txt : a.u_new_img;
+  if (u_out) u_out[r] = o.u;
+  *lterm = o.lterm;
+  *hterm = o.hterm;
 }
 
 }  // namespace fc

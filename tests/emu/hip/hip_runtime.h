@@ -84,10 +84,13 @@ extern dim3 blockDim, gridDim;
 #define __builtin_amdgcn_s_waitcnt(x) ((void)0)
 #define __builtin_amdgcn_sched_barrier(x) ((void)0)
 #define __builtin_amdgcn_readfirstlane(x) (x)
+// the lanes of a wave run in step on the GPU; here a wave that hands data from lane to lane through LDS meets
+#define __builtin_amdgcn_wave_barrier() emu::t_wave->bar.wait()
 #define __builtin_amdgcn_exp2f(x) exp2f(x)
 #define __builtin_amdgcn_rcpf(x) (1.0f / (x))
 #define __fmul_rn(a, b) ((a) * (b))
 static inline float __uint_as_float(uint32_t u) { float f; memcpy(&f, &u, 4); return f; }
+static inline uint32_t __float_as_uint(float f) { uint32_t u; memcpy(&u, &f, 4); return u; }
 static inline uint64_t wall_clock64() { return 0; }
 static inline unsigned long long atomicCAS(unsigned long long* p, unsigned long long cmp, unsigned long long val) {
   __atomic_compare_exchange_n(p, &cmp, val, false, __ATOMIC_SEQ_CST, __ATOMIC_SEQ_CST);
@@ -108,6 +111,17 @@ static inline T __shfl_xor(T v, int mask) {
   w->bar.wait();
   T r;
   memcpy(&r, w->buf[0][emu::t_lane ^ mask], sizeof(T));
+  w->bar.wait();
+  return r;
+}
+
+template <typename T>
+static inline T __shfl(T v, int from) {
+  emu::Wave* w = emu::t_wave;
+  memcpy(w->buf[0][emu::t_lane], &v, sizeof(T));
+  w->bar.wait();
+  T r;
+  memcpy(&r, w->buf[0][from], sizeof(T));
   w->bar.wait();
   return r;
 }

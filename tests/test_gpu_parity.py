@@ -404,6 +404,18 @@ def test_bf16_tiles_128(B, b, off, d, version):
         assert rel_each(outs[0][k], outs[1][k]) < 1e-4, k
 
 
+@pytest.mark.parametrize("B,b,off,d", [
+    # fewer rows than a stage is deep, the columns' numbering wrapping inside it; one stage more or less; a last row block of one
+    (7, 3, 2, 8), (16, 16, 0, 64), (17, 9, 8, 72), (129, 65, 64, 520),
+    # more local anchors than the contraction holds sums for (state phase on its own), 64-row and 128-row output tiles
+    (2048, 2048, 0, 64), (4000, 1000, 3000, 760), (1030, 1023, 7, 1016),
+    # the depth split over sixteen workgroups
+    (8192, 64, 8128, 64)])
+def test_bf16_tiles_128_edges(B, b, off, d):
+    """The shapes at which the kernels of the 128 x 128-tile path change what they do, as in test_bf16_tiles_128."""
+    test_bf16_tiles_128(B, b, off, d, V2 if B % 2 else V3)
+
+
 @pytest.mark.parametrize("B,b,off,d", BF16_SMALL[:-1] + [(1024, 128, 128, 512), (2560, 320, 320, 512), (5120, 640, 640, 512)])
 @pytest.mark.parametrize("version", [V0, V1, V2, V3])
 def test_bf16_fine_tiles(B, b, off, d, version):
