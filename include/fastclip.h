@@ -155,8 +155,8 @@ typedef struct {
                             are 128 x 128 and output tiles 64 x 64); 0 on the fp32 path */
   int32_t single_pass;   /* 1: b == B and the similarity matrix is formed once */
   int32_t gathered;      /* 1: the contrast side runs over every global anchor (flag set and b < B) */
-  int32_t fused_state;   /* 1: the state phase runs inside the fold kernel (few anchors, few partial sums) */
-  int32_t nsplit;        /* splits of the contraction's column range; 1 on the small-tile paths: tiles finished in place */
+  int32_t fused_state;   /* 1: the state phase runs inside the fold kernel or, on 128-row tiles, the contraction */
+  int32_t nsplit;        /* splits of the contraction's column range over workgroups */
   int32_t nparts;        /* partial sums per anchor and quantity that the strip phase leaves to the state phase */
 } fastclip_plan;
 fastclip_status fastclip_describe(const fastclip_config* cfg, fastclip_plan* plan);

@@ -150,7 +150,7 @@ static void plan_f32(const fastclip_config& cfg, bool lean, Layout* L) {
 static void plan_t128(const fastclip_config& cfg, bool lean, Layout* L) {
   const int64_t nA = (cfg.B + 15) / 16, nB = (cfg.b + 15) / 16, cols = (cfg.d + 63) / 64;
   double best_cost = 0.0;
-  for (int64_t rows = 64; rows <= 128; rows += 64) {
+  for (int64_t rows = 64; rows <= (L->gathered ? 64 : 128); rows += 64) {
     const int64_t tiles = 2 * ((cfg.b + rows - 1) / rows) * cols;
     for (int64_t ns = 1; ns <= 16 && ns * 32 <= L->ldE; ++ns) {
       if (ns > 1 && (lean || tiles * ns > 2048)) break;
@@ -159,8 +159,8 @@ static void plan_t128(const fastclip_config& cfg, bool lean, Layout* L) {
       // the state phase inside the contraction: 64-row tiles have room for the sums of 256 local anchors beside the rows'
       const bool fused = rows == 64 && nq <= 256 && L->nparts <= 64;
       // us: start, coefficients, sum over the waves and end of a workgroup; a 16-deep stage of its eight waves (the load path of
-      // a compute unit: 32 or 48 KiB); partial results; the state phase as a launch of its own
-      const double cost = (double)((tiles * ns + 255) / 256) * (rows == 64 ? 5.5 + 0.27 * (double)(sA + sB) : 7.0 + 0.38 * (double)(sA + sB)) +
+      // a compute unit: 32 KiB, 48 for 128 rows or with a second strip); partial results; the state phase as a launch of its own
+      const double cost = (double)((tiles * ns + 255) / 256) * (rows == 64 ? 8.0 + 0.27 * ((L->gathered ? 1.4 : 1.0) * (double)sA + (double)sB) : 9.5 + 0.38 * (double)(sA + sB)) +
                           (ns > 1 ? 2.3 + 0.1 * (double)ns : 0.0) + (fused ? 0.0 : 4.7);
       if (best_cost == 0.0 || cost < best_cost) {
         best_cost = cost;
@@ -188,16 +188,18 @@ static void make_layout(const fastclip_config& cfg, bool lean, Layout* L) {
   // 128 x 128 tiles: asked for (wherever a quarter of the large tiles' workgroups would still not fill the chip), or
   // chosen when the large tiles would occupy at most half of the compute units (measured: b = 128 .. 1024 of
   // B = 1024 .. 8192 at width 512 are 4 - 22 % faster, b = 640 of 5120, 120 large tiles, breaks even)
-  const bool small_ok = L->bf16 && !L->gathered && !L->square && !L->fine && !(cfg.flags & FASTCLIP_TILES_256);
-  // (the kernels address rows by 32-bit byte offsets and hold the coefficients of a workgroup's local anchors in LDS)
+  const bool small_ok = L->bf16 && !L->square && !L->fine && !(cfg.flags & FASTCLIP_TILES_256);
+  // (the kernels address rows by 32-bit byte offsets, number their output tiles in 16 bits and hold the coefficients of a
+  // workgroup's local anchors in LDS)
   const int64_t ld_max = cfg.ld_img > cfg.ld_txt ? cfg.ld_img : cfg.ld_txt;
   L->t128 = small_ok && ((cfg.flags & FASTCLIP_TILES_128) ? big_tiles < 192 : big_tiles <= 128) &&
-            cfg.B * ld_max < ((int64_t)1 << 30) && cfg.b <= kMaxLocalQ - 128;
+            cfg.B * ld_max < ((int64_t)1 << 30) && cfg.b <= kMaxLocalQ - 128 &&
+            2 * ((cfg.b + 63) / 64) * ((cfg.d + 63) / 64) < 32768;
   size_t at = 0;
   auto take = [&](size_t bytes) { size_t o = at; at += round_up(bytes, 256); return o; };
   const size_t fb = sizeof(float) * (size_t)L->bstride;
   if (L->t128) {
-    L->nparts = (int)((cfg.B + 127) / 128);
+    L->nparts = L->gathered ? (int)((cfg.B + 255) / 256) : (int)((cfg.B + 127) / 128);
     L->ldE = (int64_t)round_up((size_t)cfg.B, 64);
     plan_t128(cfg, lean, L);
   } else if (L->fine) {
@@ -451,7 +453,7 @@ fastclip_status fastclip_describe(const fastclip_config* cfg, fastclip_plan* pla
   if (st != FASTCLIP_OK) return st;
   fc::Layout L;
   fc::make_layout(*cfg, &L);
-  plan->tile = !L.bf16 ? 0 : (L.t128 ? 128 : (L.fine ? 64 : 256));
+  plan->tile = !L.bf16 ? 0 : (L.t128 ? (L.gathered ? 256 : 128) : (L.fine ? 64 : 256));
   plan->single_pass = L.square;
   plan->gathered = L.gathered;
   plan->fused_state = L.fused_state;

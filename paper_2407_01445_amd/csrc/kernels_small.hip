@@ -221,7 +221,7 @@ __global__ void __launch_bounds__(256) k_prep_cols(const T* __restrict__ img, co
                                                    const float* __restrict__ tau_glob_txt,
                                                    const float* __restrict__ u_glob_img,
                                                    const float* __restrict__ u_glob_txt, int version, float eps,
-                                                   float bm, float* __restrict__ colp) {
+                                                   float bm, int from_own, float* __restrict__ colp) {
   const int lane = threadIdx.x & 63;
   const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (j >= ncol) return;
@@ -247,7 +247,9 @@ __global__ void __launch_bounds__(256) k_prep_cols(const T* __restrict__ img, co
     }
   }
   if (lane == 0) {
-    const int64_t ntile = ncol >> 8, tile = j >> 8, in = j & 255;
+    // column of row j: its number, or (from_own) counted from the worker's own rows on
+    const int64_t col = !from_own || j >= B ? j : (j >= off ? j - off : j - off + B);
+    const int64_t ntile = ncol >> 8, tile = col >> 8, in = col & 255;
     float* p0 = colp + ((0 * ntile + tile) * 4) * 256 + in;   // side 0: text anchors (tau_2, u_2)
     float* p1 = colp + ((1 * ntile + tile) * 4) * 256 + in;   // side 1: image anchors (tau_1, u_1)
     p0[0] = k2; p0[256] = d2; p0[512] = c2; p0[768] = 0.f;
@@ -264,12 +266,12 @@ void launch_prep_cols(const StepCtx& c) {
     hipLaunchKernelGGL(k_prep_cols<bf16_t>, grid, block, 0, c.s, (const bf16_t*)c.buf.img_glob,
                        (const bf16_t*)c.buf.txt_glob, c.cfg.ld_img, c.cfg.ld_txt, L.B, L.ncol, L.off, L.b, L.d,
                        c.buf.tau, c.buf.tau_glob_img, c.buf.tau_glob_txt, c.buf.u_glob_img, c.buf.u_glob_txt,
-                       c.cfg.version, c.cfg.eps, bm, colp);
+                       c.cfg.version, c.cfg.eps, bm, L.t128, colp);
   else
     hipLaunchKernelGGL(k_prep_cols<float>, grid, block, 0, c.s, (const float*)c.buf.img_glob,
                        (const float*)c.buf.txt_glob, c.cfg.ld_img, c.cfg.ld_txt, L.B, L.ncol, L.off, L.b, L.d,
                        c.buf.tau, c.buf.tau_glob_img, c.buf.tau_glob_txt, c.buf.u_glob_img, c.buf.u_glob_txt,
-                       c.cfg.version, c.cfg.eps, bm, colp);
+                       c.cfg.version, c.cfg.eps, bm, L.t128, colp);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -45,23 +45,48 @@ __device__ __forceinline__ void wave_reads_done() {
 // consecutive rows of an operand read cover a 256-byte bank window.
 __device__ __forceinline__ int p_swz(int row) { return (row >> 1) & 7; }
 
+struct T128StripJob {           // one strip
+  const bf16_t *X, *A;          // contrast row 0, first local anchor row
+  const float* kscale;          // log2(e) / tau of the anchors
+  bf16_t *E, *F;                // stored strip; gathered state: second strip
+  const float* colp;            // gathered state: [tile of 256 columns][4][256] column parameters
+  float* sums;                  // [2][nparts][bstride]
+  int ldx, lda;
+};
+struct T128StripArgs {
+  T128StripJob job[2];
+  const float* diag;            // s_pp per local anchor
+  int nCB, ldE, nparts, bstride, b, B, d, off;
+};
+
 // One workgroup per tile (128 anchors against 128 contrasts of one strip), eight waves = two groups of 2 x 2 waves of
 // 64 x 64: either group takes every other 64-deep stage, so that a SIMD always has a second wave to issue from, an operand
 // read serves two products, and the loop has half the barriers; afterwards the groups exchange halves of their
 // accumulators and each finishes half of the tile's columns.  Measured at 128 anchors of 1024 pairs, d = 512, against
 // four waves on 32-deep stages through a ring of five: 12.0 -> 8.5 us, of which (in-kernel counters, 2.4 GHz) 0.4 set-up, 1.1
 // until the first step is there, 2.6 in the four steps (1.7 of products), 0.7 exchange, 1.5 exponentials, 0.5 sums.
-__global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(StripArgs a) {
+//
+// GATHERED: every element also yields the weight f = c_j 2^(s k_j - d_j) with which contrast column j, an anchor of another
+// worker, moves the local row (Eqs. 3 / 5 / 7); it goes to a second strip of the same form.  A workgroup then takes two
+// neighbouring contrast tiles one after the other and leaves one partial sum for both: with its second exponential a
+// tile is longer, and at the sizes of this path one round of workgroups does for both.
+template <bool GATHERED>
+__global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
   __shared__ __attribute__((aligned(1024))) char ring[kStepRing];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kg = wave >> 2, q4 = wave & 3, wr = q4 >> 1, wc = q4 & 1, lr = lane & 31, hk = lane >> 5;
   const int ct = blockIdx.x, at = blockIdx.y, strip = blockIdx.z;    // no divisions: they are serial instructions at the start
-  const int a0 = at * kT, c0 = ct * kT;
-  const int B = (int)a.B, b = (int)a.b, off = (int)a.off, d = (int)a.d;
+  const int a0 = at * kT;
+  const int B = a.B, b = a.b, off = a.off, d = a.d;
+  const T128StripJob& J = a.job[strip];
   // pointers pinned in scalar registers: left in the argument segment they are loaded again behind every memory fence
-  const bf16_t *Xm = wave_uniform(a.contrasts[strip]), *Am = wave_uniform(a.anchors[strip]);
-  const int ldx = (int)a.ld_contrast[strip], lda = (int)a.ld_anchor[strip];
+  const bf16_t *Xm = wave_uniform(J.X), *Am = wave_uniform(J.A);
+  const int ldx = J.ldx, lda = J.lda;
   const uint32_t ring_addr = lds_addr(ring);
+  float total = 0.f;                              // tid < 256: quantity tid / 128 of anchor tid % 128
+  for (int sub = 0; sub < (GATHERED ? 2 : 1); ++sub) {
+  const int c0 = GATHERED ? ct * 256 + sub * kT : ct * kT;
+  if (c0 >= B) break;
   // wave loads of a stage: 8 rows x 128 bytes each, four per wave and operand.  A row that does not exist is fetched as
   // the last one that does; what it yields is masked in the epilogue.
   uint32_t ox[4], oa[4];
@@ -81,9 +106,12 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(StripArgs a) {
 #pragma unroll
   for (int tj = 0; tj < 2; ++tj) {
     const int m = a0 + wc * 64 + tj * 32 + lr;
-    kk[tj] = m < b ? a.kscale[strip][m] : 0.f;
+    kk[tj] = m < b ? J.kscale[m] : 0.f;
     dk[tj] = m < b ? a.diag[m] : 0.f;
   }
+  float col = 0.f;                                // GATHERED: the tile's column parameters, k_j, d_j, c_j of 128 columns
+  if (GATHERED && tid < 3 * kT)
+    col = J.colp[(ct * 4 + (tid >> 7)) * 256 + (c0 & 255) + (tid & (kT - 1))];
   // Load i (0 .. 3: contrasts, 4 .. 7: anchors) of this wave for a step.  A stage that does not exist is requested as the last
   // one and not used: the number of loads per step is constant.
   const uint32_t my = ring_addr + (uint32_t)(kg * kStage + q4 * 4096);
@@ -190,10 +218,13 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(StripArgs a) {
         }
   };
   if (kg) give(std::true_type{}); else give(std::false_type{});
+  float* scol = (float*)(ring + 8 * 8192 + 4 * 2 * kT * 4);          // [3][128]
+  if (GATHERED && tid < 3 * kT) scol[tid] = col;
   __syncthreads();
   const float* other = (const float*)(ring + (wave ^ 4) * 8192);
   float (*sred)[2][kT] = (float (*)[2][kT])(ring + 8 * 8192);        // [contrast half, group][quantity][anchor in the tile]
-  bf16_t* __restrict__ E = a.E[strip];
+  bf16_t* __restrict__ E = J.E;
+  bf16_t* __restrict__ F = J.F;
   // MASK: the tile reaches beyond the batch or the local anchors, or holds anchors' own columns (B_{i-} excludes i)
   auto finish = [&](auto masked, auto group) {
     constexpr bool MASK = decltype(masked)::value;
@@ -206,14 +237,25 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(StripArgs a) {
 #pragma unroll
       for (int ti = 0; ti < 2; ++ti) {
         const int c_first = c0 + wr * 64 + ti * 32 + kg * 16 + 4 * hk;
-        uint32_t pk[4];
+        uint32_t pk[4], pf[4];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
+          f32x4 ck, cd, cc;
+          if constexpr (GATHERED) {
+            const float* cp = scol + c_first - c0 + 8 * h;
+            ck = *(const f32x4*)cp; cd = *(const f32x4*)(cp + kT); cc = *(const f32x4*)(cp + 2 * kT);
+          }
+          float f[4];
           const f32x4 o = *(const f32x4*)(other + ((ti * 2 + tj) * 2 + h) * 256 + lane * 4);
           float e[4];
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            const float x = fmaf(acc[ti][tj][OWN + 4 * h + q] + o[q], k, -dkk);
+            const float s = acc[ti][tj][OWN + 4 * h + q] + o[q];
+            const float x = fmaf(s, k, -dkk);
+            if constexpr (GATHERED) {                 // the local rows' c is 0: no mask for the own column
+              f[q] = cc[q] * __builtin_amdgcn_exp2f(fmaf(s, ck[q], -cd[q]));
+              if (MASK) f[q] = anchor < b ? f[q] : 0.f;
+            }
             e[q] = __builtin_amdgcn_exp2f(x);
             if (MASK) {
               const int c = c_first + 8 * h + q;
@@ -224,11 +266,15 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(StripArgs a) {
           }
           pk[2 * h] = pack_bf16x2(e[0], e[1]);
           pk[2 * h + 1] = pack_bf16x2(e[2], e[3]);
+          if constexpr (GATHERED) { pf[2 * h] = pack_bf16x2(f[0], f[1]); pf[2 * h + 1] = pack_bf16x2(f[2], f[3]); }
         }
         const int cb = ((c0 + wr * 64) >> 4) + 2 * ti + kg;
         const u32x4 w = {pk[0], pk[1], pk[2], pk[3]};
-        if (!MASK || 16 * cb < (int)a.ldE)
-          *(u32x4*)(E + (((int64_t)((a0 + wc * 64) / 32 + tj) * a.nCB + cb) * 64 + lane) * 8) = w;
+        const int64_t word = (((int64_t)((a0 + wc * 64) / 32 + tj) * a.nCB + cb) * 64 + lane) * 8;
+        if (!MASK || 16 * cb < a.ldE) {
+          *(u32x4*)(E + word) = w;
+          if constexpr (GATHERED) { const u32x4 wf = {pf[0], pf[1], pf[2], pf[3]}; *(u32x4*)(F + word) = wf; }
+        }
       }
       const float g1 = (sg[0] + sg[1]) + (sg[2] + sg[3]), x1 = (sx[0] + sx[1]) + (sx[2] + sx[3]);
       const float g2 = g1 + __shfl_xor(g1, 32), x2 = x1 + __shfl_xor(x1, 32);
@@ -238,7 +284,7 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(StripArgs a) {
       }
     }
   };
-  const bool whole = a0 + kT <= b && c0 + kT <= B && at != ct;
+  const bool whole = a0 + kT <= b && c0 + kT <= B && a0 != c0;
   if (kg) {
     if (whole) finish(std::false_type{}, std::true_type{}); else finish(std::true_type{}, std::true_type{});
   } else {
@@ -247,9 +293,13 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(StripArgs a) {
   __syncthreads();
   if (tid < 2 * kT) {
     const int q = tid >> 7, m = tid & (kT - 1);
-    if (a0 + m < b)
-      a.sums[((size_t)(2 * strip + q) * a.nparts + ct) * a.bstride + a0 + m] =
-          (sred[0][q][m] + sred[1][q][m]) + (sred[2][q][m] + sred[3][q][m]);
+    total += (sred[0][q][m] + sred[1][q][m]) + (sred[2][q][m] + sred[3][q][m]);
+  }
+  if (GATHERED) { __syncthreads(); FC_FENCE(); }
+  }
+  if (tid < 2 * kT) {
+    const int q = tid >> 7, m = tid & (kT - 1);
+    if (a0 + m < b) J.sums[((size_t)q * a.nparts + ct) * a.bstride + a0 + m] = total;
   }
 }
 
@@ -257,47 +307,58 @@ void launch_strips_t128_bf16(const StepCtx& c) {
   const Layout& L = c.L;
   const bf16_t* img = (const bf16_t*)c.buf.img_glob;
   const bf16_t* txt = (const bf16_t*)c.buf.txt_glob;
-  StripArgs a;
+  T128StripArgs a;
   memset(&a, 0, sizeof(a));
-  a.anchors[0] = img + L.off * c.cfg.ld_img;  a.ld_anchor[0] = c.cfg.ld_img;
-  a.anchors[1] = txt + L.off * c.cfg.ld_txt;  a.ld_anchor[1] = c.cfg.ld_txt;
-  a.contrasts[0] = txt;                       a.ld_contrast[0] = c.cfg.ld_txt;
-  a.contrasts[1] = img;                       a.ld_contrast[1] = c.cfg.ld_img;
+  for (int i = 0; i < 2; ++i) {
+    T128StripJob& J = a.job[i];
+    J.X = i == 0 ? txt : img;
+    J.ldx = (int)(i == 0 ? c.cfg.ld_txt : c.cfg.ld_img);
+    J.A = i == 0 ? img + L.off * c.cfg.ld_img : txt + L.off * c.cfg.ld_txt;
+    J.lda = (int)(i == 0 ? c.cfg.ld_img : c.cfg.ld_txt);
+    J.kscale = (const float*)(c.ws + (i == 0 ? L.k1 : L.k2));
+    J.E = (bf16_t*)(c.ws + L.E[i]);
+    J.sums = (float*)(c.ws + L.sums) + (size_t)(2 * i) * L.nparts * L.bstride;
+    if (L.gathered) {
+      J.F = (bf16_t*)(c.ws + L.F[i]);
+      J.colp = (const float*)(c.ws + L.colp) + (size_t)i * 4 * L.ncol;
+    }
+  }
   a.diag = (const float*)(c.ws + L.diag);
-  a.kscale[0] = (const float*)(c.ws + L.k1);
-  a.kscale[1] = (const float*)(c.ws + L.k2);
-  a.E[0] = (bf16_t*)(c.ws + L.E[0]);
-  a.E[1] = (bf16_t*)(c.ws + L.E[1]);
-  a.nCB = L.ldE / 16;
-  a.ldE = L.ldE;
-  a.sums = (float*)(c.ws + L.sums);
-  a.nparts = L.nparts; a.bstride = L.bstride; a.b = L.b; a.B = L.B; a.d = L.d; a.off = L.off;
-  a.nAT = (int)((L.b + kT - 1) / kT);
-  a.nCT = (int)((L.B + kT - 1) / kT);
-  hipLaunchKernelGGL(k_strips_t128_bf16, dim3((unsigned)a.nCT, (unsigned)a.nAT, 2), dim3(512), 0, c.s, a);
+  a.nCB = (int)(L.ldE / 16); a.ldE = (int)L.ldE; a.nparts = L.nparts; a.bstride = (int)L.bstride;
+  a.b = (int)L.b; a.B = (int)L.B; a.d = (int)L.d; a.off = (int)L.off;
+  auto* kernel = L.gathered ? k_strips_t128_bf16<true> : k_strips_t128_bf16<false>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)L.nparts, (unsigned)((L.b + kT - 1) / kT), 2), dim3(512), 0, c.s, a);
 }
 
 // ----------------------------------------------------------------------------------------------------------------
 constexpr int kO = 64;                          // columns of an output tile; its rows: 64 MB
 constexpr int kGroups = 8;                      // state phase inside: 4 groups of 64 sums for the rows, 4 for the local anchors q
-// a wave's stage: 16 deep, 2 MB KiB of the strip and 2 KiB of X; what fits 160 KiB beside the coefficients
-template <int MB> constexpr int kWStage = 2048 * (MB + 1);
-template <int MB> constexpr int kWSlots = MB == 1 ? 4 : 3;
-template <int MB> constexpr int kWRing = 8 * kWSlots<MB> * kWStage<MB>;   // 128 / 144 KiB
+// a wave's stage: 16 deep, 2 MB KiB of the strip, 2 KiB of X and, with gathered state, 2 KiB of the second strip; as many as
+// fit 160 KiB beside the coefficients
+template <int MB, bool G> constexpr int kWStage = 2048 * (MB + 1 + (G ? 1 : 0));
+template <int MB, bool G> constexpr int kWSlots = MB == 1 && !G ? 4 : 3;
+template <int MB, bool G> constexpr int kWRing = 8 * kWSlots<MB, G> * kWStage<MB, G>;   // 128 / 144 KiB
 
 struct T128Job {
   const bf16_t* E;       // fragment-ordered strip of this side
+  const bf16_t* F;       // gathered state: the weights c_j l(j, p_r) of the remote anchors j, same form as E
   const bf16_t* Eo;      // ... of the other side, whose columns 0 .. b - 1 are the contrast-side term's weights
   const bf16_t* X;       // the matrix whose rows the strips weight (texts for side 0, images for side 1): also the rows of
                          // the diagonal terms, d_img[r] -= dcoef[r] txt[off + r]
   float* out;            // d_img / d_txt
   int64_t ldx;
 };
+// Division of numbers below 2^16 by a divisor below 2^16 whose reciprocal the host has formed (0: by 1).  An integer division is
+// some forty dependent instructions at the start of a kernel that has nothing to hide them behind.
+static inline unsigned reciprocal(int divisor) { return divisor > 1 ? (unsigned)(0xffffffffu / (unsigned)divisor + 1u) : 0u; }
+__device__ __forceinline__ int div_small(int x, unsigned inv) { return inv ? (int)(((uint64_t)(unsigned)x * inv) >> 32) : x; }
+
 struct T128Args {
   T128Job job[2];
   int b, d, B, off;
   int64_t nCB;
   int tiles_m, tiles_n, nsplit;
+  unsigned inv_tiles, inv_tiles_n;      // reciprocal(2 tiles_m tiles_n), reciprocal(tiles_n)
   int nA, nB;            // 16-deep stages over the contrasts / over the local anchors
   int sliceA, sliceB;    // ... per wave
   double* part;          // nsplit > 1: [tile][split][64 x 64 floats as pairs]
@@ -324,18 +385,25 @@ struct T128Args {
 // the waves and the outputs.  128-row tiles (MB = 2) move a quarter less per product and are taken where 64-row ones need
 // a second round of workgroups; the cost model is in plan_t128.  Steps before and after (fold + contraction + finalize
 // kernels before): 128 of 1024 pairs, d = 512: 34.2 -> 22.9 us, 256 of 8192: 48.6 -> 34.5, 1024 of 1024: 37.7 -> 30.0,
-// 1000 of 4000, d = 760 (128-row tiles): 71.5 -> 64.1.
-template <int MB>
+// 1000 of 4000, d = 760 (128-row tiles): 71.5 -> 61.9; 640 of 5120 with gathered state (a pass over both strips before): 74.8 ->
+// 62.1.  With the workgroups in plain order every XCD fetched every slice of the depth: 640 of 5120 gathered 67 us.
+// GATHERED: the remote anchors' weights multiply the same rows of X, so the first sum's operand is c_own E + F, formed as
+// E + F / c_own (the sum is multiplied by c_own afterwards) between the reads and the products of a stage.
+template <int MB, bool GATHERED>
 __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, StateArgs a) {
-  constexpr int kM = 64 * MB, kStageB = kWStage<MB>, kSlotsW = kWSlots<MB>, kX = 2048 * MB;
-  __shared__ __attribute__((aligned(1024))) char ring[kWRing<MB>];
-  __shared__ float psum[MB == 1 ? 8 * kGroups * 64 : 1];  // [wave][group][anchor]: partial sums of the coefficients' inputs
+  constexpr int kM = 64 * MB, kStageB = kWStage<MB, GATHERED>, kSlotsW = kWSlots<MB, GATHERED>, kX = 2048 * MB, kF = kX + 2048;
+  __shared__ __attribute__((aligned(1024))) char ring[kWRing<MB, GATHERED>];
   __shared__ __attribute__((aligned(16))) float crow[kM], drow[kM], cq[kMaxLocalQ];
   __shared__ int flag;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 31, hk = lane >> 5;
-  const int split = blockIdx.x, tm = blockIdx.y, side = blockIdx.z & 1, tn = blockIdx.z >> 1;
-  const int tile = (tn * 2 + side) * g.tiles_m + tm;
+  // Workgroups that share an XCD (id mod 8) take neighbours in the order split, side, row tile, column tile: the same slice of
+  // the depth and the same rows of the strips, which its L2 then fetches once.
+  const int p = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+  const int tiles = 2 * g.tiles_m * g.tiles_n;
+  if (p >= tiles * g.nsplit) return;
+  const int split = div_small(p, g.inv_tiles), tile = p - split * tiles;
+  const int sm = div_small(tile, g.inv_tiles_n), tn = tile - sm * g.tiles_n, side = sm >= g.tiles_m, tm = sm - side * g.tiles_m;
   const int m0 = tm * kM, n0 = tn * kO;
   const T128Job& J = g.job[side];
   // pinned in scalar registers: left in the argument segment they are loaded again behind every memory fence
@@ -347,6 +415,10 @@ __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, State
   const bool fused = MB == 1 && a.fused;
   const bool finisher = fused && side == 0 && tn == 0 && split == 0;
   const int nqg = (nq + 63) >> 6;
+
+  // [group][anchor] partial sums of a wave, in the slot of its ring that is requested last (behind the second barrier below)
+  auto psum = [&](int w) { return (float*)(ring + (w * kSlotsW + kSlotsW - 1) * kStageB); };
+  static_assert(kStageB >= kGroups * 64 * 4, "the partial sums fit a slot");
 
   // ---- inputs of the coefficients: of the 64 rows (both sides, for the diagonal factor too) and of the q's (the other side).
   // They are requested and waited for ahead of the operands: vector memory operations complete in order.
@@ -382,7 +454,7 @@ __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, State
       for (int j = 0; j < kGroups; ++j) s[j] += v[j];
     }
 #pragma unroll
-    for (int j = 0; j < kGroups; ++j) psum[(wave * kGroups + j) * 64 + lane] = s[j];
+    for (int j = 0; j < kGroups; ++j) psum(wave)[j * 64 + lane] = s[j];
   } else {
     for (int i = tid; i < kM + nqg * 64; i += 512) {
       if (i < kM) {
@@ -441,10 +513,15 @@ __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, State
     }
     open_rows(Q0 * 16);
   };
+  const int64_t to_f = GATHERED ? (const char*)wave_uniform(J.F) - (const char*)wave_uniform(J.E) : 0;
   uint32_t fill = wring;                       // slot of stage `at`
   auto request = [&]() {
 #pragma unroll
     for (int i = 0; i < 2 * MB; ++i) dma16(src, woff[i], fill + (uint32_t)(i * 1024));
+    if (GATHERED && at < nAw) {
+#pragma unroll
+      for (int i = 0; i < 2 * MB; ++i) dma16(src + to_f, woff[i], fill + (uint32_t)(kF + i * 1024));
+    }
     dma16(X, xoff[0], fill + (uint32_t)kX);
     dma16(X, xoff[1], fill + (uint32_t)(kX + 1024));
     fill = fill + kStageB == wring + kSlotsW * kStageB ? wring : fill + kStageB;
@@ -468,9 +545,9 @@ __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, State
   FC_FENCE();
   if (fused) {
     auto total = [&](int j, int al) {
-      float s = psum[j * 64 + al];
+      float s = psum(0)[j * 64 + al];
 #pragma unroll
-      for (int w = 1; w < 8; ++w) s += psum[(w * kGroups + j) * 64 + al];
+      for (int w = 1; w < 8; ++w) s += psum(w)[j * 64 + al];
       return s;
     };
     float u;
@@ -489,14 +566,16 @@ __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, State
       cq[j] = qbase + j < g.b
                   ? anchor_coefficient(a, total(4 + (j >> 6), j & 63), side == 0 ? u2 : u1, side == 0 ? t2 : t1, &u) : 0.f;
     }
+    const int fside = wave - 6;
+    float fse = 0.f, fsx = 0.f;
+    if (finishing) { fse = total(fside, lane); fsx = total(2 + fside, lane); }
     __syncthreads();
     FC_FENCE();
     if (finishing) {
       // 64 anchors: scatter, outputs, Eq. 9, their terms of the scalars.  Nobody in this launch waits for them but the wave that
       // adds the terms up at the very end.
-      const int fside = wave - 6;
       double lterm, hterm;
-      state_finish_side<false>(a, fside, m0 + lane, fn, total(fside, lane), total(2 + fside, lane), fu, ft, &lterm, &hterm);
+      state_finish_side<false>(a, fside, m0 + lane, fn, fse, fsx, fu, ft, &lterm, &hterm);
       double* red = a.red + 2 * ((int64_t)fside * g.b + m0 + lane);
       store_agent(red, lterm);
       store_agent(red + 1, hterm);
@@ -531,6 +610,14 @@ __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, State
   auto tr = [](uint32_t addr) {
     return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(uintptr_t)addr));
   };
+  float inv_c[2 * MB];                                // GATHERED: 1 / c_own of the operand's rows (lanes run over rows)
+  if constexpr (GATHERED) {
+#pragma unroll
+    for (int t = 0; t < 2 * MB; ++t) {
+      const float c = crow[t * 32 + lr];
+      inv_c[t] = m0 + t * 32 + lr < g.b ? 1.0f / c : 0.f;
+    }
+  }
   uint32_t slot = wring;
   // Stages [i0, i1): read stage i, request the next into the slot that stage i - 1 was read from, multiply.  The requests
   // hide the reads' latency, and the products run on into the next stage's wait.
@@ -538,18 +625,21 @@ __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, State
     constexpr bool OTHER = decltype(other_side)::value;
     const float* c = cq + (Q0 * 16 - qbase) + 4 * hk;      // c_other[q], two runs of four q per lane and stage
     for (int i = i0; i < i1; ++i) {
-      // stage i has landed: at most the younger ones, 2 MB + 2 loads each, may be in flight
-      if (MB == 1 && at - i == 3) __builtin_amdgcn_s_waitcnt(0x0f78);
+      // stage i has landed: at most the younger ones, 2 MB + 2 loads each (with a second strip two more), may be in flight
+      if (kSlotsW == 4 && at - i == 3) __builtin_amdgcn_s_waitcnt(0x0f78);
+      else if (at - i == 2 && GATHERED && i + 1 < nAw) __builtin_amdgcn_s_waitcnt(0x0f76);
       else if (at - i == 2) __builtin_amdgcn_s_waitcnt(MB == 1 ? 0x0f74 : 0x0f76);
       else __builtin_amdgcn_s_waitcnt(0x0f70);
       __builtin_amdgcn_wave_barrier();
       FC_FENCE();
       u32x4 w[2 * MB];
+      u32x4 wf[GATHERED && !OTHER ? 2 * MB : 1];
       u32x2 xl[2], xh[2];
 #pragma unroll
       for (int t = 0; t < 2 * MB; ++t) {
         if constexpr (!OTHER) {
           w[t] = *(const u32x4*)(wslot + (slot - wring) + t * 1024 + lane * 16);
+          if constexpr (GATHERED) wf[t] = *(const u32x4*)(wslot + (slot - wring) + kF + t * 1024 + lane * 16);
         } else {
           const u32x2 lo = tr(slot + rq[t][0]), hi = tr(slot + rq[t][1]);
           w[t] = (u32x4){lo[0], lo[1], hi[0], hi[1]};
@@ -566,6 +656,14 @@ __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, State
       FC_PIN();
       if (at < nst) request();
       wave_reads_done();                          // the stage's slot may be filled again
+      if constexpr (GATHERED && !OTHER) {
+#pragma unroll
+        for (int t = 0; t < 2 * MB; ++t)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            w[t][e] = pack_bf16x2(fmaf(__uint_as_float(wf[t][e] << 16), inv_c[t], __uint_as_float(w[t][e] << 16)),
+                                  fmaf(__uint_as_float(wf[t][e] & 0xffff0000u), inv_c[t], __uint_as_float(w[t][e] & 0xffff0000u)));
+      }
       if constexpr (OTHER) {
 #pragma unroll
         for (int t = 0; t < 2 * MB; ++t)
@@ -691,6 +789,7 @@ void launch_contract_t128_bf16(const StepCtx& c) {
     T128Job& J = g.job[s];
     J.E = (const bf16_t*)(c.ws + L.E[s]);
     J.Eo = (const bf16_t*)(c.ws + L.E[1 - s]);
+    J.F = L.gathered ? (const bf16_t*)(c.ws + L.F[s]) : nullptr;
     J.X = (const bf16_t*)(s == 0 ? c.buf.txt_glob : c.buf.img_glob);
     J.ldx = s == 0 ? c.cfg.ld_txt : c.cfg.ld_img;
     J.out = s == 0 ? c.buf.d_img : c.buf.d_txt;
@@ -698,15 +797,18 @@ void launch_contract_t128_bf16(const StepCtx& c) {
   g.b = (int)L.b; g.d = (int)L.d; g.B = (int)L.B; g.off = (int)L.off; g.nCB = L.ldE / 16;
   g.tiles_m = (int)((L.b + L.out_rows - 1) / L.out_rows); g.tiles_n = (int)((L.d + kO - 1) / kO);
   g.nsplit = L.nsplit;
+  g.inv_tiles = reciprocal(2 * g.tiles_m * g.tiles_n);
+  g.inv_tiles_n = reciprocal(g.tiles_n);
   g.nA = (int)((L.B + 15) / 16); g.nB = (int)((L.b + 15) / 16);
   g.sliceA = (g.nA + L.nsplit * 8 - 1) / (L.nsplit * 8);
   g.sliceB = (g.nB + L.nsplit * 8 - 1) / (L.nsplit * 8);
   g.part = L.nsplit > 1 ? (double*)(c.ws + L.Opart[0]) : nullptr;
   g.arrived = (unsigned*)(c.ws + L.arrived);
   g.tau = c.buf.tau; g.rho = c.cfg.rho; g.loss = c.buf.loss; g.d_tau = c.buf.d_tau;
-  auto* kernel = L.out_rows == 64 ? k_contract_t128_bf16<1> : k_contract_t128_bf16<2>;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)g.nsplit, (unsigned)g.tiles_m, 2u * (unsigned)g.tiles_n), dim3(512), 0, c.s, g,
-                     make_state_args(c));
+  auto* kernel = L.gathered ? k_contract_t128_bf16<1, true>
+                            : (L.out_rows == 64 ? k_contract_t128_bf16<1, false> : k_contract_t128_bf16<2, false>);
+  const unsigned groups = 2u * (unsigned)(g.nsplit * g.tiles_m * g.tiles_n);
+  hipLaunchKernelGGL(kernel, dim3((groups + 7) / 8 * 8), dim3(512), 0, c.s, g, make_state_args(c));
 }
 
 }  // namespace fc

@@ -481,7 +481,7 @@ def gathered_inputs(rng, B, version):
     return ug1, ug2, tg1, tg2
 
 
-def run_gathered(B, b, off, d, version, dtype, tol, N=5000, ld_pad=0):
+def run_gathered(B, b, off, d, version, dtype, tol, N=5000, ld_pad=0, tiles=256):
     rng = np.random.default_rng(7 * B + version)
     img, txt = make_embeddings(B + d + 1, B, d, 0.5, dtype)
     idx = draw_indices(B + 2, b, N)
@@ -500,7 +500,7 @@ def run_gathered(B, b, off, d, version, dtype, tol, N=5000, ld_pad=0):
     g = GpuStep(B=B, b=b, off=off, d=d, N=N, dtype=dtype, version=version, eps=1e-6, rho=6.5, tau=0.07,
                 tau_grad_scale=1.0 / N, ld_img=d + ld_pad, ld_txt=d, u_img0=u0i, u_txt0=u0t, tau_img0=t_img,
                 tau_txt0=t_txt, gathered=dict(u_img=poisoned(ug1), u_txt=poisoned(ug2), tau_img=poisoned(tg1),
-                                              tau_txt=poisoned(tg2)))
+                                              tau_txt=poisoned(tg2)), tiles=tiles)
     g.set_inputs(img, txt, idx)
     g.step(0.6)
     u_img, u_txt = u0i.astype(np.float64), u0t.astype(np.float64)
@@ -531,6 +531,36 @@ def test_f32_gathered_state(version):
 @pytest.mark.parametrize("version", [V0, V1, V2, V3])
 def test_bf16_gathered_state(B, b, off, d, version):
     run_gathered(B, b, off, d, version, "bf16", TOL_BF16, ld_pad=8)
+
+
+@pytest.mark.parametrize("B,b,off,d", [
+    # one contrast tile of a pair, a second one that is short, columns wrapping inside a tile and inside a stage
+    (100, 9, 91, 64), (300, 130, 57, 72), (257, 65, 3, 136), (1000, 64, 936, 520),
+    # several splits; the state phase on its own
+    (2048, 256, 768, 512), (5120, 640, 3200, 512)])
+@pytest.mark.parametrize("version", [V0, V2])
+def test_bf16_gathered_state_on_small_tiles(B, b, off, d, version):
+    run_gathered(B, b, off, d, version, "bf16", TOL_BF16, ld_pad=8, tiles=None)
+
+
+@pytest.mark.parametrize("b,d,ld,at", [(3, 4, 4, 0), (5, 1020, 1024, 0), (6, 516, 516, 4), (7, 512, 512, 1), (9, 1028, 1028, 0)])
+def test_normalize_rows_alignment(b, d, ld, at):
+    """Rows of whole aligned groups of four are held in registers; an odd start, a stride or width that is none, or a wider row
+    takes the element-wise kernel: the same rows to the last bit of the rounding, whichever it is."""
+    rng = np.random.default_rng(b * d)
+    flat = np.full(at + b * ld + 8, np.nan, np.float32)
+    raw = raw_rows(rng, b, d, "f32")
+    for r in range(b):
+        flat[at + r * ld: at + r * ld + d] = raw[r]
+    t_raw = torch.from_numpy(flat).to(DEV)
+    t_unit, t_norm = torch.full((b, ld), 7.5, device=DEV), torch.empty(b, device=DEV)
+    fc.fastclip_normalize_rows(t_raw.data_ptr() + 4 * at, fc.F32, ld, b, d, t_unit, fc.F32, ld, t_norm)
+    torch.cuda.synchronize()
+    want, norm = normalize_rows(raw.astype(np.float64))
+    assert rel_each(t_norm.cpu().numpy().astype(np.float64), norm) <= 2e-7
+    # one rounding of 1 / |e| and one of the product: 2^-24 each
+    assert np.all(np.abs(t_unit[:, :d].cpu().numpy().astype(np.float64) - want) <= (2.0 ** -23 + 3e-7) * np.abs(want))
+    assert (t_unit[:, d:] == 7.5).all()
 
 
 def test_gathered_state_with_whole_batch_is_the_plain_step():
