@@ -26,12 +26,9 @@
 
 namespace fc {
 
-constexpr int kT = 128;                         // anchors and contrasts of a strip tile
+constexpr int kT = 128;                         // contrasts of a strip tile; its anchors: AT = 64 or 128
 constexpr int kD = 64;                          // depth of a strip stage: whole 128-byte lines
-constexpr int kPanel = kT * kD * 2;             // one operand of a stage: 16 KiB
-constexpr int kStage = 2 * kPanel;
-constexpr int kStep = 2 * kStage;               // a step = one stage for either group of waves
-constexpr int kStepRing = 2 * kStep;            // 128 KiB
+constexpr int kPanel = kT * kD * 2;             // the contrasts of a stage: 16 KiB
 
 // The wave's LDS reads have returned (lgkmcnt 0): what it read from may be written again.
 __device__ __forceinline__ void wave_reads_done() {
@@ -70,34 +67,37 @@ struct T128StripArgs {
 // worker, moves the local row (Eqs. 3 / 5 / 7); it goes to a second strip of the same form.  A workgroup then takes two
 // neighbouring contrast tiles one after the other and leaves one partial sum for both: with its second exponential a
 // tile is longer, and at the sizes of this path one round of workgroups does for both.
-template <bool GATHERED>
+template <int AT, bool GATHERED>
 __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
-  __shared__ __attribute__((aligned(1024))) char ring[kStepRing];
+  constexpr int WC = AT / 64, NI = WC;            // waves across the anchors; 32-row blocks of contrasts per wave
+  constexpr int kStage = kPanel + AT * kD * 2, kStep = 2 * kStage;   // a step = one stage for either group of waves
+  constexpr int NL = 4 + 2 * WC;                  // wave loads per step: 4 of the contrasts, 2 or 4 of the anchors
+  constexpr int CW = 32 * NI;                     // contrasts of a wave
+  __shared__ __attribute__((aligned(1024))) char ring[2 * kStep];    // 96 / 128 KiB
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int kg = wave >> 2, q4 = wave & 3, wr = q4 >> 1, wc = q4 & 1, lr = lane & 31, hk = lane >> 5;
+  const int kg = wave >> 2, q4 = wave & 3, wr = q4 / WC, wc = q4 % WC, lr = lane & 31, hk = lane >> 5;
   const int ct = blockIdx.x, at = blockIdx.y, strip = blockIdx.z;    // no divisions: they are serial instructions at the start
-  const int a0 = at * kT;
+  const int a0 = at * AT;
   const int B = a.B, b = a.b, off = a.off, d = a.d;
   const T128StripJob& J = a.job[strip];
   // pointers pinned in scalar registers: left in the argument segment they are loaded again behind every memory fence
   const bf16_t *Xm = wave_uniform(J.X), *Am = wave_uniform(J.A);
   const int ldx = J.ldx, lda = J.lda;
   const uint32_t ring_addr = lds_addr(ring);
-  float total = 0.f;                              // tid < 256: quantity tid / 128 of anchor tid % 128
+  float total = 0.f;                              // tid < 2 AT: quantity tid / AT of anchor tid % AT
   for (int sub = 0; sub < (GATHERED ? 2 : 1); ++sub) {
   const int c0 = GATHERED ? ct * 256 + sub * kT : ct * kT;
   if (c0 >= B) break;
   // wave loads of a stage: 8 rows x 128 bytes each, four per wave and operand.  A row that does not exist is fetched as
   // the last one that does; what it yields is masked in the epilogue.
-  uint32_t ox[4], oa[4];
+  uint32_t ox[NL];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = 8 * (4 * q4 + i) + (lane >> 3);
-    const uint32_t piece = (uint32_t)(((lane & 7) ^ p_swz(row)) * 16);
+  for (int i = 0; i < NL; ++i) {
+    const int row = (i < 4 ? 8 * (4 * q4 + i) : 8 * (2 * WC * q4 + i - 4)) + (lane >> 3);
     int g = off + (c0 + row < B ? c0 + row : B - 1);
     g -= g >= B ? B : 0;
-    ox[i] = (uint32_t)(g * ldx) * 2u + piece;
-    oa[i] = (uint32_t)((a0 + row < b ? a0 + row : b - 1) * lda) * 2u + piece;
+    const int m = a0 + row < b ? a0 + row : b - 1;
+    ox[i] = (uint32_t)(i < 4 ? g * ldx : m * lda) * 2u + (uint32_t)(((lane & 7) ^ p_swz(row)) * 16);
   }
   const int S = (d + kD - 1) / kD, steps = (S + 1) / 2;
   const int tail = (d % kD) / 8;                  // 16-byte chunks of the last stage that exist (0: all eight)
@@ -112,76 +112,81 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
   float col = 0.f;                                // GATHERED: the tile's column parameters, k_j, d_j, c_j of 128 columns
   if (GATHERED && tid < 3 * kT)
     col = J.colp[(ct * 4 + (tid >> 7)) * 256 + (c0 & 255) + (tid & (kT - 1))];
-  // Load i (0 .. 3: contrasts, 4 .. 7: anchors) of this wave for a step.  A stage that does not exist is requested as the last
+  // Load i (0 .. 3: contrasts, then anchors) of this wave for a step.  A stage that does not exist is requested as the last
   // one and not used: the number of loads per step is constant.
-  const uint32_t my = ring_addr + (uint32_t)(kg * kStage + q4 * 4096);
+  const uint32_t my = ring_addr + (uint32_t)(kg * kStage);
   auto request = [&](auto edge, int step, int i) {
     int st = step * 2 + kg;
-    uint32_t o = i < 4 ? ox[i & 3] : oa[i & 3];
+    uint32_t o = ox[i];
+    const int row8 = i < 4 ? 4 * q4 + i : 2 * WC * q4 + i - 4;        // its rows: 8 row8 .. + 7 of the panel
     if constexpr (decltype(edge)::value) {
       st = st < S ? st : S - 1;
       if (tail && st == S - 1) {                  // a chunk beyond the row is fetched as the stage's first one, and not used
-        const int row = 8 * (4 * q4 + (i & 3)) + (lane >> 3), c = (lane & 7) ^ p_swz(row);
+        const int row = 8 * row8 + (lane >> 3), c = (lane & 7) ^ p_swz(row);
         if (c >= tail) o -= (uint32_t)c * 16u;
       }
     }
-    dma16((i < 4 ? Xm : Am) + st * kD, o, my + (uint32_t)((step & 1) * kStep + (i < 4 ? 0 : kPanel) + (i & 3) * 1024));
+    dma16((i < 4 ? Xm : Am) + st * kD, o, my + (uint32_t)((step & 1) * kStep + (i < 4 ? 0 : kPanel) + row8 * 1024));
   };
 #pragma unroll
-  for (int i = 0; i < 8; ++i) request(std::true_type{}, 0, i);
+  for (int i = 0; i < NL; ++i) request(std::true_type{}, 0, i);
   if (steps > 1) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) request(std::true_type{}, 1, i);
+    for (int i = 0; i < NL; ++i) request(std::true_type{}, 1, i);
   }
-  f32x16 acc[2][2];
+  f32x16 acc[NI][2];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < NI; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  if (steps > 1) FC_WAIT_VMCNT8(); else FC_WAIT_VMCNT0();
+  if (steps == 1) FC_WAIT_VMCNT0();
+  else if (NL == 8) FC_WAIT_VMCNT8();
+  else __builtin_amdgcn_s_waitcnt(0x0f76);      // vmcnt(6)
   __syncthreads();
   FC_FENCE();
-  const int rx = wr * 64 + lr, ra = wc * 64 + lr;     // rows 32 further on share the swizzle
+  const int rx = wr * CW + lr, ra = wc * 64 + lr;     // rows 32 further on share the swizzle
   // EDGE: the step holds the last stage (which may end inside, or not exist for group 1)
-  auto read = [&](auto edge, int s, int kq, bf16x8 (&x)[2], bf16x8 (&y)[2]) {
+  auto read = [&](auto edge, int s, int kq, bf16x8 (&x)[NI], bf16x8 (&y)[2]) {
     const char* px = ring + (s & 1) * kStep + kg * kStage + rx * 128;
     const char* pa = ring + (s & 1) * kStep + kg * kStage + kPanel + ra * 128;
     const int c = 2 * kq + hk, st = s * 2 + kg;
     const int valid = st >= S ? 0 : (tail && st == S - 1 ? tail : 8);
+    const u32x4 z = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      u32x4 v = *(const u32x4*)(px + i * 4096 + ((c ^ p_swz(rx)) << 4));
+      if constexpr (decltype(edge)::value) v = c < valid ? v : z;
+      x[i] = __builtin_bit_cast(bf16x8, v);
+    }
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      u32x4 vx = *(const u32x4*)(px + i * 4096 + ((c ^ p_swz(rx)) << 4));
-      u32x4 va = *(const u32x4*)(pa + i * 4096 + ((c ^ p_swz(ra)) << 4));
-      if constexpr (decltype(edge)::value) {
-        const u32x4 z = {0u, 0u, 0u, 0u};
-        vx = c < valid ? vx : z;
-        va = c < valid ? va : z;
-      }
-      x[i] = __builtin_bit_cast(bf16x8, vx);
-      y[i] = __builtin_bit_cast(bf16x8, va);
+      u32x4 v = *(const u32x4*)(pa + i * 4096 + ((c ^ p_swz(ra)) << 4));
+      if constexpr (decltype(edge)::value) v = c < valid ? v : z;
+      y[i] = __builtin_bit_cast(bf16x8, v);
     }
   };
-  // Four products on (x, y); loads r, r + 1 of step `next` are dealt out between them: a direct-to-LDS load holds its wave for
+  // The products on (x, y); loads r, r + 1 of step `next` are dealt out between them: a direct-to-LDS load holds its wave for
   // about a hundred cycles when all eight waves issue, which the SIMD's other wave fills with its products.
-  auto multiply = [&](auto edge, const bf16x8 (&x)[2], const bf16x8 (&y)[2], bool more, int next, int r) {
-    acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[0], acc[0][0], 0, 0, 0);
-    acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[1], acc[0][1], 0, 0, 0);
-    FC_PIN();
-    if (more) request(edge, next, r);
-    FC_PIN();
-    acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], y[0], acc[1][0], 0, 0, 0);
-    acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], y[1], acc[1][1], 0, 0, 0);
-    FC_PIN();
-    if (more) request(edge, next, r + 1);
-    FC_PIN();
+  auto multiply = [&](auto edge, const bf16x8 (&x)[NI], const bf16x8 (&y)[2], bool more, int next, int r) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int p = 0; p < NI; ++p) {              // NI products, then a load
+        const int ti = NI == 2 ? h : 0, tj = NI == 2 ? p : h;
+        acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[ti], y[tj], acc[ti][tj], 0, 0, 0);
+      }
+      FC_PIN();
+      if (more && r + h < NL) request(edge, next, r + h);
+      FC_PIN();
+    }
   };
-  // Step s: loads 2 .. 7 of step s + 1 go out between its first products (0 and 1 went out behind the barrier of step s - 1);
+  // Step s: the loads from 2 on of step s + 1 go out between its first products (0 and 1 went out behind the barrier of step s - 1);
   // three quarters in, the step's panels have been read and the next step's have landed.
   auto step = [&](auto edge_here, auto edge_next, int s) {
-    bf16x8 x0[2], y0[2], x1[2], y1[2];
+    bf16x8 x0[NI], y0[2], x1[NI], y1[2];
     const bool fill = s > 0 && s + 1 < steps;
     read(edge_here, s, 0, x0, y0);
     read(edge_here, s, 1, x1, y1);
@@ -207,7 +212,7 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
     constexpr int FROM = decltype(group)::value ? 0 : 8;        // the half that the other group finishes
     float* mine = (float*)(ring + wave * 8192) + lane * 4;
 #pragma unroll
-    for (int ti = 0; ti < 2; ++ti)
+    for (int ti = 0; ti < NI; ++ti)
 #pragma unroll
       for (int tj = 0; tj < 2; ++tj)
 #pragma unroll
@@ -218,11 +223,11 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
         }
   };
   if (kg) give(std::true_type{}); else give(std::false_type{});
-  float* scol = (float*)(ring + 8 * 8192 + 4 * 2 * kT * 4);          // [3][128]
+  float* scol = (float*)(ring + 8 * 8192 + 4096);          // [3][128]
   if (GATHERED && tid < 3 * kT) scol[tid] = col;
   __syncthreads();
   const float* other = (const float*)(ring + (wave ^ 4) * 8192);
-  float (*sred)[2][kT] = (float (*)[2][kT])(ring + 8 * 8192);        // [contrast half, group][quantity][anchor in the tile]
+  float (*sred)[2][AT] = (float (*)[2][AT])(ring + 8 * 8192);        // [contrasts' wave, group][quantity][anchor in the tile]: 4 KiB
   bf16_t* __restrict__ E = J.E;
   bf16_t* __restrict__ F = J.F;
   // MASK: the tile reaches beyond the batch or the local anchors, or holds anchors' own columns (B_{i-} excludes i)
@@ -235,8 +240,8 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
       const float k = kk[tj], dkk = dk[tj] * k;
       float sg[4] = {0.f, 0.f, 0.f, 0.f}, sx[4] = {0.f, 0.f, 0.f, 0.f};   // independent chains
 #pragma unroll
-      for (int ti = 0; ti < 2; ++ti) {
-        const int c_first = c0 + wr * 64 + ti * 32 + kg * 16 + 4 * hk;
+      for (int ti = 0; ti < NI; ++ti) {
+        const int c_first = c0 + wr * CW + ti * 32 + kg * 16 + 4 * hk;
         uint32_t pk[4], pf[4];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -268,7 +273,7 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
           pk[2 * h + 1] = pack_bf16x2(e[2], e[3]);
           if constexpr (GATHERED) { pf[2 * h] = pack_bf16x2(f[0], f[1]); pf[2 * h + 1] = pack_bf16x2(f[2], f[3]); }
         }
-        const int cb = ((c0 + wr * 64) >> 4) + 2 * ti + kg;
+        const int cb = ((c0 + wr * CW) >> 4) + 2 * ti + kg;
         const u32x4 w = {pk[0], pk[1], pk[2], pk[3]};
         const int64_t word = (((int64_t)((a0 + wc * 64) / 32 + tj) * a.nCB + cb) * 64 + lane) * 8;
         if (!MASK || 16 * cb < a.ldE) {
@@ -284,21 +289,24 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
       }
     }
   };
-  const bool whole = a0 + kT <= b && c0 + kT <= B && a0 != c0;
+  const bool whole = a0 + AT <= b && c0 + kT <= B && (a0 >= c0 + kT || c0 >= a0 + AT);
   if (kg) {
     if (whole) finish(std::false_type{}, std::true_type{}); else finish(std::true_type{}, std::true_type{});
   } else {
     if (whole) finish(std::false_type{}, std::false_type{}); else finish(std::true_type{}, std::false_type{});
   }
   __syncthreads();
-  if (tid < 2 * kT) {
-    const int q = tid >> 7, m = tid & (kT - 1);
-    total += (sred[0][q][m] + sred[1][q][m]) + (sred[2][q][m] + sred[3][q][m]);
+  if (tid < 2 * AT) {
+    const int q = tid / AT, m = tid % AT;
+    float part = 0.f;
+#pragma unroll
+    for (int w = 0; w < 8 / WC; w += 2) part += sred[w][q][m] + sred[w + 1][q][m];
+    total += part;
   }
   if (GATHERED) { __syncthreads(); FC_FENCE(); }
   }
-  if (tid < 2 * kT) {
-    const int q = tid >> 7, m = tid & (kT - 1);
+  if (tid < 2 * AT) {
+    const int q = tid / AT, m = tid % AT;
     if (a0 + m < b) J.sums[((size_t)q * a.nparts + ct) * a.bstride + a0 + m] = total;
   }
 }
@@ -326,8 +334,15 @@ void launch_strips_t128_bf16(const StepCtx& c) {
   a.diag = (const float*)(c.ws + L.diag);
   a.nCB = (int)(L.ldE / 16); a.ldE = (int)L.ldE; a.nparts = L.nparts; a.bstride = (int)L.bstride;
   a.b = (int)L.b; a.B = (int)L.B; a.d = (int)L.d; a.off = (int)L.off;
-  auto* kernel = L.gathered ? k_strips_t128_bf16<true> : k_strips_t128_bf16<false>;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)L.nparts, (unsigned)((L.b + kT - 1) / kT), 2), dim3(512), 0, c.s, a);
+  // 64 anchors per tile where that still is one round of workgroups: more compute units, and a tile takes 7.0 us instead of 8.8
+  // (128 anchors of 1024, d = 512; steps: 24.0 -> 22.7 us, 256 of 2048 from raw rows 40.4 -> 38.4, 1024 of 1024 30.7 -> 30.1).
+  // Beyond one round two tiles of 64 take longer than one of 128 (3.5 us of either are its start and end).
+  const int64_t at64 = 2 * ((L.b + 63) / 64) * (int64_t)L.nparts;
+  const bool narrow = at64 <= 256;
+  auto* kernel = L.gathered ? (narrow ? k_strips_t128_bf16<64, true> : k_strips_t128_bf16<128, true>)
+                            : (narrow ? k_strips_t128_bf16<64, false> : k_strips_t128_bf16<128, false>);
+  const int64_t at_rows = narrow ? 64 : 128;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)L.nparts, (unsigned)((L.b + at_rows - 1) / at_rows), 2), dim3(512), 0, c.s, a);
 }
 
 // ----------------------------------------------------------------------------------------------------------------
