@@ -424,6 +424,8 @@ __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, State
   // pinned in scalar registers: left in the argument segment they are loaded again behind every memory fence
   const int B = __builtin_amdgcn_readfirstlane(g.B), ldx = __builtin_amdgcn_readfirstlane((int)J.ldx);
   const bf16_t* X = wave_uniform(J.X);
+  float* out = const_cast<float*>(wave_uniform(J.out));
+  const int d = __builtin_amdgcn_readfirstlane(g.d);
   const int qbase = split * 8 * g.sliceB * 16;       // this workgroup's local anchors q
   int nq = g.b - qbase < 8 * g.sliceB * 16 ? g.b - qbase : 8 * g.sliceB * 16;
   nq = nq < 0 ? 0 : nq;
@@ -503,7 +505,7 @@ __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, State
       int r = g.off + col + k;                 // below 2 B + 16: a division would take longer
       while (r >= B) r -= B;
       grow[i] = r;
-      xoff[i] = (uint32_t)(r * ldx + (n0 + pc * 8 < g.d ? n0 + pc * 8 : n0)) * 2u;
+      xoff[i] = (uint32_t)(r * ldx + (n0 + pc * 8 < d ? n0 + pc * 8 : n0)) * 2u;
     }
   };
   // Strip operand of the first sum: the fragments (m0 / 32 + i, stage), 1 KiB each.  Of the second: 16 anchors q x 64 columns r as
@@ -719,7 +721,7 @@ __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, State
   // ---- the eight waves' tiles are added up, 64 rows at a time: wave w finishes block w / 2 of them, its rows 16 (w % 2) .. + 15
   const int rl = (wave >> 2) * 32 + (wave & 1) * 16 + 4 * hk;          // row of e = 0; e = 4: 8 further on
   const int n = n0 + ((wave >> 1) & 1) * 32 + lr;
-  float* out = J.out;
+  const bool whole = m0 + kM <= g.b && n0 + kO <= d;
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
     const int row0 = mb * 64 + rl;
@@ -731,7 +733,7 @@ __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, State
     for (int e = 0; e < 8; ++e) {
       int m = m0 + row0 + 8 * (e >> 2) + (e & 3);
       m = m < g.b ? m : g.b - 1;
-      xd[e] = X[(uint32_t)((g.off + m) * ldx + (n < g.d ? n : 0))];
+      xd[e] = X[(uint32_t)((g.off + m) * ldx + (n < d ? n : 0))];
     }
     __syncthreads();
     FC_FENCE();
@@ -781,12 +783,18 @@ __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, State
       }
     }
     if (writer) {
-      float* o = out + (int64_t)(m0 + row0) * g.d + n;
-      const int rows = n < g.d ? g.b - m0 - row0 : 0;
+      float v[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int m = 8 * (e >> 2) + (e & 3);
-        if (m < rows) o[m * g.d] = sum[e >> 2][e & 3] - dc[e >> 2][e & 3] * bf2f(xd[e]);
+      for (int e = 0; e < 8; ++e) v[e] = sum[e >> 2][e & 3] - dc[e >> 2][e & 3] * bf2f(xd[e]);
+      float* o = out + (uint32_t)((m0 + row0) * d + n);
+      if (whole) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[(8 * (e >> 2) + (e & 3)) * d] = v[e];
+      } else {
+        const int rows = n < d ? g.b - m0 - row0 : 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (8 * (e >> 2) + (e & 3) < rows) o[(8 * (e >> 2) + (e & 3)) * d] = v[e];
       }
     }
   }

@@ -106,9 +106,21 @@ __device__ inline void write_scalars(const double* red, int nblocks, int64_t b, 
                                      float* loss, float* d_tau) {
   const int lane = threadIdx.x & 63;
   double A = 0.0, H = 0.0;
-  for (int i = lane; i < nblocks; i += 64) {
-    A += AGENT ? load_agent(red + 2 * i) : red[2 * i];
-    H += AGENT ? load_agent(red + 2 * i + 1) : red[2 * i + 1];
+  if (AGENT) {               // loads past the caches take their time: eight in flight
+    for (int i = lane; i < nblocks; i += 256) {
+      double x[4], y[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int j = i + 64 * q < nblocks ? i + 64 * q : i;
+        x[q] = load_agent(red + 2 * j);
+        y[q] = load_agent(red + 2 * j + 1);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (i + 64 * q < nblocks) { A += x[q]; H += y[q]; }
+    }
+  } else {
+    for (int i = lane; i < nblocks; i += 64) { A += red[2 * i]; H += red[2 * i + 1]; }
   }
   A = wave_sum_f64(A) / (double)b;
   H = wave_sum_f64(H) / (double)b;
