@@ -150,13 +150,15 @@ size_t fastclip_workspace_bytes(const fastclip_config* cfg);
  * gives, then *plan is untouched).  For callers that want to know which kernels a profile will show and for the
  * benchmark's labels; nothing in it has to be passed back. */
 typedef struct {
-  int32_t tile;          /* rows of a strip tile on the bf16 path: 256, 128, or 64 for FASTCLIP_FINE_TILES (whose strip tiles
-                            are 128 x 128 and output tiles 64 x 64); 0 on the fp32 path */
+  int32_t tile;          /* the kernels of the bf16 path: 256 those of 256 x 256 tiles, 128 those of the small tiles (strip tiles
+                            of 64 or 128 anchors by 128 contrasts), 64 FASTCLIP_FINE_TILES (strip tiles 128 x 128, output
+                            tiles 64 x 64); 0 on the fp32 path */
   int32_t single_pass;   /* 1: b == B and the similarity matrix is formed once */
   int32_t gathered;      /* 1: the contrast side runs over every global anchor (flag set and b < B) */
-  int32_t fused_state;   /* 1: the state phase runs inside the fold kernel or, on 128-row tiles, the contraction */
+  int32_t fused_state;   /* 1: the state phase runs inside the fold kernel or, with tile 128, inside the contraction */
   int32_t nsplit;        /* splits of the contraction's column range over workgroups */
-  int32_t nparts;        /* partial sums per anchor and quantity that the strip phase leaves to the state phase */
+  int32_t nparts;        /* partial sums per anchor and quantity that the strip phase leaves to the state phase (one per
+                            contrast tile; with tile 128 and gathered state one per two of them) */
 } fastclip_plan;
 fastclip_status fastclip_describe(const fastclip_config* cfg, fastclip_plan* plan);
 

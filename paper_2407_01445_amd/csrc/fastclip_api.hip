@@ -453,7 +453,7 @@ fastclip_status fastclip_describe(const fastclip_config* cfg, fastclip_plan* pla
   if (st != FASTCLIP_OK) return st;
   fc::Layout L;
   fc::make_layout(*cfg, &L);
-  plan->tile = !L.bf16 ? 0 : (L.t128 ? (L.gathered ? 256 : 128) : (L.fine ? 64 : 256));
+  plan->tile = !L.bf16 ? 0 : (L.t128 ? 128 : (L.fine ? 64 : 256));
   plan->single_pass = L.square;
   plan->gathered = L.gathered;
   plan->fused_state = L.fused_state;

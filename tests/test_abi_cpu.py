@@ -119,6 +119,13 @@ def test_describe_reports_the_plan():
     assert sq["single_pass"] == 1 and sq["tile"] == 256
     assert fc.fastclip_describe(good_cfg(emb_dtype=fc.F32))["tile"] == 0
     g = fc.fastclip_describe(good_cfg(flags=fc.GATHERED_STATE))
+    assert g["gathered"] == 1 and g["tile"] == 128 and g["nparts"] == 4
+    small = dict(B=5120, b=640, off=3200, d=512)
+    g = fc.fastclip_describe(good_cfg(flags=fc.GATHERED_STATE, **small))
+    assert g["gathered"] == 1 and g["tile"] == 128 and g["nparts"] == 20         # k_strips_t128_bf16 / k_contract_t128_bf16
+    g = fc.fastclip_describe(good_cfg(flags=fc.GATHERED_STATE | fc.TILES_256, **small))
+    assert g["gathered"] == 1 and g["tile"] == 256 and g["nparts"] == 20         # k_strips_bf16 / k_contract_bf16
+    g = fc.fastclip_describe(good_cfg(flags=fc.GATHERED_STATE, B=32768, b=1024, off=0, d=1024))
     assert g["gathered"] == 1 and g["tile"] == 256
     with pytest.raises(RuntimeError):
         fc.fastclip_describe(good_cfg(B=1))
@@ -149,8 +156,8 @@ def test_plans_are_sane_over_a_sweep_of_shapes():
 
 def test_tile_size_is_chosen_by_the_batch_size_unless_asked_for():
     """At most 128 large strip tiles: the library takes 128 x 128 tiles by itself (the layout FASTCLIP_TILES_128 asks for);
-    FASTCLIP_TILES_128 reaches up to 191 large tiles; beyond that, with gathered state and in the single-pass form the tiles
-    are large whatever is asked."""
+    FASTCLIP_TILES_128 reaches up to 191 large tiles, with gathered state as without; beyond that and in the single-pass
+    form the tiles are large whatever is asked."""
     ws = fc.fastclip_workspace_bytes
     small = dict(B=1024, b=256, off=512, d=512)                      # 8 large tiles
     assert ws(good_cfg(**small)) == ws(good_cfg(flags=fc.TILES_128, **small)) != ws(good_cfg(flags=fc.TILES_256, **small))
