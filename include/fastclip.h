@@ -81,9 +81,10 @@ typedef enum { FASTCLIP_F32 = 0, FASTCLIP_BF16 = 1 } fastclip_dtype;
 /* Tile size of the bf16 path.  By default the library chooses: batches whose 256 x 256 strip tiles would occupy at most
  * half of the compute units (2 ceil(b/256) ceil(B/256) <= 128; not in the single-pass form) run the strip phase on tiles
  * of 64 or 128 anchors by 128 contrasts (with gathered state pairs of them, 256 contrasts) and everything behind it in one
- * kernel on 64 x 64 or 128 x 64 output tiles; everything else runs on 256 x 256 tiles.  FASTCLIP_TILES_128 asks for the small tiles wherever they
- * apply (up to 191 large tiles), FASTCLIP_TILES_256 for the large ones always; both together are an error.  Same results
- * up to summation order. */
+ * kernel on 64 x 64 or 128 x 64 output tiles or, where those would need a second round of workgroups (wide rows), the
+ * contraction on 128 x 128 output tiles; everything else runs on 256 x 256 tiles.  FASTCLIP_TILES_128 asks for the small
+ * tiles wherever they apply (up to 191 large tiles), FASTCLIP_TILES_256 for the large ones always; both together are an
+ * error.  Same results up to summation order. */
 #define FASTCLIP_TILES_128 8
 #define FASTCLIP_TILES_256 16
 
@@ -155,7 +156,7 @@ typedef struct {
                             tiles 64 x 64); 0 on the fp32 path */
   int32_t single_pass;   /* 1: b == B and the similarity matrix is formed once */
   int32_t gathered;      /* 1: the contrast side runs over every global anchor (flag set and b < B) */
-  int32_t fused_state;   /* 1: the state phase runs inside the fold kernel or, with tile 128, inside the contraction */
+  int32_t fused_state;   /* 1: the state phase runs inside the fold kernel or, with tile 128, the contraction */
   int32_t nsplit;        /* splits of the contraction's column range over workgroups */
   int32_t nparts;        /* partial sums per anchor and quantity that the strip phase leaves to the state phase (one per
                             contrast tile; with tile 128 and gathered state one per two of them) */

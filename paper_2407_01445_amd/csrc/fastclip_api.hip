@@ -146,10 +146,19 @@ static void plan_f32(const fastclip_config& cfg, bool lean, Layout* L) {
   }
 }
 
-// 128 x 128-tile path: output tiles of the contraction, the split of its depth over workgroups, and who runs the state phase.
+// Every 64 x 64 block of the fold needs the coefficients of 128 anchor sides.  Forming them inside the fold saves a
+// launch, but every block then sums those anchors' partial sums again (b^2 / 32 anchor sides x nparts floats in
+// all, against 2 b x nparts once): worth it only while that stays small.
+static bool fold_forms_state(int64_t b, int nparts) {
+  return nparts <= 64 && (double)b * (double)b / 32.0 * (double)nparts * 4.0 <= 2.0 * 1024 * 1024;
+}
+
+// 128 x 128-tile path: which contraction, its output tiles, the split of its depth over workgroups, and who runs the state
+// phase.
 static void plan_t128(const fastclip_config& cfg, bool lean, Layout* L) {
   const int64_t nA = (cfg.B + 15) / 16, nB = (cfg.b + 15) / 16, cols = (cfg.d + 63) / 64;
   double best_cost = 0.0;
+  int64_t rounds = 0;
   for (int64_t rows = 64; rows <= (L->gathered ? 64 : 128); rows += 64) {
     const int64_t tiles = 2 * ((cfg.b + rows - 1) / rows) * cols;
     for (int64_t ns = 1; ns <= 16 && ns * 32 <= L->ldE; ++ns) {
@@ -158,15 +167,52 @@ static void plan_t128(const fastclip_config& cfg, bool lean, Layout* L) {
       const int64_t nq = sB * 128 < cfg.b ? sB * 128 : cfg.b;
       // the state phase inside the contraction: 64-row tiles have room for the sums of 256 local anchors beside the rows'
       const bool fused = rows == 64 && nq <= 256 && L->nparts <= 64;
+      const int64_t r = (tiles * ns + 255) / 256;
+      const double stages = (L->gathered ? 1.4 : 1.0) * (double)sA + (double)sB;   // a wave's, 16 deep; 1.4: with a second strip
       // us: start, coefficients, sum over the waves and end of a workgroup; a 16-deep stage of its eight waves (the load path of
       // a compute unit: 32 KiB, 48 for 128 rows or with a second strip); partial results; the state phase as a launch of its own
-      const double cost = (double)((tiles * ns + 255) / 256) * (rows == 64 ? 8.0 + 0.27 * ((L->gathered ? 1.4 : 1.0) * (double)sA + (double)sB) : 9.5 + 0.38 * (double)(sA + sB)) +
+      const double cost = (double)r * (rows == 64 ? 8.0 + 0.27 * stages : 9.5 + 0.38 * stages) +
                           (ns > 1 ? 2.3 + 0.1 * (double)ns : 0.0) + (fused ? 0.0 : 4.7);
       if (best_cost == 0.0 || cost < best_cost) {
         best_cost = cost;
+        rounds = r;
         L->nsplit = (int)ns; L->out_rows = (int)rows; L->fused_state = fused;
       }
     }
+  }
+  if (L->gathered) return;
+  // Contraction of kernels_wide128.hip behind the fold: its depth in 32-deep stages over `ns` workgroups per output tile.  Time
+  // in stages of a workgroup that has its compute unit to itself: a second one there stretches both by 1.45, beyond 512
+  // they run in rounds; a tile's start and end cost 4; the finalize kernel 5 + 0.42 per MiB of partial results it reads.
+  const int64_t depth = L->ldE / 32, wide_tiles = 2 * ((cfg.b + 127) / 128) * ((cfg.d + 127) / 128);
+  int64_t split = 1;
+  double wide_cost = 0.0;
+  for (int64_t ns = 1; ns <= (lean ? 1 : kMaxSplit) && ns <= depth; ++ns) {
+    const int64_t slice = (depth + ns - 1) / ns, wgs = wide_tiles * ns;
+    if ((depth + slice - 1) / slice != ns) continue;                // every split must get at least one stage
+    const double stretch = wgs <= 256 ? 1.0 : (wgs <= 512 ? 1.0 + 0.45 * (double)(wgs - 256) / 256.0
+                                                          : 1.45 * (double)((wgs + 511) / 512));
+    const double cost = stretch * (double)slice + 4.0 + (ns > 1 ? 5.0 + 0.42 / 16.0 * (double)wgs : 0.0);
+    if (ns == 1 || cost < wide_cost) { split = ns; wide_cost = cost; }
+  }
+  // It is taken where the kernel above would need a second round of workgroups, unless its own would not fill the chip twice
+  // (hardly one per compute unit, or a long range in one piece and fewer than 384) or the local anchors are so few that the
+  // fold saves nothing.  Step times, above / wide, us.  One round: 1000 of 1000 at 1024: 37 / 42, 1024 of 4096 at 1024: 67 / 70,
+  // 640 of 5120 at 1280: 74 / 94.  Two: 1000 of 1000 at 1280: 54 / 48, 1536 of 1536 at 1024: 75 / 65, 2048 of 2048 at 768:
+  // 82 / 69, 1024 of 4096 at 2048: 122 / 105.  Four: 2048 of 2048 at 2048: 170 / 115.  Excepted: 1408 of 1408 at 1280 (220
+  // workgroups): 67 / 70, 512 of 1024 at 4096 (256): 70 / 72 (but 1024 of 2048 at 2048, 256: 79 / 76), 640 of 5120 at 4096:
+  // 187 / 205, 320 of 3300 at 3072: 85 / 88.  The worst misses among 26 batch sizes at widths of 1280 to 4096: 800 of 4096 at
+  // 1536 (wide taken: 100 / 106) and 450 of 2048 at 4096 (not taken: 88 / 84).
+  const int64_t wgs = wide_tiles * split, slice = (depth + split - 1) / split;
+  if (rounds >= 2 && cfg.b > 384 && wgs > (cfg.b > 512 ? 224 : 256) && !(split == 1 && wgs < 384 && slice > 80)) {
+    L->wide = 1;
+    L->nsplit = (int)split; L->kslice = slice;
+    L->fused_state = fold_forms_state(cfg.b, L->nparts);
+    // strips of one workgroup per compute unit are two bare rounds just above 256 tiles: 1536 of 1536 at 1024: 25.2 us against 23.4
+    // with two per compute unit, 1800 of 1800 at 512: steps of 64.1 and 62.3.  With few anchor tiles (768 of 4096, 384 tiles) and at
+    // 512 tiles they are the faster ones all the same (96.1 against 100.8 at 2048).
+    const int64_t tiles = 2 * ((cfg.b + 127) / 128) * L->nparts;
+    L->wide_strips = tiles > 256 && tiles < 512 && 4 * cfg.b > 3 * cfg.B;
   }
 }
 
@@ -249,14 +295,10 @@ static void make_layout(const fastclip_config& cfg, bool lean, Layout* L) {
     L->ldE = lean ? cfg.B : (int64_t)round_up((size_t)cfg.B, 4);
     plan_f32(cfg, lean, L);
   }
-  // Every 64 x 64 block of the fold needs the coefficients of 128 anchor sides.  Forming them inside the fold saves a
-  // launch, but every block then sums those anchors' partial sums again (b^2 / 32 anchor sides x nparts floats in
-  // all, against 2 b x nparts once): worth it only while that stays small.
-  if (!L->t128)
-    L->fused_state = L->bf16 && L->nparts <= 64 &&
-                     (double)cfg.b * (double)cfg.b / 32.0 * (double)L->nparts * 4.0 <= 2.0 * 1024 * 1024;
-  // scalar partials: t128 leaves the terms of every anchor side
-  L->nstate_blocks = L->fused_state ? (L->t128 ? (int)(2 * cfg.b) : (int)((cfg.b + 63) / 64)) : state_blocks(cfg.b, L->nparts);
+  if (!L->t128) L->fused_state = L->bf16 && fold_forms_state(cfg.b, L->nparts);
+  // scalar partials: t128 without the fold leaves the terms of every anchor side
+  const bool per_anchor = L->t128 && !L->wide;
+  L->nstate_blocks = L->fused_state ? (per_anchor ? (int)(2 * cfg.b) : (int)((cfg.b + 63) / 64)) : state_blocks(cfg.b, L->nparts);
   L->diag = take(fb); L->tau1 = take(fb); L->tau2 = take(fb); L->k1 = take(fb); L->k2 = take(fb);
   L->uold1 = take(fb); L->uold2 = take(fb);
   L->sums = take(fb * 4 * (size_t)L->nparts * (!L->bf16 && L->nparts > 1 ? 2 : 1));
@@ -268,7 +310,10 @@ static void make_layout(const fastclip_config& cfg, bool lean, Layout* L) {
     // fragment-ordered strips: anchors padded to whole 256-row tiles
     const size_t rows = round_up((size_t)cfg.b, 256);
     for (int s = 0; s < 2; ++s) L->E[s] = take(esz * rows * (size_t)L->ldE);
-    if (L->t128) {     // arrival counters of the output tiles and of the scalars; [2][tiles][nsplit][64 x 64] floats
+    if (L->wide) {     // [nsplit][2 sides][b to 128][d to 128] floats, only with more than one split
+      if (L->nsplit > 1)
+        L->Opart[0] = take(sizeof(float) * (size_t)L->nsplit * 2 * round_up((size_t)cfg.b, 128) * round_up((size_t)cfg.d, 128));
+    } else if (L->t128) {     // arrival counters of the output tiles and of the scalars; [2][tiles][nsplit][64 x 64] floats
       const int64_t tiles = 2 * (L->out_rows / 64) * ((cfg.b + L->out_rows - 1) / L->out_rows) * ((cfg.d + 63) / 64);
       L->narrived = (int)tiles + 1;
       L->arrived = take(sizeof(unsigned) * (size_t)L->narrived);
@@ -358,9 +403,16 @@ static fastclip_status run_step(const fastclip_config* cfg, const fastclip_buffe
   if (c.L.gathered) launch_prep_cols(c);
   mark(FASTCLIP_PHASE_PREP);
   if (c.L.t128) {
-    launch_strips_t128_bf16(c);           mark(FASTCLIP_PHASE_STRIPS);
+    if (c.L.wide_strips) launch_strips_wide128_bf16(c);
+    else launch_strips_t128_bf16(c);
+    mark(FASTCLIP_PHASE_STRIPS);
     if (!c.L.fused_state) { launch_state(c); mark(FASTCLIP_PHASE_STATE); }
-    launch_contract_t128_bf16(c);         mark(FASTCLIP_PHASE_CONTRACT);  // outputs and scalars (and the state phase) included
+    if (c.L.wide) {
+      launch_fold_bf16(c);                mark(FASTCLIP_PHASE_LOCAL);   // with fused_state: the state phase as well
+      launch_contract_wide128_bf16(c);    mark(FASTCLIP_PHASE_CONTRACT);  // outputs and scalars included
+    } else {
+      launch_contract_t128_bf16(c);       mark(FASTCLIP_PHASE_CONTRACT);  // outputs and scalars (and the state phase) included
+    }
     launch_norm_backward(c);
   } else if (c.L.fine) {
     launch_strips_fine_bf16(c);           mark(FASTCLIP_PHASE_STRIPS);

@@ -59,7 +59,10 @@ struct Layout {
   int t128;          // 1: MFMA path on 128 x 128 strip tiles (kernels_tiles128.hip); nparts counts 128-column tiles, the
                      //    contraction's depth is cut into nsplit x 8 slices of 16-deep stages, and with one split there
                      //    are no partial results
-  int out_rows;      // t128: rows of an output tile of the contraction, 64 or 128
+  int out_rows;      // t128 without wide: rows of an output tile of the contraction, 64 or 128
+  int wide_strips;   // wide: the strips are k_strips_wide128_bf16
+  int wide;          // t128: the contraction is k_contract_wide128_bf16 (kernels_wide128.hip) behind the fold; nsplit /
+                     //    kslice count 32-deep stages
   int square;        // 1: b == B and the similarity matrix is formed once.  MFMA path: F[0] holds l2(j, p) in the
                      //    layout of E[0] until the fold transposes it into E[1]; fp32 path: E[1] holds it as [p][j]
   int64_t ncol;      // gathered: entries per column-parameter array (B rounded up to whole 256-column tiles)
@@ -74,7 +77,8 @@ struct Layout {
   size_t E[2];                       // fp32 path: float [b][ldE]; MFMA path: fragment-ordered bf16 strips
   size_t Opart[2];                   // float [nsplit][partial_split_floats(b, d)]   (MFMA path)
                                      // fp32 path with nsplit > 1: Opart[0] is double [nsplit][2][tiles][grad_tile^2]
-                                     // t128 with nsplit > 1: Opart[0] is float [2][tiles of 64 rows][nsplit][64 * 64]
+                                     // t128 with nsplit > 1: Opart[0] is float [2][tiles of 64 rows][nsplit][64 * 64],
+                                     // with wide [nsplit][2][b to 128][d to 128]
   // gathered: per global row j (= contrast column of the strips) and side s, in tiles of 256 columns
   // [s][tile][4][256]: log2(e)/tau_j, s_jj log2(e)/tau_j, c_j (0 for local rows and beyond B), unused.
   // Side 0 describes the text anchors j (l2(j, .), weights of d_img), side 1 the image anchors (l1(j, .), d_txt).
@@ -124,6 +128,8 @@ void launch_strips_fine_bf16(const StepCtx& c);    // MFMA path, fine tiles: exp
 void launch_contract_fine_bf16(const StepCtx& c);  // MFMA path, fine tiles: contractions, outputs and scalars
 void launch_strips_t128_bf16(const StepCtx& c);    // MFMA path, 128 x 128 tiles: exp strips + row sums
 void launch_contract_t128_bf16(const StepCtx& c);  // ... : (state phase,) contractions, outputs and scalars
+void launch_strips_wide128_bf16(const StepCtx& c);     // ... : strips, two workgroups per compute unit
+void launch_contract_wide128_bf16(const StepCtx& c);   // ... behind the fold: contractions, outputs and scalars
 void launch_norm_backward(const StepCtx& c);       // gradients through the L2 normalisation, if asked for
 void launch_finalize_bf16(const StepCtx& c);   // MFMA path: combine + scalars
 

@@ -13,10 +13,11 @@
 // and either kernel keeps as much in flight as the LDS holds: the strips two steps of 128 in k, the contraction 16 KiB
 // per wave, every wave on its own slice of the depth with its own LDS region, so that its main loop has no barrier.
 //
-// Column order.  The stored strips and the sums of this path number the contrasts from the worker's own rows on: column c is
-// global row (off + c) mod B.  The local anchors are columns 0 .. b - 1 whatever `off` is, so the transposing reads of
-// the contrast-side term are always aligned, and a row's own column is its own number.  Rows are addressed by 32-bit lane
-// offsets from the matrix (B ld < 2^30 elements, checked in make_layout).
+// Column order.  For this contraction the stored strips and the sums number the contrasts from the worker's own rows on:
+// column c is global row (off + c) mod B.  The local anchors are columns 0 .. b - 1 whatever `off` is, so the transposing
+// reads of the contrast-side term are always aligned, and a row's own column is its own number.  (For the contraction of
+// kernels_wide128.hip the same strips are stored by global row.)  Rows are addressed by 32-bit lane offsets from the
+// matrix (B ld < 2^30 elements, checked in make_layout).
 #include <string.h>
 
 #include <type_traits>
@@ -53,7 +54,8 @@ struct T128StripJob {           // one strip
 struct T128StripArgs {
   T128StripJob job[2];
   const float* diag;            // s_pp per local anchor
-  int nCB, ldE, nparts, bstride, b, B, d, off;
+  int nCB, ldE, nparts, bstride, b, B, d;
+  int first, own;               // global row of column 0; column of local anchor 0
 };
 
 // One workgroup per tile (128 anchors against 128 contrasts of one strip), eight waves = two groups of 2 x 2 waves of
@@ -78,7 +80,7 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
   const int kg = wave >> 2, q4 = wave & 3, wr = q4 / WC, wc = q4 % WC, lr = lane & 31, hk = lane >> 5;
   const int ct = blockIdx.x, at = blockIdx.y, strip = blockIdx.z;    // no divisions: they are serial instructions at the start
   const int a0 = at * AT;
-  const int B = a.B, b = a.b, off = a.off, d = a.d;
+  const int B = a.B, b = a.b, first = a.first, own = a.own, d = a.d;
   const T128StripJob& J = a.job[strip];
   // pointers pinned in scalar registers: left in the argument segment they are loaded again behind every memory fence
   const bf16_t *Xm = wave_uniform(J.X), *Am = wave_uniform(J.A);
@@ -94,7 +96,7 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
 #pragma unroll
   for (int i = 0; i < NL; ++i) {
     const int row = (i < 4 ? 8 * (4 * q4 + i) : 8 * (2 * WC * q4 + i - 4)) + (lane >> 3);
-    int g = off + (c0 + row < B ? c0 + row : B - 1);
+    int g = first + (c0 + row < B ? c0 + row : B - 1);
     g -= g >= B ? B : 0;
     const int m = a0 + row < b ? a0 + row : b - 1;
     ox[i] = (uint32_t)(i < 4 ? g * ldx : m * lda) * 2u + (uint32_t)(((lane & 7) ^ p_swz(row)) * 16);
@@ -264,7 +266,7 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
             e[q] = __builtin_amdgcn_exp2f(x);
             if (MASK) {
               const int c = c_first + 8 * h + q;
-              e[q] = (c < B && anchor < b && c != anchor) ? e[q] : 0.f;
+              e[q] = (c < B && anchor < b && c != own + anchor) ? e[q] : 0.f;
             }
             sg[q] += e[q];
             sx[q] = fmaf(x, e[q], sx[q]);
@@ -289,7 +291,7 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
       }
     }
   };
-  const bool whole = a0 + AT <= b && c0 + kT <= B && (a0 >= c0 + kT || c0 >= a0 + AT);
+  const bool whole = a0 + AT <= b && c0 + kT <= B && (own + a0 >= c0 + kT || c0 >= own + a0 + AT);
   if (kg) {
     if (whole) finish(std::false_type{}, std::true_type{}); else finish(std::true_type{}, std::true_type{});
   } else {
@@ -333,7 +335,8 @@ void launch_strips_t128_bf16(const StepCtx& c) {
   }
   a.diag = (const float*)(c.ws + L.diag);
   a.nCB = (int)(L.ldE / 16); a.ldE = (int)L.ldE; a.nparts = L.nparts; a.bstride = (int)L.bstride;
-  a.b = (int)L.b; a.B = (int)L.B; a.d = (int)L.d; a.off = (int)L.off;
+  a.b = (int)L.b; a.B = (int)L.B; a.d = (int)L.d;
+  a.first = L.wide ? 0 : (int)L.off; a.own = L.wide ? (int)L.off : 0;
   // 64 anchors per tile where that still is one round of workgroups: more compute units, and a tile takes 7.0 us instead of 8.8
   // (128 anchors of 1024, d = 512; steps: 24.0 -> 22.7 us, 256 of 2048 from raw rows 40.4 -> 38.4, 1024 of 1024 30.7 -> 30.1).
   // Beyond one round two tiles of 64 take longer than one of 128 (3.5 us of either are its start and end).

@@ -131,6 +131,20 @@ def test_describe_reports_the_plan():
         fc.fastclip_describe(good_cfg(B=1))
 
 
+def test_wide_rows_leave_the_one_kernel_contraction():
+    """Output tiles of 128 x 64 for which one round of workgroups is not enough: the contraction runs on 128 x 128 tiles behind
+    the fold (with the state phase in the fold for few anchors, and its own split of the column range)."""
+    plan = lambda **kw: fc.fastclip_describe(good_cfg(off=0, flags=fc.TILES_128, N=5000, **kw))
+    one_round = plan(B=1536, b=1536, d=640)                           # 2 x 12 x 10 tiles
+    assert one_round["tile"] == 128 and one_round["nsplit"] == 1
+    wide = plan(B=1536, b=1536, d=1024)
+    assert wide["tile"] == 128 and wide["nsplit"] == 2 and not wide["fused_state"]
+    for shape in (dict(B=520, b=520, d=2824), dict(B=700, b=520, d=2824)):   # more anchors than the contraction has room for
+        assert plan(**shape)["fused_state"] == 1 and plan(**shape)["nsplit"] == 1
+    few = plan(B=3300, b=320, d=3072)
+    assert few["nsplit"] == 1 and not few["fused_state"]
+
+
 def test_plans_are_sane_over_a_sweep_of_shapes():
     """Every valid bf16 shape of a sweep: the plan's splits fit the column range, the partial sums count the contrast
     tiles of the chosen size, the workspace is large enough for the two stored strips, and the tile flags behave."""
