@@ -108,9 +108,14 @@ TauUpd make_tau_upd(const fastclip_tau_update& upd) {
   return u;
 }
 
-// fp32 path: tile sizes, partial sums and the split of the gradients' depth.  lean: nothing in the workspace that only
-// speed asks for (see make_layout).
-static void plan_f32(const fastclip_config& cfg, bool lean, Layout* L) {
+// What a plan may put into the workspace for speed alone (see make_layout).
+struct Room {
+  int64_t split_bytes;     // partial results of splits
+  bool partial_sums;       // fp32 path: partial sums of the strips, which its single pass needs too
+};
+
+// fp32 path: tile sizes, partial sums and the split of the gradients' depth.
+static void plan_f32(const fastclip_config& cfg, const Room& room, Layout* L) {
   // 64 x 64 strip tiles once there is one per compute unit; below that 32 x 32, four times as many
   const int64_t strips = L->square ? 1 : 2;
   L->strip_tile = strips * ((cfg.b + 63) / 64) * ((cfg.B + 63) / 64) >= 256 ? 64 : 32;
@@ -118,7 +123,7 @@ static void plan_f32(const fastclip_config& cfg, bool lean, Layout* L) {
   // its columns, one partial per anchor tile, and keeps one per tile on either side.
   const int64_t nCT = (cfg.B + L->strip_tile - 1) / L->strip_tile;
   int64_t per = L->square ? 1 : (nCT + 63) / 64;
-  if (lean) per = nCT;
+  if (!room.partial_sums) per = nCT;
   L->per_part = (int)per;
   L->nparts = (int)((nCT + per - 1) / per);
   // Gradients: tile size and splits by the time of the fullest compute unit in cycles of a SIMD.  A stage is 1024 cycles of
@@ -134,7 +139,7 @@ static void plan_f32(const fastclip_config& cfg, bool lean, Layout* L) {
     for (int64_t ns = 1; ns <= 16 && ns <= stages; ++ns) {
       const int64_t slice = (stages + ns - 1) / ns;
       if ((stages + slice - 1) / slice != ns) continue;
-      if (ns > 1 && (lean || tiles * ns > 2048)) break;
+      if (ns > 1 && (tiles * ns > 2048 || ns * tiles * T * T * (int64_t)sizeof(double) > room.split_bytes)) break;
       const double rounds = (double)((tiles * ns + 255) / 256);
       const double cost = rounds * ((double)slice * (T == 32 ? 1330.0 : 2600.0) + 3000.0) +
                           (ns > 1 ? 4000.0 + 500.0 * (double)ns : 0.0);
@@ -155,14 +160,14 @@ static bool fold_forms_state(int64_t b, int nparts) {
 
 // 128 x 128-tile path: which contraction, its output tiles, the split of its depth over workgroups, and who runs the state
 // phase.
-static void plan_t128(const fastclip_config& cfg, bool lean, Layout* L) {
+static void plan_t128(const fastclip_config& cfg, const Room& room, Layout* L) {
   const int64_t nA = (cfg.B + 15) / 16, nB = (cfg.b + 15) / 16, cols = (cfg.d + 63) / 64;
   double best_cost = 0.0;
   int64_t rounds = 0;
   for (int64_t rows = 64; rows <= (L->gathered ? 64 : 128); rows += 64) {
     const int64_t tiles = 2 * ((cfg.b + rows - 1) / rows) * cols;
     for (int64_t ns = 1; ns <= 16 && ns * 32 <= L->ldE; ++ns) {
-      if (ns > 1 && (lean || tiles * ns > 2048)) break;
+      if (ns > 1 && (tiles * ns > 2048 || ns * tiles * rows * 64 * (int64_t)sizeof(float) > room.split_bytes)) break;
       const int64_t sA = (nA + ns * 8 - 1) / (ns * 8), sB = (nB + ns * 8 - 1) / (ns * 8);
       const int64_t nq = sB * 128 < cfg.b ? sB * 128 : cfg.b;
       // the state phase inside the contraction: 64-row tiles have room for the sums of 256 local anchors beside the rows'
@@ -187,9 +192,10 @@ static void plan_t128(const fastclip_config& cfg, bool lean, Layout* L) {
   const int64_t depth = L->ldE / 32, wide_tiles = 2 * ((cfg.b + 127) / 128) * ((cfg.d + 127) / 128);
   int64_t split = 1;
   double wide_cost = 0.0;
-  for (int64_t ns = 1; ns <= (lean ? 1 : kMaxSplit) && ns <= depth; ++ns) {
+  for (int64_t ns = 1; ns <= kMaxSplit && ns <= depth; ++ns) {
     const int64_t slice = (depth + ns - 1) / ns, wgs = wide_tiles * ns;
     if ((depth + slice - 1) / slice != ns) continue;                // every split must get at least one stage
+    if (ns > 1 && wgs * 128 * 128 * (int64_t)sizeof(float) > room.split_bytes) break;
     const double stretch = wgs <= 256 ? 1.0 : (wgs <= 512 ? 1.0 + 0.45 * (double)(wgs - 256) / 256.0
                                                           : 1.45 * (double)((wgs + 511) / 512));
     const double cost = stretch * (double)slice + 4.0 + (ns > 1 ? 5.0 + 0.42 / 16.0 * (double)wgs : 0.0);
@@ -216,7 +222,7 @@ static void plan_t128(const fastclip_config& cfg, bool lean, Layout* L) {
   }
 }
 
-static void make_layout(const fastclip_config& cfg, bool lean, Layout* L) {
+static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L) {
   memset(L, 0, sizeof(*L));
   L->B = cfg.B; L->b = cfg.b; L->off = cfg.off; L->d = cfg.d; L->N = cfg.N;
   L->bf16 = cfg.emb_dtype == FASTCLIP_BF16;
@@ -226,7 +232,7 @@ static void make_layout(const fastclip_config& cfg, bool lean, Layout* L) {
   // forming the similarity matrix once halves the MFMA work of the strip phase but doubles the epilogue of every
   // tile: it pays once the tiles outnumber the compute units (below that one tile's latency is the phase's time)
   const int64_t bt = (cfg.B + kTileContrasts - 1) / kTileContrasts;
-  L->square = cfg.b == cfg.B && (L->bf16 ? 2 * bt * bt > 256 || (cfg.flags & FASTCLIP_SINGLE_PASS) : !lean);
+  L->square = cfg.b == cfg.B && (L->bf16 ? 2 * bt * bt > 256 || (cfg.flags & FASTCLIP_SINGLE_PASS) : room.partial_sums);
   // Fine tiles (opt-in) where 256 x 256 tiles would leave most of the chip idle: fewer large strip tiles than three
   // quarters of the compute units (one per compute unit is what the large-tile kernels are built for).
   const int64_t big_tiles = 2 * ((cfg.b + 255) / 256) * ((cfg.B + 255) / 256);
@@ -247,7 +253,7 @@ static void make_layout(const fastclip_config& cfg, bool lean, Layout* L) {
   if (L->t128) {
     L->nparts = L->gathered ? (int)((cfg.B + 255) / 256) : (int)((cfg.B + 127) / 128);
     L->ldE = (int64_t)round_up((size_t)cfg.B, 64);
-    plan_t128(cfg, lean, L);
+    plan_t128(cfg, room, L);
   } else if (L->fine) {
     L->nparts = (int)((cfg.B + 127) / 128);
     L->ldE = (int64_t)round_up((size_t)cfg.B, 64);
@@ -292,8 +298,8 @@ static void make_layout(const fastclip_config& cfg, bool lean, Layout* L) {
     L->kslice = (stages + best - 1) / best;
     L->nsplit = (int)((stages + L->kslice - 1) / L->kslice);
   } else {
-    L->ldE = lean ? cfg.B : (int64_t)round_up((size_t)cfg.B, 4);
-    plan_f32(cfg, lean, L);
+    L->ldE = room.partial_sums ? (int64_t)round_up((size_t)cfg.B, 4) : cfg.B;
+    plan_f32(cfg, room, L);
   }
   if (!L->t128) L->fused_state = L->bf16 && fold_forms_state(cfg.b, L->nparts);
   // scalar partials: t128 without the fold leaves the terms of every anchor side
@@ -348,16 +354,26 @@ static void make_layout(const fastclip_config& cfg, bool lean, Layout* L) {
   L->total = at;
 }
 
-// The fp32 path's workspace: partial sums and splits take a few per cent on top of the stored strips.  A configuration that
-// fits the static array without them and would not fit with them goes without, so that fastclip_step_static keeps taking it.
-// So does one of the 128 x 128-tile path with its splits.
+// A configuration of the fp32 path or of the 128 x 128 tiles whose stored strips fit the array of fastclip_step_static fits it
+// whole, so that every such configuration is taken there, and with the same layout whichever entry point runs it.  What the step
+// has in its workspace for speed alone gives way in this order: splits as far as their partial results do not fit (a split
+// more or less is a few per cent; 2600 of 2600 fp32 pairs at width 512 keep their single pass and take 577 us instead
+// of 1460 without it), then, where the strips alone leave less than the partial sums take (the last 5 % below the
+// array's size), the fp32 path's partial sums and single pass, at two to three times the time.
 void make_layout(const fastclip_config& cfg, Layout* L) {
-  make_layout(cfg, false, L);
-  if ((!L->bf16 || L->t128) && L->total > (size_t)FASTCLIP_STATIC_SCRATCH_BYTES) {
-    Layout small;
-    make_layout(cfg, true, &small);
-    if (small.total <= (size_t)FASTCLIP_STATIC_SCRATCH_BYTES) *L = small;
+  constexpr int64_t kLimit = FASTCLIP_STATIC_SCRATCH_BYTES;
+  make_layout(cfg, Room{INT64_MAX, true}, L);
+  if ((L->bf16 && !L->t128) || (int64_t)L->total <= kLimit) return;
+  Layout small;
+  make_layout(cfg, Room{0, true}, &small);
+  if ((int64_t)small.total <= kLimit) {
+    // beside the partial results a split plan of the fp32 path has an arrival counter for each of its at most 1024 tiles
+    make_layout(cfg, Room{kLimit - (int64_t)small.total - 4096, true}, L);
+    if ((int64_t)L->total > kLimit) *L = small;
+    return;
   }
+  make_layout(cfg, Room{0, false}, &small);
+  if ((int64_t)small.total <= kLimit) *L = small;
 }
 
 static fastclip_status run_step(const fastclip_config* cfg, const fastclip_buffers* bufs, void* workspace,

@@ -131,6 +131,19 @@ def test_describe_reports_the_plan():
         fc.fastclip_describe(good_cfg(B=1))
 
 
+def test_f32_plan_gives_up_its_splits_before_its_single_pass():
+    """Strips that fit the array of fastclip_step_static together with the partial sums: what would not fit is the partial
+    results of the gradients' splits, and they alone give way."""
+    for B in (2300, 2500, 2560, 2600, 2700, 2800):                    # 40 .. 60 MiB of strips
+        cfg = good_cfg(emb_dtype=fc.F32, B=B, b=B, off=0, d=512, N=9000)
+        assert fc.fastclip_workspace_bytes(cfg) <= fc.STATIC_SCRATCH_BYTES
+        plan = fc.fastclip_describe(cfg)
+        assert plan["single_pass"] == 1 and plan["nparts"] == -(-B // 64), (B, plan)
+    for shape in (dict(B=8000, b=1000, d=64), dict(B=5120, b=640, d=1024)):
+        plan = fc.fastclip_describe(good_cfg(emb_dtype=fc.F32, off=0, N=9000, **shape))
+        assert plan["nparts"] >= 40, (shape, plan)
+
+
 def test_wide_rows_leave_the_one_kernel_contraction():
     """Output tiles of 128 x 64 for which one round of workgroups is not enough: the contraction runs on 128 x 128 tiles behind
     the fold (with the state phase in the fold for few anchors, and its own split of the column range)."""

@@ -59,6 +59,19 @@ def test_static_scratch_step_equals_the_step_twice_in_a_row_second_input_smaller
     same_bits(*both_ways((2048, 1536, 256, 64), fc.V0, "bf16", 14))     # larger again: the state phase is its own kernel
 
 
+@pytest.mark.parametrize("shape,version", [
+    ((2600, 2600, 0, 512), fc.V2),      # fits without the partial results that the gradients' splits would have
+    ((2840, 2840, 0, 40), fc.V3),       # ... and without the single pass and the partial sums: 61.5 MiB of strips
+    ((8192, 1020, 3333, 72), fc.V0)])   # the same where there are two strips to form in any case
+def test_static_scratch_takes_what_fits_without_the_extras(shape, version):
+    """The fp32 path's strips fill the array and what makes the step faster has to give way: one layout for both entry
+    points, bit for bit the same outputs."""
+    B, b, off, d = shape
+    plain, static = both_ways(shape, version, "f32", 15)
+    assert fc.STATIC_SCRATCH_BYTES * 0.8 < fc.fastclip_workspace_bytes(plain.config(0.6)) <= fc.STATIC_SCRATCH_BYTES
+    same_bits(plain, static)
+
+
 def test_static_scratch_rejects_what_does_not_fit():
     cfg = fc.make_config(version=fc.V2, emb_dtype=fc.BF16, B=32768, b=1024, off=17408, d=1024, N=10 ** 6, gamma=0.5,
                          eps=1e-6, rho=8.5)
