@@ -201,18 +201,22 @@ static void plan_t128(const fastclip_config& cfg, const Room& room, Layout* L) {
     const double cost = stretch * (double)slice + 4.0 + (ns > 1 ? 5.0 + 0.42 / 16.0 * (double)wgs : 0.0);
     if (ns == 1 || cost < wide_cost) { split = ns; wide_cost = cost; }
   }
-  // It is taken where the kernel above would need a second round of workgroups, unless its own would not fill the chip twice
-  // (hardly one per compute unit, or a long range in one piece and fewer than 384) or the local anchors are so few that the
-  // fold saves nothing.  Step times, above / wide, us.  One round: 1000 of 1000 at 1024: 37 / 42, 1024 of 4096 at 1024: 67 / 70,
-  // 640 of 5120 at 1280: 74 / 94.  Two: 1000 of 1000 at 1280: 54 / 48, 1536 of 1536 at 1024: 75 / 65, 2048 of 2048 at 768:
-  // 82 / 69, 1024 of 4096 at 2048: 122 / 105.  Four: 2048 of 2048 at 2048: 170 / 115.  Excepted: 1408 of 1408 at 1280 (220
-  // workgroups): 67 / 70, 512 of 1024 at 4096 (256): 70 / 72 (but 1024 of 2048 at 2048, 256: 79 / 76), 640 of 5120 at 4096:
-  // 187 / 205, 320 of 3300 at 3072: 85 / 88.  The worst misses among 26 batch sizes at widths of 1280 to 4096: 800 of 4096 at
-  // 1536 (wide taken: 100 / 106) and 450 of 2048 at 4096 (not taken: 88 / 84).
-  const int64_t wgs = wide_tiles * split, slice = (depth + split - 1) / split;
-  if (rounds >= 2 && cfg.b > 384 && wgs > (cfg.b > 512 ? 224 : 256) && !(split == 1 && wgs < 384 && slice > 80)) {
+  // It is taken where the kernel above would need a second round of workgroups, except
+  //  - with fewer than one workgroup per compute unit, or few local anchors (the fold saves little),
+  //  - with one split, fewer than 384 workgroups and local anchors that are a small part of the batch: some compute units
+  //    get two long workgroups and most one,
+  //  - with an odd number of workgroups (over 1 split) in a column of tiles: they go to the XCDs in turn, and then every L2
+  //    sees the whole of the strips.
+  // Step times, above / wide, us.  One round: 1000 of 1000 at 1024: 37 / 42, 1024 of 4096 at 1024: 67 / 70, 640 of 5120 at
+  // 1280: 74 / 94.  Two: 1000 of 1000 at 1280: 54 / 48, 1536 of 1536 at 1024: 75 / 65, 2048 of 2048 at 768: 82 / 69 and at 1024
+  // (256 workgroups): 89 / 86, 1024 of 4096 at 2048: 122 / 105.  Four: 2048 of 2048 at 2048: 170 / 115.  Excepted, in this order:
+  // 1408 of 1408 at 1280 (220): 67 / 70, 320 of 3300 at 4096: 98 / 102; 640 of 5120 at 4096: 187 / 205, 553 of 2523 at
+  // 4096: 116 / 124; 1344 of 1546 at 736 (3 splits, 11 rows of tiles): 62 / 67, 800 of 4096 at 1536 (3, 7): 100 / 106.
+  const int64_t rows_of_tiles = (cfg.b + 127) / 128, wgs = wide_tiles * split;
+  if (rounds >= 2 && cfg.b > 384 && wgs >= (cfg.b > 512 ? 256 : 257) &&
+      !(split == 1 && wgs < 384 && cfg.B > cfg.b + 640) && !(split > 1 && (split * rows_of_tiles) % 2)) {
     L->wide = 1;
-    L->nsplit = (int)split; L->kslice = slice;
+    L->nsplit = (int)split; L->kslice = (depth + split - 1) / split;
     L->fused_state = fold_forms_state(cfg.b, L->nparts);
     // strips of one workgroup per compute unit are two bare rounds just above 256 tiles: 1536 of 1536 at 1024: 25.2 us against 23.4
     // with two per compute unit, 1800 of 1800 at 512: steps of 64.1 and 62.3.  With few anchor tiles (768 of 4096, 384 tiles) and at

@@ -413,7 +413,7 @@ def test_bf16_tiles_128(B, b, off, d, version):
     (8192, 64, 8128, 64),
     # contraction on 128 x 128 output tiles behind the fold: ragged everywhere, one split; rows that are not the first; a
     # last row block of one; two splits, strips of two workgroups per compute unit with a guarded last stage
-    (520, 520, 0, 2824), (700, 520, 133, 2824), (1100, 1025, 75, 2048), (1450, 1400, 33, 808)])
+    (520, 520, 0, 3208), (700, 520, 133, 3208), (1100, 1025, 75, 2048), (1450, 1400, 33, 808)])
 def test_bf16_tiles_128_edges(B, b, off, d):
     """The shapes at which the kernels of the 128 x 128-tile path change what they do, as in test_bf16_tiles_128."""
     test_bf16_tiles_128(B, b, off, d, V2 if B % 2 else V3)
