@@ -82,8 +82,9 @@ typedef enum { FASTCLIP_F32 = 0, FASTCLIP_BF16 = 1 } fastclip_dtype;
  * half of the compute units (2 ceil(b/256) ceil(B/256) <= 128; not in the single-pass form) run the strip phase on tiles
  * of 64 or 128 anchors by 128 contrasts (with gathered state pairs of them, 256 contrasts) and everything behind it in one
  * kernel on 64 x 64 or 128 x 64 output tiles or, where those would need a second round of workgroups (wide rows), the
- * contraction on 128 x 128 output tiles; everything else runs on 256 x 256 tiles.  FASTCLIP_TILES_128 asks for the small
- * tiles wherever they apply (up to 191 large tiles), FASTCLIP_TILES_256 for the large ones always; both together are an
+ * contraction on 128 x 128 output tiles; everything else runs on 256 x 256 tiles, and so do batches with gathered state
+ * whose rows are so wide that those take less time.  FASTCLIP_TILES_128 asks for the small tiles wherever they apply (up
+ * to 191 large tiles; not those gathered batches), FASTCLIP_TILES_256 for the large ones always; both together are an
  * error.  Same results up to summation order. */
 #define FASTCLIP_TILES_128 8
 #define FASTCLIP_TILES_256 16
@@ -182,7 +183,8 @@ fastclip_status fastclip_step(const fastclip_config* cfg, const fastclip_buffers
  * ends.  The call allocates and frees nothing (no hipMalloc / hipFree, no allocating library routine); on its first
  * call on a device it looks the array's device address up (hipGetSymbolAddress) and keeps it.
  *   - A configuration whose fastclip_workspace_bytes() exceeds FASTCLIP_STATIC_SCRATCH_BYTES is refused with
- *     FASTCLIP_ERR_WORKSPACE before anything is launched (64 MiB holds the paper's own shapes: up to 640 local
+ *     FASTCLIP_ERR_WORKSPACE before anything is launched, except that small batches with gathered state and wide rows
+ *     run here on the small tiles, which need less (same results up to summation order, more time) (64 MiB holds the paper's own shapes: up to 640 local
  *     anchors of a global batch of 5120 at width 512, and 1024 x 1024 x 512 or 256 of 8192 x 512).
  *   - All calls on one GPU share that GPU's array, whatever their stream: calls that overlap in time on one GPU race
  *     on it.  Calls that follow each other on one stream, or are ordered by events, are safe.  The array keeps the

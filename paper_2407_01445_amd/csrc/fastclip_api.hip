@@ -159,10 +159,10 @@ static bool fold_forms_state(int64_t b, int nparts) {
 }
 
 // 128 x 128-tile path: which contraction, its output tiles, the split of its depth over workgroups, and who runs the state
-// phase.
-static void plan_t128(const fastclip_config& cfg, const Room& room, Layout* L) {
+// phase.  False: the 256 x 256 tiles take less time (gathered state).
+static bool plan_t128(const fastclip_config& cfg, const Room& room, Layout* L) {
   const int64_t nA = (cfg.B + 15) / 16, nB = (cfg.b + 15) / 16, cols = (cfg.d + 63) / 64;
-  double best_cost = 0.0;
+  double best_cost = 0.0, in_a_row = 0.0;
   int64_t rounds = 0;
   for (int64_t rows = 64; rows <= (L->gathered ? 64 : 128); rows += 64) {
     const int64_t tiles = 2 * ((cfg.b + rows - 1) / rows) * cols;
@@ -180,12 +180,21 @@ static void plan_t128(const fastclip_config& cfg, const Room& room, Layout* L) {
                           (ns > 1 ? 2.3 + 0.1 * (double)ns : 0.0) + (fused ? 0.0 : 4.7);
       if (best_cost == 0.0 || cost < best_cost) {
         best_cost = cost;
-        rounds = r;
+        rounds = r; in_a_row = (double)r * stages;
         L->nsplit = (int)ns; L->out_rows = (int)rows; L->fused_state = fused;
       }
     }
   }
-  if (L->gathered) return;
+  if (L->gathered) {
+    // The 256 x 256 tiles fetch a quarter of the bytes per product, at the price of a pass over both strips (fold), partial
+    // results and their sum.  Up to 104 stages in a row the small tiles are the faster ones, small / large, us: 640 of 5120 at width
+    // 768 (61 stages) 68 / 87, 1024 of 2048 at 1024 (61) 68 / 79, 256 of 8192 at 2048 (92) 106 / 118, 768 of 4096 at 1024 (102)
+    // 91 / 93.  Beyond, the large ones: 1024 of 4096 at 1024 (106) 98 / 96, 640 of 5120 at 1024 (122) 99 / 96, 512 of 8192 at
+    // 1280 (187) 131 / 111, 1024 of 4096 at 4096 (422) 363 / 203.  With a ragged batch or width the large strip tiles take twice
+    // as long: 700 of 3000 at 4096 (238) 226 / 253.  No room for splits: none for the partial results of the large tiles either.
+    const bool whole = cfg.B % 256 == 0 && cfg.d % 64 == 0;
+    return room.split_bytes == 0 || in_a_row <= (whole ? 104.0 : 240.0);
+  }
   // Contraction of kernels_wide128.hip behind the fold: its depth in 32-deep stages over `ns` workgroups per output tile.  Time
   // in stages of a workgroup that has its compute unit to itself: a second one there stretches both by 1.45, beyond 512
   // they run in rounds; a tile's start and end cost 4; the finalize kernel 5 + 0.42 per MiB of partial results it reads.
@@ -224,6 +233,7 @@ static void plan_t128(const fastclip_config& cfg, const Room& room, Layout* L) {
     const int64_t tiles = 2 * ((cfg.b + 127) / 128) * L->nparts;
     L->wide_strips = tiles > 256 && tiles < 512 && 4 * cfg.b > 3 * cfg.B;
   }
+  return true;
 }
 
 static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L) {
@@ -257,7 +267,10 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
   if (L->t128) {
     L->nparts = L->gathered ? (int)((cfg.B + 255) / 256) : (int)((cfg.B + 127) / 128);
     L->ldE = (int64_t)round_up((size_t)cfg.B, 64);
-    plan_t128(cfg, room, L);
+    if (!plan_t128(cfg, room, L)) L->t128 = L->out_rows = 0;
+  }
+  if (L->t128) {
+    // planned
   } else if (L->fine) {
     L->nparts = (int)((cfg.B + 127) / 128);
     L->ldE = (int64_t)round_up((size_t)cfg.B, 64);
@@ -382,7 +395,8 @@ void make_layout(const fastclip_config& cfg, Layout* L) {
 
 static fastclip_status run_step(const fastclip_config* cfg, const fastclip_buffers* bufs, void* workspace,
                                 size_t workspace_bytes, void* stream, float* phase_ms,
-                                const fastclip_tau_update* upd = nullptr, const fastclip_tau_state* tst = nullptr) {
+                                const fastclip_tau_update* upd = nullptr, const fastclip_tau_state* tst = nullptr,
+                                const Layout* planned = nullptr) {
   fastclip_status st = validate(cfg, bufs);
   if (st != FASTCLIP_OK) return st;
   if (!bufs) return FASTCLIP_ERR_NULL;
@@ -403,7 +417,8 @@ static fastclip_status run_step(const fastclip_config* cfg, const fastclip_buffe
       return FASTCLIP_ERR_VALUE;
     if (cfg->version != FASTCLIP_V1) { c.tau_upd = make_tau_upd(*upd); c.tau_st = *tst; }
   }
-  make_layout(*cfg, &c.L);
+  if (planned) c.L = *planned;
+  else make_layout(*cfg, &c.L);
   if (!workspace) return FASTCLIP_ERR_NULL;
   if (workspace_bytes < c.L.total || ((uintptr_t)workspace & 255)) return FASTCLIP_ERR_WORKSPACE;
   c.ws = (char*)workspace;
@@ -505,11 +520,13 @@ fastclip_status fastclip_step_static(const fastclip_config* cfg, const fastclip_
   if (st != FASTCLIP_OK) return st;
   fc::Layout L;
   fc::make_layout(*cfg, &L);
+  // gathered state on the 256 x 256 tiles for the time they take, where the small ones would fit the array
+  if (L.total > (size_t)FASTCLIP_STATIC_SCRATCH_BYTES) fc::make_layout(*cfg, fc::Room{0, true}, &L);
   if (L.total > (size_t)FASTCLIP_STATIC_SCRATCH_BYTES) return FASTCLIP_ERR_WORKSPACE;
   void* ws = nullptr;
   const fastclip_status sp = fc::static_scratch(&ws);
   if (sp != FASTCLIP_OK) return sp;
-  return fc::run_step(cfg, bufs, ws, (size_t)FASTCLIP_STATIC_SCRATCH_BYTES, stream, nullptr);
+  return fc::run_step(cfg, bufs, ws, (size_t)FASTCLIP_STATIC_SCRATCH_BYTES, stream, nullptr, nullptr, nullptr, &L);
 }
 
 size_t fastclip_workspace_bytes(const fastclip_config* cfg) {

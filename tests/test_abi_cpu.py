@@ -144,6 +144,18 @@ def test_f32_plan_gives_up_its_splits_before_its_single_pass():
         assert plan["nparts"] >= 40, (shape, plan)
 
 
+def test_gathered_state_takes_the_tiles_that_take_less_time():
+    """Gathered state on the small tiles while a workgroup of the contraction has few stages in a row, on the large ones with
+    wide rows, asked for or not; a ragged batch stays on the small ones for longer."""
+    tile = lambda flags=0, **kw: fc.fastclip_describe(good_cfg(off=0, N=9000, flags=flags | fc.GATHERED_STATE, **kw))["tile"]
+    for shape in (dict(B=5120, b=640, d=512), dict(B=2048, b=1024, d=1024), dict(B=8192, b=256, d=2048),
+                  dict(B=1024, b=512, d=4096), dict(B=3000, b=700, d=2048)):
+        assert tile(**shape) == tile(fc.TILES_128, **shape) == 128 and tile(fc.TILES_256, **shape) == 256, shape
+    for shape in (dict(B=4096, b=1024, d=1024), dict(B=4096, b=1024, d=4096), dict(B=8192, b=512, d=1280),
+                  dict(B=16384, b=256, d=2048)):
+        assert tile(**shape) == tile(fc.TILES_128, **shape) == 256, shape
+
+
 def test_wide_rows_leave_the_one_kernel_contraction():
     """Output tiles of 128 x 64 for which one round of workgroups is not enough: the contraction runs on 128 x 128 tiles behind
     the fold (with the state phase in the fold for few anchors, and its own split of the column range)."""

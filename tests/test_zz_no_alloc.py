@@ -72,6 +72,34 @@ def test_static_scratch_takes_what_fits_without_the_extras(shape, version):
     same_bits(plain, static)
 
 
+def test_static_scratch_takes_gathered_wide_rows():
+    """A step with gathered state and wide rows runs on the large tiles, whose partial results do not fit the array; on the small
+    ones it does, and the outputs agree up to rounding: the weights of the contraction are rounded to bf16 on either path
+    (gradients within the 2e-2 of the bf16 path), sums of 4096 positive numbers are added up in fp32 (4096 x 2^-24)."""
+    B, b, off, d, N = 4096, 1024, 1024, 2048, 6000
+    rng = np.random.default_rng(21)
+    img, txt = make_embeddings(22, B, d, 0.5, "bf16")
+    idx = draw_indices(23, b, N)
+    u0i, u0t = rng.uniform(0.05, 2.0, N).astype(np.float32), rng.uniform(0.05, 2.0, N).astype(np.float32)
+    glob = dict(u_img=rng.uniform(0.05, 2.0, B), u_txt=rng.uniform(0.05, 2.0, B))
+    runs = []
+    for static in (False, True):
+        g = GpuStep(B=B, b=b, off=off, d=d, N=N, dtype="bf16", version=fc.V3, eps=1e-6, rho=6.5, tau=0.07, u_img0=u0i, u_txt0=u0t,
+                    gathered=glob, tiles=None)
+        g.set_inputs(img, txt, idx)
+        assert fc.fastclip_workspace_bytes(g.config(0.6)) > fc.STATIC_SCRATCH_BYTES
+        if static:
+            fc.fastclip_step_static(g.config(0.6), g.buffers())
+            torch.cuda.synchronize()
+        else:
+            g.step(0.6)
+        runs.append(g)
+    for k, tol in (("d_img", 2e-2), ("d_txt", 2e-2), ("g_img", 2.5e-4), ("g_txt", 2.5e-4), ("u_img", 2.5e-4),
+                   ("u_txt", 2.5e-4)):
+        x, y = getattr(runs[0], k).double(), getattr(runs[1], k).double()
+        assert float((x - y).abs().max()) <= tol * float(x.abs().max()), k
+
+
 def test_static_scratch_rejects_what_does_not_fit():
     cfg = fc.make_config(version=fc.V2, emb_dtype=fc.BF16, B=32768, b=1024, off=17408, d=1024, N=10 ** 6, gamma=0.5,
                          eps=1e-6, rho=8.5)
