@@ -243,10 +243,11 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
   L->bstride = (int64_t)round_up((size_t)cfg.b, kTileContrasts);   // whole anchor tiles: the strip kernel works on 256 rows
   L->gathered = (cfg.flags & FASTCLIP_GATHERED_STATE) && cfg.b < cfg.B;
   L->ncol = (int64_t)round_up((size_t)cfg.B, kTileContrasts);
+  L->few = !L->bf16 && (cfg.B <= kFewPairs || (cfg.B <= kFewNarrowPairs && cfg.d <= 128));
   // forming the similarity matrix once halves the MFMA work of the strip phase but doubles the epilogue of every
   // tile: it pays once the tiles outnumber the compute units (below that one tile's latency is the phase's time)
   const int64_t bt = (cfg.B + kTileContrasts - 1) / kTileContrasts;
-  L->square = cfg.b == cfg.B && (L->bf16 ? 2 * bt * bt > 256 || (cfg.flags & FASTCLIP_SINGLE_PASS) : room.partial_sums);
+  L->square = cfg.b == cfg.B && (L->bf16 ? 2 * bt * bt > 256 || (cfg.flags & FASTCLIP_SINGLE_PASS) : room.partial_sums && !L->few);
   // Fine tiles (opt-in) where 256 x 256 tiles would leave most of the chip idle: fewer large strip tiles than three
   // quarters of the compute units (one per compute unit is what the large-tile kernels are built for).
   const int64_t big_tiles = 2 * ((cfg.b + 255) / 256) * ((cfg.B + 255) / 256);
@@ -316,7 +317,8 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
     L->nsplit = (int)((stages + L->kslice - 1) / L->kslice);
   } else {
     L->ldE = room.partial_sums ? (int64_t)round_up((size_t)cfg.B, 4) : cfg.B;
-    plan_f32(cfg, room, L);
+    if (L->few) L->nparts = L->nsplit = 1;
+    else plan_f32(cfg, room, L);
   }
   if (!L->t128) L->fused_state = L->bf16 && fold_forms_state(cfg.b, L->nparts);
   // scalar partials: t128 without the fold leaves the terms of every anchor side
@@ -462,6 +464,10 @@ static fastclip_status run_step(const fastclip_config* cfg, const fastclip_buffe
     launch_contract_bf16(c);              mark(FASTCLIP_PHASE_CONTRACT);
     launch_finalize_bf16(c);
     launch_norm_backward(c);
+  } else if (c.L.few) {
+    launch_strips_f32_few(c);             mark(FASTCLIP_PHASE_STRIPS);
+    launch_state(c);                      mark(FASTCLIP_PHASE_STATE);
+    launch_grad_f32_few(c);
   } else {
     launch_strips_f32(c);                 mark(FASTCLIP_PHASE_STRIPS);
     launch_state(c);                      mark(FASTCLIP_PHASE_STATE);

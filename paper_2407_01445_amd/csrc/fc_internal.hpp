@@ -12,6 +12,8 @@ typedef uint16_t bf16_t;  // raw bf16 bits in memory
 
 constexpr int kTileContrasts = 256;  // contrast rows per workgroup tile of the strip kernel
 constexpr int kMaxSplit = 64;
+constexpr int kFewPairs = 16;        // fp32 path: up to this many pairs in plain loops (kernels_f32.hip),
+constexpr int kFewNarrowPairs = 24;  // ... up to this many of width 128 or less
 constexpr int kMaxLocalQ = 2560;     // 128 x 128-tile path: local anchors whose coefficients a workgroup of the contraction holds
 
 // State kernel: threads per anchor side that share the work of adding up that side's partial sums (a power of two up to
@@ -43,6 +45,7 @@ struct Layout {
   int bf16;          // 1: MFMA path, 0: fp32 accuracy path
   int nparts;        // partial row sums per anchor and quantity written by the strip phase
   int64_t bstride;   // anchors padded to whole tiles of 256 (stride of the per-anchor arrays)
+  int few;           // 1: fp32 path in plain loops (few pairs)
   int per_part;      // fp32 path: contrast tiles behind one partial sum
   int strip_tile, grad_tile;   // fp32 path: tile sizes of k_strips_f64 / k_grad_f64 (32 or 64)
   int64_t ldE;       // contrast columns of the stored exp strips (MFMA path: multiple of 64; fp32 path: B)
@@ -122,6 +125,8 @@ void launch_state_phase(const fastclip_config& cfg, const fastclip_buffers& buf,
                         hipStream_t s);    // the state phase on its own, one partial sum per anchor and quantity
 bool state_records_are_canonical(const float* u_img, const float* u_txt, const fastclip_tau_state& t, int64_t stride);
 void launch_grad_f32(const StepCtx& c);        // accuracy path: gradients + scalars
+void launch_strips_f32_few(const StepCtx& c);  // ... for few pairs
+void launch_grad_f32_few(const StepCtx& c);    // ... the gradients through the normalisation included
 void launch_fold_bf16(const StepCtx& c);       // MFMA path: local contrast-side weights folded into the strips
 void launch_contract_bf16(const StepCtx& c);   // MFMA path: strips x X contractions
 void launch_strips_fine_bf16(const StepCtx& c);    // MFMA path, fine tiles: exp strips + row sums

@@ -676,4 +676,153 @@ void launch_grad_f32(const StepCtx& c) {
   else hipLaunchKernelGGL((k_grad_f64<32, 64>), grid, dim3(512), 0, c.s, g);
 }
 
+// ------------------------------------------------------------------------------------------
+// Few pairs (at most kFewPairs, kFewNarrowPairs of narrow rows): both phases in plain loops.  There a 32 x 32 tile is mostly padding, and its products
+// come one after the other in a single workgroup (per side of the output and 32 columns); a wavefront per dot product
+// spreads the few that there are over the chip.  What bounds it: launches (four dependent ones) and, for wide rows, the
+// loads' latency.  Steps, tiles / plain, us: 2 pairs at width 64: 17.8 / 17.1, at 1024 29.4 / 17.7, 1 of 2 at 1869
+// (unaligned) 56.1 / 23.9, 10 at 1915 47.9 / 45.1, 12 of 16 at 77: 21.7 / 20.0, 23 at 2: 20.4 / 19.7; with more pairs the
+// tiles: 23 at 303: 24.7 / 28.2, 64 at 32: 18.6 / 23.0, at 512 26 / 67.
+//
+// Strips (Proc. 1).  Block (r, side): anchor r against every contrast row j != p; side 0: image anchor vs texts (l1), side 1:
+// text anchor vs images (l2).  One wavefront per contrast row, fp64 accumulation; stores l as fp32 and the two row sums.
+__global__ void __launch_bounds__(256) k_strips_f32_few(const float* __restrict__ img, const float* __restrict__ txt,
+                                                        int64_t ld_img, int64_t ld_txt, int64_t off, int64_t B,
+                                                        int64_t d, const float* __restrict__ diag,
+                                                        const float* __restrict__ tau1, const float* __restrict__ tau2,
+                                                        float* __restrict__ E1, float* __restrict__ E2, int64_t ldE,
+                                                        float* __restrict__ sums, int64_t bstride,
+                                                        const float* __restrict__ colp, int64_t ncol,
+                                                        float* __restrict__ F1, float* __restrict__ F2) {
+  const int64_t r = blockIdx.x;
+  const int side = blockIdx.y;
+  const int64_t p = off + r;
+  const float* anchor = side == 0 ? img + p * ld_img : txt + p * ld_txt;
+  const float* X = side == 0 ? txt : img;
+  const int64_t ldx = side == 0 ? ld_txt : ld_img;
+  float* E = (side == 0 ? E1 : E2) + r * ldE;
+  float* F = colp ? (side == 0 ? F1 : F2) + r * ldE : nullptr;   // gathered: c_j l(j, p) of every remote anchor j
+  const double s_pp = (double)diag[r];
+  const double tau = (double)(side == 0 ? tau1[r] : tau2[r]);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double sg = 0.0, sh = 0.0;
+  for (int64_t j = wave; j < B; j += 4) {
+    const float* x = X + j * ldx;
+    double acc = 0.0;
+    for (int64_t k = lane; k < d; k += 64) acc += (double)anchor[k] * (double)x[k];
+    acc = wave_sum_f64(acc);
+    const double xs = acc - s_pp;
+    const double e = j == p ? 0.0 : exp(xs / tau);
+    if (lane == 0) E[j] = (float)e;
+    if (F && lane == 0) {
+      const float* cp = colp + (((int64_t)side * (ncol >> 8) + (j >> 8)) * 4) * 256 + (j & 255);
+      const double cj = (double)cp[512];
+      F[j] = cj == 0.0 ? 0.f : (float)(cj * exp2(acc * (double)cp[0] - (double)cp[256]));
+    }
+    sg += e;
+    sh += xs * e;
+  }
+  __shared__ double red[2][4];
+  if (lane == 0) { red[0][wave] = sg; red[1][wave] = sh; }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    // quantities 0,1 belong to side 0 (sum e1, sum x1 e1), 2,3 to side 1; nparts == 1 on this path
+    sums[(size_t)(2 * side + 0) * bstride + r] = (float)(red[0][0] + red[0][1] + red[0][2] + red[0][3]);
+    sums[(size_t)(2 * side + 1) * bstride + r] = (float)(red[1][0] + red[1][1] + red[1][2] + red[1][3]);
+  }
+}
+
+void launch_strips_f32_few(const StepCtx& c) {
+  const Layout& L = c.L;
+  dim3 grid((unsigned)L.b, 2), block(256);
+  hipLaunchKernelGGL(k_strips_f32_few, grid, block, 0, c.s, (const float*)c.buf.img_glob, (const float*)c.buf.txt_glob,
+                     c.cfg.ld_img, c.cfg.ld_txt, L.off, L.B, L.d, (const float*)(c.ws + L.diag),
+                     (const float*)(c.ws + L.tau1), (const float*)(c.ws + L.tau2), (float*)(c.ws + L.E[0]),
+                     (float*)(c.ws + L.E[1]), L.ldE, (float*)(c.ws + L.sums), L.bstride,
+                     L.gathered ? (const float*)(c.ws + L.colp) : nullptr, L.ncol,
+                     L.gathered ? (float*)(c.ws + L.F[0]) : nullptr, L.gathered ? (float*)(c.ws + L.F[1]) : nullptr);
+}
+
+// Gradients (Eqs. 2-7 for the local rows).  Block (r, side) writes one output row:
+//   side 0: d_img[r] = c1_r * sum_j l1(r,j) txt_j - (c1_r M g1_r + c2_r M g2_r) txt_p
+//                      + sum_{r' != r} c2_{r'} l2(r', p) txt_{p'}
+//   side 1: the mirror image.  The stored strips hold l with the anchor's own column zeroed.
+__global__ void __launch_bounds__(256) k_grad_f32_few(const float* __restrict__ img, const float* __restrict__ txt,
+                                                      int64_t ld_img, int64_t ld_txt, int64_t off, int64_t b, int64_t B,
+                                                      int64_t d, const float* __restrict__ E1, const float* __restrict__ E2,
+                                                      int64_t ldE, const float* __restrict__ c1, const float* __restrict__ c2,
+                                                      const float* __restrict__ dcoef, float* __restrict__ d_img,
+                                                      float* __restrict__ d_txt, const double* __restrict__ red, int nblocks,
+                                                      int version, const float* __restrict__ tau, float rho,
+                                                      float* __restrict__ loss, float* __restrict__ d_tau,
+                                                      const float* __restrict__ F1, const float* __restrict__ F2,
+                                                      const float* __restrict__ norm_img,
+                                                      const float* __restrict__ norm_txt) {
+  const int64_t r = blockIdx.x;
+  const int side = blockIdx.y;
+  const int64_t p = off + r;
+  const float* Fown = F1 ? (side == 0 ? F1 : F2) + r * ldE : nullptr;   // gathered: remote anchors' weights
+  const float* X = side == 0 ? txt : img;       // rows that the exp weights multiply
+  const int64_t ldx = side == 0 ? ld_txt : ld_img;
+  const float* Eown = (side == 0 ? E1 : E2) + r * ldE;       // l of this anchor over all contrasts
+  const float* Eoth = side == 0 ? E2 : E1;                   // l of the other local anchors at column p
+  const float* cown = side == 0 ? c1 : c2;
+  const float* coth = side == 0 ? c2 : c1;
+  float* out = (side == 0 ? d_img : d_txt) + r * d;
+  int cw = 32;
+  while (cw < 256 && cw < d) cw <<= 1;
+  const int groups = 256 / cw;
+  const int cl = threadIdx.x % cw, grp = threadIdx.x / cw;
+  __shared__ double red2[256];
+  for (int64_t c0 = 0; c0 < d; c0 += cw) {
+    const int64_t col = c0 + cl;
+    double acc = 0.0, acc6 = 0.0;
+    if (col < d) {
+      for (int64_t j = grp; j < B; j += groups) acc += (double)Eown[j] * (double)X[j * ldx + col];
+      for (int64_t q = grp; q < b; q += groups)
+        acc6 += (double)coth[q] * (double)Eoth[q * ldE + p] * (double)X[(off + q) * ldx + col];
+      if (Fown)
+        for (int64_t j = grp; j < B; j += groups) acc6 += (double)Fown[j] * (double)X[j * ldx + col];
+    }
+    red2[threadIdx.x] = (double)cown[r] * acc + acc6;
+    __syncthreads();
+    if (grp == 0 && col < d) {
+      double t = 0.0;
+      for (int g = 0; g < groups; ++g) t += red2[g * cw + cl];
+      out[col] = (float)(t - (double)dcoef[r] * (double)X[p * ldx + col]);
+    }
+    __syncthreads();
+  }
+  if (norm_img) {
+    // gradient through e^ = e / |e|: out := (out - e^ (e^ . out)) / |e|, e^ = this side's own row (see k_finalize_bf16)
+    const float* ep = side == 0 ? img + p * ld_img : txt + p * ld_txt;
+    double dot = 0.0;
+    for (int64_t col = threadIdx.x; col < d; col += 256) dot += (double)out[col] * (double)ep[col];
+    red2[threadIdx.x] = dot;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+      if ((int)threadIdx.x < w) red2[threadIdx.x] += red2[threadIdx.x + w];
+      __syncthreads();
+    }
+    dot = red2[0];
+    const double inv = 1.0 / (double)(side == 0 ? norm_img[r] : norm_txt[r]);
+    for (int64_t col = threadIdx.x; col < d; col += 256)
+      out[col] = (float)(((double)out[col] - dot * (double)ep[col]) * inv);
+  }
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 64)
+    write_scalars(red, nblocks, b, version, tau, rho, loss, d_tau);
+}
+
+void launch_grad_f32_few(const StepCtx& c) {
+  const Layout& L = c.L;
+  dim3 grid((unsigned)L.b, 2), block(256);
+  hipLaunchKernelGGL(k_grad_f32_few, grid, block, 0, c.s, (const float*)c.buf.img_glob, (const float*)c.buf.txt_glob,
+                     c.cfg.ld_img, c.cfg.ld_txt, L.off, L.b, L.B, L.d, (const float*)(c.ws + L.E[0]),
+                     (const float*)(c.ws + L.E[1]), L.ldE, (const float*)(c.ws + L.c1), (const float*)(c.ws + L.c2),
+                     (const float*)(c.ws + L.dcoef), c.buf.d_img, c.buf.d_txt, (const double*)(c.ws + L.red),
+                     L.nstate_blocks, c.cfg.version, c.buf.tau, c.cfg.rho, c.buf.loss, c.buf.d_tau,
+                     L.gathered ? (const float*)(c.ws + L.F[0]) : nullptr,
+                     L.gathered ? (const float*)(c.ws + L.F[1]) : nullptr, c.buf.norm_img, c.buf.norm_txt);
+}
+
 }  // namespace fc

@@ -451,3 +451,11 @@ def test_f32_workspace_takes_no_more_than_the_strips_where_the_static_array_asks
     assert strips < fc.fastclip_workspace_bytes(fits) <= fc.STATIC_SCRATCH_BYTES
     assert fc.fastclip_describe(fits)["nparts"] == 1
     assert fc.fastclip_describe(good_cfg(emb_dtype=fc.F32, B=8192, b=512, off=0, d=64, N=5000))["nparts"] > 1
+
+
+def test_few_fp32_pairs_take_no_tiles():
+    """Few fp32 pairs run in plain loops: two strips, one partial sum, one split whatever the tiled path would take."""
+    for shape, plain in ((dict(B=2, b=2, d=1024), 1), (dict(B=16, b=16, d=512), 1), (dict(B=24, b=24, d=128), 1),
+                         (dict(B=17, b=17, d=136), 0), (dict(B=25, b=25, d=8), 0)):
+        plan = fc.fastclip_describe(good_cfg(emb_dtype=fc.F32, off=0, N=100, **shape))
+        assert plan["single_pass"] == 1 - plain and plan["nparts"] == plan["nsplit"] == 1, (shape, plan)

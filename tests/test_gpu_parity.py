@@ -111,6 +111,8 @@ F32_TILE_SHAPES = [
     (4500, 70, 3, 36, 0),          # several contrast tiles behind one partial sum
     (1030, 1030, 0, 68, 0),        # 64 x 64 tiles, the whole batch local, ragged
     (2100, 550, 1201, 40, 4),      # 64 x 64 tiles, two strips, ragged
+    # the last batches in plain loops, the first on tiles
+    (16, 5, 9, 300, 0), (17, 5, 9, 300, 0), (24, 24, 0, 77, 1), (25, 25, 0, 77, 1), (24, 24, 0, 130, 0),
 ]
 
 
@@ -146,6 +148,11 @@ def test_f32_tiles_at_their_edges(B, b, off, d, pad, version):
 @pytest.mark.parametrize("version", [V0, V2])
 def test_f32_gathered_state_on_several_tiles(version):
     run_gathered(300, 130, 170, 72, version, "f32", TOL_F32)
+
+
+@pytest.mark.parametrize("version", [V0, V2])
+def test_f32_gathered_state_on_few_pairs(version):
+    run_gathered(23, 6, 11, 70, version, "f32", TOL_F32, N=200, ld_pad=3)
 
 
 # Two draws of a 400-case random sweep of the fp32 path on which the loss nearly cancels (case A: tau mean(log) = -0.911
@@ -778,7 +785,7 @@ def test_step_with_temperature_update_three_iterations(dtype, tol, shape, versio
 
 @pytest.mark.parametrize("tiles", [256, None])   # the large-tile kernels; the library's choice (small tiles here)
 # ------------------------------------------------------------------------------- cosine similarity, MBCL
-@pytest.mark.parametrize("dtype,tol,shape", [("f32", TOL_F32, (37, 11, 13, 19)), ("bf16", TOL_BF16, (700, 300, 133, 72)),
+@pytest.mark.parametrize("dtype,tol,shape", [("f32", TOL_F32, (37, 11, 13, 19)), ("f32", TOL_F32, (20, 9, 7, 70)), ("bf16", TOL_BF16, (700, 300, 133, 72)),
                                              ("bf16", TOL_BF16, (768, 512, 256, 128))])
 @pytest.mark.parametrize("version", [V2, V3])
 def test_gradients_through_normalisation(dtype, tol, shape, version, tiles):
@@ -842,7 +849,7 @@ def test_normalize_rows(raw_dtype, unit_dtype, b, d, pad):
 
 
 @pytest.mark.parametrize("tiles", [256, None])   # the large-tile kernels; the library's choice (small tiles here)
-@pytest.mark.parametrize("dtype,tol,shape", [("f32", TOL_F32, (37, 11, 13, 19)), ("bf16", TOL_BF16, (700, 300, 133, 72)),
+@pytest.mark.parametrize("dtype,tol,shape", [("f32", TOL_F32, (37, 11, 13, 19)), ("f32", TOL_F32, (20, 9, 7, 70)), ("bf16", TOL_BF16, (700, 300, 133, 72)),
                                              ("bf16", TOL_BF16, (1024, 320, 704, 128))])
 @pytest.mark.parametrize("version", [V2, V3])
 def test_from_raw_encoder_rows_to_gradients_of_raw_rows(dtype, tol, shape, version, tiles):
