@@ -212,18 +212,18 @@ static bool plan_t128(const fastclip_config& cfg, const Room& room, Layout* L) {
   }
   // It is taken where the kernel above would need a second round of workgroups, except
   //  - with fewer than one workgroup per compute unit, or few local anchors (the fold saves little),
-  //  - with one split, fewer than 384 workgroups and local anchors that are a small part of the batch: some compute units
-  //    get two long workgroups and most one,
+  //  - with one split and a few workgroups over one per compute unit, two on some: where the kernel above has two rounds, and
+  //    below 384 where the local anchors are a small part of the batch,
   //  - with an odd number of workgroups (over 1 split) in a column of tiles: they go to the XCDs in turn, and then every L2
   //    sees the whole of the strips.
   // Step times, above / wide, us.  One round: 1000 of 1000 at 1024: 37 / 42, 1024 of 4096 at 1024: 67 / 70, 640 of 5120 at
   // 1280: 74 / 94.  Two: 1000 of 1000 at 1280: 54 / 48, 1536 of 1536 at 1024: 75 / 65, 2048 of 2048 at 768: 82 / 69 and at 1024
   // (256 workgroups): 89 / 86, 1024 of 4096 at 2048: 122 / 105.  Four: 2048 of 2048 at 2048: 170 / 115.  Excepted, in this order:
-  // 1408 of 1408 at 1280 (220): 67 / 70, 320 of 3300 at 4096: 98 / 102; 640 of 5120 at 4096: 187 / 205, 553 of 2523 at
-  // 4096: 116 / 124; 1344 of 1546 at 736 (3 splits, 11 rows of tiles): 62 / 67, 800 of 4096 at 1536 (3, 7): 100 / 106.
+  // 1408 of 1408 at 1280 (220): 67 / 70, 320 of 3300 at 4096: 98 / 102; 1435 of 1435 at 1288 (264): 91 / 96, 640 of
+  // 5120 at 4096 (320): 187 / 205; 1344 of 1546 at 736 (3 splits, 11 rows of tiles): 62 / 67, 800 of 4096 at 1536 (3, 7): 100 / 106.
   const int64_t rows_of_tiles = (cfg.b + 127) / 128, wgs = wide_tiles * split;
   if (rounds >= 2 && cfg.b > 384 && wgs >= (cfg.b > 512 ? 256 : 257) &&
-      !(split == 1 && wgs < 384 && cfg.B > cfg.b + 640) && !(split > 1 && (split * rows_of_tiles) % 2)) {
+      !(split == 1 && wgs > 256 && (rounds == 2 || (wgs < 384 && cfg.B > cfg.b + 640))) && !(split > 1 && (split * rows_of_tiles) % 2)) {
     L->wide = 1;
     L->nsplit = (int)split; L->kslice = (depth + split - 1) / split;
     L->fused_state = fold_forms_state(cfg.b, L->nparts);
