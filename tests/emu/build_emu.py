@@ -2,8 +2,9 @@
 hip/hip_runtime.h of this folder, linked with emu_main.cpp into _build/emu/emu_step, AddressSanitizer on.
 
 The sources are copied with the few constructs a host compiler cannot take replaced by calls into the stand-in: inline
-assembly (direct-to-LDS loads, accumulator reads) and the LDS address-space attribute.  Nothing else differs: indexing,
-guards, barriers and the order of operations are the product's."""
+assembly (direct-to-LDS loads, accumulator reads) and the LDS address-space attribute.  Indexing, guards, barriers and the
+order of operations are the product's.  So that a small shape can run what the library's plans keep for large ones, the rules
+in PLAN_RULES also listen to environment variables (EMU_...): unset, they decide as in the product."""
 from __future__ import annotations
 
 import os
@@ -41,6 +42,36 @@ def _asm_replacement(m):
     raise RuntimeError("inline assembly the emulation does not know: " + t)
 
 
+def _forced(expr, name, kind="atoi"):
+    return '(getenv("%s") ? %s(getenv("%s")) : (%s))' % (name, kind, name, expr)
+
+
+# (file, the product's text, what the emulation compiles instead); every text must be there, so that a rule that changes
+# here fails loudly
+PLAN_RULES = [
+    # small tiles: rows of an output tile and splits of k_contract_t128_bf16; the 128 x 128 contraction; either kind of strips
+    ("fastclip_api.hip", "  for (int64_t rows = 64; rows <= (L->gathered ? 64 : 128); rows += 64) {",
+     '  for (int64_t rows = 64; rows <= (L->gathered ? 64 : 128); rows += 64) {\n'
+     '    if (getenv("EMU_OUT_ROWS") && atoi(getenv("EMU_OUT_ROWS")) != rows) continue;'),
+    ("fastclip_api.hip", "      if (best_cost == 0.0 || cost < best_cost) {",
+     '      if (getenv("EMU_NSPLIT") && atoi(getenv("EMU_NSPLIT")) != ns) continue;\n'
+     '      if (best_cost == 0.0 || cost < best_cost) {'),
+    ("fastclip_api.hip", "    if (ns == 1 || cost < wide_cost) { split = ns; wide_cost = cost; }",
+     '    if (getenv("EMU_NSPLIT") && atoi(getenv("EMU_NSPLIT")) != ns) continue;\n'
+     '    if (wide_cost == 0.0 || cost < wide_cost) { split = ns; wide_cost = cost; }'),
+    ("fastclip_api.hip", "  if (rounds >= 2 && cfg.b > 384", '  if (getenv("EMU_WIDE") ? atoi(getenv("EMU_WIDE")) : rounds >= 2 && cfg.b > 384'),
+    ("fastclip_api.hip", "L->wide_strips = tiles > 256 && tiles < 512 && 4 * cfg.b > 3 * cfg.B;",
+     "L->wide_strips = " + _forced("tiles > 256 && tiles < 512 && 4 * cfg.b > 3 * cfg.B", "EMU_WIDE_STRIPS") + ";"),
+    ("kernels_tiles128.hip", "const bool narrow = at64 <= 256;", "const bool narrow = " + _forced("at64 <= 256", "EMU_NARROW") + ";"),
+    # fp32 path: tile sizes, plain loops, what is left of a plan that has to fit the static array
+    ("fastclip_api.hip", "((cfg.B + 63) / 64) >= 256 ? 64 : 32;", "((cfg.B + 63) / 64) >= " + _forced("256", "EMU_F32_TILES") + " ? 64 : 32;"),
+    ("fastclip_api.hip", "  for (int T = 32; T <= 64; T += 32) {",
+     '  for (int T = 32; T <= 64; T += 32) {\n    if (getenv("EMU_GRAD_TILE") && atoi(getenv("EMU_GRAD_TILE")) != T) continue;'),
+    ("fastclip_api.hip", "  constexpr int64_t kLimit = FASTCLIP_STATIC_SCRATCH_BYTES;",
+     "  const int64_t kLimit = " + _forced("FASTCLIP_STATIC_SCRATCH_BYTES", "EMU_STATIC_BYTES") + ";"),
+]
+
+
 def generate():
     gen = os.path.join(OUT, "gen")
     os.makedirs(gen, exist_ok=True)
@@ -52,6 +83,11 @@ def generate():
             s = open(os.path.join(d, n)).read()
             s = s.replace("__attribute__((address_space(3)))", "")
             s = re.sub(r'asm volatile\((?:[^;]|\n)*?\);', _asm_replacement, s)
+            for name, text, instead in PLAN_RULES:
+                if name == n:
+                    if text not in s:
+                        raise RuntimeError("%s: the rule has changed: %s" % (name, text))
+                    s = s.replace(text, instead)
             out = os.path.join(gen, n.replace(".hip", ".inc"))
             open(out, "w").write(s)
             if n.endswith(".hip"):

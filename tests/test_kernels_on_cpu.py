@@ -133,8 +133,14 @@ def run_case(exe, tmp_path, *, B, b, off, d, version, dtype="bf16", flags=0, ld_
 
 
 CASES = [
-    # fp32 accuracy path
+    # fp32 accuracy path: rows that are no 16-byte words (everything through registers); whole stages, the whole batch
+    # local; a ragged last stage behind a whole one; rows padded to words, two strips; few pairs in plain loops, plain and gathered
     dict(B=37, b=11, off=13, d=19, version=V2, dtype="f32", ld_img=23),
+    dict(B=64, b=64, off=0, d=64, version=V2, dtype="f32"),
+    dict(B=66, b=66, off=0, d=36, version=V3, dtype="f32"),
+    dict(B=130, b=70, off=33, d=68, version=V0, dtype="f32", ld_img=72),
+    dict(B=16, b=5, off=9, d=30, version=V3, dtype="f32", ld_img=33),
+    dict(B=23, b=6, off=11, d=70, version=V2, dtype="f32", gathered=True),
     # MFMA path, every tile ragged: guarded strip tiles on the ring (rows replaced by the last one), ragged last stage,
     # contraction with a guarded tail, fused state phase in the fold; padding between the rows of one side
     dict(B=300, b=140, off=100, d=72, version=V3, ld_img=80, flags=fc.TILES_256),
@@ -145,10 +151,12 @@ CASES = [
     dict(B=300, b=300, off=0, d=72, version=V2, flags=fc.SINGLE_PASS),
     # ... and on whole tiles (column pass of the persistent kernel)
     dict(B=512, b=512, off=0, d=128, version=V3, flags=fc.SINGLE_PASS),
-    # contrast side over every global anchor (second strip, remote fold)
+    # contrast side over every global anchor (second strip, remote fold), ragged and on whole tiles (the persistent kernel)
+    dict(B=300, b=100, off=50, d=72, version=V2, gathered=True, flags=fc.TILES_256),
+    dict(B=512, b=256, off=256, d=128, version=V3, gathered=True, flags=fc.TILES_256),
+    # ... on the small tiles, the library's own choice (pairs of contrast tiles, second strip added in the contraction)
     dict(B=300, b=100, off=50, d=72, version=V2, gathered=True),
-    # the library's own choice for a small batch: 128 x 128 tiles
-    # 128 x 128 tiles (opt-in): ragged everywhere with a guarded last stage; whole stages on the ring with rows replaced;
+    # 128 x 128 tiles, the library's own choice for a small batch: ragged everywhere with a guarded last stage; whole stages on the ring with rows replaced;
     # the whole batch local with a width below one stage; several splits with the finalize kernel
     dict(B=300, b=140, off=100, d=72, version=V3, ld_txt=80),
     dict(B=512, b=300, off=212, d=128, version=V2, flags=fc.TILES_128),
@@ -165,6 +173,32 @@ def test_step_of_the_host_built_kernels_matches_the_oracle_under_asan(emu_step, 
     run_case(emu_step, tmp_path, **case)
 
 
+# Kernels that the library's plans keep for larger shapes than the emulation has time for: the plan is forced (build_emu.PLAN_RULES)
+FORCED = [
+    # small tiles: contraction on 128 x 128 output tiles behind the fold, with and without splits; strips of two workgroups
+    # per compute unit with it; strips of 128 anchors and output tiles of 128 rows; splits of either row count; with gathered state
+    dict(plan=dict(WIDE=1, NSPLIT=1), B=300, b=140, off=100, d=72, version=V2, ld_txt=80),
+    dict(plan=dict(WIDE=1, NSPLIT=3), B=257, b=257, off=0, d=40, version=V3),
+    dict(plan=dict(WIDE=1, WIDE_STRIPS=1), B=300, b=140, off=100, d=72, version=V0, ld_txt=80),
+    dict(plan=dict(OUT_ROWS=128, NARROW=0), B=200, b=140, off=33, d=72, version=V2),
+    dict(plan=dict(OUT_ROWS=128, NSPLIT=2), B=200, b=140, off=33, d=72, version=V3),
+    dict(plan=dict(OUT_ROWS=64, NSPLIT=2, NARROW=0), B=200, b=140, off=33, d=72, version=V3, gathered=True),
+    # fp32 path: 64 x 64 tiles of strips and gradients, splits, the single pass on them; splits with gathered state; one partial
+    # sum over several tiles, as where the strips alone fill the static array
+    dict(plan=dict(F32_TILES=1, GRAD_TILE=64, NSPLIT=2), B=150, b=70, off=33, d=68, ld_img=72, version=V3, dtype="f32"),
+    dict(plan=dict(F32_TILES=1, GRAD_TILE=64), B=70, b=70, off=0, d=64, version=V2, dtype="f32"),
+    dict(plan=dict(NSPLIT=3), B=130, b=40, off=70, d=128, version=V2, dtype="f32", gathered=True),
+    dict(plan=dict(STATIC_BYTES=60000), B=70, b=70, off=0, d=36, version=V2, dtype="f32"),
+]
+
+
+@pytest.mark.parametrize("case", FORCED, ids=lambda c: "-".join("%s%s" % (k, v) for k, v in c.items()))
+def test_plans_of_larger_shapes_on_the_host_built_kernels(emu_step, tmp_path, monkeypatch, case):
+    for k, v in case["plan"].items():
+        monkeypatch.setenv("EMU_" + k, str(v))
+    run_case(emu_step, tmp_path, **{k: v for k, v in case.items() if k != "plan"})
+
+
 @pytest.mark.parametrize("seed", range(8))
 def test_random_small_shapes_on_the_host_built_kernels(emu_step, tmp_path, seed):
     """Shapes, strides, version and path drawn at random (seeded): B up to 300, any b and off, widths of 8 .. 320 that are
@@ -178,7 +212,7 @@ def test_random_small_shapes_on_the_host_built_kernels(emu_step, tmp_path, seed)
     d = 8 * rng.choice([1, 2, 3, 4, 8, 9, 16, 17, 24, 32, 33, 40])
     path = ["256", "128", "auto", "fine", "single", "gathered", "128", "256"][seed]
     flags = {"256": fc.TILES_256, "128": fc.TILES_128, "auto": 0, "fine": fc.FINE_TILES, "single": fc.SINGLE_PASS,
-             "gathered": 0}[path]
+             "gathered": fc.TILES_256}[path]
     if path == "single":
         b, off = B, 0
     run_case(emu_step, tmp_path, B=B, b=b, off=off, d=d, version=rng.randint(0, 3), flags=flags,
@@ -282,12 +316,14 @@ def test_step_with_temperature_update_of_the_host_built_kernels(emu_step, tmp_pa
 
 
 # ------------------------------------------------------------------ the small entry points
-@pytest.mark.parametrize("b,d,n", [(37, 19, 300), (5, 4104, 2), (130, 72, 1), (1, 1, 1000)])
-def test_small_entry_points_of_the_host_built_kernels(emu_step, tmp_path, b, d, n):
-    """fastclip_normalize_rows (a wavefront per row, padded rows on both sides), fastclip_check_indices (hash table on
+@pytest.mark.parametrize("b,d,n,pads", [(37, 19, 300, (3, 5)), (5, 4104, 2, (3, 5)), (130, 72, 1, (3, 5)), (1, 1, 1000, (3, 5)),
+                                        (37, 72, 3, (4, 8)), (9, 1024, 3, (0, 0)), (5, 1028, 3, (0, 4))])
+def test_small_entry_points_of_the_host_built_kernels(emu_step, tmp_path, b, d, n, pads):
+    """fastclip_normalize_rows (a wavefront per row, padded rows on both sides; whole groups of four elements up to a width of
+    1024, and behind it), fastclip_check_indices (hash table on
     the device; distinct indices pass, a repeated one is reported), fastclip_state_update (Eq. 1 alone)."""
     rng = np.random.default_rng(b + d)
-    ld_raw, ld_unit, N = d + 3, d + 5, 4 * n + 7
+    ld_raw, ld_unit, N = d + pads[0], d + pads[1], 4 * n + 7
     raw = np.full((b, ld_raw), np.nan, np.float32)
     raw[:, :d] = rng.normal(0, 1, (b, d)) * rng.uniform(0.1, 30.0, (b, 1))
     idx = draw_indices(9, n, N)
