@@ -548,9 +548,51 @@ def test_bf16_gathered_state(B, b, off, d, version):
     (100, 9, 91, 64), (300, 130, 57, 72), (257, 65, 3, 136), (1000, 64, 936, 520),
     # several splits; the state phase on its own
     (2048, 256, 768, 512), (5120, 640, 3200, 512)])
-@pytest.mark.parametrize("version", [V0, V2])
+@pytest.mark.parametrize("version", [V0, V1, V2, V3])
 def test_bf16_gathered_state_on_small_tiles(B, b, off, d, version):
     run_gathered(B, b, off, d, version, "bf16", TOL_BF16, ld_pad=8, tiles=None)
+
+
+@pytest.mark.parametrize("B,b,off,d", [(300, 130, 57, 72), (1000, 600, 200, 72)])    # state phase in the contraction; on its own
+@pytest.mark.parametrize("version", [V2, V3])
+def test_gathered_state_on_small_tiles_with_temperature_update(B, b, off, d, version):
+    """fastclip_step_update_tau with gathered state is fastclip_step followed by fastclip_temperature_update: the same bits
+    in every output and in the state (one set of kernels), the temperatures and moments to a few units in the last place
+    (the same arithmetic in another kernel, whose multiply-adds may be contracted differently)."""
+    N = 3000
+    rng = np.random.default_rng(B + version)
+    img, txt = make_embeddings(B + 31, B, d, 0.5, "bf16")
+    idx = draw_indices(B + 32, b, N)
+    u0i, u0t = (rng.uniform(0.05, 2.0, N).astype(np.float32) for _ in range(2))
+    t_img, t_txt = (rng.uniform(0.05, 0.1, N).astype(np.float32) for _ in range(2))
+    ug1, ug2, tg1, tg2 = gathered_inputs(rng, B, version)
+    upd = fc.make_tau_update(optimizer=ADAMW, step=3, lr=2e-3, beta1=0.9, beta2=0.98, eps=1e-6, tau_min=0.01)
+    runs = []
+    for fused in (True, False):
+        g = GpuStep(B=B, b=b, off=off, d=d, N=N, dtype="bf16", version=version, eps=1e-6, rho=6.5, tau=0.07, u_img0=u0i,
+                    u_txt0=u0t, tau_img0=t_img, tau_txt0=t_txt, gathered=dict(u_img=ug1, u_txt=ug2, tau_img=tg1, tau_txt=tg2),
+                    tiles=None)
+        assert fc.fastclip_describe(g.config(0.6))["tile"] == 128
+        g.set_inputs(img, txt, idx)
+        z = lambda n: torch.full((n,), 0.01, dtype=torch.float32, device=DEV)
+        moments = {k: z(N) for k in ("m_img", "v_img", "m_txt", "v_txt")} if version == V2 else dict(m=z(1), v=z(1))
+        tau = dict(tau_img=g.tau_img, tau_txt=g.tau_txt) if version == V2 else dict(tau=g.tau)
+        state = fc.make_tau_state(**tau, **moments)
+        if fused:
+            g.step_update_tau(0.6, upd, state)
+        else:
+            g.step(0.6)
+            fc.fastclip_temperature_update(version, upd, state, g.idx, b, N, g.d_tau, g.d_tau_img, g.d_tau_txt)
+            torch.cuda.synchronize()
+        runs.append((g, dict(tau, **moments)))
+    (g, s), (h, t) = runs
+    for k in ("d_img", "d_txt", "loss", "d_tau", "d_tau_img", "d_tau_txt", "g_img", "g_txt", "u_new_img", "u_new_txt", "u_img", "u_txt"):
+        assert torch.equal(getattr(g, k).view(torch.int32), getattr(h, k).view(torch.int32)), k
+    for k in s:
+        assert float((s[k] - t[k]).abs().max()) <= 8 * 2.0 ** -23 * float(t[k].abs().max()), k
+    moved = s["tau_img"] if version == V2 else s["tau"]
+    start = torch.from_numpy(t_img).to(DEV) if version == V2 else torch.full_like(moved, 0.07)
+    assert int((moved != start).sum()) == (b if version == V2 else 1)
 
 
 @pytest.mark.parametrize("b,d,ld,at", [(3, 4, 4, 0), (5, 1020, 1024, 0), (6, 516, 516, 4), (7, 512, 512, 1), (9, 1028, 1028, 0)])
