@@ -373,12 +373,18 @@ def main():
                                 "frac_of_peak": round(mc["tflops"] * 1e12 / PEAK_BF16_FLOPS, 4),
                                 "kernel_frac_of_measured_ceiling": round(achieved / mc["tflops"], 4),
                                 "kind": "k_mfma_ceiling: independent 32x32x16 bf16 MFMAs on pseudo-random register operands"}
-    # what the two MFMA kernels execute: whole 256-row tiles, two strips unless the whole batch is local in whole
-    # tiles on more tiles than compute units (one similarity pass), two contractions over the padded column range
+    # what the two MFMA kernels execute: whole tiles, two strips unless the whole batch is local in whole tiles on more
+    # tiles than compute units (one similarity pass), two contractions over the padded column range.  Small tiles: 64 anchors
+    # by 128 contrasts (128 anchors pad the same at the workloads' sizes), output tiles of 64 columns, and the local
+    # anchors' contrast-side term as further depth of the contraction instead of a pass over the strips before it.
     up = lambda x, m: (x + m - 1) // m * m
     tile = plan["tile"]
-    executed = {"strips": (1 if plan["single_pass"] else 2) * 2.0 * up(b, tile) * up(B, tile) * d,
-                "contract": 2 * 2.0 * up(b, tile) * up(B, 64) * up(d, tile)}
+    if tile == 128:
+        executed = {"strips": 2 * 2.0 * up(b, 64) * up(B, 128) * d,
+                    "contract": 2 * 2.0 * up(b, 64) * (up(B, 16) + up(b, 16)) * up(d, 64)}
+    else:
+        executed = {"strips": (1 if plan["single_pass"] else 2) * 2.0 * up(b, tile) * up(B, tile) * d,
+                    "contract": 2 * 2.0 * up(b, tile) * up(B, 64) * up(d, tile)}
     gemm_ms = phase_ms["strips"] + phase_ms["contract"]
     gemm_phases = {"algorithmic_tflops": round((alg["strips"] + alg["contract"]) / (gemm_ms * 1e-3) / 1e12, 2),
                    "frac_of_bf16_peak": round((alg["strips"] + alg["contract"]) / (gemm_ms * 1e-3) / PEAK_BF16_FLOPS, 4),
