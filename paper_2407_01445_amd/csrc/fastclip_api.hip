@@ -253,8 +253,11 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
   const int64_t big_tiles = 2 * ((cfg.b + 255) / 256) * ((cfg.B + 255) / 256);
   L->fine = (cfg.flags & FASTCLIP_FINE_TILES) && L->bf16 && !L->gathered && !L->square && big_tiles < 192;
   // 128 x 128 tiles: asked for (wherever a quarter of the large tiles' workgroups would still not fill the chip), or
-  // chosen when the large tiles would occupy at most half of the compute units (measured: b = 128 .. 1024 of
-  // B = 1024 .. 8192 at width 512 are 4 - 22 % faster, b = 640 of 5120, 120 large tiles, breaks even)
+  // chosen when the large tiles would occupy at most half of the compute units.  Steps on small / large tiles, us, width 512:
+  // 128 of 1024 (8 large tiles) 21 / 42, 1024 of 1024 (32) 30 / 49, 640 of 5120 (120) 47 / 58, 1024 of 4096 (128) 50 / 63, 2048 of
+  // 2048 (128) 56 / 66; at width 1024 2048 of 2048 breaks even (86 / 85).  Above, small tiles are still the faster ones for ragged
+  // batches (1200 of 4600, 180 large tiles: 71 / 103) and narrow rows (1024 of 5120, 160: 49 / 55 at 256, 61 / 69 at 512, 84 /
+  // 84 at 1024) but not for large whole ones (2304 of 2304, 162: 84 / 79 at 512, 114 / 101 at 1024).
   const bool small_ok = L->bf16 && !L->square && !L->fine && !(cfg.flags & FASTCLIP_TILES_256);
   // (the kernels address rows by 32-bit byte offsets, number their output tiles in 16 bits and hold the coefficients of a
   // workgroup's local anchors in LDS)
@@ -375,9 +378,9 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
 
 // A configuration of the fp32 path or of the 128 x 128 tiles whose stored strips fit the array of fastclip_step_static fits it
 // whole, so that every such configuration is taken there, and with the same layout whichever entry point runs it.  What the step
-// has in its workspace for speed alone gives way in this order: splits as far as their partial results do not fit (a split
-// more or less is a few per cent; 2600 of 2600 fp32 pairs at width 512 keep their single pass and take 577 us instead
-// of 1460 without it), then, where the strips alone leave less than the partial sums take (the last 5 % below the
+// has in its workspace for speed alone gives way in this order: splits as far as their partial results do not fit (a few per
+// cent mostly, at worst a quarter: 1000 of 8000 fp32 pairs at width 64 take 227 us, 177 with its two splits; 2600 of 2600 at width
+// 512 keep their single pass and take 577, with three splits 537, without the single pass 1460), then, where the strips alone leave less than the partial sums take (the last 5 % below the
 // array's size), the fp32 path's partial sums and single pass, at two to three times the time.
 void make_layout(const fastclip_config& cfg, Layout* L) {
   constexpr int64_t kLimit = FASTCLIP_STATIC_SCRATCH_BYTES;

@@ -48,7 +48,8 @@ struct Layout {
   int few;           // 1: fp32 path in plain loops (few pairs)
   int per_part;      // fp32 path: contrast tiles behind one partial sum
   int strip_tile, grad_tile;   // fp32 path: tile sizes of k_strips_f64 / k_grad_f64 (32 or 64)
-  int64_t ldE;       // contrast columns of the stored exp strips (MFMA path: multiple of 64; fp32 path: B)
+  int64_t ldE;       // contrast columns of the stored exp strips (MFMA path: multiple of 64; fp32 path: of 4, or B
+                     // itself where the strips alone fill the static array)
   int nsplit;        // split of the contraction over its column range
   int64_t kslice;    // 32-deep stages per split (fp32 path: stages of the gradient kernel's depth)
   int nstate_blocks; // scalar partials: one per block of the state kernel, per diagonal block of the fused fold, or (t128 with
@@ -86,8 +87,9 @@ struct Layout {
   // [s][tile][4][256]: log2(e)/tau_j, s_jj log2(e)/tau_j, c_j (0 for local rows and beyond B), unused.
   // Side 0 describes the text anchors j (l2(j, .), weights of d_img), side 1 the image anchors (l1(j, .), d_txt).
   size_t colp;
-  size_t F[2];                       // gathered: the second stored strip c_j l(j, p_r), same form as E, folded into E
-                                     // after the state phase (MFMA path) or summed directly (fp32 path)
+  size_t F[2];                       // gathered: the second stored strip c_j l(j, p_r), same form as E, folded into E after
+                                     // the state phase (256 x 256 tiles), added in the contraction (t128) or summed
+                                     // directly (fp32 path)
   size_t total;
 };
 

@@ -6,6 +6,7 @@
 //                l = exp((s - s_ii) / tau) stored as fp32, and per anchor the sums of l and of (s - s_ii) l.
 //  k_grad_f64    the gradients of Eqs. 2-7 as matrix products on T x T output tiles: the weights
 //                w[r][j] = c_own[r] l_own(r, j) + (contrast side) are formed in fp64 while a stage is brought into LDS.
+//  k_strips_f32_few, k_grad_f32_few  the same in plain loops, for two dozen pairs at most (at the end of this file).
 //
 // What bounds them: the fp64 pipes.  A 16x16x4 product takes 64 cycles of its SIMD (measured, dependent or not: 32 flop per
 // cycle and SIMD, the fp64 vector rate as well), and no other vector instruction of the SIMD issues meanwhile (measured:

@@ -211,8 +211,9 @@ void launch_normalize_rows(const void* raw, int raw_bf16, int64_t ld_raw, int64_
 // Anchor j contributes c_j l2(j, p) txt_j to the image gradient of a local row p and c_j l1(j, p) img_j to its text
 // gradient, with l2(j, p) = exp((s_pj - s_jj) / tau2_j), l1(j, p) = exp((s_jp - s_jj) / tau1_j) and
 // c_j = kappa_j / (|B_k| |B_j-| (eps + u_j^{t+1})): the strips already form s_pj and s_jp, so all they need per
-// column j is log2(e)/tau_j, s_jj log2(e)/tau_j and c_j.  Local rows get c = 0 (their u^{t+1} is only known after
-// the state phase; the fold after the state phase handles them), and so do the padding columns beyond B.
+// column j is log2(e)/tau_j, s_jj log2(e)/tau_j and c_j.  Local rows get c = 0: their u^{t+1} is only known after
+// the state phase, and their share is the local contrast-side term of what follows it (the fold, or further depth of the
+// contraction on the small tiles and on the fp32 path).  So do the padding columns beyond B.
 template <typename T>
 __global__ void __launch_bounds__(256) k_prep_cols(const T* __restrict__ img, const T* __restrict__ txt, int64_t ld_img,
                                                    int64_t ld_txt, int64_t B, int64_t ncol, int64_t off, int64_t b,

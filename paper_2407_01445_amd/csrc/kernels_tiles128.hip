@@ -58,12 +58,14 @@ struct T128StripArgs {
   int first, own;               // global row of column 0; column of local anchor 0
 };
 
-// One workgroup per tile (128 anchors against 128 contrasts of one strip), eight waves = two groups of 2 x 2 waves of
+// One workgroup per tile (AT = 128: 128 anchors against 128 contrasts of one strip), eight waves = two groups of 2 x 2 waves of
 // 64 x 64: either group takes every other 64-deep stage, so that a SIMD always has a second wave to issue from, an operand
 // read serves two products, and the loop has half the barriers; afterwards the groups exchange halves of their
-// accumulators and each finishes half of the tile's columns.  Measured at 128 anchors of 1024 pairs, d = 512, against
-// four waves on 32-deep stages through a ring of five: 12.0 -> 8.5 us, of which (in-kernel counters, 2.4 GHz) 0.4 set-up, 1.1
-// until the first step is there, 2.6 in the four steps (1.7 of products), 0.7 exchange, 1.5 exponentials, 0.5 sums.
+// accumulators and each finishes half of the tile's columns.  AT = 64: the four waves of a group take 32 contrasts each.
+// Measured with AT = 128 at 128 anchors of 1024 pairs, d = 512 (a shape that takes AT = 64 now, see the launch), against four
+// waves on 32-deep stages through a ring of five (k_strips_wide128_bf16): 12.0 -> 8.5 us, of which (in-kernel counters, 2.4
+// GHz) 0.4 set-up, 1.1 until the first step is there, 2.6 in the four steps (1.7 of products), 0.7 exchange, 1.5
+// exponentials, 0.5 sums.
 //
 // GATHERED: every element also yields the weight f = c_j 2^(s k_j - d_j) with which contrast column j, an anchor of another
 // worker, moves the local row (Eqs. 3 / 5 / 7); it goes to a second strip of the same form.  A workgroup then takes two
@@ -402,9 +404,10 @@ struct T128Args {
 // 512 cycles against 256 of products (650 - 880 measured), and about 5 us go into the start, the coefficients, the sum over
 // the waves and the outputs.  128-row tiles (MB = 2) move a quarter less per product and are taken where 64-row ones need
 // a second round of workgroups; the cost model is in plan_t128.  Steps before and after (fold + contraction + finalize
-// kernels before): 128 of 1024 pairs, d = 512: 34.2 -> 22.9 us, 256 of 8192: 48.6 -> 34.5, 1024 of 1024: 37.7 -> 30.0,
-// 1000 of 4000, d = 760 (128-row tiles): 71.5 -> 61.9; 640 of 5120 with gathered state (a pass over both strips before): 74.8 ->
-// 62.1.  With the workgroups in plain order every XCD fetched every slice of the depth: 640 of 5120 gathered 67 us.
+// kernels before; strips of 64 anchors included): 128 of 1024 pairs, d = 512: 34.7 -> 20.7 us, 256 of 8192: 47.8 -> 31.2,
+// 1024 of 1024: 37.9 -> 30.1, 1000 of 4000, d = 760, rows of 768 (128-row tiles): 71.5 -> 61.9; 640 of 5120 with gathered state
+// (a pass over both strips before): 72.5 -> 60.8.  With the workgroups in plain order every XCD fetched every slice of the
+// depth: 640 of 5120 gathered 67 us.
 // GATHERED: the remote anchors' weights multiply the same rows of X, so the first sum's operand is c_own E + F, formed as
 // E + F / c_own (the sum is multiplied by c_own afterwards) between the reads and the products of a stage.
 template <int MB, bool GATHERED>
