@@ -195,9 +195,22 @@ static bool plan_t128(const fastclip_config& cfg, const Room& room, Layout* L) {
     const bool whole = cfg.B % 256 == 0 && cfg.d % 64 == 0;
     return room.split_bytes == 0 || in_a_row <= (whole ? 104.0 : 240.0);
   }
-  // Contraction of kernels_wide128.hip behind the fold: its depth in 32-deep stages over `ns` workgroups per output tile.  Time
-  // in stages of a workgroup that has its compute unit to itself: a second one there stretches both by 1.45, beyond 512
-  // they run in rounds; a tile's start and end cost 4; the finalize kernel 5 + 0.42 per MiB of partial results it reads.
+  // Contraction of kernels_wide128.hip behind the fold.
+  // It is taken where the kernel above would need a second round of workgroups, except
+  //  - with few local anchors (the fold saves little) or fewer than one workgroup per compute unit,
+  //  - with one split and a few workgroups over one per compute unit, two on some: where the kernel above has two rounds, and
+  //    below 384 where the local anchors are a small part of the batch,
+  //  - with an odd number of workgroups (over 1 split) in a column of tiles: they go to the XCDs in turn, and then every L2
+  //    sees the whole of the strips.
+  // Step times, above / wide, us.  One round: 1000 of 1000 at 1024: 37 / 42, 1024 of 4096 at 1024: 67 / 70, 640 of 5120 at
+  // 1280: 74 / 94.  Two: 1000 of 1000 at 1280: 54 / 48, 1536 of 1536 at 1024: 75 / 65, 2048 of 2048 at 768: 82 / 69 and at 1024
+  // (256 workgroups): 89 / 86, 1024 of 4096 at 2048: 122 / 105.  Four: 2048 of 2048 at 2048: 170 / 115.  Excepted, in this order:
+  // 320 of 3300 at 4096: 98 / 102, 1408 of 1408 at 1280 (220): 67 / 70; 1435 of 1435 at 1288 (264): 91 / 96, 640 of 5120 at
+  // 4096 (320): 187 / 205; 1344 of 1546 at 736 (3 splits, 11 rows of tiles): 62 / 67, 800 of 4096 at 1536 (3, 7): 100 / 106.
+  if (rounds < 2 || cfg.b <= 384) return true;
+  // Its depth in 32-deep stages goes over `split` workgroups per output tile.  Time in stages of a workgroup that has its
+  // compute unit to itself: a second one there stretches both by 1.45, beyond 512 they run in rounds; a tile's start and end
+  // cost 4; the finalize kernel 5 + 0.42 per MiB of partial results it reads.
   const int64_t depth = L->ldE / 32, wide_tiles = 2 * ((cfg.b + 127) / 128) * ((cfg.d + 127) / 128);
   int64_t split = 1;
   double wide_cost = 0.0;
@@ -210,20 +223,10 @@ static bool plan_t128(const fastclip_config& cfg, const Room& room, Layout* L) {
     const double cost = stretch * (double)slice + 4.0 + (ns > 1 ? 5.0 + 0.42 / 16.0 * (double)wgs : 0.0);
     if (ns == 1 || cost < wide_cost) { split = ns; wide_cost = cost; }
   }
-  // It is taken where the kernel above would need a second round of workgroups, except
-  //  - with fewer than one workgroup per compute unit, or few local anchors (the fold saves little),
-  //  - with one split and a few workgroups over one per compute unit, two on some: where the kernel above has two rounds, and
-  //    below 384 where the local anchors are a small part of the batch,
-  //  - with an odd number of workgroups (over 1 split) in a column of tiles: they go to the XCDs in turn, and then every L2
-  //    sees the whole of the strips.
-  // Step times, above / wide, us.  One round: 1000 of 1000 at 1024: 37 / 42, 1024 of 4096 at 1024: 67 / 70, 640 of 5120 at
-  // 1280: 74 / 94.  Two: 1000 of 1000 at 1280: 54 / 48, 1536 of 1536 at 1024: 75 / 65, 2048 of 2048 at 768: 82 / 69 and at 1024
-  // (256 workgroups): 89 / 86, 1024 of 4096 at 2048: 122 / 105.  Four: 2048 of 2048 at 2048: 170 / 115.  Excepted, in this order:
-  // 1408 of 1408 at 1280 (220): 67 / 70, 320 of 3300 at 4096: 98 / 102; 1435 of 1435 at 1288 (264): 91 / 96, 640 of
-  // 5120 at 4096 (320): 187 / 205; 1344 of 1546 at 736 (3 splits, 11 rows of tiles): 62 / 67, 800 of 4096 at 1536 (3, 7): 100 / 106.
   const int64_t rows_of_tiles = (cfg.b + 127) / 128, wgs = wide_tiles * split;
-  if (rounds >= 2 && cfg.b > 384 && wgs >= (cfg.b > 512 ? 256 : 257) &&
-      !(split == 1 && wgs > 256 && (rounds == 2 || (wgs < 384 && cfg.B > cfg.b + 640))) && !(split > 1 && (split * rows_of_tiles) % 2)) {
+  const bool some_have_two = split == 1 && wgs > 256 && (rounds == 2 || (wgs < 384 && cfg.B > cfg.b + 640));
+  const bool no_shared_l2 = split > 1 && (split * rows_of_tiles) % 2;
+  if (wgs >= (cfg.b > 512 ? 256 : 257) && !some_have_two && !no_shared_l2) {
     L->wide = 1;
     L->nsplit = (int)split; L->kslice = (depth + split - 1) / split;
     L->fused_state = fold_forms_state(cfg.b, L->nparts);
@@ -377,11 +380,12 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
 }
 
 // A configuration of the fp32 path or of the 128 x 128 tiles whose stored strips fit the array of fastclip_step_static fits it
-// whole, so that every such configuration is taken there, and with the same layout whichever entry point runs it.  What the step
-// has in its workspace for speed alone gives way in this order: splits as far as their partial results do not fit (a few per
-// cent mostly, at worst a quarter: 1000 of 8000 fp32 pairs at width 64 take 227 us, 177 with its two splits; 2600 of 2600 at width
-// 512 keep their single pass and take 577, with three splits 537, without the single pass 1460), then, where the strips alone leave less than the partial sums take (the last 5 % below the
-// array's size), the fp32 path's partial sums and single pass, at two to three times the time.
+// whole, so that every such configuration is taken there, and with the same layout whichever entry point runs it.  What the
+// step has in its workspace for speed alone gives way in this order: splits as far as their partial results do not fit (a few
+// per cent mostly, at worst a quarter: 1000 of 8000 fp32 pairs at width 64 take 227 us, 177 with two splits; 2600 of 2600 at
+// width 512 keep their single pass and take 577, with three splits 537, without the single pass 1460), then, where the strips
+// alone leave less than the partial sums take (the last 5 % below the array's size), the fp32 path's partial sums and single
+// pass, at two to three times the time.
 void make_layout(const fastclip_config& cfg, Layout* L) {
   constexpr int64_t kLimit = FASTCLIP_STATIC_SCRATCH_BYTES;
   make_layout(cfg, Room{INT64_MAX, true}, L);

@@ -59,7 +59,9 @@ PLAN_RULES = [
     ("fastclip_api.hip", "    if (ns == 1 || cost < wide_cost) { split = ns; wide_cost = cost; }",
      '    if (getenv("EMU_NSPLIT") && atoi(getenv("EMU_NSPLIT")) != ns) continue;\n'
      '    if (wide_cost == 0.0 || cost < wide_cost) { split = ns; wide_cost = cost; }'),
-    ("fastclip_api.hip", "  if (rounds >= 2 && cfg.b > 384", '  if (getenv("EMU_WIDE") ? atoi(getenv("EMU_WIDE")) : rounds >= 2 && cfg.b > 384'),
+    ("fastclip_api.hip", "  if (rounds < 2 || cfg.b <= 384) return true;",
+     '  if (getenv("EMU_WIDE") ? !atoi(getenv("EMU_WIDE")) : rounds < 2 || cfg.b <= 384) return true;'),
+    ("fastclip_api.hip", "  if (wgs >= (cfg.b > 512 ? 256 : 257) &&", '  if (getenv("EMU_WIDE") || wgs >= (cfg.b > 512 ? 256 : 257) &&'),
     ("fastclip_api.hip", "L->wide_strips = tiles > 256 && tiles < 512 && 4 * cfg.b > 3 * cfg.B;",
      "L->wide_strips = " + _forced("tiles > 256 && tiles < 512 && 4 * cfg.b > 3 * cfg.B", "EMU_WIDE_STRIPS") + ";"),
     ("kernels_tiles128.hip", "const bool narrow = at64 <= 256;", "const bool narrow = " + _forced("at64 <= 256", "EMU_NARROW") + ";"),
