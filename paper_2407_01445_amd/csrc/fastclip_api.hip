@@ -379,21 +379,20 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
   L->total = at;
 }
 
-// A configuration of the fp32 path or of the 128 x 128 tiles whose stored strips fit the array of fastclip_step_static fits it
-// whole, so that every such configuration is taken there, and with the same layout whichever entry point runs it.  What the
-// step has in its workspace for speed alone gives way in this order: splits as far as their partial results do not fit (a few
-// per cent mostly, at worst a quarter: 1000 of 8000 fp32 pairs at width 64 take 227 us, 177 with two splits; 2600 of 2600 at
-// width 512 keep their single pass and take 577, with three splits 537, without the single pass 1460), then, where the strips
-// alone leave less than the partial sums take (the last 5 % below the array's size), the fp32 path's partial sums and single
-// pass, at two to three times the time.
+// A configuration of the fp32 path whose stored strips fit the array of fastclip_step_static fits it whole, so that every such
+// configuration is taken there, and with the same layout whichever entry point runs it.  What the step has in its workspace
+// for speed alone gives way in this order: splits as far as their partial results do not fit (a few per cent mostly, at worst
+// a quarter: 1000 of 8000 pairs at width 64 take 227 us, 177 with two splits; 2600 of 2600 at width 512 keep their single pass
+// and take 577, with three splits 537, without the single pass 1460), then, where the strips alone leave less than the partial
+// sums take (the last 5 % below the array's size), the partial sums and the single pass, at two to three times the time.
 void make_layout(const fastclip_config& cfg, Layout* L) {
   constexpr int64_t kLimit = FASTCLIP_STATIC_SCRATCH_BYTES;
   make_layout(cfg, Room{INT64_MAX, true}, L);
-  if ((L->bf16 && !L->t128) || (int64_t)L->total <= kLimit) return;
+  if (L->bf16 || (int64_t)L->total <= kLimit) return;
   Layout small;
   make_layout(cfg, Room{0, true}, &small);
   if ((int64_t)small.total <= kLimit) {
-    // beside the partial results a split plan of the fp32 path has an arrival counter for each of its at most 1024 tiles
+    // beside the partial results a split plan has an arrival counter for each of its at most 1024 tiles
     make_layout(cfg, Room{kLimit - (int64_t)small.total - 4096, true}, L);
     if ((int64_t)L->total > kLimit) *L = small;
     return;
@@ -533,7 +532,7 @@ fastclip_status fastclip_step_static(const fastclip_config* cfg, const fastclip_
   if (st != FASTCLIP_OK) return st;
   fc::Layout L;
   fc::make_layout(*cfg, &L);
-  // gathered state on the 256 x 256 tiles for the time they take, where the small ones would fit the array
+  // the small tiles without partial results, also for gathered state that is on the 256 x 256 tiles for the time they take
   if (L.total > (size_t)FASTCLIP_STATIC_SCRATCH_BYTES) fc::make_layout(*cfg, fc::Room{0, true}, &L);
   if (L.total > (size_t)FASTCLIP_STATIC_SCRATCH_BYTES) return FASTCLIP_ERR_WORKSPACE;
   void* ws = nullptr;

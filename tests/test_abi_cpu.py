@@ -156,6 +156,14 @@ def test_gathered_state_takes_the_tiles_that_take_less_time():
         assert tile(**shape) == tile(fc.TILES_128, **shape) == 256, shape
 
 
+def test_small_tile_plan_does_not_depend_on_the_static_array():
+    """Splits whose partial results take the workspace over the 64 MiB of fastclip_step_static's array: only that entry point
+    does without them."""
+    cfg = good_cfg(B=2048, b=2048, off=0, d=2264, N=5000)
+    assert fc.fastclip_workspace_bytes(cfg) > fc.STATIC_SCRATCH_BYTES
+    assert fc.fastclip_describe(cfg)["tile"] == 128 and fc.fastclip_describe(cfg)["nsplit"] > 1
+
+
 def test_wide_rows_leave_the_one_kernel_contraction():
     """Output tiles of 128 x 64 for which one round of workgroups is not enough: the contraction runs on 128 x 128 tiles behind
     the fold (with the state phase in the fold for few anchors, and its own split of the column range)."""

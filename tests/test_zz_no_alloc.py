@@ -72,11 +72,13 @@ def test_static_scratch_takes_what_fits_without_the_extras(shape, version):
     same_bits(plain, static)
 
 
-def test_static_scratch_takes_gathered_wide_rows():
-    """A step with gathered state and wide rows runs on the large tiles, whose partial results do not fit the array; on the small
-    ones it does, and the outputs agree up to rounding: the weights of the contraction are rounded to bf16 on either path
-    (gradients within the 2e-2 of the bf16 path), sums of 4096 positive numbers are added up in fp32 (4096 x 2^-24)."""
-    B, b, off, d, N = 4096, 1024, 1024, 2048, 6000
+@pytest.mark.parametrize("shape,gathered", [((4096, 1024, 1024, 2048), True), ((2048, 2048, 0, 2264), False)])
+def test_static_scratch_takes_small_tiles_without_splits(shape, gathered):
+    """A step with gathered state and wide rows runs on the large tiles, one on the small tiles with many splits of the
+    contraction, and the partial results of either do not fit the array; on the small tiles without splits they do, and the
+    outputs agree up to rounding: the weights of the contraction are rounded to bf16 on either path (gradients within the
+    2e-2 of the bf16 path), sums of 4096 positive numbers are added up in fp32 (4096 x 2^-24)."""
+    (B, b, off, d), N = shape, 6000
     rng = np.random.default_rng(21)
     img, txt = make_embeddings(22, B, d, 0.5, "bf16")
     idx = draw_indices(23, b, N)
@@ -85,7 +87,7 @@ def test_static_scratch_takes_gathered_wide_rows():
     runs = []
     for static in (False, True):
         g = GpuStep(B=B, b=b, off=off, d=d, N=N, dtype="bf16", version=fc.V3, eps=1e-6, rho=6.5, tau=0.07, u_img0=u0i, u_txt0=u0t,
-                    gathered=glob, tiles=None)
+                    gathered=glob if gathered else None, tiles=None)
         g.set_inputs(img, txt, idx)
         assert fc.fastclip_workspace_bytes(g.config(0.6)) > fc.STATIC_SCRATCH_BYTES
         if static:
