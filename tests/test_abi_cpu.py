@@ -152,7 +152,7 @@ def test_gathered_state_takes_the_tiles_that_take_less_time():
                   dict(B=1024, b=512, d=4096), dict(B=3000, b=700, d=2048)):
         assert tile(**shape) == tile(fc.TILES_128, **shape) == 128 and tile(fc.TILES_256, **shape) == 256, shape
     for shape in (dict(B=4096, b=1024, d=1024), dict(B=4096, b=1024, d=4096), dict(B=8192, b=512, d=1280),
-                  dict(B=16384, b=256, d=2048)):
+                  dict(B=16384, b=256, d=2048), dict(B=4096, b=1024, d=1376), dict(B=2432, b=1216, d=2376)):
         assert tile(**shape) == tile(fc.TILES_128, **shape) == 256, shape
 
 
