@@ -204,13 +204,14 @@ static bool plan_t128(const fastclip_config& cfg, const Room& room, Layout* L) {
   //  - with one split and a few workgroups over one per compute unit, two on some: where the kernel above has two rounds, and
   //    below 384 where the local anchors are a small part of the batch,
   //  - with an odd number of workgroups (over 1 split) in a column of tiles: they go to the XCDs in turn, and then every L2
-  //    sees the whole of the strips.
+  //    sees the whole of the strips; not where most of the batch is local, which doubles the depth above (1896 of 1896 at 640,
+  //    3 splits of 15 rows of tiles: 80 / 71).
   // Step times, above / wide, us.  One round: 1000 of 1000 at 1024: 37 / 42, 1024 of 4096 at 1024: 67 / 70, 640 of 5120 at
   // 1280: 74 / 94.  Two: 1000 of 1000 at 1280: 54 / 48, 1536 of 1536 at 1024: 75 / 65, 2048 of 2048 at 768: 82 / 69 and at 1024
   // (256 workgroups): 89 / 86, 1024 of 4096 at 2048: 122 / 105.  Four: 2048 of 2048 at 2048: 170 / 115.  Excepted, in this order:
-  // 320 of 3300 at 4096: 98 / 102, 1408 of 1408 at 1280 (220): 67 / 70; 1435 of 1435 at 1288 (264): 91 / 96, 640 of 5120 at
+  // 320 of 3300 at 4096: 98 / 102, 411 of 2055 at 2104: 65 / 70, 1408 of 1408 at 1280 (220): 67 / 70; 1435 of 1435 at 1288 (264): 91 / 96, 640 of 5120 at
   // 4096 (320): 187 / 205; 1344 of 1546 at 736 (3 splits, 11 rows of tiles): 62 / 67, 800 of 4096 at 1536 (3, 7): 100 / 106.
-  if (rounds < 2 || cfg.b <= 384) return true;
+  if (rounds < 2 || cfg.b < 448) return true;
   // Its depth in 32-deep stages goes over `split` workgroups per output tile.  Time in stages of a workgroup that has its
   // compute unit to itself: a second one there stretches both by 1.45, beyond 512 they run in rounds; a tile's start and end
   // cost 4; the finalize kernel 5 + 0.42 per MiB of partial results it reads.
@@ -228,16 +229,18 @@ static bool plan_t128(const fastclip_config& cfg, const Room& room, Layout* L) {
   }
   const int64_t rows_of_tiles = (cfg.b + 127) / 128, wgs = wide_tiles * split;
   const bool some_have_two = split == 1 && wgs > 256 && (rounds == 2 || (wgs < 384 && cfg.B > cfg.b + 640));
-  const bool no_shared_l2 = split > 1 && (split * rows_of_tiles) % 2;
+  const bool no_shared_l2 = split > 1 && (split * rows_of_tiles) % 2 && 10 * cfg.b < 9 * cfg.B;
   if (wgs >= (cfg.b > 512 ? 256 : 257) && !some_have_two && !no_shared_l2) {
     L->wide = 1;
     L->nsplit = (int)split; L->kslice = (depth + split - 1) / split;
     L->fused_state = fold_forms_state(cfg.b, L->nparts);
-    // strips of one workgroup per compute unit are two bare rounds just above 256 tiles: 1536 of 1536 at 1024: 25.2 us against 23.4
-    // with two per compute unit, 1800 of 1800 at 512: steps of 64.1 and 62.3.  With few anchor tiles (768 of 4096, 384 tiles) and at
-    // 512 tiles they are the faster ones all the same (96.1 against 100.8 at 2048).
+    // Strips of one workgroup per compute unit are two bare rounds just above 256 tiles, and with an odd number of contrast tiles
+    // the XCDs share no panels either.  Those / two workgroups per compute unit, us: strips of 1536 of 1536 at 1024 25.2 / 23.4,
+    // of 960 of 2880 at 1440 (23 contrast tiles) 41 / 37, of 1344 of 2688 at 1120 (21) 37 / 32; steps of 1800 of 1800 at 512
+    // 64.1 / 62.3.  With few anchors (768 of 4096, 384 tiles) and at 512 tiles the former are the faster ones all the same
+    // (96.1 / 100.8 at 2048).
     const int64_t tiles = 2 * ((cfg.b + 127) / 128) * L->nparts;
-    L->wide_strips = tiles > 256 && tiles < 512 && 4 * cfg.b > 3 * cfg.B;
+    L->wide_strips = tiles > 256 && tiles < 512 && (4 * cfg.b > 3 * cfg.B || L->nparts % 2);
   }
   return true;
 }

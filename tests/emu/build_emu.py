@@ -59,11 +59,11 @@ PLAN_RULES = [
     ("fastclip_api.hip", "    if (ns == 1 || cost < wide_cost) { split = ns; wide_cost = cost; }",
      '    if (getenv("EMU_NSPLIT") && atoi(getenv("EMU_NSPLIT")) != ns) continue;\n'
      '    if (wide_cost == 0.0 || cost < wide_cost) { split = ns; wide_cost = cost; }'),
-    ("fastclip_api.hip", "  if (rounds < 2 || cfg.b <= 384) return true;",
-     '  if (getenv("EMU_WIDE") ? !atoi(getenv("EMU_WIDE")) : rounds < 2 || cfg.b <= 384) return true;'),
+    ("fastclip_api.hip", "  if (rounds < 2 || cfg.b < 448) return true;",
+     '  if (getenv("EMU_WIDE") ? !atoi(getenv("EMU_WIDE")) : rounds < 2 || cfg.b < 448) return true;'),
     ("fastclip_api.hip", "  if (wgs >= (cfg.b > 512 ? 256 : 257) &&", '  if (getenv("EMU_WIDE") || wgs >= (cfg.b > 512 ? 256 : 257) &&'),
-    ("fastclip_api.hip", "L->wide_strips = tiles > 256 && tiles < 512 && 4 * cfg.b > 3 * cfg.B;",
-     "L->wide_strips = " + _forced("tiles > 256 && tiles < 512 && 4 * cfg.b > 3 * cfg.B", "EMU_WIDE_STRIPS") + ";"),
+    ("fastclip_api.hip", "L->wide_strips = tiles > 256 && tiles < 512 && (4 * cfg.b > 3 * cfg.B || L->nparts % 2);",
+     "L->wide_strips = " + _forced("tiles > 256 && tiles < 512 && (4 * cfg.b > 3 * cfg.B || L->nparts % 2)", "EMU_WIDE_STRIPS") + ";"),
     ("kernels_tiles128.hip", "const bool narrow = at64 <= 256;", "const bool narrow = " + _forced("at64 <= 256", "EMU_NARROW") + ";"),
     # fp32 path: tile sizes, plain loops, what is left of a plan that has to fit the static array
     ("fastclip_api.hip", "((cfg.B + 63) / 64) >= 256 ? 64 : 32;", "((cfg.B + 63) / 64) >= " + _forced("256", "EMU_F32_TILES") + " ? 64 : 32;"),

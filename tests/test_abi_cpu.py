@@ -179,6 +179,9 @@ def test_wide_rows_leave_the_one_kernel_contraction():
                   dict(B=2523, b=553, d=4096), dict(B=1546, b=1344, d=736)):
         p = plan(**shape)
         assert p["nsplit"] == 1 and not p["fused_state"], (shape, p)
+    assert plan(B=2200, b=440, d=2104)["nsplit"] == 1 and plan(B=2200, b=460, d=2104)["nsplit"] == 3
+    # an odd number of them per column, but nearly all of the batch local
+    assert plan(B=1896, b=1896, d=640)["nsplit"] == 3 and plan(B=2048, b=1896, d=640)["nsplit"] == 3
 
 
 def test_plans_are_sane_over_a_sweep_of_shapes():
