@@ -202,15 +202,16 @@ static bool plan_t128(const fastclip_config& cfg, const Room& room, Layout* L) {
   // It is taken where the kernel above would need a second round of workgroups, except
   //  - with few local anchors (the fold saves little) or fewer than one workgroup per compute unit,
   //  - with one split and a few workgroups over one per compute unit, two on some: where the kernel above has two rounds, and
-  //    below 384 where the local anchors are a small part of the batch,
+  //    below 384 workgroups where the local anchors are a small part of the batch,
   //  - with an odd number of workgroups (over 1 split) in a column of tiles: they go to the XCDs in turn, and then every L2
   //    sees the whole of the strips; not where most of the batch is local, which doubles the depth above (1896 of 1896 at 640,
   //    3 splits of 15 rows of tiles: 80 / 71).
   // Step times, above / wide, us.  One round: 1000 of 1000 at 1024: 37 / 42, 1024 of 4096 at 1024: 67 / 70, 640 of 5120 at
   // 1280: 74 / 94.  Two: 1000 of 1000 at 1280: 54 / 48, 1536 of 1536 at 1024: 75 / 65, 2048 of 2048 at 768: 82 / 69 and at 1024
   // (256 workgroups): 89 / 86, 1024 of 4096 at 2048: 122 / 105.  Four: 2048 of 2048 at 2048: 170 / 115.  Excepted, in this order:
-  // 320 of 3300 at 4096: 98 / 102, 411 of 2055 at 2104: 65 / 70, 1408 of 1408 at 1280 (220): 67 / 70; 1435 of 1435 at 1288 (264): 91 / 96, 640 of 5120 at
-  // 4096 (320): 187 / 205; 1344 of 1546 at 736 (3 splits, 11 rows of tiles): 62 / 67, 800 of 4096 at 1536 (3, 7): 100 / 106.
+  // 320 of 3300 at 4096: 98 / 102, 411 of 2055 at 2104: 65 / 70, 1408 of 1408 at 1280 (220): 67 / 70; 1435 of 1435 at 1288 (264):
+  // 91 / 96, 640 of 5120 at 4096 (320): 187 / 205; 1344 of 1546 at 736 (3 splits, 11 rows of tiles): 62 / 67, 800 of 4096 at 1536
+  // (3, 7): 100 / 106.
   if (rounds < 2 || cfg.b < 448) return true;
   // Its depth in 32-deep stages goes over `split` workgroups per output tile.  Time in stages of a workgroup that has its
   // compute unit to itself: a second one there stretches both by 1.45, beyond 512 they run in rounds; a tile's start and end
