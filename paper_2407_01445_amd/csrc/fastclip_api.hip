@@ -187,16 +187,17 @@ static bool plan_t128(const fastclip_config& cfg, const Room& room, Layout* L) {
   }
   if (L->gathered) {
     // The 256 x 256 tiles fetch a quarter of the bytes per product, at the price of a pass over both strips (fold), partial
-    // results and their sum.  Up to 104 stages in a row the small tiles are the faster ones, small / large, us: 640 of 5120 at width
-    // 768 (61 stages) 68 / 87, 1024 of 2048 at 1024 (61) 68 / 79, 256 of 8192 at 2048 (92) 106 / 118, 768 of 4096 at 1024 (102)
-    // 91 / 93.  Beyond, the large ones: 1024 of 4096 at 1024 (106) 98 / 96, 640 of 5120 at 1024 (122) 99 / 96, 512 of 8192 at
-    // 1280 (187) 131 / 111, 1024 of 4096 at 4096 (422) 363 / 203.  With a ragged batch or width the large strip tiles take up to
-    // twice as long, the more so the fewer there are: 700 of 3000 (72 large tiles) at 4096 (238 stages) 226 / 253, 1000 of 4000
-    // (128) at 1024 (106) 96 / 140; but 1024 of 4096 (128) at 1376 (158) 140 / 131, 1216 of 2432 (100) at 2376 (220) 217 / 168.  No
-    // room for splits: none for the partial results of the large tiles either.
-    const bool whole = cfg.B % 256 == 0 && cfg.d % 64 == 0;
-    const double big_tiles = 2.0 * (double)(((cfg.b + 255) / 256) * ((cfg.B + 255) / 256));
-    return room.split_bytes == 0 || in_a_row <= (whole ? 104.0 : 135.0 * (big_tiles < 128.0 ? 128.0 / big_tiles : 1.0));
+    // results and their sum.  Up to 104 stages in a row the small tiles are the faster ones, small / large, us: 640 of 5120 at
+    // width 768 (61 stages) 68 / 87, 1024 of 2048 at 1024 (61) 68 / 79, 256 of 8192 at 2048 (92) 106 / 118, 768 of 4096 at 1024
+    // (102) 91 / 93.  Beyond, the large ones: 1024 of 4096 at 1024 (106) 98 / 96, 640 of 5120 at 1024 (122) 99 / 96, 512 of 8192
+    // at 1280 (187) 131 / 111, 1024 of 4096 at 4096 (422) 363 / 203.  The large strip tiles take longer, up to twice, for a ragged
+    // batch, and somewhat longer for rows that end inside a stage.  Ragged batches: 1000 of 4000 at 1024 (106) 103 / 145, 791 of
+    // 3880 at 3072 (252) 227 / 237, 702 of 4212 at 3072 (261) 233 / 242, 1135 of 2322 at 4096 (320) 285 / 275, 1000 of 4000 at 3072
+    // (317) 267 / 249.  Ragged rows: 700 of 4900 at 760 (121) 107 / 120, 768 of 5376 at 1000 (130) 128 / 133, 452 of 7969 at 1376
+    // (140) 144 / 142, 1024 of 4096 at 1376 (158) 140 / 131, 768 of 4105 at 2408 (209) 212 / 174, 997 of 2991 at 3936 (333)
+    // 303 / 205.  No room for splits: none for the partial results of the large tiles either.
+    const double limit = cfg.d % 64 ? 140.0 : (cfg.B % 256 ? 270.0 : 104.0);
+    return room.split_bytes == 0 || in_a_row <= limit;
   }
   // Contraction of kernels_wide128.hip behind the fold.
   // It is taken where the kernel above would need a second round of workgroups, except

@@ -149,10 +149,12 @@ def test_gathered_state_takes_the_tiles_that_take_less_time():
     wide rows, asked for or not; a ragged batch stays on the small ones for longer."""
     tile = lambda flags=0, **kw: fc.fastclip_describe(good_cfg(off=0, N=9000, flags=flags | fc.GATHERED_STATE, **kw))["tile"]
     for shape in (dict(B=5120, b=640, d=512), dict(B=2048, b=1024, d=1024), dict(B=8192, b=256, d=2048),
-                  dict(B=1024, b=512, d=4096), dict(B=3000, b=700, d=2048)):
+                  dict(B=1024, b=512, d=4096), dict(B=3000, b=700, d=2048), dict(B=3880, b=791, d=3072),
+                  dict(B=4000, b=1000, d=1024), dict(B=4900, b=700, d=760)):
         assert tile(**shape) == tile(fc.TILES_128, **shape) == 128 and tile(fc.TILES_256, **shape) == 256, shape
     for shape in (dict(B=4096, b=1024, d=1024), dict(B=4096, b=1024, d=4096), dict(B=8192, b=512, d=1280),
-                  dict(B=16384, b=256, d=2048), dict(B=4096, b=1024, d=1376), dict(B=2432, b=1216, d=2376)):
+                  dict(B=16384, b=256, d=2048), dict(B=4096, b=1024, d=1376), dict(B=2432, b=1216, d=2376),
+                  dict(B=4000, b=1000, d=3072)):
         assert tile(**shape) == tile(fc.TILES_128, **shape) == 256, shape
 
 
