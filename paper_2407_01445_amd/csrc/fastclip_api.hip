@@ -205,8 +205,9 @@ static bool plan_t128(const fastclip_config& cfg, const Room& room, Layout* L) {
   //  - with one split and a few workgroups over one per compute unit, two on some: where the kernel above has two rounds, and
   //    below 384 workgroups where the local anchors are a small part of the batch,
   //  - with an odd number of workgroups (over 1 split) in a column of tiles: they go to the XCDs in turn, and then every L2
-  //    sees the whole of the strips; not where most of the batch is local, which doubles the depth above (1896 of 1896 at 640,
-  //    3 splits of 15 rows of tiles: 80 / 71).
+  //    sees the whole of the strips; not where most of the batch is local, which doubles the depth above, and the kernel above
+  //    would have two rounds of its 128-row tiles (1896 of 1896 at 640, 3 splits of 15 rows of tiles: 80 / 71; but with two of
+  //    64-row tiles 1344 of 1344 at 768, 11 rows: 51 / 55).
   // Step times, above / wide, us.  One round: 1000 of 1000 at 1024: 37 / 42, 1024 of 4096 at 1024: 67 / 70, 640 of 5120 at
   // 1280: 74 / 94.  Two: 1000 of 1000 at 1280: 54 / 48, 1536 of 1536 at 1024: 75 / 65, 2048 of 2048 at 768: 82 / 69 and at 1024
   // (256 workgroups): 89 / 86, 1024 of 4096 at 2048: 122 / 105.  Four: 2048 of 2048 at 2048: 170 / 115.  Excepted, in this order:
@@ -231,7 +232,7 @@ static bool plan_t128(const fastclip_config& cfg, const Room& room, Layout* L) {
   }
   const int64_t rows_of_tiles = (cfg.b + 127) / 128, wgs = wide_tiles * split;
   const bool some_have_two = split == 1 && wgs > 256 && (rounds == 2 || (wgs < 384 && cfg.B > cfg.b + 640));
-  const bool no_shared_l2 = split > 1 && (split * rows_of_tiles) % 2 && 10 * cfg.b < 9 * cfg.B;
+  const bool no_shared_l2 = split > 1 && (split * rows_of_tiles) % 2 && (L->out_rows == 64 || 10 * cfg.b < 9 * cfg.B);
   if (wgs >= (cfg.b > 512 ? 256 : 257) && !some_have_two && !no_shared_l2) {
     L->wide = 1;
     L->nsplit = (int)split; L->kslice = (depth + split - 1) / split;

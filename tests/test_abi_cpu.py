@@ -178,7 +178,7 @@ def test_wide_rows_leave_the_one_kernel_contraction():
         assert plan(**shape)["fused_state"] == 1 and plan(**shape)["nsplit"] == 1
     # exceptions: few anchors; few workgroups; slightly more than one per compute unit; an odd number of them per column
     for shape in (dict(B=3300, b=320, d=3072), dict(B=1408, b=1408, d=1280), dict(B=1435, b=1435, d=1288),
-                  dict(B=2523, b=553, d=4096), dict(B=1546, b=1344, d=736)):
+                  dict(B=2523, b=553, d=4096), dict(B=1546, b=1344, d=736), dict(B=1344, b=1344, d=768)):
         p = plan(**shape)
         assert p["nsplit"] == 1 and not p["fused_state"], (shape, p)
     assert plan(B=2200, b=440, d=2104)["nsplit"] == 1 and plan(B=2200, b=460, d=2104)["nsplit"] == 3
