@@ -202,18 +202,24 @@ static bool plan_t128(const fastclip_config& cfg, const Room& room, Layout* L) {
   // Contraction of kernels_wide128.hip behind the fold.
   // It is taken where the kernel above would need a second round of workgroups, except
   //  - with few local anchors (the fold saves little) or fewer than one workgroup per compute unit,
-  //  - with one split and a few workgroups over one per compute unit, two on some: where the kernel above has two rounds, and
-  //    below 384 workgroups where the local anchors are a small part of the batch,
+  //  - with a few workgroups over one per compute unit, two on some.  One split: where the kernel above has two rounds, and below
+  //    384 workgroups with fewer than eight rows of tiles, or an odd number of them and, the more rows the more, contrasts that
+  //    are not local.  More splits: below 416 workgroups with up to five rows of tiles, below 304 with up to seven,
   //  - with an odd number of workgroups (over 1 split) in a column of tiles: they go to the XCDs in turn, and then every L2
   //    sees the whole of the strips; not where most of the batch is local, which doubles the depth above, and the kernel above
   //    would have two rounds of its 128-row tiles (1896 of 1896 at 640, 3 splits of 15 rows of tiles: 80 / 71; but with two of
   //    64-row tiles 1344 of 1344 at 768, 11 rows: 51 / 55).
   // Step times, above / wide, us.  One round: 1000 of 1000 at 1024: 37 / 42, 1024 of 4096 at 1024: 67 / 70, 640 of 5120 at
-  // 1280: 74 / 94.  Two: 1000 of 1000 at 1280: 54 / 48, 1536 of 1536 at 1024: 75 / 65, 2048 of 2048 at 768: 82 / 69 and at 1024
-  // (256 workgroups): 89 / 86, 1024 of 4096 at 2048: 122 / 105.  Four: 2048 of 2048 at 2048: 170 / 115.  Excepted, in this order:
-  // 320 of 3300 at 4096: 98 / 102, 411 of 2055 at 2104: 65 / 70, 1408 of 1408 at 1280 (220): 67 / 70; 1435 of 1435 at 1288 (264):
-  // 91 / 96, 640 of 5120 at 4096 (320): 187 / 205; 1344 of 1546 at 736 (3 splits, 11 rows of tiles): 62 / 67, 800 of 4096 at 1536
-  // (3, 7): 100 / 106.
+  // 1280: 74 / 94.  Two: 1000 of 1000 at 1280: 54 / 48, 1536 of 1536 at 1024: 75 / 65, 2048 of 2048 at 768: 82 / 69 and at
+  // 1024 (256 workgroups): 89 / 86, 1024 of 4096 at 2048: 122 / 105.  Four: 2048 of 2048 at 2048: 170 / 115.  Excepted, in
+  // this order: 320 of 3300 at 4096: 98 / 102, 411 of 2055 at 2104: 65 / 70, 1408 of 1408 at 1280 (220): 67 / 70; 1435 of 1435
+  // at 1288 (264): 91 / 96, 640 of 5120 at 4096 (320, 5 rows): 187 / 205, 576 of 576 at 4096 (320, 5) 75 / 89, 768 of 768 at
+  // 3072 (288, 6) 75 / 82, 832 of 2496 at 2560 (280, 7) 130 / 142, 1137 of 2241 at 2560 (360, 9) 140 / 154, 1084 of 1164 at
+  // 2560 (360, 9) 93 / 96, 1372 of 2010 at 1536 (264, 11) 106 / 113 (but 900 of 3600 at 2560 (320, 8) 166 / 154, 1212 of 1212
+  // at 2048 (320, 10) 87 / 80, 1344 of 1344 at 1536 (264, 11) 89 / 82, 1383 of 1630 at 1536 (264, 11) 106 / 104, 1664 of 1664
+  // at 1280 (260, 13) 112 / 94), 576 of 1092 at 2264 (2 splits, 360, 5) 63 / 75, 640 of 2453 at 2560 (2, 400, 5) 83 / 87, 690
+  // of 1428 at 1472 (2, 288, 6) 50 / 55 (but 700 of 2800 at 2048 (2, 384, 6) 98 / 91, 512 of 3584 at 2560 (3, 480, 4) 91 /
+  // 89); 1344 of 1546 at 736 (3 splits, 11 rows of tiles): 62 / 67, 800 of 4096 at 1536 (3, 7): 100 / 106.
   if (rounds < 2 || cfg.b < 448) return true;
   // Its depth in 32-deep stages goes over `split` workgroups per output tile.  Time in stages of a workgroup that has its
   // compute unit to itself: a second one there stretches both by 1.45, beyond 512 they run in rounds; a tile's start and end
@@ -231,7 +237,9 @@ static bool plan_t128(const fastclip_config& cfg, const Room& room, Layout* L) {
     if (ns == 1 || cost < wide_cost) { split = ns; wide_cost = cost; }
   }
   const int64_t rows_of_tiles = (cfg.b + 127) / 128, wgs = wide_tiles * split;
-  const bool some_have_two = split == 1 && wgs > 256 && (rounds == 2 || (wgs < 384 && cfg.B > cfg.b + 640));
+  const bool few_rows = rows_of_tiles < 8 || (rows_of_tiles % 2 && cfg.B > cfg.b + 64 + 192 * (rows_of_tiles - 9));
+  const bool some_have_two = wgs > 256 && (split == 1 ? rounds == 2 || (wgs < 384 && few_rows)
+                                                      : wgs < (rows_of_tiles < 6 ? 416 : (rows_of_tiles < 8 ? 304 : 0)));
   const bool no_shared_l2 = split > 1 && (split * rows_of_tiles) % 2 && (L->out_rows == 64 || 10 * cfg.b < 9 * cfg.B);
   if (wgs >= (cfg.b > 512 ? 256 : 257) && !some_have_two && !no_shared_l2) {
     L->wide = 1;

@@ -174,14 +174,16 @@ def test_wide_rows_leave_the_one_kernel_contraction():
     assert one_round["tile"] == 128 and one_round["nsplit"] == 1
     wide = plan(B=1536, b=1536, d=1024)
     assert wide["tile"] == 128 and wide["nsplit"] == 2 and not wide["fused_state"]
-    for shape in (dict(B=520, b=520, d=3400), dict(B=700, b=520, d=3400)):   # more anchors than the contraction has room for
+    for shape in (dict(B=900, b=900, d=2072), dict(B=1100, b=900, d=2072), dict(B=1060, b=1060, d=2560)):   # more anchors than the contraction has room for
         assert plan(**shape)["fused_state"] == 1 and plan(**shape)["nsplit"] == 1
     # exceptions: few anchors; few workgroups; slightly more than one per compute unit; an odd number of them per column
     for shape in (dict(B=3300, b=320, d=3072), dict(B=1408, b=1408, d=1280), dict(B=1435, b=1435, d=1288),
-                  dict(B=2523, b=553, d=4096), dict(B=1546, b=1344, d=736), dict(B=1344, b=1344, d=768)):
+                  dict(B=2523, b=553, d=4096), dict(B=1546, b=1344, d=736), dict(B=1344, b=1344, d=768),
+                  dict(B=576, b=576, d=4096), dict(B=768, b=768, d=3072), dict(B=2241, b=1137, d=2560),
+                  dict(B=1092, b=576, d=2264), dict(B=1428, b=690, d=1472)):
         p = plan(**shape)
         assert p["nsplit"] == 1 and not p["fused_state"], (shape, p)
-    assert plan(B=2200, b=440, d=2104)["nsplit"] == 1 and plan(B=2200, b=460, d=2104)["nsplit"] == 3
+    assert plan(B=3584, b=440, d=2560)["nsplit"] == 1 and plan(B=3584, b=512, d=2560)["nsplit"] == 3
     # an odd number of them per column, but nearly all of the batch local
     assert plan(B=1896, b=1896, d=640)["nsplit"] == 3 and plan(B=2048, b=1896, d=640)["nsplit"] == 3
 
