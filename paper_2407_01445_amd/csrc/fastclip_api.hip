@@ -460,7 +460,6 @@ static fastclip_status run_step(const fastclip_config* cfg, const fastclip_buffe
   };
   mark(-1);
   launch_prep(c);
-  if (c.L.gathered) launch_prep_cols(c);
   mark(FASTCLIP_PHASE_PREP);
   if (c.L.t128) {
     if (c.L.wide_strips) launch_strips_wide128_bf16(c);

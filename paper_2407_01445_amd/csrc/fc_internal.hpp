@@ -117,8 +117,8 @@ struct StepCtx {
   fastclip_tau_state tau_st;
 };
 
-void launch_prep(const StepCtx& c);            // s_ii, temperature gather / broadcast
-void launch_prep_cols(const StepCtx& c);       // gathered: s_jj, temperature and coefficient of every global anchor
+void launch_prep(const StepCtx& c);            // s_ii, temperature gather / broadcast; gathered: s_jj, temperature and
+                                               // coefficient of every global anchor
 void launch_strips_f32(const StepCtx& c);      // accuracy path: exp strips + row sums
 void launch_strips_bf16(const StepCtx& c);     // MFMA path: exp strips + row sums
 void launch_state(const StepCtx& c);           // Eq. 1, coefficients, scalar partials

@@ -57,7 +57,7 @@ struct F32StripArgs {
   float* E[2];                  // [b][ldE] l of the anchors; square: E[1] is [b][ldE] l2(j, p) at [p][j]
   float* F[2];                  // gathered: c_j l(j, p) of the remote anchors j
   int64_t ldE;
-  const float* colp;            // gathered: column parameters (see k_prep_cols), else nullptr
+  const float* colp;            // gathered: column parameters (see k_prep), else nullptr
   int64_t ncol;
   float* sums;                  // nparts == 1: float [4][bstride]
   double* sums64;               // nparts > 1: [4][nparts][bstride]

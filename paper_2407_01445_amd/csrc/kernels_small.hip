@@ -49,66 +49,120 @@ __device__ inline double row_dot(const bf16_t* pi, const bf16_t* pt, int64_t d, 
   return acc;
 }
 
+// Gathered state (Alg. 1 line 8; Eqs. 3 / 5 / 7 over every global anchor; GATHERED): one wavefront per global row j, the local
+// rows as above.  Remote anchor j contributes c_j l2(j, p) txt_j to the image gradient of a local row p and c_j l1(j, p) img_j
+// to its text gradient, with l2(j, p) = exp((s_pj - s_jj) / tau2_j), l1(j, p) = exp((s_jp - s_jj) / tau1_j) and
+// c_j = kappa_j / (|B_k| |B_j-| (eps + u_j^{t+1})): the strips already form s_pj and s_jp, so all they need per column j is
+// log2(e)/tau_j, s_jj log2(e)/tau_j and c_j.  Local rows get c = 0: their u^{t+1} is only known after the state phase, and their
+// share is the local contrast-side term of what follows it (the fold, or further depth of the contraction on the small
+// tiles and on the fp32 path).  So do the padding columns beyond B.
+// What bounds it: the launch and two dependent gathers for a small batch, reading both matrices (5.7 TB/s) for a large one.
+// Local and remote rows are one launch, in which either's latency hides behind the other's; as two launches 640 of 5120 at
+// width 512 took 4.7 + 4.0 us, 1024 of 32768 at 1024 4.8 + 23.7.
 template <typename T>
-__global__ void __launch_bounds__(256) k_prep(const T* __restrict__ img, const T* __restrict__ txt, int64_t ld_img,
-                                              int64_t ld_txt, int64_t off, int64_t b, int64_t d,
-                                              const int64_t* __restrict__ idx, const float* __restrict__ tau,
-                                              const float* __restrict__ tau_img, const float* __restrict__ tau_txt,
-                                              const float* __restrict__ u_img, const float* __restrict__ u_txt,
-                                              int64_t stride, int version, float* __restrict__ diag,
-                                              float* __restrict__ tau1,
-                                              float* __restrict__ tau2, float* __restrict__ k1, float* __restrict__ k2,
-                                              float* __restrict__ uold1, float* __restrict__ uold2, unsigned* __restrict__ arrived,
-                                              int narrived) {
+struct PrepArgs {
+  const T *img, *txt;
+  int64_t ld_img, ld_txt, B, off, b, d;
+  const int64_t* idx;
+  const float *tau, *tau_img, *tau_txt, *u_img, *u_txt;
+  int64_t stride;
+  int version;
+  float *diag, *tau1, *tau2, *k1, *k2, *uold1, *uold2;
+  unsigned* arrived;
+  int narrived;
+  // gathered state
+  const float *tau_glob_img, *tau_glob_txt, *u_glob_img, *u_glob_txt;
+  float eps, bm;
+  int from_own;
+  int64_t ncol;
+  float* colp;
+};
+
+template <typename T, bool GATHERED>
+__global__ void __launch_bounds__(256) k_prep(PrepArgs<T> a) {
   const int lane = threadIdx.x & 63;
-  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < narrived; i += (int)(gridDim.x * 256)) arrived[i] = 0u;
-  if (r >= b) return;
+  const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < a.narrived; i += (int)(gridDim.x * 256)) a.arrived[i] = 0u;
+  if (w >= (GATHERED ? a.ncol : a.b)) return;
+  const int64_t j = GATHERED ? w : a.off + w, r = j - a.off;      // global row; local anchor
+  const bool local = !GATHERED || (r >= 0 && r < a.b);            // wave-uniform
   float t1 = 0.f, t2 = 0.f, u1 = 0.f, u2 = 0.f;
-  if (lane == 0) {        // issue the gathers by dataset index before the dot product so that the latencies overlap:
-    const int64_t n = idx[r] * stride;   // the temperatures, and u^t of Eq. 1 for the state phase (nothing writes u
-    u1 = u_img[n];                       // before that phase)
-    u2 = u_txt[n];
-    if (version == FASTCLIP_V2) {
-      t1 = tau_img[n];
-      t2 = tau_txt[n];
+  if (lane == 0 && (local || j < a.B)) {
+    // issue the gathers before the dot product so that the latencies overlap: by dataset index the temperatures, and u^t of
+    // Eq. 1 for the state phase (nothing writes u before that phase); of a remote anchor what its worker has sent
+    const int64_t n = local ? a.idx[r] * a.stride : j;
+    u1 = (local ? a.u_img : a.u_glob_img)[n];
+    u2 = (local ? a.u_txt : a.u_glob_txt)[n];
+    if (a.version == FASTCLIP_V2) {
+      t1 = (local ? a.tau_img : a.tau_glob_img)[n];
+      t2 = (local ? a.tau_txt : a.tau_glob_txt)[n];
     } else {
-      t1 = t2 = tau[0];
+      t1 = t2 = a.tau[0];
     }
   }
-  const double acc = wave_sum(row_dot(img + (off + r) * ld_img, txt + (off + r) * ld_txt, d, lane));
-  if (lane == 0) {
-    diag[r] = (float)acc;
-    tau1[r] = t1;
-    tau2[r] = t2;
-    k1[r] = kLog2e / t1;
-    k2[r] = kLog2e / t2;
-    uold1[r] = u1;
-    uold2[r] = u2;
+  double s_jj = 0.0;
+  if (!GATHERED || j < a.B) s_jj = wave_sum(row_dot(a.img + j * a.ld_img, a.txt + j * a.ld_txt, a.d, lane));
+  if (lane != 0) return;
+  float k1 = 0.f, k2 = 0.f;
+  if (local || j < a.B) { k1 = kLog2e / t1; k2 = kLog2e / t2; }
+  if (local) {
+    a.diag[r] = (float)s_jj;
+    a.tau1[r] = t1;
+    a.tau2[r] = t2;
+    a.k1[r] = k1;
+    a.k2[r] = k2;
+    a.uold1[r] = u1;
+    a.uold2[r] = u2;
+  }
+  if constexpr (GATHERED) {
+    float c1 = 0.f, c2 = 0.f;
+    if (local) k1 = k2 = 0.f;
+    else if (j < a.B) {
+      c1 = 1.0f / (a.bm * (a.eps + u1));
+      c2 = 1.0f / (a.bm * (a.eps + u2));
+      if (a.version == FASTCLIP_V0) { c1 /= t1; c2 /= t2; }
+    }
+    // column of row j: its number, or (from_own) counted from the worker's own rows on
+    const int64_t col = !a.from_own || j >= a.B ? j : (j >= a.off ? j - a.off : j - a.off + a.B);
+    const int64_t ntile = a.ncol >> 8, tile = col >> 8, in = col & 255;
+    float* p0 = a.colp + ((0 * ntile + tile) * 4) * 256 + in;   // side 0: text anchors (tau_2, u_2)
+    float* p1 = a.colp + ((1 * ntile + tile) * 4) * 256 + in;   // side 1: image anchors (tau_1, u_1)
+    p0[0] = k2; p0[256] = (float)(s_jj * (double)k2); p0[512] = c2; p0[768] = 0.f;
+    p1[0] = k1; p1[256] = (float)(s_jj * (double)k1); p1[512] = c1; p1[768] = 0.f;
   }
 }
 
-void launch_prep(const StepCtx& c) {
+template <typename T>
+static void launch_prep_rows(const StepCtx& c) {
   const Layout& L = c.L;
-  float* diag = (float*)(c.ws + L.diag);
-  float* tau1 = (float*)(c.ws + L.tau1);
-  float* tau2 = (float*)(c.ws + L.tau2);
-  float* k1 = (float*)(c.ws + L.k1);
-  float* k2 = (float*)(c.ws + L.k2);
-  float* uold1 = (float*)(c.ws + L.uold1);
-  float* uold2 = (float*)(c.ws + L.uold2);
-  unsigned* arrived = (unsigned*)(c.ws + L.arrived);
-  dim3 grid((unsigned)((L.b + 3) / 4)), block(256);
-  if (L.bf16)
-    hipLaunchKernelGGL(k_prep<bf16_t>, grid, block, 0, c.s, (const bf16_t*)c.buf.img_glob, (const bf16_t*)c.buf.txt_glob,
-                       c.cfg.ld_img, c.cfg.ld_txt, L.off, L.b, L.d, c.buf.idx, c.buf.tau, c.buf.tau_img,
-                       c.buf.tau_txt, c.buf.u_img, c.buf.u_txt, c.cfg.state_stride, c.cfg.version, diag, tau1, tau2, k1, k2,
-                       uold1, uold2, arrived, L.narrived);
-  else
-    hipLaunchKernelGGL(k_prep<float>, grid, block, 0, c.s, (const float*)c.buf.img_glob, (const float*)c.buf.txt_glob,
-                       c.cfg.ld_img, c.cfg.ld_txt, L.off, L.b, L.d, c.buf.idx, c.buf.tau, c.buf.tau_img,
-                       c.buf.tau_txt, c.buf.u_img, c.buf.u_txt, c.cfg.state_stride, c.cfg.version, diag, tau1, tau2, k1, k2,
-                       uold1, uold2, arrived, L.narrived);
+  PrepArgs<T> a;
+  memset(&a, 0, sizeof(a));
+  a.img = (const T*)c.buf.img_glob; a.txt = (const T*)c.buf.txt_glob;
+  a.ld_img = c.cfg.ld_img; a.ld_txt = c.cfg.ld_txt; a.B = L.B; a.off = L.off; a.b = L.b; a.d = L.d;
+  a.idx = c.buf.idx; a.tau = c.buf.tau; a.tau_img = c.buf.tau_img; a.tau_txt = c.buf.tau_txt;
+  a.u_img = c.buf.u_img; a.u_txt = c.buf.u_txt; a.stride = c.cfg.state_stride; a.version = c.cfg.version;
+  a.diag = (float*)(c.ws + L.diag);
+  a.tau1 = (float*)(c.ws + L.tau1); a.tau2 = (float*)(c.ws + L.tau2);
+  a.k1 = (float*)(c.ws + L.k1); a.k2 = (float*)(c.ws + L.k2);
+  a.uold1 = (float*)(c.ws + L.uold1); a.uold2 = (float*)(c.ws + L.uold2);
+  a.arrived = (unsigned*)(c.ws + L.arrived); a.narrived = L.narrived;
+  const int64_t rows = L.gathered ? L.ncol : L.b;
+  const dim3 grid((unsigned)((rows + 3) / 4)), block(256);
+  if (!L.gathered) {
+    hipLaunchKernelGGL((k_prep<T, false>), grid, block, 0, c.s, a);
+    return;
+  }
+  a.tau_glob_img = c.buf.tau_glob_img; a.tau_glob_txt = c.buf.tau_glob_txt;
+  a.u_glob_img = c.buf.u_glob_img; a.u_glob_txt = c.buf.u_glob_txt;
+  a.eps = c.cfg.eps; a.bm = (float)L.b * (float)(L.B - 1);
+  a.from_own = L.t128; a.ncol = L.ncol;
+  a.colp = (float*)(c.ws + L.colp);
+  hipLaunchKernelGGL((k_prep<T, true>), grid, block, 0, c.s, a);
+}
+
+void launch_prep(const StepCtx& c) {
+  if (c.L.bf16) launch_prep_rows<bf16_t>(c);
+  else launch_prep_rows<float>(c);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -204,75 +258,6 @@ void launch_normalize_rows(const void* raw, int raw_bf16, int64_t ld_raw, int64_
   else if (raw_bf16) normalize_rows<bf16_t, float>(raw, ld_raw, b, d, unit, ld_unit, norm, s);
   else if (unit_bf16) normalize_rows<float, bf16_t>(raw, ld_raw, b, d, unit, ld_unit, norm, s);
   else normalize_rows<float, float>(raw, ld_raw, b, d, unit, ld_unit, norm, s);
-}
-
-// ------------------------------------------------------------------------------------------
-// Gathered state (Alg. 1 line 8; Eqs. 3 / 5 / 7 over every global anchor): one wavefront per global row j.
-// Anchor j contributes c_j l2(j, p) txt_j to the image gradient of a local row p and c_j l1(j, p) img_j to its text
-// gradient, with l2(j, p) = exp((s_pj - s_jj) / tau2_j), l1(j, p) = exp((s_jp - s_jj) / tau1_j) and
-// c_j = kappa_j / (|B_k| |B_j-| (eps + u_j^{t+1})): the strips already form s_pj and s_jp, so all they need per
-// column j is log2(e)/tau_j, s_jj log2(e)/tau_j and c_j.  Local rows get c = 0: their u^{t+1} is only known after
-// the state phase, and their share is the local contrast-side term of what follows it (the fold, or further depth of the
-// contraction on the small tiles and on the fp32 path).  So do the padding columns beyond B.
-template <typename T>
-__global__ void __launch_bounds__(256) k_prep_cols(const T* __restrict__ img, const T* __restrict__ txt, int64_t ld_img,
-                                                   int64_t ld_txt, int64_t B, int64_t ncol, int64_t off, int64_t b,
-                                                   int64_t d, const float* __restrict__ tau,
-                                                   const float* __restrict__ tau_glob_img,
-                                                   const float* __restrict__ tau_glob_txt,
-                                                   const float* __restrict__ u_glob_img,
-                                                   const float* __restrict__ u_glob_txt, int version, float eps,
-                                                   float bm, int from_own, float* __restrict__ colp) {
-  const int lane = threadIdx.x & 63;
-  const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (j >= ncol) return;
-  float k1 = 0.f, k2 = 0.f, d1 = 0.f, d2 = 0.f, c1 = 0.f, c2 = 0.f;
-  const bool remote = j < B && (j < off || j >= off + b);
-  if (remote) {                                  // wave-uniform
-    float t1 = 0.f, t2 = 0.f, u1 = 0.f, u2 = 0.f;
-    if (lane == 0) {
-      if (version == FASTCLIP_V2) { t1 = tau_glob_img[j]; t2 = tau_glob_txt[j]; }
-      else t1 = t2 = tau[0];
-      u1 = u_glob_img[j];
-      u2 = u_glob_txt[j];
-    }
-    const double s_jj = wave_sum(row_dot(img + j * ld_img, txt + j * ld_txt, d, lane));
-    if (lane == 0) {
-      k1 = kLog2e / t1;
-      k2 = kLog2e / t2;
-      d1 = (float)(s_jj * (double)k1);
-      d2 = (float)(s_jj * (double)k2);
-      c1 = 1.0f / (bm * (eps + u1));
-      c2 = 1.0f / (bm * (eps + u2));
-      if (version == FASTCLIP_V0) { c1 /= t1; c2 /= t2; }
-    }
-  }
-  if (lane == 0) {
-    // column of row j: its number, or (from_own) counted from the worker's own rows on
-    const int64_t col = !from_own || j >= B ? j : (j >= off ? j - off : j - off + B);
-    const int64_t ntile = ncol >> 8, tile = col >> 8, in = col & 255;
-    float* p0 = colp + ((0 * ntile + tile) * 4) * 256 + in;   // side 0: text anchors (tau_2, u_2)
-    float* p1 = colp + ((1 * ntile + tile) * 4) * 256 + in;   // side 1: image anchors (tau_1, u_1)
-    p0[0] = k2; p0[256] = d2; p0[512] = c2; p0[768] = 0.f;
-    p1[0] = k1; p1[256] = d1; p1[512] = c1; p1[768] = 0.f;
-  }
-}
-
-void launch_prep_cols(const StepCtx& c) {
-  const Layout& L = c.L;
-  float* colp = (float*)(c.ws + L.colp);
-  const float bm = (float)L.b * (float)(L.B - 1);
-  dim3 grid((unsigned)((L.ncol + 3) / 4)), block(256);
-  if (L.bf16)
-    hipLaunchKernelGGL(k_prep_cols<bf16_t>, grid, block, 0, c.s, (const bf16_t*)c.buf.img_glob,
-                       (const bf16_t*)c.buf.txt_glob, c.cfg.ld_img, c.cfg.ld_txt, L.B, L.ncol, L.off, L.b, L.d,
-                       c.buf.tau, c.buf.tau_glob_img, c.buf.tau_glob_txt, c.buf.u_glob_img, c.buf.u_glob_txt,
-                       c.cfg.version, c.cfg.eps, bm, L.t128, colp);
-  else
-    hipLaunchKernelGGL(k_prep_cols<float>, grid, block, 0, c.s, (const float*)c.buf.img_glob,
-                       (const float*)c.buf.txt_glob, c.cfg.ld_img, c.cfg.ld_txt, L.B, L.ncol, L.off, L.b, L.d,
-                       c.buf.tau, c.buf.tau_glob_img, c.buf.tau_glob_txt, c.buf.u_glob_img, c.buf.u_glob_txt,
-                       c.cfg.version, c.cfg.eps, bm, L.t128, colp);
 }
 
 // ------------------------------------------------------------------------------------------
