@@ -170,14 +170,16 @@ static bool plan_t128(const fastclip_config& cfg, const Room& room, Layout* L) {
       if (ns > 1 && (tiles * ns > 2048 || ns * tiles * rows * 64 * (int64_t)sizeof(float) > room.split_bytes)) break;
       const int64_t sA = (nA + ns * 8 - 1) / (ns * 8), sB = (nB + ns * 8 - 1) / (ns * 8);
       const int64_t nq = sB * 128 < cfg.b ? sB * 128 : cfg.b;
-      // the state phase inside the contraction: 64-row tiles have room for the sums of 256 local anchors beside the rows'
-      const bool fused = rows == 64 && nq <= 256 && L->nparts <= 64;
       const int64_t r = (tiles * ns + 255) / 256;
+      // The state phase inside the contraction: every workgroup adds up the partial sums of its rows and of its q's, at the 57
+      // bytes per clock of a compute unit, which takes less than a launch of its own (4.7 us) while it happens once.
+      const bool fused = r == 1 || (rows == 64 && nq <= 256 && L->nparts <= 64);
+      const double coef_us = (double)((nq + 2 * rows) * L->nparts * 4) / (57.0 * 2400.0);
       const double stages = (L->gathered ? 1.4 : 1.0) * (double)sA + (double)sB;   // a wave's, 16 deep; 1.4: with a second strip
       // us: start, coefficients, sum over the waves and end of a workgroup; a 16-deep stage of its eight waves (the load path of
       // a compute unit: 32 KiB, 48 for 128 rows or with a second strip); partial results; the state phase as a launch of its own
       const double cost = (double)r * (rows == 64 ? 8.0 + 0.27 * stages : 9.5 + 0.38 * stages) +
-                          (ns > 1 ? 2.3 + 0.1 * (double)ns : 0.0) + (fused ? 0.0 : 4.7);
+                          (ns > 1 ? 2.3 + 0.1 * (double)ns : 0.0) + (fused ? (nq > 256 || rows > 64 ? coef_us : 0.0) : 4.7);
       if (best_cost == 0.0 || cost < best_cost) {
         best_cost = cost;
         rounds = r; in_a_row = (double)r * stages;
@@ -343,10 +345,14 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
     if (L->few) L->nparts = L->nsplit = 1;
     else plan_f32(cfg, room, L);
   }
+  if (L->t128 && !L->gathered && !L->wide_strips) {
+    const int64_t rows = strips_t128_narrow(*L) ? 64 : 128, tiles = 2 * ((cfg.b + rows - 1) / rows) * L->nparts;
+    L->own_prep = (tiles + 255) / 256 * rows * cfg.d <= 200000;
+  }
   if (!L->t128) L->fused_state = L->bf16 && fold_forms_state(cfg.b, L->nparts);
-  // scalar partials: t128 without the fold leaves the terms of every anchor side
-  const bool per_anchor = L->t128 && !L->wide;
-  L->nstate_blocks = L->fused_state ? (per_anchor ? (int)(2 * cfg.b) : (int)((cfg.b + 63) / 64)) : state_blocks(cfg.b, L->nparts);
+  // scalar partials: t128 without the fold leaves those of 64 anchors of one side, in whole groups of 256 anchors
+  const int64_t out_blocks = L->t128 && !L->wide ? 8 * ((cfg.b + 255) / 256) : 0;
+  L->nstate_blocks = L->fused_state ? (int)(out_blocks ? out_blocks : (cfg.b + 63) / 64) : state_blocks(cfg.b, L->nparts);
   L->diag = take(fb); L->tau1 = take(fb); L->tau2 = take(fb); L->k1 = take(fb); L->k2 = take(fb);
   L->uold1 = take(fb); L->uold2 = take(fb);
   L->sums = take(fb * 4 * (size_t)L->nparts * (!L->bf16 && L->nparts > 1 ? 2 : 1));
@@ -459,8 +465,7 @@ static fastclip_status run_step(const fastclip_config* cfg, const fastclip_buffe
     if (phase >= 0) { (void)hipEventCreate(&ev[nev]); (void)hipEventRecord(ev[nev], c.s); phase_of[nev - 1] = phase; ++nev; }
   };
   mark(-1);
-  launch_prep(c);
-  mark(FASTCLIP_PHASE_PREP);
+  if (!c.L.own_prep) { launch_prep(c); mark(FASTCLIP_PHASE_PREP); }
   if (c.L.t128) {
     if (c.L.wide_strips) launch_strips_wide128_bf16(c);
     else launch_strips_t128_bf16(c);

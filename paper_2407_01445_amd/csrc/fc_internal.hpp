@@ -53,7 +53,7 @@ struct Layout {
   int nsplit;        // split of the contraction over its column range
   int64_t kslice;    // 32-deep stages per split (fp32 path: stages of the gradient kernel's depth)
   int nstate_blocks; // scalar partials: one per block of the state kernel, per diagonal block of the fused fold, or (t128 with
-                     // fused_state) per anchor side
+                     // fused_state) per 64 anchors and side
   int fused_state;   // 1: MFMA path, few anchors and few partial sums: the fold kernel (t128: the contraction) runs the
                      //    state phase itself
   int gathered;      // 1: contrast-side estimator over every global anchor (FASTCLIP_GATHERED_STATE and b < B)
@@ -65,6 +65,7 @@ struct Layout {
                      //    are no partial results
   int out_rows;      // t128 without wide: rows of an output tile of the contraction, 64 or 128
   int wide_strips;   // wide: the strips are k_strips_wide128_bf16
+  int own_prep;      // t128: k_strips_t128_bf16 prepares its anchors itself, k_prep is not launched
   int wide;          // t128: the contraction is k_contract_wide128_bf16 (kernels_wide128.hip) behind the fold; nsplit /
                      //    kslice count 32-deep stages
   int square;        // 1: b == B and the similarity matrix is formed once.  MFMA path: F[0] holds l2(j, p) in the
@@ -92,6 +93,12 @@ struct Layout {
                                      // directly (fp32 path)
   size_t total;
 };
+
+// Anchors of a tile of k_strips_t128_bf16: 64 where that still is one round of workgroups: more compute units, and a tile takes
+// 7.0 us instead of 8.8 (128 anchors of 1024, d = 512; steps: 24.0 -> 22.7 us, 256 of 2048 from raw rows 40.4 -> 38.4, 1024 of
+// 1024 30.7 -> 30.1), else 128: beyond one round two tiles of 64 take longer than one of 128 (3.5 us of either are its start
+// and end).
+static inline bool strips_t128_narrow(const Layout& L) { return 2 * ((L.b + 63) / 64) * (int64_t)L.nparts <= 256; }
 
 fastclip_status validate(const fastclip_config* cfg, const fastclip_buffers* bufs);
 void make_layout(const fastclip_config& cfg, Layout* L);

@@ -3,6 +3,7 @@
 #include <string.h>
 
 #include "fc_internal.hpp"
+#include "mfma_common.hpp"
 #include "state_common.hpp"
 
 namespace fc {
@@ -80,6 +81,7 @@ struct PrepArgs {
 
 template <typename T, bool GATHERED>
 __global__ void __launch_bounds__(256) k_prep(PrepArgs<T> a) {
+  warm_arguments<sizeof(PrepArgs<T>)>();
   const int lane = threadIdx.x & 63;
   const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < a.narrived; i += (int)(gridDim.x * 256)) a.arrived[i] = 0u;
@@ -406,7 +408,7 @@ __global__ void __launch_bounds__(256) k_state(StateArgs a) {
       (side ? a.c2 : a.c1)[r] = o.c;
       if (a.version == FASTCLIP_V2) (side ? a.d_tau_txt : a.d_tau_img)[r] = o.gt;
       float* g_out = side ? a.g_txt : a.g_img;
-      if (g_out) g_out[r] = se * (1.0f / a.M);
+      if (g_out) g_out[r] = se * a.inv_M;
       float* u_out = side ? a.u_new_txt : a.u_new_img;
       if (u_out) u_out[r] = o.u;
     }
@@ -440,7 +442,7 @@ StateArgs make_state_args(const StepCtx& c) {
   a.bstride = L.bstride; a.b = L.b;
   a.fused = L.fused_state;
   a.stride = c.cfg.state_stride;
-  a.M = (float)(L.B - 1); a.gamma = c.cfg.gamma; a.eps = c.cfg.eps; a.rho = c.cfg.rho;
+  a.M = (float)(L.B - 1); a.inv_M = 1.0f / a.M; a.bM = (float)L.b * a.M; a.gamma = c.cfg.gamma; a.eps = c.cfg.eps; a.rho = c.cfg.rho;
   a.tau_scale = c.cfg.tau_grad_scale; a.version = c.cfg.version;
   a.c1 = (float*)(c.ws + L.c1); a.c2 = (float*)(c.ws + L.c2); a.dcoef = (float*)(c.ws + L.dcoef);
   a.red = (double*)(c.ws + L.red);
@@ -479,7 +481,7 @@ void launch_state_phase(const fastclip_config& cfg, const fastclip_buffers& buf,
   a.idx = buf.idx; a.u_img = buf.u_img; a.u_txt = buf.u_txt;
   a.sums = sums; a.nparts = 1; a.bstride = cfg.b; a.b = cfg.b;
   a.stride = cfg.state_stride;
-  a.M = (float)(cfg.B - 1); a.gamma = cfg.gamma; a.eps = cfg.eps; a.rho = cfg.rho;
+  a.M = (float)(cfg.B - 1); a.inv_M = 1.0f / a.M; a.bM = (float)cfg.b * a.M; a.gamma = cfg.gamma; a.eps = cfg.eps; a.rho = cfg.rho;
   a.tau_scale = cfg.tau_grad_scale; a.version = cfg.version;
   a.c1 = coef; a.c2 = coef + cfg.b; a.dcoef = coef + 2 * cfg.b;
   a.red = red;

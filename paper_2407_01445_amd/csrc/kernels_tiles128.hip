@@ -43,6 +43,8 @@ __device__ __forceinline__ void wave_reads_done() {
 // consecutive rows of an operand read cover a 256-byte bank window.
 __device__ __forceinline__ int p_swz(int row) { return (row >> 1) & 7; }
 
+constexpr float kLog2e = 1.4426950408889634f;
+
 struct T128StripJob {           // one strip
   const bf16_t *X, *A;          // contrast row 0, first local anchor row
   const float* kscale;          // log2(e) / tau of the anchors
@@ -50,12 +52,21 @@ struct T128StripJob {           // one strip
   const float* colp;            // gathered state: [tile of 256 columns][4][256] column parameters
   float* sums;                  // [2][nparts][bstride]
   int ldx, lda;
+  // PREP: the side's temperatures and u by dataset index, and where they go for the state phase
+  const float *tau, *u;
+  float *tau_out, *u_out;
 };
 struct T128StripArgs {
   T128StripJob job[2];
   const float* diag;            // s_pp per local anchor
   int nCB, ldE, nparts, bstride, b, B, d;
   int first, own;               // global row of column 0; column of local anchor 0
+  // PREP
+  const int64_t* idx;
+  const float* tau_glob;        // nullptr: one temperature per sample (V2)
+  int64_t stride;
+  unsigned* arrived;            // counters of the contraction, zeroed here
+  int narrived;
 };
 
 // One workgroup per tile (AT = 128: 128 anchors against 128 contrasts of one strip), eight waves = two groups of 2 x 2 waves of
@@ -71,8 +82,15 @@ struct T128StripArgs {
 // worker, moves the local row (Eqs. 3 / 5 / 7); it goes to a second strip of the same form.  A workgroup then takes two
 // neighbouring contrast tiles one after the other and leaves one partial sum for both: with its second exponential a
 // tile is longer, and at the sizes of this path one round of workgroups does for both.
-template <int AT, bool GATHERED>
+//
+// PREP: the workgroup prepares its anchors itself and k_prep is not launched: s_ii = <a_i, x_i> from the anchor rows that pass
+// through LDS anyway and the partner rows, eight lanes per anchor and one 16-byte chunk each, summed as in k_prep (fp32 within a
+// chunk, fp64 over the chunks), and temperature and u^t by dataset index.  The partner's chunk of a step is requested a
+// step ahead and used behind the step's barrier, when everything requested before it has landed.
+template <int AT, bool GATHERED, bool PREP>
 __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
+  static_assert(!(GATHERED && PREP), "gathered state is prepared by k_prep");
+  constexpr int NP = AT / 64;                     // PREP: anchors per group of eight lanes
   constexpr int WC = AT / 64, NI = WC;            // waves across the anchors; 32-row blocks of contrasts per wave
   constexpr int kStage = kPanel + AT * kD * 2, kStep = 2 * kStage;   // a step = one stage for either group of waves
   constexpr int NL = 4 + 2 * WC;                  // wave loads per step: 4 of the contrasts, 2 or 4 of the anchors
@@ -89,9 +107,8 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
   const int ldx = J.ldx, lda = J.lda;
   const uint32_t ring_addr = lds_addr(ring);
   float total = 0.f;                              // tid < 2 AT: quantity tid / AT of anchor tid % AT
-  for (int sub = 0; sub < (GATHERED ? 2 : 1); ++sub) {
+  auto tile = [&](int sub) {
   const int c0 = GATHERED ? ct * 256 + sub * kT : ct * kT;
-  if (c0 >= B) break;
   // wave loads of a stage: 8 rows x 128 bytes each, four per wave and operand.  A row that does not exist is fetched as
   // the last one that does; what it yields is masked in the epilogue.
   uint32_t ox[NL];
@@ -110,8 +127,74 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
 #pragma unroll
   for (int tj = 0; tj < 2; ++tj) {
     const int m = a0 + wc * 64 + tj * 32 + lr;
-    kk[tj] = m < b ? J.kscale[m] : 0.f;
-    dk[tj] = m < b ? a.diag[m] : 0.f;
+    kk[tj] = !PREP && m < b ? J.kscale[m] : 0.f;
+    dk[tj] = !PREP && m < b ? a.diag[m] : 0.f;
+  }
+  // PREP: anchors 64 i + 8 wave + lane / 8 of the tile, chunk lane % 8 of every stage
+  const int prow = 8 * wave + (lane >> 3), pch = lane & 7;
+  uint32_t po[NP];
+  u32x4 partner[2][NP], mine[2][NP];              // [stage of the step][anchor]
+  double dot[NP];
+  int64_t n = 0;                                  // tid < AT: the anchor's dataset index
+  float tau = 1.f, u_old = 0.f;
+  const bool keeper = ct == 0;                    // of the workgroups that prepare these anchors the one that leaves them in memory
+  auto chunks_of = [&](int st) { return st >= S ? 0 : (tail && st == S - 1 ? tail : 8); };
+  auto fetch_partner = [&](auto edge, int step) { // a chunk that does not exist is fetched as the first one, and not used
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      int st = 2 * step + g;
+      uint32_t back = 0u;
+      if constexpr (decltype(edge)::value) {
+        back = pch < chunks_of(st) ? 0u : (uint32_t)pch * 16u;
+        st = st < S ? st : S - 1;
+      }
+#pragma unroll
+      for (int i = 0; i < NP; ++i) partner[g][i] = *(const u32x4*)((const char*)(Xm + st * kD) + (po[i] - back));
+    }
+  };
+  auto read_mine = [&](int step) {
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int i = 0; i < NP; ++i)
+        mine[g][i] = *(const u32x4*)(ring + (step & 1) * kStep + g * kStage + kPanel + (64 * i + prow) * 128 + ((pch ^ p_swz(prow)) << 4));
+  };
+  auto add_dots = [&](auto edge, int step) {
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      const bool there = !decltype(edge)::value || pch < chunks_of(2 * step + g);
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        float part = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const uint32_t x = mine[g][i][w], y = partner[g][i][w];      // (bit_cast of a vector's element takes element 0)
+          part = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, x), __builtin_bit_cast(bf16x2, y), part, false);
+        }
+        dot[i] += (double)(there ? part : 0.f);
+      }
+    }
+  };
+  auto gather = [&]() {                           // behind the index
+    if (tid < AT && a0 + tid < b) {
+      if (!a.tau_glob) tau = J.tau[n * a.stride];
+      if (keeper) u_old = J.u[n * a.stride];
+    }
+  };
+  if constexpr (PREP) {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int m = a0 + 64 * i + prow;
+      po[i] = (uint32_t)((first + own + (m < b ? m : b - 1)) * ldx) * 2u + (uint32_t)pch * 16u;
+      dot[i] = 0.0;
+    }
+    if (tid < AT && a0 + tid < b) {
+      n = a.idx[a0 + tid];
+      if (a.tau_glob) tau = a.tau_glob[0];
+    }
+    fetch_partner(std::true_type{}, 0);
+    const int wg = (strip * (int)gridDim.y + at) * (int)gridDim.x + ct, wgs = 2 * (int)gridDim.y * (int)gridDim.x;
+    for (int i = wg * 512 + tid; i < a.narrived; i += wgs * 512) a.arrived[i] = 0u;
   }
   float col = 0.f;                                // GATHERED: the tile's column parameters, k_j, d_j, c_j of 128 columns
   if (GATHERED && tid < 3 * kT)
@@ -194,6 +277,7 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
     const bool fill = s > 0 && s + 1 < steps;
     read(edge_here, s, 0, x0, y0);
     read(edge_here, s, 1, x1, y1);
+    if constexpr (PREP) read_mine(s);
     multiply(edge_next, x0, y0, fill, s + 1, 2);
     read(edge_here, s, 2, x0, y0);
     multiply(edge_next, x1, y1, fill, s + 1, 4);
@@ -205,6 +289,11 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
       FC_FENCE();
     }
     multiply(std::true_type{}, x1, y1, s + 2 < steps, s + 2, 0);
+    if constexpr (PREP) {                         // while the products run
+      add_dots(edge_here, s);
+      if (s == 0) gather();
+      if (s + 1 < steps) fetch_partner(edge_next, s + 1);
+    }
   };
   int s = 0;
   for (; s + 2 < steps; ++s) step(std::false_type{}, std::false_type{}, s);
@@ -227,9 +316,26 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
         }
   };
   if (kg) give(std::true_type{}); else give(std::false_type{});
-  float* scol = (float*)(ring + 8 * 8192 + 4096);          // [3][128]
+  float* scol = (float*)(ring + 8 * 8192 + 4096);          // GATHERED: [3][128]; PREP: [2][AT], log2(e) / tau and s_ii
   if (GATHERED && tid < 3 * kT) scol[tid] = col;
+  if constexpr (PREP) {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+#pragma unroll
+      for (int o = 1; o < 8; o <<= 1) dot[i] += __shfl_xor(dot[i], o);
+      if (pch == 0) scol[AT + 64 * i + prow] = a0 + 64 * i + prow < b ? (float)dot[i] : 0.f;
+    }
+    if (tid < AT) scol[tid] = a0 + tid < b ? kLog2e / tau : 0.f;
+    if (keeper && tid < AT && a0 + tid < b) { J.tau_out[a0 + tid] = tau; J.u_out[a0 + tid] = u_old; }
+  }
   __syncthreads();
+  if constexpr (PREP) {
+#pragma unroll
+    for (int tj = 0; tj < 2; ++tj) {
+      kk[tj] = scol[wc * 64 + tj * 32 + lr];
+      dk[tj] = scol[AT + wc * 64 + tj * 32 + lr];
+    }
+  }
   const float* other = (const float*)(ring + (wave ^ 4) * 8192);
   float (*sred)[2][AT] = (float (*)[2][AT])(ring + 8 * 8192);        // [contrasts' wave, group][quantity][anchor in the tile]: 4 KiB
   bf16_t* __restrict__ E = J.E;
@@ -308,7 +414,9 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
     total += part;
   }
   if (GATHERED) { __syncthreads(); FC_FENCE(); }
-  }
+  };
+  tile(0);
+  if (GATHERED && ct * 256 + kT < B) tile(1);
   if (tid < 2 * AT) {
     const int q = tid / AT, m = tid % AT;
     if (a0 + m < b) J.sums[((size_t)q * a.nparts + ct) * a.bstride + a0 + m] = total;
@@ -339,20 +447,28 @@ void launch_strips_t128_bf16(const StepCtx& c) {
   a.nCB = (int)(L.ldE / 16); a.ldE = (int)L.ldE; a.nparts = L.nparts; a.bstride = (int)L.bstride;
   a.b = (int)L.b; a.B = (int)L.B; a.d = (int)L.d;
   a.first = L.wide ? 0 : (int)L.off; a.own = L.wide ? (int)L.off : 0;
-  // 64 anchors per tile where that still is one round of workgroups: more compute units, and a tile takes 7.0 us instead of 8.8
-  // (128 anchors of 1024, d = 512; steps: 24.0 -> 22.7 us, 256 of 2048 from raw rows 40.4 -> 38.4, 1024 of 1024 30.7 -> 30.1).
-  // Beyond one round two tiles of 64 take longer than one of 128 (3.5 us of either are its start and end).
-  const int64_t at64 = 2 * ((L.b + 63) / 64) * (int64_t)L.nparts;
-  const bool narrow = at64 <= 256;
-  auto* kernel = L.gathered ? (narrow ? k_strips_t128_bf16<64, true> : k_strips_t128_bf16<128, true>)
-                            : (narrow ? k_strips_t128_bf16<64, false> : k_strips_t128_bf16<128, false>);
+  const bool narrow = strips_t128_narrow(L);
+  if (L.own_prep) {
+    a.idx = c.buf.idx; a.stride = c.cfg.state_stride;
+    a.tau_glob = c.cfg.version == FASTCLIP_V2 ? nullptr : c.buf.tau;
+    a.arrived = (unsigned*)(c.ws + L.arrived); a.narrived = L.narrived;
+    for (int i = 0; i < 2; ++i) {
+      a.job[i].tau = i == 0 ? c.buf.tau_img : c.buf.tau_txt;
+      a.job[i].u = i == 0 ? c.buf.u_img : c.buf.u_txt;
+      a.job[i].tau_out = (float*)(c.ws + (i == 0 ? L.tau1 : L.tau2));
+      a.job[i].u_out = (float*)(c.ws + (i == 0 ? L.uold1 : L.uold2));
+    }
+  }
+  auto* kernel = L.gathered ? (narrow ? k_strips_t128_bf16<64, true, false> : k_strips_t128_bf16<128, true, false>)
+                 : L.own_prep ? (narrow ? k_strips_t128_bf16<64, false, true> : k_strips_t128_bf16<128, false, true>)
+                              : (narrow ? k_strips_t128_bf16<64, false, false> : k_strips_t128_bf16<128, false, false>);
   const int64_t at_rows = narrow ? 64 : 128;
   hipLaunchKernelGGL(kernel, dim3((unsigned)L.nparts, (unsigned)((L.b + at_rows - 1) / at_rows), 2), dim3(512), 0, c.s, a);
 }
 
 // ----------------------------------------------------------------------------------------------------------------
 constexpr int kO = 64;                          // columns of an output tile; its rows: 64 MB
-constexpr int kGroups = 8;                      // state phase inside: 4 groups of 64 sums for the rows, 4 for the local anchors q
+constexpr int kMaxQ = (kMaxLocalQ + 511) / 512;   // local anchors per thread whose coefficients a workgroup forms
 // a wave's stage: 16 deep, 2 MB KiB of the strip, 2 KiB of X and, with gathered state, 2 KiB of the second strip; as many as
 // fit 160 KiB beside the coefficients
 template <int MB, bool G> constexpr int kWStage = 2048 * (MB + 1 + (G ? 1 : 0));
@@ -382,7 +498,12 @@ struct T128Args {
   int nA, nB;            // 16-deep stages over the contrasts / over the local anchors
   int sliceA, sliceB;    // ... per wave
   double* part;          // nsplit > 1: [tile][split][64 x 64 floats as pairs]
-  unsigned* arrived;     // per 64 rows of an output tile, then one for the scalars (64-row tiles); 0 before the launch (k_prep)
+  unsigned* arrived;     // per 64 rows of an output tile; 0 before the launch
+  unsigned* scalars_arrived;   // the same for the workgroups or waves whose terms the scalars are made of
+  const double* red;
+  int version;
+  int nterms;            // pairs in the state phase's list of the scalars' terms
+  int finishers;         // leading workgroups that run the state phase; 0: the first workgroups of side 0 do
   float rho;
   const float* tau;
   float *loss, *d_tau;
@@ -396,9 +517,10 @@ struct T128Args {
 // loop.  Then the eight waves' tiles are added up through LDS, and with several splits by the last workgroup to arrive.
 //
 // The state phase rides along: every workgroup forms the coefficients that it needs from the partial sums (same
-// instructions, same order, hence the same bits everywhere) while its first stages are on their way, the workgroups of
-// side 0, split 0 and the first columns finish their 64 anchors.  When that is too much to read again and again
-// (plan_t128), k_state has run before and the coefficients are read.
+// instructions, same order, hence the same bits everywhere) while its first stages are on their way.  The anchors are finished
+// (scatter, Eq. 9, loss) by workgroups of their own where compute units are left for them, else by the last waves of the
+// workgroups of side 0, split 0 and the first columns, which are late by that (4 us in the chain of one of 12 us).  When there
+// is more than one round of workgroups (plan_t128), k_state has run before and the coefficients are read.
 //
 // What bounds it: operands come at 64 bytes per clock and compute unit, so eight 16-deep stages of 64 x 64 tiles (32 KiB) take
 // 512 cycles against 256 of products (650 - 880 measured), and about 5 us go into the start, the coefficients, the sum over
@@ -410,19 +532,60 @@ struct T128Args {
 // depth: 640 of 5120 gathered 67 us.
 // GATHERED: the remote anchors' weights multiply the same rows of X, so the first sum's operand is c_own E + F, formed as
 // E + F / c_own (the sum is multiplied by c_own afterwards) between the reads and the products of a stage.
+constexpr size_t kStateAt = (sizeof(T128Args) + 7) / 8 * 8;      // the kernel's second argument
+
+// The state phase of 256 anchors by a workgroup of its own (one of g.finishers), a thread per side of an anchor: scatter, outputs,
+// Eq. 9, the terms of the scalars, which the last of these workgroups adds up.
+// True in the wave that is to form the scalars.
+__device__ __forceinline__ bool t128_finish(const T128Args& g, const StateArgs& a, int* flag) {
+  const int tid = threadIdx.x, side = __builtin_amdgcn_readfirstlane(tid >> 8), r = (int)blockIdx.x * 256 + (tid & 255);
+  double lterm = 0.0, hterm = 0.0;
+  if (r < g.b) {
+    const int64_t n = a.idx[r] * a.stride;
+    const float u = (side ? a.uold2 : a.uold1)[r], tau = (side ? a.tau2 : a.tau1)[r];
+    float m = 0.f, v = 0.f;
+    if (a.version == FASTCLIP_V2 && a.tau_upd.optimizer) {
+      m = (side ? a.m_txt : a.m_img)[n];
+      const float* pv = side ? a.v_txt : a.v_img;
+      if (pv) v = pv[n];
+    }
+    const float* e = a.sums + (size_t)(2 * side) * a.nparts * a.bstride + r;
+    const float* x = e + (size_t)a.nparts * a.bstride;
+    float se = 0.f, sx = 0.f;
+    for (int p0 = 0; p0 < a.nparts; p0 += 8) {          // eight partial sums of either quantity in flight at once
+      float ve[8], vx[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const size_t o = (size_t)(p0 + i < a.nparts ? p0 + i : p0) * a.bstride;
+        ve[i] = e[o];
+        vx[i] = x[o];
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) { se += p0 + i < a.nparts ? ve[i] : 0.f; sx += p0 + i < a.nparts ? vx[i] : 0.f; }
+    }
+    state_finish_side<false>(a, side, r, n, se, sx, u, tau, m, v, &lterm, &hterm);
+  }
+  lterm = wave_sum_f64(lterm);
+  hterm = wave_sum_f64(hterm);
+  if ((tid & 63) == 0) {
+    double* red = a.red + 2 * ((int64_t)blockIdx.x * 8 + (tid >> 6));
+    store_agent(red, lterm);
+    store_agent(red + 1, hterm);
+  }
+  return last_to_arrive(g.scalars_arrived, (unsigned)g.finishers, flag) && tid < 64;
+}
+
 template <int MB, bool GATHERED>
-__global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, StateArgs a) {
+__device__ __forceinline__ bool t128_tile(const T128Args& g, const StateArgs& a, char* ring, float* crow, float (*drow)[64 * MB],
+                                          float* cq, int* flag) {
   constexpr int kM = 64 * MB, kStageB = kWStage<MB, GATHERED>, kSlotsW = kWSlots<MB, GATHERED>, kX = 2048 * MB, kF = kX + 2048;
-  __shared__ __attribute__((aligned(1024))) char ring[kWRing<MB, GATHERED>];
-  __shared__ __attribute__((aligned(16))) float crow[kM], drow[kM], cq[kMaxLocalQ];
-  __shared__ int flag;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 31, hk = lane >> 5;
   // Workgroups that share an XCD (id mod 8) take neighbours in the order split, side, row tile, column tile: the same slice of
   // the depth and the same rows of the strips, which its L2 then fetches once.
-  const int p = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+  const int wg = (int)blockIdx.x - g.finishers, p = (wg & 7) * (((int)gridDim.x - g.finishers) >> 3) + (wg >> 3);
   const int tiles = 2 * g.tiles_m * g.tiles_n;
-  if (p >= tiles * g.nsplit) return;
+  if (p >= tiles * g.nsplit) return false;
   const int split = div_small(p, g.inv_tiles), tile = p - split * tiles;
   const int sm = div_small(tile, g.inv_tiles_n), tn = tile - sm * g.tiles_n, side = sm >= g.tiles_m, tm = sm - side * g.tiles_m;
   const int m0 = tm * kM, n0 = tn * kO;
@@ -430,66 +593,11 @@ __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, State
   // pinned in scalar registers: left in the argument segment they are loaded again behind every memory fence
   const int B = __builtin_amdgcn_readfirstlane(g.B), ldx = __builtin_amdgcn_readfirstlane((int)J.ldx);
   const bf16_t* X = wave_uniform(J.X);
-  float* out = const_cast<float*>(wave_uniform(J.out));
   const int d = __builtin_amdgcn_readfirstlane(g.d);
   const int qbase = split * 8 * g.sliceB * 16;       // this workgroup's local anchors q
   int nq = g.b - qbase < 8 * g.sliceB * 16 ? g.b - qbase : 8 * g.sliceB * 16;
   nq = nq < 0 ? 0 : nq;
-  const bool fused = MB == 1 && a.fused;
-  const bool finisher = fused && side == 0 && tn == 0 && split == 0;
-  const int nqg = (nq + 63) >> 6;
-
-  // [group][anchor] partial sums of a wave, in the slot of its ring that is requested last (behind the second barrier below)
-  auto psum = [&](int w) { return (float*)(ring + (w * kSlotsW + kSlotsW - 1) * kStageB); };
-  static_assert(kStageB >= kGroups * 64 * 4, "the partial sums fit a slot");
-
-  // ---- inputs of the coefficients: of the 64 rows (both sides, for the diagonal factor too) and of the q's (the other side).
-  // They are requested and waited for ahead of the operands: vector memory operations complete in order.
-  const bool finishing = finisher && wave >= 6 && m0 + lane < g.b;       // wave 6: image side, wave 7: text side
-  int64_t fn = 0;
-  float fu = 0.f, ft = 1.f, u1 = 0.f, t1 = 1.f, u2 = 0.f, t2 = 1.f;
-  if (fused) {
-    if (finishing) {
-      fn = a.idx[m0 + lane] * a.stride;
-      fu = (wave == 6 ? a.uold1 : a.uold2)[m0 + lane];
-      ft = (wave == 6 ? a.tau1 : a.tau2)[m0 + lane];
-    }
-    const int m = tid < 64 ? m0 + tid : qbase + tid - 64;
-    if (m < g.b && tid < 64 + nqg * 64) { u1 = a.uold1[m]; t1 = a.tau1[m]; u2 = a.uold2[m]; t2 = a.tau2[m]; }
-    // group 0, 1: sum of l of the rows, image / text side; 2, 3: of (s - s_ii) l (finishers); then the q's
-    const float* p[kGroups];
-    float s[kGroups];
-#pragma unroll
-    for (int j = 0; j < kGroups; ++j) {
-      const int quantity = j < 4 ? (j & 1) * 2 + (j >> 1) : 2 * (1 - side);
-      const int m1 = (j < 4 ? m0 : qbase + (j - 4) * 64) + lane;          // what a lane beyond the anchors adds up is not used
-      p[j] = a.sums + (size_t)quantity * a.nparts * a.bstride + (m1 < g.b ? m1 : g.b - 1);
-      s[j] = 0.f;
-    }
-#pragma unroll 8
-    for (int pt = wave; pt < a.nparts; pt += 8) {
-      const size_t o = (size_t)pt * a.bstride;
-      float v[kGroups];
-#pragma unroll
-      for (int j = 0; j < kGroups; ++j)
-        if (j < 2 || (j < 4 ? finisher : j - 4 < nqg)) v[j] = p[j][o]; else v[j] = 0.f;
-#pragma unroll
-      for (int j = 0; j < kGroups; ++j) s[j] += v[j];
-    }
-#pragma unroll
-    for (int j = 0; j < kGroups; ++j) psum(wave)[j * 64 + lane] = s[j];
-  } else {
-    for (int i = tid; i < kM + nqg * 64; i += 512) {
-      if (i < kM) {
-        crow[i] = m0 + i < g.b ? (side == 0 ? a.c1 : a.c2)[m0 + i] : 0.f;
-        drow[i] = m0 + i < g.b ? a.dcoef[m0 + i] : 0.f;
-      } else {
-        const int q = qbase + i - kM;
-        cq[i - kM] = q < g.b ? (side == 0 ? a.c2 : a.c1)[q] : 0.f;
-      }
-    }
-  }
-  FC_FENCE();
+  const int nq16 = (nq + 15) & ~15;                  // coefficients that the stages over the local anchors read
 
   // ---- operand requests
   const int unit = split * 8 + wave;
@@ -527,8 +635,8 @@ __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, State
     for (int i = 0; i < 2 * MB; ++i) woff[i] = (uint32_t)(lane * 16) + (uint32_t)i * row_block;
     open_rows(A0 * 16);
   };
+  const char* src_other = wave_uniform((const char*)J.Eo + ((int64_t)(Q0 >> 1) * g.nCB + (m0 >> 4)) * 1024 + (Q0 & 1) * 256);
   auto open_other = [&]() {
-    src = wave_uniform((const char*)J.Eo + ((int64_t)(Q0 >> 1) * g.nCB + (m0 >> 4)) * 1024 + (Q0 & 1) * 256);
 #pragma unroll
     for (int i = 0; i < 2 * MB; ++i) {
       const int cb = 2 * i + (lane >> 5), h = (lane >> 4) & 1, q = (lane & 15) ^ (4 * h) ^ (8 * (cb & 1));
@@ -549,10 +657,10 @@ __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, State
     dma16(X, xoff[1], fill + (uint32_t)(kX + 1024));
     fill = fill + kStageB == wring + kSlotsW * kStageB ? wring : fill + kStageB;
     ++at;
+    src = at == nAw ? src_other : src + (at < nAw ? 1024u : (((Q0 + at - nAw) & 1) ? 256u : row_block - 256u));
     if (at == nAw) {
       open_other();
     } else {
-      src += at < nAw ? 1024u : (((Q0 + at - nAw) & 1) ? 256u : row_block - 256u);
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         grow[j] += 16; xoff[j] += next_rows;
@@ -560,49 +668,192 @@ __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, State
       }
     }
   };
+  src = src_other;
   if (nAw > 0) open_own(); else open_other();
-  for (int s = 0; s < kSlotsW - 1 && s < nst; ++s) request();
+  if (nst > 0) request();
 
-  // ---- the coefficients
-  __syncthreads();
-  FC_FENCE();
+  // ---- the coefficients: of the rows (both sides, for the diagonal factor too) and of the q's (the other side).  Their inputs are
+  // requested behind the first stage, the other stages behind the inputs' arrival: vector memory operations complete in order.
+  auto request_more = [&]() {
+    for (int s = 1; s < kSlotsW - 1 && s < nst; ++s) request();
+  };
+  const bool fused = a.fused;
+  const bool finisher = fused && g.finishers == 0 && side == 0 && tn == 0 && split == 0;
+  constexpr int kFin = 2 * MB;                       // a finisher's last waves finish 64 anchors each: image sides, then text sides
+  const int fw = wave - (8 - kFin), fside = fw >= MB, frow = (fside ? fw - MB : fw) * 64 + lane;
+  const bool finishing = finisher && fw >= 0 && m0 + frow < g.b;
+  double lterm = 0.0, hterm = 0.0;
   if (fused) {
-    auto total = [&](int j, int al) {
-      float s = psum(0)[j * 64 + al];
-#pragma unroll
-      for (int w = 1; w < 8; ++w) s += psum(w)[j * 64 + al];
-      return s;
-    };
-    float u;
-    if (tid < 64) {
-      float c1 = 0.f, c2 = 0.f, dc = 0.f;
-      if (m0 + tid < g.b) {
-        const float s1 = total(0, tid), s2 = total(1, tid);
-        c1 = anchor_coefficient(a, s1, u1, t1, &u);
-        c2 = anchor_coefficient(a, s2, u2, t2, &u);
-        dc = __fmul_rn(c1, s1) + __fmul_rn(c2, s2);
-      }
-      crow[tid] = side == 0 ? c1 : c2;
-      drow[tid] = dc;
-    } else if (tid < 64 + nqg * 64) {
-      const int j = tid - 64;
-      cq[j] = qbase + j < g.b
-                  ? anchor_coefficient(a, total(4 + (j >> 6), j & 63), side == 0 ? u2 : u1, side == 0 ? t2 : t1, &u) : 0.f;
+    // Sums of the q's: groups of 256 anchors, one wave load per group and partial sum, dealt out to the waves: wave w takes group
+    // w % groups_w (and that plus 8) and every slices-th partial sum.
+    const int groups = (nq + 255) >> 8;
+    const int lg = groups > 4 ? 3 : (groups > 2 ? 2 : (groups > 1 ? 1 : 0)), groups_w = 1 << lg, slices = 8 >> lg;
+    // partial sums of a wave, [4 quantities][rows] and [2 groups][256], in the slot of its ring that is requested last (behind the
+    // second barrier below)
+    auto psum = [&](int w) { return (float*)(ring + (w * kSlotsW + kSlotsW - 1) * kStageB); };
+    static_assert(kStageB >= (4 * kM + 512) * 4 && kMaxLocalQ <= 16 * 256, "the partial sums fit a slot");
+    // Addresses are a wave-uniform base and a 32-bit byte offset per lane: what bounds this part is the number of instructions
+    // (with 64-bit addresses per lane 6500 cycles from the first request to the sums in LDS).
+    auto at = [](const float* base, uint32_t bytes) { return *(const float*)((const char*)base + bytes); };
+    const int rside = wave >= MB, row = tid & (kM - 1);      // tid < 2 kM: side and row of a coefficient
+    const bool rows_here = tid < 2 * kM && m0 + row < g.b;
+    int64_t fn = 0;                                  // dataset index
+    float fu = 0.f, ft = 1.f, fm = 0.f, fv = 0.f, ur = 0.f, tr = 1.f, uq[kMaxQ], tq[kMaxQ];
+    const uint32_t last_anchor = (uint32_t)(g.b - 1);
+    if (finisher && fw >= 0) {                       // anchors that do not exist as the last one
+      const uint32_t m = (uint32_t)(m0 + frow) < last_anchor ? (uint32_t)(m0 + frow) : last_anchor;
+      fn = *(const int64_t*)((const char*)a.idx + m * 8u);
+      fu = at(wave_uniform(fside ? a.uold2 : a.uold1), m * 4u);
+      ft = at(wave_uniform(fside ? a.tau2 : a.tau1), m * 4u);
     }
-    const int fside = wave - 6;
-    float fse = 0.f, fsx = 0.f;
-    if (finishing) { fse = total(fside, lane); fsx = total(2 + fside, lane); }
+    if (wave < 2 * MB) {
+      const uint32_t m = (uint32_t)(m0 + row) < last_anchor ? (uint32_t)(m0 + row) : last_anchor;
+      ur = at(wave_uniform(rside ? a.uold2 : a.uold1), m * 4u);
+      tr = at(wave_uniform(rside ? a.tau2 : a.tau1), m * 4u);
+    }
+    const float *u_other = wave_uniform(side ? a.uold1 : a.uold2), *t_other = wave_uniform(side ? a.tau1 : a.tau2);
+    const int j0 = (tid - 2 * kM) & 511, jw = (wave * 64 - 2 * kM) & 511;    // q's behind the threads that have the rows
+#pragma unroll
+    for (int i = 0; i < kMaxQ; ++i) {
+      uq[i] = 0.f; tq[i] = 1.f;
+      if (jw + 512 * i < nq) {                       // wave-uniform
+        const uint32_t m = (uint32_t)(qbase + j0 + 512 * i) < last_anchor ? (uint32_t)(qbase + j0 + 512 * i) : last_anchor;
+        uq[i] = at(u_other, m * 4u);
+        tq[i] = at(t_other, m * 4u);
+      }
+    }
+    // four anchors per lane; what lies behind the anchors (up to bstride) is added up and not used
+    const int bs = (int)a.bstride, nparts = a.nparts;
+    const char* sums = (const char*)wave_uniform(a.sums);
+    auto words_at = [&](int quantity, int m) { return (uint32_t)(quantity * nparts * bs + (m < bs ? m : bs - 4)) * 4u; };
+    auto words = [&](int pt, uint32_t off) { return *(const f32x4*)(sums + (uint32_t)(pt * bs) * 4u + off); };
+    // partial sums wave, wave + 8, .. of the rows (MB = 1: a lane's quantity is lane / 16; MB = 2: 2 (lane / 32) + i), and
+    // wave / groups_w, + slices, .. of the wave's group of q's: up to 16 of the latter in flight at once
+    uint32_t pr[MB];
+    f32x4 sr[MB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      pr[i] = words_at(MB == 1 ? lane >> 4 : 2 * (lane >> 5) + i, m0 + 4 * (lane & (16 * MB - 1)));
+      sr[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    const int last_part = nparts - 1;
+    int ptr = wave;                                  // next partial sum of the rows
+    for (int gi = 0, gr = wave & (groups_w - 1); gi == 0 || gr < groups; ++gi, gr += 8) {
+      const uint32_t pq = words_at(2 * (1 - side), qbase + gr * 256 + 4 * lane);
+      f32x4 sq = zero;
+      // the next N partial sums of the q's, and the rows' that come up meanwhile (a slices-th as many)
+      auto sweep = [&](auto count, int pt) {
+        constexpr int N = decltype(count)::value;
+        f32x4 vq[N], vr[MB][N];
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+          vq[e] = zero;
+#pragma unroll
+          for (int i = 0; i < MB; ++i) vr[i][e] = zero;
+          if (pt + e * slices <= last_part) vq[e] = words(pt + e * slices, pq);
+          if ((e << 3) < (N << (3 - lg)) && ptr + 8 * e <= last_part) {
+#pragma unroll
+            for (int i = 0; i < MB; ++i)
+              if (i == 0 || finisher) vr[i][e] = words(ptr + 8 * e, pr[i]);
+          }
+        }
+        FC_PIN();
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+          sq += vq[e];
+#pragma unroll
+          for (int i = 0; i < MB; ++i) sr[i] += vr[i][e];
+        }
+        ptr += ((N << (3 - lg)) + 7) & ~7;
+      };
+      for (int pt = wave >> lg; pt <= last_part;) {
+        const int left = ((last_part - pt) >> (3 - lg)) + 1;     // slices: a power of two
+        if (left > 8) { sweep(std::integral_constant<int, 16>{}, pt); pt += 16 * slices; }
+        else if (left > 2) { sweep(std::integral_constant<int, 8>{}, pt); pt += 8 * slices; }
+        else { sweep(std::integral_constant<int, 2>{}, pt); pt += 2 * slices; }
+      }
+      if (gr < groups) *(f32x4*)(psum(wave) + 4 * kM + gi * 256 + 4 * lane) = sq;
+    }
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+      *(f32x4*)(psum(wave) + (MB == 1 ? lane >> 4 : 2 * (lane >> 5) + i) * kM + 4 * (lane & (16 * MB - 1))) = sr[i];
+    if (finisher && fw >= 0) {
+      const StateArgs& la = late_argument<kStateAt>(a);
+      if (la.version == FASTCLIP_V2 && la.tau_upd.optimizer) {      // the temperature's moments, by now addressable
+        fm = (fside ? la.m_txt : la.m_img)[fn * la.stride];
+        const float* pv = fside ? la.v_txt : la.v_img;
+        if (pv) fv = pv[fn * la.stride];
+      }
+    }
+    request_more();
     __syncthreads();
     FC_FENCE();
-    if (finishing) {
-      // 64 anchors: scatter, outputs, Eq. 9, their terms of the scalars.  Nobody in this launch waits for them but the wave that
-      // adds the terms up at the very end.
-      double lterm, hterm;
-      state_finish_side<false>(a, fside, m0 + lane, fn, fse, fsx, fu, ft, &lterm, &hterm);
-      double* red = a.red + 2 * ((int64_t)fside * g.b + m0 + lane);
-      store_agent(red, lterm);
-      store_agent(red + 1, hterm);
+    auto add8 = [](const float (&w)[8]) { return ((w[0] + w[1]) + (w[2] + w[3])) + ((w[4] + w[5]) + (w[6] + w[7])); };
+    auto row_total = [&](int quantity, int al) {
+      float w[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) w[i] = psum(i)[quantity * kM + al];
+      return add8(w);
+    };
+    if (finisher && fw >= 0) {
+      // nobody in this launch waits for its results but the wave that adds the terms up at the very end
+      const StateArgs& la = late_argument<kStateAt>(a);
+      if (finishing)
+        state_finish_side<false>(la, fside, m0 + frow, fn * la.stride, row_total(2 * fside, frow), row_total(2 * fside + 1, frow),
+                                 fu, ft, fm, fv, &lterm, &hterm);
     }
+    float u;
+    if (tid < 2 * kM) {
+      float c = 0.f, ce = 0.f;
+      if (rows_here) {
+        const float s = row_total(2 * rside, row);
+        c = anchor_coefficient(a, s, ur, tr, &u);
+        ce = __fmul_rn(c, s);
+      }
+      if (rside == side) crow[row] = c;
+      drow[rside][row] = ce;
+    }
+#pragma unroll
+    for (int i = 0; i < kMaxQ; ++i) {
+      const int j = j0 + 512 * i;
+      if (jw + 512 * i >= nq16) break;               // wave-uniform
+      float c = 0.f;
+      if (j < nq) {
+        const int gr = j >> 8, at = 4 * kM + (gr >> 3) * 256 + (j & 255);
+        float w[8];                                  // all eight reads at once, also where there are fewer slices
+#pragma unroll
+        for (int sl = 0; sl < 8; ++sl) {
+          w[sl] = psum((gr & (groups_w - 1)) + ((sl < slices ? sl : 0) << lg))[at];
+          w[sl] = sl < slices ? w[sl] : 0.f;
+        }
+        c = anchor_coefficient(a, add8(w), uq[i], tq[i], &u);
+      }
+      if (j < nq16) cq[j] = c;
+    }
+    __syncthreads();
+    FC_FENCE();
+    if (finisher && fw >= 0) {
+      // both sums over the wave in one run: the lower half of the lanes carries the loss terms, the upper half the h terms
+      double v = (lane < 32 ? lterm : hterm) + __shfl_xor(lane < 32 ? hterm : lterm, 32);
+#pragma unroll
+      for (int o = 16; o > 0; o >>= 1) v += __shfl_xor(v, o);
+      if (lr == 0) store_agent(const_cast<double*>(late_argument<0>(g).red) + 2 * (tm * kFin + fw) + hk, v);
+    }
+  } else {
+    request_more();
+    for (int i = tid; i < kM + nq16; i += 512) {
+      if (i < kM) {
+        crow[i] = m0 + i < g.b ? (side == 0 ? a.c1 : a.c2)[m0 + i] : 0.f;
+        drow[0][i] = m0 + i < g.b ? a.dcoef[m0 + i] : 0.f;
+        drow[1][i] = 0.f;
+      } else {
+        const int q = qbase + i - kM;
+        cq[i - kM] = q < g.b ? (side == 0 ? a.c2 : a.c1)[q] : 0.f;
+      }
+    }
+    __syncthreads();
+    FC_FENCE();
   }
 
   // ---- main loop
@@ -715,31 +966,33 @@ __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, State
     }
   run(std::true_type{}, nAw, nst);
 
-  // Either finishing wave counts itself once its stores are acknowledged at agent scope (they are long since); the answer is
+  const T128Args& lg = late_argument<0>(g);
+  // The finishing waves count themselves once their stores are acknowledged at agent scope (they are long since); the answer is
   // looked at behind the outputs.
   unsigned scalars_before = 0;
-  if (finisher && wave >= 6) {
+  if (finisher && fw >= 0) {
     __builtin_amdgcn_s_waitcnt(0x0f70);
     FC_FENCE();
     if (lane == 0)
-      scalars_before = __hip_atomic_fetch_add(g.arrived + 2 * g.tiles_m * g.tiles_n, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      scalars_before = __hip_atomic_fetch_add(lg.scalars_arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  float* out = const_cast<float*>(wave_uniform(side ? lg.job[1].out : lg.job[0].out));
   // ---- the eight waves' tiles are added up, 64 rows at a time: wave w finishes block w / 2 of them, its rows 16 (w % 2) .. + 15
   const int rl = (wave >> 2) * 32 + (wave & 1) * 16 + 4 * hk;          // row of e = 0; e = 4: 8 further on
   const int n = n0 + ((wave >> 1) & 1) * 32 + lr;
-  const bool whole = m0 + kM <= g.b && n0 + kO <= d;
+  const bool whole = m0 + kM <= lg.b && n0 + kO <= d;
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
     const int row0 = mb * 64 + rl;
     bf16_t xd[8];                              // the diagonal terms' rows, requested ahead of the sums
     f32x4 dc[2];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) dc[h] = *(const f32x4*)(drow + row0 + 8 * h);
+    for (int h = 0; h < 2; ++h) dc[h] = *(const f32x4*)(drow[0] + row0 + 8 * h) + *(const f32x4*)(drow[1] + row0 + 8 * h);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       int m = m0 + row0 + 8 * (e >> 2) + (e & 3);
-      m = m < g.b ? m : g.b - 1;
-      xd[e] = X[(uint32_t)((g.off + m) * ldx + (n < d ? n : 0))];
+      m = m < lg.b ? m : lg.b - 1;
+      xd[e] = X[(uint32_t)((lg.off + m) * ldx + (n < d ? n : 0))];
     }
     __syncthreads();
     FC_FENCE();
@@ -767,25 +1020,34 @@ __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, State
       }
     }
     bool writer = true;
-    if (g.nsplit > 1) {
-      const size_t slab = (size_t)g.nsplit * (kO * kO / 2);
-      double* all = g.part + (size_t)(tile * MB + mb) * slab + wave * 256 + lane;
+    if (lg.nsplit > 1) {
+      const size_t slab = (size_t)lg.nsplit * (kO * kO / 2);
+      double* all = lg.part + (size_t)(tile * MB + mb) * slab + wave * 256 + lane;
 #pragma unroll
       for (int p = 0; p < 4; ++p) {
         const u32x2 w = {__float_as_uint(sum[p >> 1][2 * (p & 1)]), __float_as_uint(sum[p >> 1][2 * (p & 1) + 1])};
         store_agent(all + (size_t)split * (kO * kO / 2) + p * 64, __builtin_bit_cast(double, w));
       }
-      writer = last_to_arrive(g.arrived + tile * MB + mb, (unsigned)g.nsplit, &flag);
+      writer = last_to_arrive(lg.arrived + tile * MB + mb, (unsigned)lg.nsplit, flag);
       if (writer) {
         sum[0] = sum[1] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-        for (int s = 0; s < g.nsplit; ++s)
+        for (int s0 = 0; s0 < lg.nsplit; s0 += 4) {      // the partial results of four splits in flight at once
+          double w[4][4];
 #pragma unroll
-          for (int p = 0; p < 4; ++p) {
-            const u32x2 w = __builtin_bit_cast(u32x2, load_agent(all + (size_t)s * (kO * kO / 2) + p * 64));
-            sum[p >> 1][2 * (p & 1)] += __uint_as_float(w[0]);
-            sum[p >> 1][2 * (p & 1) + 1] += __uint_as_float(w[1]);
-          }
+          for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+              w[s][p] = load_agent(all + (size_t)(s0 + s < lg.nsplit ? s0 + s : s0) * (kO * kO / 2) + p * 64);
+          FC_PIN();
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+              const u32x2 v = __builtin_bit_cast(u32x2, w[s][p]);
+              sum[p >> 1][2 * (p & 1)] += s0 + s < lg.nsplit ? __uint_as_float(v[0]) : 0.f;
+              sum[p >> 1][2 * (p & 1) + 1] += s0 + s < lg.nsplit ? __uint_as_float(v[1]) : 0.f;
+            }
+        }
       }
     }
     if (writer) {
@@ -797,17 +1059,29 @@ __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, State
 #pragma unroll
         for (int e = 0; e < 8; ++e) o[(8 * (e >> 2) + (e & 3)) * d] = v[e];
       } else {
-        const int rows = n < d ? g.b - m0 - row0 : 0;
+        const int rows = n < d ? lg.b - m0 - row0 : 0;
 #pragma unroll
         for (int e = 0; e < 8; ++e)
           if (8 * (e >> 2) + (e & 3) < rows) o[(8 * (e >> 2) + (e & 3)) * d] = v[e];
       }
     }
   }
-  // ---- scalars, by the wave that finished the last anchors
-  bool last = side == 0 && tn == 0 && tm == 0 && split == 0 && wave == 7;
-  if (fused) last = finisher && wave >= 6 && (unsigned)__shfl((int)scalars_before, 0) + 1u == 2u * (unsigned)g.tiles_m;
-  if (last) write_scalars<true>(a.red, fused ? 2 * g.b : (int)a.ntiles, g.b, a.version, g.tau, g.rho, g.loss, g.d_tau);
+  // scalars, by the wave that finished the last anchors
+  if (fused) return finisher && fw >= 0 && (unsigned)__shfl((int)scalars_before, 0) + 1u == (unsigned)(kFin * lg.tiles_m);
+  return side == 0 && tn == 0 && tm == 0 && split == 0 && wave == 7;
+}
+
+template <int MB, bool GATHERED>
+__global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, StateArgs a) {
+  __shared__ __attribute__((aligned(1024))) char ring[kWRing<MB, GATHERED>];
+  __shared__ __attribute__((aligned(16))) float crow[64 * MB], drow[2][64 * MB], cq[kMaxLocalQ];
+  __shared__ int flag;
+  warm_arguments<sizeof(T128Args) + sizeof(StateArgs)>();
+  // (one place that calls write_scalars: see there)
+  const bool last = (int)blockIdx.x < g.finishers ? t128_finish(late_argument<0>(g), late_argument<kStateAt>(a), &flag)
+                                                  : t128_tile<MB, GATHERED>(g, a, ring, crow, drow, cq, &flag);
+  const T128Args& lg = late_argument<0>(g);
+  if (last) write_scalars<true>(lg.red, lg.nterms, lg.b, lg.version, lg.tau, lg.rho, lg.loss, lg.d_tau);
 }
 
 void launch_contract_t128_bf16(const StepCtx& c) {
@@ -833,11 +1107,17 @@ void launch_contract_t128_bf16(const StepCtx& c) {
   g.sliceB = (g.nB + L.nsplit * 8 - 1) / (L.nsplit * 8);
   g.part = L.nsplit > 1 ? (double*)(c.ws + L.Opart[0]) : nullptr;
   g.arrived = (unsigned*)(c.ws + L.arrived);
+  g.scalars_arrived = g.arrived + L.narrived - 1;
   g.tau = c.buf.tau; g.rho = c.cfg.rho; g.loss = c.buf.loss; g.d_tau = c.buf.d_tau;
+  g.red = (const double*)(c.ws + L.red); g.version = c.cfg.version;
   auto* kernel = L.gathered ? k_contract_t128_bf16<1, true>
                             : (L.out_rows == 64 ? k_contract_t128_bf16<1, false> : k_contract_t128_bf16<2, false>);
-  const unsigned groups = 2u * (unsigned)(g.nsplit * g.tiles_m * g.tiles_n);
-  hipLaunchKernelGGL(kernel, dim3((groups + 7) / 8 * 8), dim3(512), 0, c.s, g, make_state_args(c));
+  const unsigned groups = (2u * (unsigned)(g.nsplit * g.tiles_m * g.tiles_n) + 7) / 8 * 8;
+  // the state phase has workgroups of its own where compute units are left for them
+  const unsigned finishers = (unsigned)((L.b + 255) / 256);
+  g.finishers = L.fused_state && groups + finishers <= 256 ? (int)finishers : 0;
+  g.nterms = !L.fused_state ? L.nstate_blocks : (g.finishers ? 8 * g.finishers : 2 * (L.out_rows / 64) * g.tiles_m);
+  hipLaunchKernelGGL(kernel, dim3(groups + (unsigned)g.finishers), dim3(512), 0, c.s, g, make_state_args(c));
 }
 
 }  // namespace fc

@@ -56,6 +56,39 @@ __device__ __forceinline__ void dma4(const void* uniform_base, uint32_t lane_byt
                : "v"(lane_byte_off), "s"(uniform_base), "s"(__builtin_amdgcn_readfirstlane(lds_byte_addr))
                : "memory");
 }
+// One word of every 64 bytes of a kernel's arguments (BYTES in all), so that they come into the scalar cache at once and not line
+// by line where they are used, a trip to memory each: 2700 -> 1100 cycles to the first address of a kernel with 600 bytes of
+// them.  By hand: values that the compiler knows it keeps, and spills.
+template <size_t BYTES>
+__device__ __forceinline__ void warm_arguments() {
+  static_assert((BYTES >= 0x104 && BYTES <= 0x140) || (BYTES >= 0x204 && BYTES <= 0x280), "the words below cover the arguments");
+  uint32_t w0, w1, w2, w3, w4, w5, w6, w7, w8;
+  if constexpr (BYTES <= 0x140) {
+    asm volatile("s_load_dword %0, %5, 0x0\n\ts_load_dword %1, %5, 0x40\n\ts_load_dword %2, %5, 0x80\n\t"
+                 "s_load_dword %3, %5, 0xc0\n\ts_load_dword %4, %5, 0x100\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&s"(w0), "=&s"(w1), "=&s"(w2), "=&s"(w3), "=&s"(w4)
+                 : "s"(__builtin_amdgcn_kernarg_segment_ptr()));
+  } else {
+    asm volatile("s_load_dword %0, %9, 0x0\n\ts_load_dword %1, %9, 0x40\n\ts_load_dword %2, %9, 0x80\n\t"
+                 "s_load_dword %3, %9, 0xc0\n\ts_load_dword %4, %9, 0x100\n\ts_load_dword %5, %9, 0x140\n\t"
+                 "s_load_dword %6, %9, 0x180\n\ts_load_dword %7, %9, 0x1c0\n\ts_load_dword %8, %9, 0x200\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&s"(w0), "=&s"(w1), "=&s"(w2), "=&s"(w3), "=&s"(w4), "=&s"(w5), "=&s"(w6), "=&s"(w7), "=&s"(w8)
+                 : "s"(__builtin_amdgcn_kernarg_segment_ptr()));
+  }
+}
+// A kernel's argument (OFFSET bytes into them) to be read where it is used: the compiler loads the fields of a struct at the
+// kernel's start and keeps them all in scalar registers from there on.
+template <size_t OFFSET, typename T>
+__device__ __forceinline__ const T& late_argument(const T& arg) {
+#ifdef __AMDGCN__
+  auto p = (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr() + OFFSET;
+  asm volatile("" : "+s"(p));
+  return *(const T*)(const char*)p;
+#else
+  return arg;
+#endif
+}
 __device__ __forceinline__ float bf2f(uint16_t x) { return __uint_as_float((uint32_t)x << 16); }
 __device__ __forceinline__ uint16_t f2bf(float x) { return __builtin_bit_cast(uint16_t, (__bf16)x); }
 
@@ -83,8 +116,8 @@ __device__ __forceinline__ bf16x8 join_halves(u32x2 lo, u32x2 hi) {
   const u32x4 r = {lo[0], lo[1], hi[0], hi[1]};
   return __builtin_bit_cast(bf16x8, r);
 }
+typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-  typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
   bf16x2 p;
   p[0] = (__bf16)lo;
   p[1] = (__bf16)hi;

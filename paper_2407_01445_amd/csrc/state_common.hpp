@@ -50,6 +50,7 @@ struct StateArgs {
   int64_t bstride, b;
   int64_t stride;      // elements between consecutive samples in u_img / u_txt (and the temperature arrays)
   float M, gamma, eps, rho, tau_scale;
+  float inv_M, bM;    // 1 / M; b M: each rounded once, on the host
   int version;
   float *c1, *c2, *dcoef;
   double* red;        // [blocks][2]: per-block sums of the anchors' loss terms and h terms
@@ -145,9 +146,9 @@ __device__ inline float ema_update(float u_old, float g, float gamma) {
 // One side of one anchor: the sum of its exponentials over the contrasts (M g), u^t and the temperature give
 // u^{t+1} (Eq. 1) and the coefficient of Eqs. 2-7.  Every kernel that needs a coefficient forms it here.
 __device__ inline float anchor_coefficient(const StateArgs& a, float sum_e, float u_old, float tau, float* u_new) {
-  const float u = ema_update(u_old, sum_e * (1.0f / a.M), a.gamma);
+  const float u = ema_update(u_old, sum_e * a.inv_M, a.gamma);
   *u_new = u;
-  float c = 1.0f / (((float)a.b * a.M) * (a.eps + u));
+  float c = 1.0f / (a.bM * (a.eps + u));
   if (a.version == FASTCLIP_V0) c /= tau;
   return c;
 }
@@ -182,7 +183,7 @@ __device__ inline SideResult state_side(const StateArgs& a, float sum_e, float s
     o.hterm = h / e;
   } else {
     const float e = a.eps + o.u;
-    const float h = sum_xe * (1.0f / a.M);
+    const float h = sum_xe * a.inv_M;
     const float l = logf(e);
     if (a.version == FASTCLIP_V2) {
       o.gt = a.tau_scale * (l + a.rho - h / (tau * e));
@@ -217,7 +218,7 @@ __device__ inline void state_finish_anchor(const StateArgs& a, int64_t r, const 
       tau_step(a.tau_upd, a.tau_txt + n, a.m_txt + n, a.v_txt ? a.v_txt + n : nullptr, o2.gt);
     }
   }
-  const float invM = 1.0f / a.M;
+  const float invM = a.inv_M;
   if (a.g_img) a.g_img[r] = s[0] * invM;
   if (a.g_txt) a.g_txt[r] = s[2] * invM;
   if (a.u_new_img) a.u_new_img[r] = o1.u;
@@ -229,21 +230,25 @@ __device__ inline void state_finish_anchor(const StateArgs& a, int64_t r, const 
 }
 
 // One side (0: image, 1: text) of local anchor r, whose record is n = idx[r] stride: scatter of u^{t+1}, Eq. 9 (and the
-// temperature step if asked for), optional outputs, the side's terms of the scalars.  The coefficients stay with the caller.
+// temperature step if asked for, from the moments m and v that the caller has gathered), optional outputs, the side's terms of
+// the scalars.  The coefficients stay with the caller.
 template <bool PRECISE>
 __device__ inline void state_finish_side(const StateArgs& a, int side, int64_t r, int64_t n, float sum_e, float sum_xe,
-                                         float u_old, float tau, double* lterm, double* hterm) {
+                                         float u_old, float tau, float m, float v, double* lterm, double* hterm) {
   const SideResult o = state_side<PRECISE>(a, sum_e, sum_xe, u_old, tau);
   (side ? a.u_txt : a.u_img)[n] = o.u;
   if (a.version == FASTCLIP_V2) {
     (side ? a.d_tau_txt : a.d_tau_img)[r] = o.gt;
     if (a.tau_upd.optimizer) {
-      float* pv = side ? a.v_txt : a.v_img;
-      tau_step(a.tau_upd, (side ? a.tau_txt : a.tau_img) + n, (side ? a.m_txt : a.m_img) + n, pv ? pv + n : nullptr, o.gt);
+      const bool two = a.tau_upd.optimizer == FASTCLIP_TAU_ADAMW || a.tau_upd.optimizer == FASTCLIP_TAU_LAMB;
+      tau_step_values(a.tau_upd, tau, m, v, o.gt);
+      if (two) (side ? a.v_txt : a.v_img)[n] = v;
+      (side ? a.m_txt : a.m_img)[n] = m;
+      (side ? a.tau_txt : a.tau_img)[n] = tau;
     }
   }
   float* g_out = side ? a.g_txt : a.g_img;
-  if (g_out) g_out[r] = sum_e * (1.0f / a.M);
+  if (g_out) g_out[r] = sum_e * a.inv_M;
   float* u_out = side ? a.u_new_txt : a.u_new_img;
   if (u_out) u_out[r] = o.u;
   *lterm = o.lterm;

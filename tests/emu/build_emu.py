@@ -35,6 +35,8 @@ def _asm_replacement(m):
         return "emu_dma(uniform_base, lane_byte_off, lds_byte_addr, 16);"
     if "global_load_lds_dword " in t:
         return "emu_dma(uniform_base, lane_byte_off, lds_byte_addr, 4);"
+    if "s_load_dword" in t:                      # arguments into the scalar cache
+        return "(void)w0, (void)w8;"
     if "v_accvgpr_read_b32" in t:
         return "x = in_agpr;"
     if re.search(r'asm volatile\(""', t):         # keeps a value alive, nothing to run
@@ -64,7 +66,8 @@ PLAN_RULES = [
     ("fastclip_api.hip", "  if (wgs >= (cfg.b > 512 ? 256 : 257) &&", '  if (getenv("EMU_WIDE") || wgs >= (cfg.b > 512 ? 256 : 257) &&'),
     ("fastclip_api.hip", "L->wide_strips = tiles > 256 && tiles < 512 && (4 * cfg.b > 3 * cfg.B || L->nparts % 2);",
      "L->wide_strips = " + _forced("tiles > 256 && tiles < 512 && (4 * cfg.b > 3 * cfg.B || L->nparts % 2)", "EMU_WIDE_STRIPS") + ";"),
-    ("kernels_tiles128.hip", "const bool narrow = at64 <= 256;", "const bool narrow = " + _forced("at64 <= 256", "EMU_NARROW") + ";"),
+    ("fc_internal.hpp", "return 2 * ((L.b + 63) / 64) * (int64_t)L.nparts <= 256;",
+     "return " + _forced("2 * ((L.b + 63) / 64) * (int64_t)L.nparts <= 256", "EMU_NARROW") + ";"),
     # fp32 path: tile sizes, plain loops, what is left of a plan that has to fit the static array
     ("fastclip_api.hip", "((cfg.B + 63) / 64) >= 256 ? 64 : 32;", "((cfg.B + 63) / 64) >= " + _forced("256", "EMU_F32_TILES") + " ? 64 : 32;"),
     ("fastclip_api.hip", "  for (int T = 32; T <= 64; T += 32) {",

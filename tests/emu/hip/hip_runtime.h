@@ -91,6 +91,15 @@ extern dim3 blockDim, gridDim;
 #define __fmul_rn(a, b) ((a) * (b))
 static inline float __uint_as_float(uint32_t u) { float f; memcpy(&f, &u, 4); return f; }
 static inline uint32_t __float_as_uint(float f) { uint32_t u; memcpy(&u, &f, 4); return u; }
+template <typename V>
+static inline float emu_fdot2(const V& a, const V& b, float c) {        // bf16 pairs
+  uint32_t x, y;
+  memcpy(&x, &a, 4);
+  memcpy(&y, &b, 4);
+  c = fmaf(__uint_as_float(x << 16), __uint_as_float(y << 16), c);
+  return fmaf(__uint_as_float(x & 0xffff0000u), __uint_as_float(y & 0xffff0000u), c);
+}
+#define __builtin_amdgcn_fdot2_f32_bf16(a, b, c, clamp) emu_fdot2(a, b, c)
 static inline uint64_t wall_clock64() { return 0; }
 static inline unsigned long long atomicCAS(unsigned long long* p, unsigned long long cmp, unsigned long long val) {
   __atomic_compare_exchange_n(p, &cmp, val, false, __ATOMIC_SEQ_CST, __ATOMIC_SEQ_CST);
