@@ -161,25 +161,33 @@ static bool fold_forms_state(int64_t b, int nparts) {
 // 128 x 128-tile path: which contraction, its output tiles, the split of its depth over workgroups, and who runs the state
 // phase.  False: the 256 x 256 tiles take less time (gathered state).
 static bool plan_t128(const fastclip_config& cfg, const Room& room, Layout* L) {
-  const int64_t nA = (cfg.B + 15) / 16, nB = (cfg.b + 15) / 16, cols = (cfg.d + 63) / 64;
   double best_cost = 0.0, in_a_row = 0.0;
   int64_t rounds = 0;
-  for (int64_t rows = 64; rows <= (L->gathered ? 64 : 128); rows += 64) {
-    const int64_t tiles = 2 * ((cfg.b + rows - 1) / rows) * cols;
-    for (int64_t ns = 1; ns <= 16 && ns * 32 <= L->ldE; ++ns) {
+  for (int64_t rows = L->gathered ? 64 : 32; rows <= (L->gathered ? 64 : 128); rows *= 2) {
+    const int64_t cols = rows == 32 ? 32 : 64, depth = rows == 32 ? 32 : 16;      // 32 x 32 tiles: stages of 32
+    const int64_t nA = (cfg.B + depth - 1) / depth, nB = (cfg.b + depth - 1) / depth;
+    const int64_t tiles = 2 * ((cfg.b + rows - 1) / rows) * ((cfg.d + cols - 1) / cols);
+    for (int64_t ns = 1; ns <= (rows == 32 ? 1 : 16) && ns * 32 <= L->ldE; ++ns) {
+      if (rows == 32 && tiles > 256) break;
       if (ns > 1 && (tiles * ns > 2048 || ns * tiles * rows * 64 * (int64_t)sizeof(float) > room.split_bytes)) break;
       const int64_t sA = (nA + ns * 8 - 1) / (ns * 8), sB = (nB + ns * 8 - 1) / (ns * 8);
-      const int64_t nq = sB * 128 < cfg.b ? sB * 128 : cfg.b;
+      const int64_t nq = sB * 8 * depth < cfg.b ? sB * 8 * depth : cfg.b;
       const int64_t r = (tiles * ns + 255) / 256;
       // The state phase inside the contraction: every workgroup adds up the partial sums of its rows and of its q's, at the 57
       // bytes per clock of a compute unit, which takes less than a launch of its own (4.7 us) while it happens once.
       const bool fused = r == 1 || (rows == 64 && nq <= 256 && L->nparts <= 64);
       const double coef_us = (double)((nq + 2 * rows) * L->nparts * 4) / (57.0 * 2400.0);
       const double stages = (L->gathered ? 1.4 : 1.0) * (double)sA + (double)sB;   // a wave's, 16 deep; 1.4: with a second strip
-      // us: start, coefficients, sum over the waves and end of a workgroup; a 16-deep stage of its eight waves (the load path of
-      // a compute unit: 32 KiB, 48 for 128 rows or with a second strip); partial results; the state phase as a launch of its own
-      const double cost = (double)r * (rows == 64 ? 8.0 + 0.27 * stages : 9.5 + 0.38 * stages) +
-                          (ns > 1 ? 2.3 + 0.1 * (double)ns : 0.0) + (fused ? (nq > 256 || rows > 64 ? coef_us : 0.0) : 4.7);
+      // compute units left for workgroups that finish the anchors?
+      const bool full = (tiles * ns + 7) / 8 * 8 + (cfg.b + 255) / 256 > 256;
+      // us: start, coefficients, sum over the waves and end of a workgroup; a stage of its eight waves (the load path of a
+      // compute unit: 32 KiB, 48 for 128 rows or with a second strip; 16 deep, on 32 x 32 tiles 32 deep, for which latency is the
+      // bound); partial results; the state phase as a launch of its own or by the workgroups of the first columns.  Steps on
+      // 32 x 32 / 64 x 64 tiles (their best split), us, width 512: 128 of 1024 13.7 / 16.9, 256 of 2048 18.1 / 19.8, 256 of 4096
+      // 23.3 / 23.3, 128 of 4096 22.4 / 20.5, 256 of 8192 36.7 / 30.6; width 256: 512 of 512 15.2 / 16.3, 512 of 2048 18.9 / 20.3,
+      // 512 of 4096 25.6 / 25.4; 128 of 1024 at 1024 19.0 / 20.1.
+      const double cost = (double)r * (rows == 32 ? 4.1 + 0.62 * stages : (rows == 64 ? 8.0 + 0.27 * stages : 9.5 + 0.38 * stages)) +
+                          (ns > 1 ? 2.3 + 0.25 * (double)ns : 0.0) + (fused ? (nq > 256 || rows > 64 ? coef_us : 0.0) + (full ? 1.2 : 0.0) : 4.7);
       if (best_cost == 0.0 || cost < best_cost) {
         best_cost = cost;
         rounds = r; in_a_row = (double)r * stages;
@@ -350,8 +358,13 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
     L->own_prep = (tiles + 255) / 256 * rows * cfg.d <= 200000;
   }
   if (!L->t128) L->fused_state = L->bf16 && fold_forms_state(cfg.b, L->nparts);
-  // scalar partials: t128 without the fold leaves those of 64 anchors of one side, in whole groups of 256 anchors
-  const int64_t out_blocks = L->t128 && !L->wide ? 8 * ((cfg.b + 255) / 256) : 0;
+  // scalar partials: t128 without the fold leaves those of its finishing waves, eight of a workgroup of 256 anchors or the tiles'
+  int64_t out_blocks = 0;
+  if (L->t128 && !L->wide) {
+    const int64_t of_tiles = t128_finishing_waves(L->out_rows) * ((cfg.b + L->out_rows - 1) / L->out_rows);
+    out_blocks = 8 * ((cfg.b + 255) / 256);
+    out_blocks = of_tiles > out_blocks ? of_tiles : out_blocks;
+  }
   L->nstate_blocks = L->fused_state ? (int)(out_blocks ? out_blocks : (cfg.b + 63) / 64) : state_blocks(cfg.b, L->nparts);
   L->diag = take(fb); L->tau1 = take(fb); L->tau2 = take(fb); L->k1 = take(fb); L->k2 = take(fb);
   L->uold1 = take(fb); L->uold2 = take(fb);
@@ -368,7 +381,7 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
       if (L->nsplit > 1)
         L->Opart[0] = take(sizeof(float) * (size_t)L->nsplit * 2 * round_up((size_t)cfg.b, 128) * round_up((size_t)cfg.d, 128));
     } else if (L->t128) {     // arrival counters of the output tiles and of the scalars; [2][tiles][nsplit][64 x 64] floats
-      const int64_t tiles = 2 * (L->out_rows / 64) * ((cfg.b + L->out_rows - 1) / L->out_rows) * ((cfg.d + 63) / 64);
+      const int64_t tiles = L->nsplit > 1 ? 2 * (L->out_rows / 64) * ((cfg.b + L->out_rows - 1) / L->out_rows) * ((cfg.d + 63) / 64) : 0;
       L->narrived = (int)tiles + 1;
       L->arrived = take(sizeof(unsigned) * (size_t)L->narrived);
       if (L->nsplit > 1) L->Opart[0] = take(sizeof(float) * (size_t)L->nsplit * (size_t)tiles * 64 * 64);

@@ -53,7 +53,7 @@ struct Layout {
   int nsplit;        // split of the contraction over its column range
   int64_t kslice;    // 32-deep stages per split (fp32 path: stages of the gradient kernel's depth)
   int nstate_blocks; // scalar partials: one per block of the state kernel, per diagonal block of the fused fold, or (t128 with
-                     // fused_state) per 64 anchors and side
+                     // fused_state) per wave that finishes anchors
   int fused_state;   // 1: MFMA path, few anchors and few partial sums: the fold kernel (t128: the contraction) runs the
                      //    state phase itself
   int gathered;      // 1: contrast-side estimator over every global anchor (FASTCLIP_GATHERED_STATE and b < B)
@@ -63,7 +63,7 @@ struct Layout {
   int t128;          // 1: MFMA path on 128 x 128 strip tiles (kernels_tiles128.hip); nparts counts 128-column tiles, the
                      //    contraction's depth is cut into nsplit x 8 slices of 16-deep stages, and with one split there
                      //    are no partial results
-  int out_rows;      // t128 without wide: rows of an output tile of the contraction, 64 or 128
+  int out_rows;      // t128 without wide: rows of an output tile of the contraction, 32, 64 or 128
   int wide_strips;   // wide: the strips are k_strips_wide128_bf16
   int own_prep;      // t128: k_strips_t128_bf16 prepares its anchors itself, k_prep is not launched
   int wide;          // t128: the contraction is k_contract_wide128_bf16 (kernels_wide128.hip) behind the fold; nsplit /
@@ -99,6 +99,9 @@ struct Layout {
 // 1024 30.7 -> 30.1), else 128: beyond one round two tiles of 64 take longer than one of 128 (3.5 us of either are its start
 // and end).
 static inline bool strips_t128_narrow(const Layout& L) { return 2 * ((L.b + 63) / 64) * (int64_t)L.nparts <= 256; }
+
+// Waves of k_contract_t128_bf16 that finish the anchors of an output tile where no workgroup of its own does.
+static inline int t128_finishing_waves(int out_rows) { return out_rows == 32 ? 2 : out_rows / 32; }
 
 fastclip_status validate(const fastclip_config* cfg, const fastclip_buffers* bufs);
 void make_layout(const fastclip_config& cfg, Layout* L);

@@ -467,13 +467,15 @@ void launch_strips_t128_bf16(const StepCtx& c) {
 }
 
 // ----------------------------------------------------------------------------------------------------------------
-constexpr int kO = 64;                          // columns of an output tile; its rows: 64 MB
+// Output tiles of 32 RB rows: RB = 1 (32 x 32), 2 (64 x 64) or 4 (128 x 64).  A wave's stage is KS 16-deep steps, NA KiB of the
+// strip, 2 KiB of X and, with gathered state, the second strip; as many stages as fit 160 KiB beside the coefficients.
+template <int RB> constexpr int kCB = RB == 1 ? 1 : 2;      // blocks of 32 columns
+template <int RB> constexpr int kKS = RB == 1 ? 2 : 1;
+template <int RB> constexpr int kNA = RB * kKS<RB>;
+template <int RB, bool G> constexpr int kWStage = 1024 * (kNA<RB> * (G ? 2 : 1) + 2);
+template <int RB, bool G> constexpr int kWSlots = RB < 4 && !G ? 4 : 3;
+template <int RB, bool G> constexpr int kWRing = 8 * kWSlots<RB, G> * kWStage<RB, G>;   // 128 / 144 KiB
 constexpr int kMaxQ = (kMaxLocalQ + 511) / 512;   // local anchors per thread whose coefficients a workgroup forms
-// a wave's stage: 16 deep, 2 MB KiB of the strip, 2 KiB of X and, with gathered state, 2 KiB of the second strip; as many as
-// fit 160 KiB beside the coefficients
-template <int MB, bool G> constexpr int kWStage = 2048 * (MB + 1 + (G ? 1 : 0));
-template <int MB, bool G> constexpr int kWSlots = MB == 1 && !G ? 4 : 3;
-template <int MB, bool G> constexpr int kWRing = 8 * kWSlots<MB, G> * kWStage<MB, G>;   // 128 / 144 KiB
 
 struct T128Job {
   const bf16_t* E;       // fragment-ordered strip of this side
@@ -495,7 +497,7 @@ struct T128Args {
   int64_t nCB;
   int tiles_m, tiles_n, nsplit;
   unsigned inv_tiles, inv_tiles_n;      // reciprocal(2 tiles_m tiles_n), reciprocal(tiles_n)
-  int nA, nB;            // 16-deep stages over the contrasts / over the local anchors
+  int nA, nB;            // stages over the contrasts / over the local anchors
   int sliceA, sliceB;    // ... per wave
   double* part;          // nsplit > 1: [tile][split][64 x 64 floats as pairs]
   unsigned* arrived;     // per 64 rows of an output tile; 0 before the launch
@@ -575,10 +577,11 @@ __device__ __forceinline__ bool t128_finish(const T128Args& g, const StateArgs& 
   return last_to_arrive(g.scalars_arrived, (unsigned)g.finishers, flag) && tid < 64;
 }
 
-template <int MB, bool GATHERED>
-__device__ __forceinline__ bool t128_tile(const T128Args& g, const StateArgs& a, char* ring, float* crow, float (*drow)[64 * MB],
+template <int RB, bool GATHERED>
+__device__ __forceinline__ bool t128_tile(const T128Args& g, const StateArgs& a, char* ring, float* crow, float (*drow)[32 * RB],
                                           float* cq, int* flag) {
-  constexpr int kM = 64 * MB, kStageB = kWStage<MB, GATHERED>, kSlotsW = kWSlots<MB, GATHERED>, kX = 2048 * MB, kF = kX + 2048;
+  constexpr int kM = 32 * RB, kStageB = kWStage<RB, GATHERED>, kSlotsW = kWSlots<RB, GATHERED>;
+  constexpr int CB = kCB<RB>, KS = kKS<RB>, NA = kNA<RB>, kD16 = 16 * KS, kO = 32 * CB, kX = 1024 * NA, kF = kX + 2048;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 31, hk = lane >> 5;
   // Workgroups that share an XCD (id mod 8) take neighbours in the order split, side, row tile, column tile: the same slice of
@@ -594,10 +597,10 @@ __device__ __forceinline__ bool t128_tile(const T128Args& g, const StateArgs& a,
   const int B = __builtin_amdgcn_readfirstlane(g.B), ldx = __builtin_amdgcn_readfirstlane((int)J.ldx);
   const bf16_t* X = wave_uniform(J.X);
   const int d = __builtin_amdgcn_readfirstlane(g.d);
-  const int qbase = split * 8 * g.sliceB * 16;       // this workgroup's local anchors q
-  int nq = g.b - qbase < 8 * g.sliceB * 16 ? g.b - qbase : 8 * g.sliceB * 16;
+  const int qbase = split * 8 * g.sliceB * kD16;     // this workgroup's local anchors q
+  int nq = g.b - qbase < 8 * g.sliceB * kD16 ? g.b - qbase : 8 * g.sliceB * kD16;
   nq = nq < 0 ? 0 : nq;
-  const int nq16 = (nq + 15) & ~15;                  // coefficients that the stages over the local anchors read
+  const int nq16 = (nq + kD16 - 1) & ~(kD16 - 1);    // coefficients that the stages over the local anchors read
 
   // ---- operand requests
   const int unit = split * 8 + wave;
@@ -607,63 +610,67 @@ __device__ __forceinline__ bool t128_tile(const T128Args& g, const StateArgs& a,
   const uint32_t wring = lds_addr(ring) + (uint32_t)(wave * kSlotsW * kStageB);
   const char* wslot = ring + wave * kSlotsW * kStageB;
   // X: two wave loads of 8 rows x 128 bytes; 16-byte piece p of stage row k at piece p ^ (4 ((k >> 1) & 1)), so that the 4 rows x
-  // 64 bytes that a transposing read touches cover a bank window.  Rows wrap at B; pieces beyond the width are fetched as the
-  // row's first of the tile and reach no output.
+  // 64 bytes that a transposing read touches cover a bank window.  RB = 1: of 16 rows x 64 bytes, which do as they are.  Rows
+  // wrap at B; pieces beyond the width are fetched as the row's first of the tile and reach no output.
   int grow[2];
   uint32_t xoff[2];
-  const uint32_t wrap = (uint32_t)(B * ldx) * 2u, next_rows = (uint32_t)(16 * ldx) * 2u;
-  auto open_rows = [&](int col) {              // columns col .. col + 15
+  const uint32_t wrap = (uint32_t)(B * ldx) * 2u, next_rows = (uint32_t)(kD16 * ldx) * 2u;
+  auto open_rows = [&](int col) {              // columns col .. col + kD16 - 1
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const int k = 8 * i + (lane >> 3), pc = (lane & 7) ^ (((k >> 1) & 1) << 2);
-      int r = g.off + col + k;                 // below 2 B + 16: a division would take longer
+      const int k = RB == 1 ? 16 * i + (lane >> 2) : 8 * i + (lane >> 3);
+      const int pc = RB == 1 ? lane & 3 : (lane & 7) ^ (((k >> 1) & 1) << 2);
+      int r = g.off + col + k;                 // below 2 B + 32: a division would take longer
       while (r >= B) r -= B;
       grow[i] = r;
       xoff[i] = (uint32_t)(r * ldx + (n0 + pc * 8 < d ? n0 + pc * 8 : n0)) * 2u;
     }
   };
-  // Strip operand of the first sum: the fragments (m0 / 32 + i, stage), 1 KiB each.  Of the second: 16 anchors q x 64 columns r as
-  // 128 chunks of 16 bytes, [column block][half][q] with q at q ^ (4 half) ^ (8 (column block & 1)), again for the transposing
-  // reads' bank windows.
+  // Strip operand of the first sum: the fragments (m0 / 32 + i, stage), 1 KiB each; RB = 1: (m0 / 32, 2 stage + i).  Of the second:
+  // 16 KS anchors q x kM columns r as chunks of 16 bytes, [column block][half][q] with q at q ^ (4 half) ^ (8 (column block & 1)),
+  // again for the transposing reads' bank windows.
   const char* src = nullptr;                   // uniform; stage `at` comes from src + woff[i]
-  uint32_t woff[2 * MB];
+  uint32_t woff[NA];
   const uint32_t row_block = (uint32_t)g.nCB * 1024u;
   int at = 0;                                  // next stage to request
   auto open_own = [&]() {
-    src = wave_uniform((const char*)J.E + ((int64_t)(m0 >> 5) * g.nCB + A0) * 1024);
+    src = wave_uniform((const char*)J.E + ((int64_t)(m0 >> 5) * g.nCB + A0 * KS) * 1024);
 #pragma unroll
-    for (int i = 0; i < 2 * MB; ++i) woff[i] = (uint32_t)(lane * 16) + (uint32_t)i * row_block;
-    open_rows(A0 * 16);
+    for (int i = 0; i < NA; ++i) woff[i] = (uint32_t)(lane * 16) + (uint32_t)i * (RB == 1 ? 1024u : row_block);
+    open_rows(A0 * kD16);
   };
-  const char* src_other = wave_uniform((const char*)J.Eo + ((int64_t)(Q0 >> 1) * g.nCB + (m0 >> 4)) * 1024 + (Q0 & 1) * 256);
+  const char* src_other = wave_uniform((const char*)J.Eo + ((int64_t)(KS == 2 ? Q0 : Q0 >> 1) * g.nCB + (m0 >> 4)) * 1024 +
+                                       (KS == 2 ? 0 : (Q0 & 1) * 256));
   auto open_other = [&]() {
 #pragma unroll
-    for (int i = 0; i < 2 * MB; ++i) {
-      const int cb = 2 * i + (lane >> 5), h = (lane >> 4) & 1, q = (lane & 15) ^ (4 * h) ^ (8 * (cb & 1));
+    for (int i = 0; i < NA; ++i) {
+      const int cb = RB == 1 ? i : 2 * i + (lane >> 5), h = RB == 1 ? lane >> 5 : (lane >> 4) & 1;
+      const int q = (lane & (kD16 - 1)) ^ (4 * h) ^ (8 * (cb & 1));
       woff[i] = (uint32_t)((cb * 64 + q + 32 * h) * 16);
     }
-    open_rows(Q0 * 16);
+    open_rows(Q0 * kD16);
   };
   const int64_t to_f = GATHERED ? (const char*)wave_uniform(J.F) - (const char*)wave_uniform(J.E) : 0;
   uint32_t fill = wring;                       // slot of stage `at`
   auto request = [&]() {
 #pragma unroll
-    for (int i = 0; i < 2 * MB; ++i) dma16(src, woff[i], fill + (uint32_t)(i * 1024));
+    for (int i = 0; i < NA; ++i) dma16(src, woff[i], fill + (uint32_t)(i * 1024));
     if (GATHERED && at < nAw) {
 #pragma unroll
-      for (int i = 0; i < 2 * MB; ++i) dma16(src + to_f, woff[i], fill + (uint32_t)(kF + i * 1024));
+      for (int i = 0; i < NA; ++i) dma16(src + to_f, woff[i], fill + (uint32_t)(kF + i * 1024));
     }
     dma16(X, xoff[0], fill + (uint32_t)kX);
     dma16(X, xoff[1], fill + (uint32_t)(kX + 1024));
     fill = fill + kStageB == wring + kSlotsW * kStageB ? wring : fill + kStageB;
     ++at;
-    src = at == nAw ? src_other : src + (at < nAw ? 1024u : (((Q0 + at - nAw) & 1) ? 256u : row_block - 256u));
+    src = at == nAw ? src_other
+                    : src + (at < nAw ? 1024u * KS : (KS == 2 ? row_block : (((Q0 + at - nAw) & 1) ? 256u : row_block - 256u)));
     if (at == nAw) {
       open_other();
     } else {
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        grow[j] += 16; xoff[j] += next_rows;
+        grow[j] += kD16; xoff[j] += next_rows;
         if (grow[j] >= B) { grow[j] -= B; xoff[j] -= wrap; }
       }
     }
@@ -679,9 +686,9 @@ __device__ __forceinline__ bool t128_tile(const T128Args& g, const StateArgs& a,
   };
   const bool fused = a.fused;
   const bool finisher = fused && g.finishers == 0 && side == 0 && tn == 0 && split == 0;
-  constexpr int kFin = 2 * MB;                       // a finisher's last waves finish 64 anchors each: image sides, then text sides
-  const int fw = wave - (8 - kFin), fside = fw >= MB, frow = (fside ? fw - MB : fw) * 64 + lane;
-  const bool finishing = finisher && fw >= 0 && m0 + frow < g.b;
+  constexpr int kFin = RB == 1 ? 2 : RB;             // a finisher's last waves finish a side of (up to) 64 anchors each, images first
+  const int fw = wave - (8 - kFin), fside = fw >= kFin / 2, frow = (fside ? fw - kFin / 2 : fw) * 64 + lane;
+  const bool finishing = finisher && fw >= 0 && frow < kM && m0 + frow < g.b;
   double lterm = 0.0, hterm = 0.0;
   if (fused) {
     // Sums of the q's: groups of 256 anchors, one wave load per group and partial sum, dealt out to the waves: wave w takes group
@@ -695,7 +702,10 @@ __device__ __forceinline__ bool t128_tile(const T128Args& g, const StateArgs& a,
     // Addresses are a wave-uniform base and a 32-bit byte offset per lane: what bounds this part is the number of instructions
     // (with 64-bit addresses per lane 6500 cycles from the first request to the sums in LDS).
     auto at = [](const float* base, uint32_t bytes) { return *(const float*)((const char*)base + bytes); };
-    const int rside = wave >= MB, row = tid & (kM - 1);      // tid < 2 kM: side and row of a coefficient
+    const int rside = RB == 1 ? hk : wave >= RB / 2, row = tid & (kM - 1);      // tid < 2 kM: side and row of a coefficient
+    auto one_of = [&](const float* img, const float* txt) {       // RB = 1: the side differs between lanes
+      return RB == 1 ? (rside ? txt : img) : wave_uniform(rside ? txt : img);
+    };
     const bool rows_here = tid < 2 * kM && m0 + row < g.b;
     int64_t fn = 0;                                  // dataset index
     float fu = 0.f, ft = 1.f, fm = 0.f, fv = 0.f, ur = 0.f, tr = 1.f, uq[kMaxQ], tq[kMaxQ];
@@ -706,10 +716,10 @@ __device__ __forceinline__ bool t128_tile(const T128Args& g, const StateArgs& a,
       fu = at(wave_uniform(fside ? a.uold2 : a.uold1), m * 4u);
       ft = at(wave_uniform(fside ? a.tau2 : a.tau1), m * 4u);
     }
-    if (wave < 2 * MB) {
+    if (wave < RB) {
       const uint32_t m = (uint32_t)(m0 + row) < last_anchor ? (uint32_t)(m0 + row) : last_anchor;
-      ur = at(wave_uniform(rside ? a.uold2 : a.uold1), m * 4u);
-      tr = at(wave_uniform(rside ? a.tau2 : a.tau1), m * 4u);
+      ur = at(one_of(a.uold1, a.uold2), m * 4u);
+      tr = at(one_of(a.tau1, a.tau2), m * 4u);
     }
     const float *u_other = wave_uniform(side ? a.uold1 : a.uold2), *t_other = wave_uniform(side ? a.tau1 : a.tau2);
     const int j0 = (tid - 2 * kM) & 511, jw = (wave * 64 - 2 * kM) & 511;    // q's behind the threads that have the rows
@@ -727,13 +737,15 @@ __device__ __forceinline__ bool t128_tile(const T128Args& g, const StateArgs& a,
     const char* sums = (const char*)wave_uniform(a.sums);
     auto words_at = [&](int quantity, int m) { return (uint32_t)(quantity * nparts * bs + (m < bs ? m : bs - 4)) * 4u; };
     auto words = [&](int pt, uint32_t off) { return *(const f32x4*)(sums + (uint32_t)(pt * bs) * 4u + off); };
-    // partial sums wave, wave + 8, .. of the rows (MB = 1: a lane's quantity is lane / 16; MB = 2: 2 (lane / 32) + i), and
+    // partial sums wave, wave + 8, .. of the rows (a lane's quantity: lane / 16; RB = 4: 2 (lane / 32) + i; RB = 1: lane / 8 % 4), and
     // wave / groups_w, + slices, .. of the wave's group of q's: up to 16 of the latter in flight at once
-    uint32_t pr[MB];
-    f32x4 sr[MB];
+    constexpr int NR = RB == 4 ? 2 : 1;
+    const int rq0 = RB == 4 ? 2 * (lane >> 5) : (RB == 1 ? (lane >> 3) & 3 : lane >> 4), r4 = 4 * (lane & (8 * RB - 1));
+    uint32_t pr[NR];
+    f32x4 sr[NR];
 #pragma unroll
-    for (int i = 0; i < MB; ++i) {
-      pr[i] = words_at(MB == 1 ? lane >> 4 : 2 * (lane >> 5) + i, m0 + 4 * (lane & (16 * MB - 1)));
+    for (int i = 0; i < NR; ++i) {
+      pr[i] = words_at(rq0 + i, m0 + r4);
       sr[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -745,16 +757,16 @@ __device__ __forceinline__ bool t128_tile(const T128Args& g, const StateArgs& a,
       // the next N partial sums of the q's, and the rows' that come up meanwhile (a slices-th as many)
       auto sweep = [&](auto count, int pt) {
         constexpr int N = decltype(count)::value;
-        f32x4 vq[N], vr[MB][N];
+        f32x4 vq[N], vr[NR][N];
 #pragma unroll
         for (int e = 0; e < N; ++e) {
           vq[e] = zero;
 #pragma unroll
-          for (int i = 0; i < MB; ++i) vr[i][e] = zero;
+          for (int i = 0; i < NR; ++i) vr[i][e] = zero;
           if (pt + e * slices <= last_part) vq[e] = words(pt + e * slices, pq);
           if ((e << 3) < (N << (3 - lg)) && ptr + 8 * e <= last_part) {
 #pragma unroll
-            for (int i = 0; i < MB; ++i)
+            for (int i = 0; i < NR; ++i)
               if (i == 0 || finisher) vr[i][e] = words(ptr + 8 * e, pr[i]);
           }
         }
@@ -763,7 +775,7 @@ __device__ __forceinline__ bool t128_tile(const T128Args& g, const StateArgs& a,
         for (int e = 0; e < N; ++e) {
           sq += vq[e];
 #pragma unroll
-          for (int i = 0; i < MB; ++i) sr[i] += vr[i][e];
+          for (int i = 0; i < NR; ++i) sr[i] += vr[i][e];
         }
         ptr += ((N << (3 - lg)) + 7) & ~7;
       };
@@ -776,8 +788,7 @@ __device__ __forceinline__ bool t128_tile(const T128Args& g, const StateArgs& a,
       if (gr < groups) *(f32x4*)(psum(wave) + 4 * kM + gi * 256 + 4 * lane) = sq;
     }
 #pragma unroll
-    for (int i = 0; i < MB; ++i)
-      *(f32x4*)(psum(wave) + (MB == 1 ? lane >> 4 : 2 * (lane >> 5) + i) * kM + 4 * (lane & (16 * MB - 1))) = sr[i];
+    for (int i = 0; i < NR; ++i) *(f32x4*)(psum(wave) + (rq0 + i) * kM + r4) = sr[i];
     if (finisher && fw >= 0) {
       const StateArgs& la = late_argument<kStateAt>(a);
       if (la.version == FASTCLIP_V2 && la.tau_upd.optimizer) {      // the temperature's moments, by now addressable
@@ -857,37 +868,40 @@ __device__ __forceinline__ bool t128_tile(const T128Args& g, const StateArgs& a,
   }
 
   // ---- main loop
-  f32x16 acc[2 * MB][2];
+  f32x16 acc[RB][CB];
 #pragma unroll
-  for (int i = 0; i < 2 * MB; ++i)
+  for (int i = 0; i < RB; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < CB; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
   // lane offsets of the operand reads inside a slot: transposing reads take 4 rows x 16 columns per group of 16 lanes, source
   // lane s row s / 4, columns 4 (s % 4) ..; the halves h = 0, 1 of a read are 8 rows apart
   const int s16 = lane & 15, c16 = (lane >> 4) & 1;
-  uint32_t rx[2], rq[2 * MB][2];
+  uint32_t rx[2], rq[NA][2];                          // of column block t / row block t; RB = 1: of 16-deep step t
+  constexpr uint32_t kXHalf = RB == 1 ? 512u : 1024u;
   const int k0 = 4 * hk + (s16 >> 2);                 // 8 rows further on: the same swizzles
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     const int nl = t * 32 + c16 * 16 + 4 * (s16 & 3);
-    rx[t] = (uint32_t)(kX + k0 * 128 + (((nl >> 3) ^ (((k0 >> 1) & 1) << 2)) << 4) + ((nl & 7) << 1));
+    rx[t] = RB == 1 ? (uint32_t)(kX + (16 * t + k0) * 64 + (nl & 31) * 2)
+                    : (uint32_t)(kX + k0 * 128 + (((nl >> 3) ^ (((k0 >> 1) & 1) << 2)) << 4) + ((nl & 7) << 1));
   }
 #pragma unroll
-  for (int t = 0; t < 2 * MB; ++t) {
-    const int cb = 2 * t + c16, r4 = s16 & 3, hh = r4 & 1;
+  for (int t = 0; t < NA; ++t) {
+    const int cb = RB == 1 ? c16 : 2 * t + c16, r4 = s16 & 3, hh = r4 & 1;
 #pragma unroll
     for (int h = 0; h < 2; ++h)
-      rq[t][h] = (uint32_t)(cb * 512 + hh * 256 + ((8 * h + k0) ^ (4 * hh) ^ (8 * (cb & 1))) * 16 + (r4 >> 1) * 8);
+      rq[t][h] = (uint32_t)((cb * 2 + hh) * (16 * kD16) +
+                            (((RB == 1 ? 16 * t : 0) + 8 * h + k0) ^ (4 * hh) ^ (8 * (cb & 1))) * 16 + (r4 >> 1) * 8);
   }
   auto tr = [](uint32_t addr) {
     return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(uintptr_t)addr));
   };
-  float inv_c[2 * MB];                                // GATHERED: 1 / c_own of the operand's rows (lanes run over rows)
+  float inv_c[RB];                                    // GATHERED: 1 / c_own of the operand's rows (lanes run over rows)
   if constexpr (GATHERED) {
 #pragma unroll
-    for (int t = 0; t < 2 * MB; ++t) {
+    for (int t = 0; t < RB; ++t) {
       const float c = crow[t * 32 + lr];
       inv_c[t] = m0 + t * 32 + lr < g.b ? 1.0f / c : 0.f;
     }
@@ -897,20 +911,20 @@ __device__ __forceinline__ bool t128_tile(const T128Args& g, const StateArgs& a,
   // hide the reads' latency, and the products run on into the next stage's wait.
   auto run = [&](auto other_side, int i0, int i1) {
     constexpr bool OTHER = decltype(other_side)::value;
-    const float* c = cq + (Q0 * 16 - qbase) + 4 * hk;      // c_other[q], two runs of four q per lane and stage
+    const float* c = cq + (Q0 * kD16 - qbase) + 4 * hk;    // c_other[q], two runs of four q per lane and 16-deep step
     for (int i = i0; i < i1; ++i) {
-      // stage i has landed: at most the younger ones, 2 MB + 2 loads each (with a second strip two more), may be in flight
+      // stage i has landed: at most the younger ones, NA + 2 loads each (with a second strip two more), may be in flight
       if (kSlotsW == 4 && at - i == 3) __builtin_amdgcn_s_waitcnt(0x0f78);
       else if (at - i == 2 && GATHERED && i + 1 < nAw) __builtin_amdgcn_s_waitcnt(0x0f76);
-      else if (at - i == 2) __builtin_amdgcn_s_waitcnt(MB == 1 ? 0x0f74 : 0x0f76);
+      else if (at - i == 2) __builtin_amdgcn_s_waitcnt(NA == 2 ? 0x0f74 : 0x0f76);
       else __builtin_amdgcn_s_waitcnt(0x0f70);
       __builtin_amdgcn_wave_barrier();
       FC_FENCE();
-      u32x4 w[2 * MB];
-      u32x4 wf[GATHERED && !OTHER ? 2 * MB : 1];
+      u32x4 w[NA];
+      u32x4 wf[GATHERED && !OTHER ? NA : 1];
       u32x2 xl[2], xh[2];
 #pragma unroll
-      for (int t = 0; t < 2 * MB; ++t) {
+      for (int t = 0; t < NA; ++t) {
         if constexpr (!OTHER) {
           w[t] = *(const u32x4*)(wslot + (slot - wring) + t * 1024 + lane * 16);
           if constexpr (GATHERED) wf[t] = *(const u32x4*)(wslot + (slot - wring) + kF + t * 1024 + lane * 16);
@@ -922,17 +936,21 @@ __device__ __forceinline__ bool t128_tile(const T128Args& g, const StateArgs& a,
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         xl[t] = tr(slot + rx[t]);
-        xh[t] = tr(slot + rx[t] + 1024u);
+        xh[t] = tr(slot + rx[t] + kXHalf);
       }
-      f32x4 cl, ch;
-      if constexpr (OTHER) { cl = *(const f32x4*)c; ch = *(const f32x4*)(c + 8); c += 16; }
+      f32x4 cl[KS], ch[KS];
+      if constexpr (OTHER) {
+#pragma unroll
+        for (int k = 0; k < KS; ++k) { cl[k] = *(const f32x4*)(c + 16 * k); ch[k] = *(const f32x4*)(c + 16 * k + 8); }
+        c += kD16;
+      }
       slot = slot + kStageB == wring + kSlotsW * kStageB ? wring : slot + kStageB;
       FC_PIN();
       if (at < nst) request();
       wave_reads_done();                          // the stage's slot may be filled again
       if constexpr (GATHERED && !OTHER) {
 #pragma unroll
-        for (int t = 0; t < 2 * MB; ++t)
+        for (int t = 0; t < NA; ++t)
 #pragma unroll
           for (int e = 0; e < 4; ++e)
             w[t][e] = pack_bf16x2(fmaf(__uint_as_float(wf[t][e] << 16), inv_c[t], __uint_as_float(w[t][e] << 16)),
@@ -940,27 +958,30 @@ __device__ __forceinline__ bool t128_tile(const T128Args& g, const StateArgs& a,
       }
       if constexpr (OTHER) {
 #pragma unroll
-        for (int t = 0; t < 2 * MB; ++t)
+        for (int t = 0; t < NA; ++t)
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const float c0 = e < 2 ? cl[2 * e] : ch[2 * e - 4], c1 = e < 2 ? cl[2 * e + 1] : ch[2 * e - 3];
+            const int k = RB == 1 ? t : 0;
+            const float c0 = e < 2 ? cl[k][2 * e] : ch[k][2 * e - 4], c1 = e < 2 ? cl[k][2 * e + 1] : ch[k][2 * e - 3];
             w[t][e] = pack_bf16x2(__uint_as_float(w[t][e] << 16) * c0, __uint_as_float(w[t][e] & 0xffff0000u) * c1);
           }
       }
 #pragma unroll
-      for (int t = 0; t < 4 * MB; ++t)
-        acc[t >> 1][t & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w[t >> 1]),
-                                                                      join_halves(xl[t & 1], xh[t & 1]), acc[t >> 1][t & 1], 0, 0, 0);
+      for (int t = 0; t < 2 * RB; ++t) {
+        const int wt = RB == 1 ? t : t >> 1, ti = RB == 1 ? 0 : t >> 1, tj = RB == 1 ? 0 : t & 1;
+        acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w[wt]),
+                                                              join_halves(xl[t & 1], xh[t & 1]), acc[ti][tj], 0, 0, 0);
+      }
     }
   };
   run(std::false_type{}, 0, nAw);
 #pragma unroll
-  for (int ti = 0; ti < 2 * MB; ++ti)
+  for (int ti = 0; ti < RB; ++ti)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const f32x4 c = *(const f32x4*)(crow + ti * 32 + 8 * q + 4 * hk);
 #pragma unroll
-      for (int tj = 0; tj < 2; ++tj)
+      for (int tj = 0; tj < CB; ++tj)
 #pragma unroll
         for (int v = 0; v < 4; ++v) acc[ti][tj][4 * q + v] *= c[v];
     }
@@ -977,92 +998,122 @@ __device__ __forceinline__ bool t128_tile(const T128Args& g, const StateArgs& a,
       scalars_before = __hip_atomic_fetch_add(lg.scalars_arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   float* out = const_cast<float*>(wave_uniform(side ? lg.job[1].out : lg.job[0].out));
-  // ---- the eight waves' tiles are added up, 64 rows at a time: wave w finishes block w / 2 of them, its rows 16 (w % 2) .. + 15
-  const int rl = (wave >> 2) * 32 + (wave & 1) * 16 + 4 * hk;          // row of e = 0; e = 4: 8 further on
-  const int n = n0 + ((wave >> 1) & 1) * 32 + lr;
-  const bool whole = m0 + kM <= lg.b && n0 + kO <= d;
+  if constexpr (RB == 1) {
+    // 32 x 32: a thread finishes two rows of a column, values 2 (lane & 1) .. of word `wave / 2` of lane 32 (wave & 1) + lane / 2
+    const int row0 = 8 * (wave >> 1) + 4 * (wave & 1) + 2 * (lane & 1), n = n0 + (lane >> 1);
+    bf16_t xd[2];
+    float dc[2];
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    const int row0 = mb * 64 + rl;
-    bf16_t xd[8];                              // the diagonal terms' rows, requested ahead of the sums
-    f32x4 dc[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) dc[h] = *(const f32x4*)(drow[0] + row0 + 8 * h) + *(const f32x4*)(drow[1] + row0 + 8 * h);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      int m = m0 + row0 + 8 * (e >> 2) + (e & 3);
-      m = m < lg.b ? m : lg.b - 1;
+    for (int e = 0; e < 2; ++e) {
+      const int m = m0 + row0 + e < lg.b ? m0 + row0 + e : lg.b - 1;
       xd[e] = X[(uint32_t)((lg.off + m) * ldx + (n < d ? n : 0))];
+      dc[e] = drow[0][row0 + e] + drow[1][row0 + e];
     }
     __syncthreads();
     FC_FENCE();
-    {
-      float* o = (float*)(ring + wave * 16384) + lane * 4;
 #pragma unroll
-      for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-        for (int tj = 0; tj < 2; ++tj)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const f32x16& v = acc[mb * 2 + ti][tj];
-            *(f32x4*)(o + ((ti * 2 + tj) * 4 + q) * 256) = (f32x4){v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
-          }
-    }
+    for (int q = 0; q < 4; ++q)
+      *(f32x4*)((float*)(ring + wave * 4096) + q * 256 + lane * 4) =
+          (f32x4){acc[0][0][4 * q], acc[0][0][4 * q + 1], acc[0][0][4 * q + 2], acc[0][0][4 * q + 3]};
     __syncthreads();
-    f32x4 sum[2];
-    {
-      const float* p = (const float*)ring + wave * 512 + lane * 4;
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    const float* p = (const float*)ring + (wave >> 1) * 256 + ((wave & 1) * 32 + (lane >> 1)) * 4 + 2 * (lane & 1);
+    f32x2 w[8];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        sum[h] = *(const f32x4*)(p + h * 256);
+    for (int i = 0; i < 8; ++i) w[i] = *(const f32x2*)(p + i * 1024);
+    const f32x2 sum = ((w[0] + w[1]) + (w[2] + w[3])) + ((w[4] + w[5]) + (w[6] + w[7]));
+    float* o = out + (uint32_t)((m0 + row0) * d + n);
 #pragma unroll
-        for (int w = 1; w < 8; ++w) sum[h] += *(const f32x4*)(p + w * 4096 + h * 256);
+    for (int e = 0; e < 2; ++e)
+      if (n < d && m0 + row0 + e < lg.b) o[e * d] = sum[e] - dc[e] * bf2f(xd[e]);
+  } else {
+    // ---- the eight waves' tiles are added up; larger tiles 64 rows at a time: wave w finishes block w / 2 of them, its rows 16 (w % 2) .. + 15
+    const int rl = (wave >> 2) * 32 + (wave & 1) * 16 + 4 * hk;          // row of e = 0; e = 4: 8 further on
+    const int n = n0 + ((wave >> 1) & 1) * 32 + lr;
+    const bool whole = m0 + kM <= lg.b && n0 + kO <= d;
+#pragma unroll
+    for (int mb = 0; mb < RB / 2; ++mb) {
+      const int row0 = mb * 64 + rl;
+      bf16_t xd[8];                              // the diagonal terms' rows, requested ahead of the sums
+      f32x4 dc[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) dc[h] = *(const f32x4*)(drow[0] + row0 + 8 * h) + *(const f32x4*)(drow[1] + row0 + 8 * h);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        int m = m0 + row0 + 8 * (e >> 2) + (e & 3);
+        m = m < lg.b ? m : lg.b - 1;
+        xd[e] = X[(uint32_t)((lg.off + m) * ldx + (n < d ? n : 0))];
       }
-    }
-    bool writer = true;
-    if (lg.nsplit > 1) {
-      const size_t slab = (size_t)lg.nsplit * (kO * kO / 2);
-      double* all = lg.part + (size_t)(tile * MB + mb) * slab + wave * 256 + lane;
+      __syncthreads();
+      FC_FENCE();
+      {
+        float* o = (float*)(ring + wave * 16384) + lane * 4;
 #pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        const u32x2 w = {__float_as_uint(sum[p >> 1][2 * (p & 1)]), __float_as_uint(sum[p >> 1][2 * (p & 1) + 1])};
-        store_agent(all + (size_t)split * (kO * kO / 2) + p * 64, __builtin_bit_cast(double, w));
-      }
-      writer = last_to_arrive(lg.arrived + tile * MB + mb, (unsigned)lg.nsplit, flag);
-      if (writer) {
-        sum[0] = sum[1] = (f32x4){0.f, 0.f, 0.f, 0.f};
-        for (int s0 = 0; s0 < lg.nsplit; s0 += 4) {      // the partial results of four splits in flight at once
-          double w[4][4];
+        for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
-          for (int s = 0; s < 4; ++s)
+          for (int tj = 0; tj < 2; ++tj)
 #pragma unroll
-            for (int p = 0; p < 4; ++p)
-              w[s][p] = load_agent(all + (size_t)(s0 + s < lg.nsplit ? s0 + s : s0) * (kO * kO / 2) + p * 64);
-          FC_PIN();
-#pragma unroll
-          for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
-              const u32x2 v = __builtin_bit_cast(u32x2, w[s][p]);
-              sum[p >> 1][2 * (p & 1)] += s0 + s < lg.nsplit ? __uint_as_float(v[0]) : 0.f;
-              sum[p >> 1][2 * (p & 1) + 1] += s0 + s < lg.nsplit ? __uint_as_float(v[1]) : 0.f;
+            for (int q = 0; q < 4; ++q) {
+              const f32x16& v = acc[mb * 2 + ti][tj];
+              *(f32x4*)(o + ((ti * 2 + tj) * 4 + q) * 256) = (f32x4){v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
             }
+      }
+      __syncthreads();
+      f32x4 sum[2];
+      {
+        const float* p = (const float*)ring + wave * 512 + lane * 4;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          sum[h] = *(const f32x4*)(p + h * 256);
+#pragma unroll
+          for (int w = 1; w < 8; ++w) sum[h] += *(const f32x4*)(p + w * 4096 + h * 256);
         }
       }
-    }
-    if (writer) {
-      float v[8];
+      bool writer = true;
+      if (lg.nsplit > 1) {
+        const size_t slab = (size_t)lg.nsplit * (kO * kO / 2);
+        double* all = lg.part + (size_t)(tile * (RB / 2) + mb) * slab + wave * 256 + lane;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = sum[e >> 2][e & 3] - dc[e >> 2][e & 3] * bf2f(xd[e]);
-      float* o = out + (uint32_t)((m0 + row0) * d + n);
-      if (whole) {
+        for (int p = 0; p < 4; ++p) {
+          const u32x2 w = {__float_as_uint(sum[p >> 1][2 * (p & 1)]), __float_as_uint(sum[p >> 1][2 * (p & 1) + 1])};
+          store_agent(all + (size_t)split * (kO * kO / 2) + p * 64, __builtin_bit_cast(double, w));
+        }
+        writer = last_to_arrive(lg.arrived + tile * (RB / 2) + mb, (unsigned)lg.nsplit, flag);
+        if (writer) {
+          sum[0] = sum[1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+          for (int s0 = 0; s0 < lg.nsplit; s0 += 4) {      // the partial results of four splits in flight at once
+            double w[4][4];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) o[(8 * (e >> 2) + (e & 3)) * d] = v[e];
-      } else {
-        const int rows = n < d ? lg.b - m0 - row0 : 0;
+            for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (8 * (e >> 2) + (e & 3) < rows) o[(8 * (e >> 2) + (e & 3)) * d] = v[e];
+              for (int p = 0; p < 4; ++p)
+                w[s][p] = load_agent(all + (size_t)(s0 + s < lg.nsplit ? s0 + s : s0) * (kO * kO / 2) + p * 64);
+            FC_PIN();
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+              for (int p = 0; p < 4; ++p) {
+                const u32x2 v = __builtin_bit_cast(u32x2, w[s][p]);
+                sum[p >> 1][2 * (p & 1)] += s0 + s < lg.nsplit ? __uint_as_float(v[0]) : 0.f;
+                sum[p >> 1][2 * (p & 1) + 1] += s0 + s < lg.nsplit ? __uint_as_float(v[1]) : 0.f;
+              }
+          }
+        }
+      }
+      if (writer) {
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = sum[e >> 2][e & 3] - dc[e >> 2][e & 3] * bf2f(xd[e]);
+        float* o = out + (uint32_t)((m0 + row0) * d + n);
+        if (whole) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) o[(8 * (e >> 2) + (e & 3)) * d] = v[e];
+        } else {
+          const int rows = n < d ? lg.b - m0 - row0 : 0;
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (8 * (e >> 2) + (e & 3) < rows) o[(8 * (e >> 2) + (e & 3)) * d] = v[e];
+        }
       }
     }
   }
@@ -1071,15 +1122,15 @@ __device__ __forceinline__ bool t128_tile(const T128Args& g, const StateArgs& a,
   return side == 0 && tn == 0 && tm == 0 && split == 0 && wave == 7;
 }
 
-template <int MB, bool GATHERED>
+template <int RB, bool GATHERED>
 __global__ void __launch_bounds__(512, 2) k_contract_t128_bf16(T128Args g, StateArgs a) {
-  __shared__ __attribute__((aligned(1024))) char ring[kWRing<MB, GATHERED>];
-  __shared__ __attribute__((aligned(16))) float crow[64 * MB], drow[2][64 * MB], cq[kMaxLocalQ];
+  __shared__ __attribute__((aligned(1024))) char ring[kWRing<RB, GATHERED>];
+  __shared__ __attribute__((aligned(16))) float crow[32 * RB], drow[2][32 * RB], cq[kMaxLocalQ];
   __shared__ int flag;
   warm_arguments<sizeof(T128Args) + sizeof(StateArgs)>();
   // (one place that calls write_scalars: see there)
   const bool last = (int)blockIdx.x < g.finishers ? t128_finish(late_argument<0>(g), late_argument<kStateAt>(a), &flag)
-                                                  : t128_tile<MB, GATHERED>(g, a, ring, crow, drow, cq, &flag);
+                                                  : t128_tile<RB, GATHERED>(g, a, ring, crow, drow, cq, &flag);
   const T128Args& lg = late_argument<0>(g);
   if (last) write_scalars<true>(lg.red, lg.nterms, lg.b, lg.version, lg.tau, lg.rho, lg.loss, lg.d_tau);
 }
@@ -1098,11 +1149,12 @@ void launch_contract_t128_bf16(const StepCtx& c) {
     J.out = s == 0 ? c.buf.d_img : c.buf.d_txt;
   }
   g.b = (int)L.b; g.d = (int)L.d; g.B = (int)L.B; g.off = (int)L.off; g.nCB = L.ldE / 16;
-  g.tiles_m = (int)((L.b + L.out_rows - 1) / L.out_rows); g.tiles_n = (int)((L.d + kO - 1) / kO);
+  const int64_t out_cols = L.out_rows == 32 ? 32 : 64, depth = L.out_rows == 32 ? 32 : 16;      // columns of a tile; a stage
+  g.tiles_m = (int)((L.b + L.out_rows - 1) / L.out_rows); g.tiles_n = (int)((L.d + out_cols - 1) / out_cols);
   g.nsplit = L.nsplit;
   g.inv_tiles = reciprocal(2 * g.tiles_m * g.tiles_n);
   g.inv_tiles_n = reciprocal(g.tiles_n);
-  g.nA = (int)((L.B + 15) / 16); g.nB = (int)((L.b + 15) / 16);
+  g.nA = (int)((L.B + depth - 1) / depth); g.nB = (int)((L.b + depth - 1) / depth);
   g.sliceA = (g.nA + L.nsplit * 8 - 1) / (L.nsplit * 8);
   g.sliceB = (g.nB + L.nsplit * 8 - 1) / (L.nsplit * 8);
   g.part = L.nsplit > 1 ? (double*)(c.ws + L.Opart[0]) : nullptr;
@@ -1110,13 +1162,14 @@ void launch_contract_t128_bf16(const StepCtx& c) {
   g.scalars_arrived = g.arrived + L.narrived - 1;
   g.tau = c.buf.tau; g.rho = c.cfg.rho; g.loss = c.buf.loss; g.d_tau = c.buf.d_tau;
   g.red = (const double*)(c.ws + L.red); g.version = c.cfg.version;
-  auto* kernel = L.gathered ? k_contract_t128_bf16<1, true>
-                            : (L.out_rows == 64 ? k_contract_t128_bf16<1, false> : k_contract_t128_bf16<2, false>);
+  auto* kernel = L.gathered ? k_contract_t128_bf16<2, true>
+                 : L.out_rows == 32 ? k_contract_t128_bf16<1, false>
+                                    : (L.out_rows == 64 ? k_contract_t128_bf16<2, false> : k_contract_t128_bf16<4, false>);
   const unsigned groups = (2u * (unsigned)(g.nsplit * g.tiles_m * g.tiles_n) + 7) / 8 * 8;
   // the state phase has workgroups of its own where compute units are left for them
   const unsigned finishers = (unsigned)((L.b + 255) / 256);
   g.finishers = L.fused_state && groups + finishers <= 256 ? (int)finishers : 0;
-  g.nterms = !L.fused_state ? L.nstate_blocks : (g.finishers ? 8 * g.finishers : 2 * (L.out_rows / 64) * g.tiles_m);
+  g.nterms = !L.fused_state ? L.nstate_blocks : (g.finishers ? 8 * g.finishers : t128_finishing_waves(L.out_rows) * g.tiles_m);
   hipLaunchKernelGGL(kernel, dim3(groups + (unsigned)g.finishers), dim3(512), 0, c.s, g, make_state_args(c));
 }
 

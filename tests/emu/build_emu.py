@@ -52,8 +52,8 @@ def _forced(expr, name, kind="atoi"):
 # here fails loudly
 PLAN_RULES = [
     # small tiles: rows of an output tile and splits of k_contract_t128_bf16; the 128 x 128 contraction; either kind of strips
-    ("fastclip_api.hip", "  for (int64_t rows = 64; rows <= (L->gathered ? 64 : 128); rows += 64) {",
-     '  for (int64_t rows = 64; rows <= (L->gathered ? 64 : 128); rows += 64) {\n'
+    ("fastclip_api.hip", "  for (int64_t rows = L->gathered ? 64 : 32; rows <= (L->gathered ? 64 : 128); rows *= 2) {",
+     '  for (int64_t rows = L->gathered ? 64 : 32; rows <= (L->gathered ? 64 : 128); rows *= 2) {\n'
      '    if (getenv("EMU_OUT_ROWS") && atoi(getenv("EMU_OUT_ROWS")) != rows) continue;'),
     ("fastclip_api.hip", "      if (best_cost == 0.0 || cost < best_cost) {",
      '      if (getenv("EMU_NSPLIT") && atoi(getenv("EMU_NSPLIT")) != ns) continue;\n'
@@ -66,6 +66,8 @@ PLAN_RULES = [
     ("fastclip_api.hip", "  if (wgs >= (cfg.b > 512 ? 256 : 257) &&", '  if (getenv("EMU_WIDE") || wgs >= (cfg.b > 512 ? 256 : 257) &&'),
     ("fastclip_api.hip", "L->wide_strips = tiles > 256 && tiles < 512 && (4 * cfg.b > 3 * cfg.B || L->nparts % 2);",
      "L->wide_strips = " + _forced("tiles > 256 && tiles < 512 && (4 * cfg.b > 3 * cfg.B || L->nparts % 2)", "EMU_WIDE_STRIPS") + ";"),
+    ("fastclip_api.hip", "L->own_prep = (tiles + 255) / 256 * rows * cfg.d <= 200000;",
+     "L->own_prep = " + _forced("(tiles + 255) / 256 * rows * cfg.d <= 200000", "EMU_OWN_PREP") + ";"),
     ("fc_internal.hpp", "return 2 * ((L.b + 63) / 64) * (int64_t)L.nparts <= 256;",
      "return " + _forced("2 * ((L.b + 63) / 64) * (int64_t)L.nparts <= 256", "EMU_NARROW") + ";"),
     # fp32 path: tile sizes, plain loops, what is left of a plan that has to fit the static array

@@ -426,6 +426,19 @@ def test_bf16_tiles_128_edges(B, b, off, d):
     test_bf16_tiles_128(B, b, off, d, V2 if B % 2 else V3)
 
 
+@pytest.mark.parametrize("B,b,off,d", [
+    (33, 33, 0, 8), (40, 1, 39, 40), (65, 31, 34, 24),       # 32 x 32 output tiles: one stage, one row, widths inside a tile
+    (300, 256, 40, 512), (257, 255, 2, 504),                 # ... on every compute unit: the anchors finished by the first columns
+    (1100, 130, 700, 200),                                   # ... several stages per wave, rows that wrap around the batch
+    (700, 600, 60, 256), (1300, 1030, 270, 128),             # coefficients of several groups of 256 local anchors: 3, 5 and, with a
+    (2400, 2310, 90, 64),                                    # second pass, 10; eight partial sums and more per wave
+    (2304, 1000, 1200, 760), (3000, 520, 100, 72)])          # 128-row tiles; anchors of several finishing workgroups, splits
+def test_bf16_small_tile_plans(B, b, off, d):
+    """The plans of the small tiles at the sizes where they change what they do (tile size, who forms the coefficients and who
+    finishes the anchors, groups and slices of the partial sums), as in test_bf16_tiles_128."""
+    test_bf16_tiles_128(B, b, off, d, V2 if d % 3 else V3)
+
+
 @pytest.mark.parametrize("B,b,off,d", BF16_SMALL[:-1] + [(1024, 128, 128, 512), (2560, 320, 320, 512), (5120, 640, 640, 512)])
 @pytest.mark.parametrize("version", [V0, V1, V2, V3])
 def test_bf16_fine_tiles(B, b, off, d, version):
