@@ -328,26 +328,37 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
   } else if (L->bf16) {
     L->nparts = (int)((cfg.B + kTileContrasts - 1) / kTileContrasts);
     L->ldE = (int64_t)round_up((size_t)cfg.B, 64);
-    // Split of the contraction over its column range.  A workgroup owns one 256 x 256 output tile of one side and
-    // `slice` stages; the 256 compute units take the workgroups in rounds.  Cost model in units of one stage time:
-    // rounds x (slice + 12 for writing the partial tile) + 0.05 per split and output tile for the finalize pass that
-    // adds the partial results up.
+    // Split of the contraction over its column range, and the columns of its output tiles.  A workgroup owns one output
+    // tile of 256 rows of one side and `slice` stages; the 256 compute units take the workgroups in rounds.  Cost model in
+    // units of the time of one stage of 256 columns: rounds x (slice + 12 for writing the partial tile) + 0.05 per split
+    // and output tile for the finalize pass that adds the partial results up.
+    // 192 columns, a stage of which takes 0.8 of one of 256, where that leaves less of a row's last tile or of the chip's last
+    // round unused.  Steps with 256 / with the chosen 192 columns, us: 4096 of 4096 at 768 131 / 129, at 640 125 / 123, at 576
+    // 122 / 112, at 384 105 / 97, at 128 86 / 81; 1024 of 8192 at 768 87.4 / 82.5, at 192 59.5 / 55.1; 512 of 32768 at 768
+    // 148 / 126; 2048 of 16384 at 576 196 / 177; 3000 of 3000 at 768 143 / 139; 2560 of 2560 at 960 106 / 95.
     const int64_t stages = L->ldE / 32;
-    const int64_t tiles = ((cfg.b + 255) / 256) * ((cfg.d + 255) / 256) * 2;
     int64_t max_split = stages / 8;
     if (max_split > kMaxSplit) max_split = kMaxSplit;
     if (max_split < 1) max_split = 1;
-    int64_t best = 1;
     double best_cost = 0.0;
-    for (int64_t ns = 1; ns <= max_split; ++ns) {
-      const int64_t slice = (stages + ns - 1) / ns;
-      const int64_t used = (stages + slice - 1) / slice;          // splits that really get stages
-      const int64_t rounds = (tiles * used + 255) / 256;
-      const double cost = (double)rounds * (double)(slice + 12) + 0.05 * (double)tiles * (double)used;
-      if (ns == 1 || cost < best_cost) { best = ns; best_cost = cost; }
+    size_t most = 0;
+    for (int cols = 256; cols >= 192; cols -= 64) {
+      const double width = cols == 256 ? 1.0 : 0.80;
+      const int64_t tiles = ((cfg.b + 255) / 256) * ((cfg.d + cols - 1) / cols) * 2;
+      for (int64_t ns = 1; ns <= max_split; ++ns) {
+        const int64_t slice = (stages + ns - 1) / ns;
+        const int64_t used = (stages + slice - 1) / slice;          // splits that really get stages
+        const size_t partial = (size_t)used * partial_split_floats(cfg.b, cfg.d, cols);
+        if (cols < 256 && partial > most) break;                    // no more workspace than on whole tiles
+        const int64_t rounds = (tiles * used + 255) / 256;
+        const double cost = (double)rounds * width * (double)(slice + 12) + 0.05 * (double)tiles * (double)used * (double)cols / 256.0;
+        if (best_cost == 0.0 || cost < best_cost) {
+          best_cost = cost;
+          L->out_cols = cols; L->nsplit = (int)used; L->kslice = slice;
+        }
+      }
+      if (cols == 256) most = (size_t)L->nsplit * partial_split_floats(cfg.b, cfg.d, 256);
     }
-    L->kslice = (stages + best - 1) / best;
-    L->nsplit = (int)((stages + L->kslice - 1) / L->kslice);
   } else {
     L->ldE = room.partial_sums ? (int64_t)round_up((size_t)cfg.B, 4) : cfg.B;
     if (L->few) L->nparts = L->nsplit = 1;
@@ -390,7 +401,7 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
         L->Opart[0] = take(sizeof(float) * (size_t)L->nsplit * 2 * round_up((size_t)cfg.b, 64) * round_up((size_t)cfg.d, 64));
     } else {
       for (int s = 0; s < 2; ++s)
-        L->Opart[s] = take(sizeof(float) * (size_t)L->nsplit * partial_split_floats(cfg.b, cfg.d));
+        L->Opart[s] = take(sizeof(float) * (size_t)L->nsplit * partial_split_floats(cfg.b, cfg.d, L->out_cols));
     }
   } else {
     for (int s = 0; s < 2; ++s) L->E[s] = take(esz * (size_t)cfg.b * (size_t)L->ldE);

@@ -31,12 +31,10 @@ static inline int state_blocks(int64_t b, int nparts) {
 
 static inline size_t round_up(size_t x, size_t m) { return (x + m - 1) / m * m; }
 
-// One split's partial result of the contraction is kept as whole 256 x 256 tiles, each laid out as
-// [64 groups of 4 rows][256 columns][4 rows] (tile = (n / 256) * tiles_m + m / 256): floats per tile, and per split
-// for b rows of width d.
-constexpr size_t kPartialTileFloats = 256 * 256;
-__host__ __device__ static inline size_t partial_split_floats(int64_t b, int64_t d) {
-  return (size_t)((b + 255) / 256) * (size_t)((d + 255) / 256) * kPartialTileFloats;
+// One split's partial result of the contraction is kept as whole output tiles of 256 rows and `cols` columns, each laid
+// out as [64 groups of 4 rows][cols][4 rows] (tile = (n / cols) * tiles_m + m / 256): floats per split for b rows of width d.
+__host__ __device__ static inline size_t partial_split_floats(int64_t b, int64_t d, int cols) {
+  return (size_t)((b + 255) / 256) * (size_t)((d + cols - 1) / cols) * (size_t)(256 * cols);
 }
 
 // Where everything lives inside the caller's workspace (byte offsets, 256-byte aligned).
@@ -64,6 +62,7 @@ struct Layout {
                      //    contraction's depth is cut into nsplit x 8 slices of 16-deep stages, and with one split there
                      //    are no partial results
   int out_rows;      // t128 without wide: rows of an output tile of the contraction, 32, 64 or 128
+  int out_cols;      // MFMA path, 256-row tiles: columns of an output tile of the contraction, 256 or 192
   int wide_strips;   // wide: the strips are k_strips_wide128_bf16
   int own_prep;      // t128: k_strips_t128_bf16 prepares its anchors itself, k_prep is not launched
   int wide;          // t128: the contraction is k_contract_wide128_bf16 (kernels_wide128.hip) behind the fold; nsplit /
@@ -80,7 +79,7 @@ struct Layout {
   size_t c1, c2, dcoef;              // float[bstride]
   size_t red;                        // double[nstate_blocks][2]
   size_t E[2];                       // fp32 path: float [b][ldE]; MFMA path: fragment-ordered bf16 strips
-  size_t Opart[2];                   // float [nsplit][partial_split_floats(b, d)]   (MFMA path)
+  size_t Opart[2];                   // float [nsplit][partial_split_floats(b, d, out_cols)]   (MFMA path)
                                      // fp32 path with nsplit > 1: Opart[0] is double [nsplit][2][tiles][grad_tile^2]
                                      // t128 with nsplit > 1: Opart[0] is float [2][tiles of 64 rows][nsplit][64 * 64],
                                      // with wide [nsplit][2][b to 128][d to 128]

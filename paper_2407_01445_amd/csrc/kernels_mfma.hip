@@ -36,6 +36,7 @@ namespace fc {
 //
 // Strip kernel: both operands are K-contiguous row tiles.  A operand = 256 contrast rows, B operand = 256 anchor rows.
 struct StripTile {
+  static constexpr int NJ = 4;   // 32-column blocks of the B operand per wave
   const bf16_t *X, *A;   // wave-uniform: first contrast row / first anchor row of the tile
   int64_t ldx, lda;
   uint32_t oa[4], ob[4]; // per-lane byte offsets of the 4 + 4 wave loads of a stage (relative to X / A, stage 0)
@@ -94,16 +95,32 @@ struct StripTile {
 };
 
 // Contraction kernel: A operand = 8 anchor blocks x 2 column blocks of Efrag per stage (fragments are copied as they
-// are), B operand = 32 rows x 256 columns of X in its natural layout, read with transposing LDS reads.
+// are), B operand = 32 rows x 64 NJ columns of X in its natural layout, read with transposing LDS reads.
+// What bounds it: the matrix cores at the clock that the power limit leaves (1.2 PFLOP/s for 1024 of 32768 at 1024), and
+// writing the partial tiles.  NJ = 4: 256 x 256 output tiles; NJ = 3: 256 x 192, three quarters of the MFMAs for 28 of 32 KiB
+// a stage, for widths and batches that 256 columns cut badly (the rule and both sides are where the plan is made).
+// LDS image of the B operand: rows of 64 NJ columns, 16-byte piece p of row k at piece position p ^ nswz(k), so that the
+// 4 rows x 64 bytes of a transposing read cover all 64 banks.  256 columns (512 bytes a row): nt_swz.  192 columns: rows are
+// 384 bytes apart, every other one half the banks further, and rows 2 and 3 of four take the other quarter.
+template <int NJ_>
 struct ContractTile {
+  static constexpr int NJ = NJ_;
+  static constexpr int kCols = 64 * NJ, kPieces = 8 * NJ;
   const bf16_t* Efr;       // wave-uniform: fragment (ab0, column block 0) of the strip
   const bf16_t* Xn;        // wave-uniform: X + n0
   int64_t ldx;
-  uint32_t oa[4], ob[4];   // per-lane byte offsets of the wave loads (A: relative to Efr; B: relative to row 0 of a stage)
-  uint32_t la[4], lb[4];
+  uint32_t oa[4], ob[NJ];  // per-lane byte offsets of the wave loads (A: relative to Efr; B: relative to row 0 of a stage)
+  uint32_t la[4], lb[NJ];
   int wm, wn, lane;
   int64_t n0, N, B;   // guarded path
 
+  static __device__ __forceinline__ int nswz(int k) { return NJ == 4 ? nt_swz(k) : ((k >> 1) & 1) << 2; }
+  // row of the stage and logical piece that lane `lane` of wave load f (0 .. 4 NJ - 1) fetches
+  __device__ __forceinline__ void b_piece(int f, int* k, int* piece) const {
+    const int at = f * 64 + lane;
+    *k = at / kPieces;
+    *piece = (at - *k * kPieces) ^ nswz(*k);
+  }
   __device__ __forceinline__ void setup(const bf16_t* E, int64_t nCB, int64_t ab0, const bf16_t* X_, int64_t ldx_,
                                         int64_t n0_, int64_t N_, int64_t B_, int tid) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, kept in SGPRs
@@ -115,8 +132,12 @@ struct ContractTile {
       const int f = wave * 4 + i;                       // fragment f = 2 * (anchor block) + (column block in stage)
       oa[i] = (uint32_t)(((f >> 1) * (int)nCB + (f & 1)) * 512 + lane * 8) * 2u;
       la[i] = (uint32_t)(f * 1024);
-      const int k = 2 * f + (lane >> 5);                // wave load f covers stage rows 2 f, 2 f + 1
-      const int piece = (lane & 31) ^ nt_swz(k);        // logical piece fetched into position (lane & 31)
+    }
+#pragma unroll
+    for (int i = 0; i < NJ; ++i) {
+      const int f = wave * NJ + i;
+      int k, piece;
+      b_piece(f, &k, &piece);
       ob[i] = (uint32_t)(k * (int)ldx_ + piece * 8) * 2u;
       lb[i] = (uint32_t)(kOpBytes + f * 1024);
     }
@@ -134,8 +155,12 @@ struct ContractTile {
     for (int i = 0; i < 4; ++i) {
       const int f = wave * 4 + i;
       *(u32x4*)(slot + f * 1024 + lane * 16) = *(const u32x4*)((const char*)(Efr + (int64_t)stage * 1024) + oa[i]);
-      const int k = 2 * f + (lane >> 5);
-      const int piece = (lane & 31) ^ nt_swz(k);
+    }
+#pragma unroll
+    for (int i = 0; i < NJ; ++i) {
+      const int f = wave * NJ + i;
+      int k, piece;
+      b_piece(f, &k, &piece);
       const int64_t c = (int64_t)stage * BK + k;        // contrast column = row of X
       const bool ok = c < B && (n0 + piece * 8 < N);
       u32x4 v = {0u, 0u, 0u, 0u};
@@ -150,10 +175,10 @@ struct ContractTile {
   // (half 0 / 1), each taking 4 rows x 16 columns per group of 16 lanes (source lane s: row s / 4, columns 4 (s % 4) ..).
   __device__ __forceinline__ u32x2 read_b_half(const char* slot, int t, int kk, int half) const {
     const int h = lane >> 5, s = lane & 15;
-    const int n = wn * 128 + t * 32 + ((lane >> 4) & 1) * 16 + 4 * (s & 3);   // first of 4 columns read by this lane
+    const int n = wn * (kCols / 2) + t * 32 + ((lane >> 4) & 1) * 16 + 4 * (s & 3);   // first of 4 columns read by this lane
     const int k = 16 * kk + 8 * half + 4 * h + (s >> 2);
     const char* base = slot + kOpBytes + ((n & 7) << 1);
-    lds_v4s* p = (lds_v4s*)(uintptr_t)lds_addr(base + nt_off(k, n >> 3));
+    lds_v4s* p = (lds_v4s*)(uintptr_t)lds_addr(base + k * (kPieces * 16) + (((n >> 3) ^ nswz(k)) << 4));
     return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(p));
   }
   __device__ __forceinline__ bf16x8 read_b(const char* slot, int t, int kk) const {
@@ -174,7 +199,7 @@ struct ContractTile {
 // over a whole stage time, so that the load unit sees a steady trickle instead of a burst: the four A-operand loads
 // in the second half of stage x-4 (DMAA, into the slot just retired), the four B-operand loads in the first half of
 // stage x-3 (DMAB).  cur / nxt / prv / pp: byte offsets of the slots of stages s, s+1, s-1, s-2 in a ring of five.
-// WAIT: loads that may stay in flight at the barrier (those of stages s+2 and s+3): 16, 8 or 0.
+// WAIT: loads that may stay in flight at the barrier, those of stages s+2 and s+3: 2 L, L or 0 for L = 4 + NJ per stage.
 // The barrier is the bare instruction: the LDS reads of the first half need not have returned (their slot is written
 // again only after the NEXT stage's barrier, and their consumers wait for them by themselves), so there is no
 // "wait for all LDS traffic" in front of it as __syncthreads() would put.
@@ -199,21 +224,46 @@ struct ContractTile {
     FC_SLOT(3, 1, AP, BLP, BHP, if (RD) AQ[2] = T.read_a(src, 2, KQ))                                               \
     FC_SLOT(3, 2, AP, BLP, BHP, if (RD) AQ[3] = T.read_a(src, 3, KQ))                                               \
     FC_SLOT(3, 3, AP, BLP, BHP, D3)
+// The same for three blocks of 32 columns: 12 MFMAs, 4 + 6 reads.
+#define FC_HALF3(AP, BLP, BHP, AQ, BLQ, BHQ, src, KQ, RD, D0, D1, D2, D3)                                           \
+    FC_SLOT(0, 0, AP, BLP, BHP, if (RD) BLQ[0] = T.read_b_half(src, 0, KQ, 0))                                      \
+    FC_SLOT(0, 1, AP, BLP, BHP, if (RD) BHQ[0] = T.read_b_half(src, 0, KQ, 1))                                      \
+    FC_SLOT(0, 2, AP, BLP, BHP, if (RD) AQ[0] = T.read_a(src, 0, KQ))                                               \
+    FC_SLOT(1, 0, AP, BLP, BHP, if (RD) BLQ[1] = T.read_b_half(src, 1, KQ, 0); D0)                                  \
+    FC_SLOT(1, 1, AP, BLP, BHP, if (RD) BHQ[1] = T.read_b_half(src, 1, KQ, 1))                                      \
+    FC_SLOT(1, 2, AP, BLP, BHP, if (RD) BLQ[2] = T.read_b_half(src, 2, KQ, 0))                                      \
+    FC_SLOT(2, 0, AP, BLP, BHP, if (RD) BHQ[2] = T.read_b_half(src, 2, KQ, 1))                                      \
+    FC_SLOT(2, 1, AP, BLP, BHP, D1)                                                                                 \
+    FC_SLOT(2, 2, AP, BLP, BHP, if (RD) AQ[1] = T.read_a(src, 1, KQ))                                               \
+    FC_SLOT(3, 0, AP, BLP, BHP, if (RD) AQ[2] = T.read_a(src, 2, KQ))                                               \
+    FC_SLOT(3, 1, AP, BLP, BHP, if (RD) AQ[3] = T.read_a(src, 3, KQ); D3)                                           \
+    FC_SLOT(3, 2, AP, BLP, BHP, D2)
 #define FC_STAGE(T, MORE, DMAB, DMAA, WAIT)                                                                         \
   {                                                                                                                 \
     const char* sl = ring + cur;                                                                                    \
     const uint32_t bslot = ring_addr + pp;                                                                          \
-    FC_HALF(a0, bl0, bh0, a1, bl1, bh1, sl, 1, true, if (DMAB) T.dma(4, s0 + s + 3, bslot),                         \
-            if (DMAB) T.dma(5, s0 + s + 3, bslot), if (DMAB) T.dma(6, s0 + s + 3, bslot),                           \
-            if (DMAB) T.dma(7, s0 + s + 3, bslot))                                                                  \
-    if (WAIT == 16) FC_WAIT_VMCNT16(); else if (WAIT == 8) FC_WAIT_VMCNT8(); else FC_WAIT_VMCNT0();                 \
+if constexpr (NJ == 4) {                                                                                        \
+      FC_HALF(a0, bl0, bh0, a1, bl1, bh1, sl, 1, true, if (DMAB) T.dma(4, s0 + s + 3, bslot),                       \
+              if (DMAB) T.dma(5, s0 + s + 3, bslot), if (DMAB) T.dma(6, s0 + s + 3, bslot),                         \
+              if (DMAB) T.dma(7, s0 + s + 3, bslot))                                                                \
+    } else {                                                                                                        \
+      FC_HALF3(a0, bl0, bh0, a1, bl1, bh1, sl, 1, true, if (DMAB) T.dma(4, s0 + s + 3, bslot),                      \
+               if (DMAB) T.dma(5, s0 + s + 3, bslot), if (DMAB) T.dma(6, s0 + s + 3, bslot), )                      \
+    }                                                                                                               \
+    wait_vmcnt<WAIT>();                                                                                             \
     __builtin_amdgcn_s_barrier();                                                                                   \
     FC_PIN();                                                                                                       \
     const char* nx = ring + nxt;                                                                                    \
     const uint32_t aslot = ring_addr + prv;                                                                         \
-    FC_HALF(a1, bl1, bh1, a0, bl0, bh0, nx, 0, MORE, if (DMAA) T.dma(0, s0 + s + 4, aslot),                         \
-            if (DMAA) T.dma(1, s0 + s + 4, aslot), if (DMAA) T.dma(2, s0 + s + 4, aslot),                           \
-            if (DMAA) T.dma(3, s0 + s + 4, aslot))                                                                  \
+    if constexpr (NJ == 4) {                                                                                        \
+      FC_HALF(a1, bl1, bh1, a0, bl0, bh0, nx, 0, MORE, if (DMAA) T.dma(0, s0 + s + 4, aslot),                       \
+              if (DMAA) T.dma(1, s0 + s + 4, aslot), if (DMAA) T.dma(2, s0 + s + 4, aslot),                         \
+              if (DMAA) T.dma(3, s0 + s + 4, aslot))                                                                \
+    } else {                                                                                                        \
+      FC_HALF3(a1, bl1, bh1, a0, bl0, bh0, nx, 0, MORE, if (DMAA) T.dma(0, s0 + s + 4, aslot),                      \
+               if (DMAA) T.dma(1, s0 + s + 4, aslot), if (DMAA) T.dma(2, s0 + s + 4, aslot),                        \
+               if (DMAA) T.dma(3, s0 + s + 4, aslot))                                                               \
+    }                                                                                                               \
     pp = prv; prv = cur; cur = nxt;                                                                                 \
     nxt = (nxt + (uint32_t)kStageBytes == (uint32_t)kRingBytes) ? 0u : nxt + (uint32_t)kStageBytes;                 \
     ++s;                                                                                                            \
@@ -228,7 +278,7 @@ __device__ __forceinline__ void ring_prologue(const Tile& T, uint32_t ring_addr,
   for (int p = 0; p < 4; ++p)
     if (p < S) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
+      for (int i = 0; i < 4 + Tile::NJ; ++i)
         if (p < 3 || i < 4 || S == 4) T.dma(i, s0 + p, ring_addr + p * kStageBytes);
     }
 }
@@ -237,25 +287,27 @@ __device__ __forceinline__ void ring_prologue(const Tile& T, uint32_t ring_addr,
 // nothing else may have touched the ring since.  Vector memory operations complete in order, so every wait names
 // the number of younger loads that may stay in flight.  On return no wave reads the ring any more.
 template <typename Tile>
-__device__ __forceinline__ void ring_mainloop(f32x16 (&acc)[4][4], const Tile& T, char* ring, uint32_t ring_addr,
+__device__ __forceinline__ void ring_mainloop(f32x16 (&acc)[4][Tile::NJ], const Tile& T, char* ring, uint32_t ring_addr,
                                               int s0, int S) {
+  constexpr int NJ = Tile::NJ, L = 4 + NJ;
   // stage 0 has landed; stages 1, 2 and (half or all of) 3 may be in flight
-  if (S >= 5) FC_WAIT_VMCNT20(); else if (S == 4) FC_WAIT_VMCNT24(); else FC_WAIT_VMCNT0();
+  if (S >= 5) wait_vmcnt<2 * L + 4>(); else if (S == 4) wait_vmcnt<3 * L>(); else wait_vmcnt<0>();
   __syncthreads();
   bf16x8 a0[4], a1[4];
-  u32x2 bl0[4], bh0[4], bl1[4], bh1[4];
+  u32x2 bl0[NJ], bh0[NJ], bl1[NJ], bh1[NJ];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    a0[t] = T.read_a(ring, t, 0);
+  for (int t = 0; t < 4; ++t) a0[t] = T.read_a(ring, t, 0);
+#pragma unroll
+  for (int t = 0; t < NJ; ++t) {
     bl0[t] = T.read_b_half(ring, t, 0, 0);
     bh0[t] = T.read_b_half(ring, t, 0, 1);
   }
   uint32_t cur = 0u, nxt = (uint32_t)kStageBytes, prv = 4u * (uint32_t)kStageBytes, pp = 3u * (uint32_t)kStageBytes;
   int s = 0;
-  while (s + 4 < S) FC_STAGE(T, true, true, true, 16)               // s = 0 .. S-5
-  while (s + 4 == S && S >= 5) FC_STAGE(T, true, true, false, 16)   // s = S-4: the last B-operand loads
-  while (s + 3 < S) FC_STAGE(T, true, false, false, 16)             // S == 4 only
-  while (s + 2 < S) FC_STAGE(T, true, false, false, 8)
+  while (s + 4 < S) FC_STAGE(T, true, true, true, 2 * L)               // s = 0 .. S-5
+  while (s + 4 == S && S >= 5) FC_STAGE(T, true, true, false, 2 * L)   // s = S-4: the last B-operand loads
+  while (s + 3 < S) FC_STAGE(T, true, false, false, 2 * L)             // S == 4 only
+  while (s + 2 < S) FC_STAGE(T, true, false, false, L)
   while (s + 1 < S) FC_STAGE(T, true, false, false, 0)
   FC_STAGE(T, false, false, false, 0)
   __syncthreads();
@@ -263,9 +315,9 @@ __device__ __forceinline__ void ring_mainloop(f32x16 (&acc)[4][4], const Tile& T
 
 // Same contraction for tiles with a ragged edge: one stage at a time through registers, zero fill outside.
 template <typename Tile>
-__device__ __forceinline__ void guarded_mainloop(f32x16 (&acc)[4][4], const Tile& T, char* ring, int s0, int S,
+__device__ __forceinline__ void guarded_mainloop(f32x16 (&acc)[4][Tile::NJ], const Tile& T, char* ring, int s0, int S,
                                                  int tid) {
-  bf16x8 a[4], bq[4];
+  bf16x8 a[4], bq[Tile::NJ];
   for (int s = 0; s < S; ++s) {
     __syncthreads();
     T.fill_guarded(s0 + s, ring, tid);
@@ -273,11 +325,13 @@ __device__ __forceinline__ void guarded_mainloop(f32x16 (&acc)[4][4], const Tile
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) { a[t] = T.read_a(ring, t, kk); bq[t] = T.read_b(ring, t, kk); }
+      for (int t = 0; t < 4; ++t) a[t] = T.read_a(ring, t, kk);
+#pragma unroll
+      for (int t = 0; t < Tile::NJ; ++t) bq[t] = T.read_b(ring, t, kk);
 #pragma unroll
       for (int ti = 0; ti < 4; ++ti)
 #pragma unroll
-        for (int tj = 0; tj < 4; ++tj) FC_MM(ti, tj, a, bq);
+        for (int tj = 0; tj < Tile::NJ; ++tj) FC_MM(ti, tj, a, bq);
     }
   }
   __syncthreads();
@@ -743,7 +797,7 @@ void launch_fold_bf16(const StepCtx& c) {
 struct ContractJob {
   const bf16_t* E;    // fragment-ordered strip: l of the local anchors with the contrast-side weights folded in
   const bf16_t* X;    // the matrix whose rows the strip weights: texts for strip 0, images for strip 1
-  float* C;           // [nsplit][tile][64 groups of 4 rows][256 columns][4 rows]: whole 256 x 256 tiles
+  float* C;           // [nsplit][tile][64 groups of 4 rows][64 NJ columns][4 rows]: whole tiles
   int64_t ldx;
   size_t split_stride;
   int64_t nCB;        // column blocks (of 16) per anchor block of E
@@ -755,7 +809,9 @@ struct ContractArgs {
   int nsplit, tiles_m, tiles_n;
 };
 
+template <int NJ>
 __global__ void __launch_bounds__(256) k_contract_bf16(ContractArgs g) {
+  constexpr int W = 64 * NJ;       // columns of an output tile
   __shared__ __attribute__((aligned(1024))) char ring[kRingBytes];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
@@ -766,22 +822,22 @@ __global__ void __launch_bounds__(256) k_contract_bf16(ContractArgs g) {
   const ContractJob& J = g.job[ji];
   const int split = local % g.nsplit;            // consecutive ids -> different XCDs -> different column slices
   const int tile = local / g.nsplit;
-  const int64_t m0 = (int64_t)(tile % g.tiles_m) * 256, n0 = (int64_t)(tile / g.tiles_m) * 256;
+  const int64_t m0 = (int64_t)(tile % g.tiles_m) * 256, n0 = (int64_t)(tile / g.tiles_m) * W;
   const int s0 = split * J.slice;
   const int S = (s0 + J.slice <= J.stages ? J.slice : J.stages - s0);
 
-  f32x16 acc[4][4];
+  f32x16 acc[4][NJ];
   zero_acc(acc);
   if (S > 0) {
-    ContractTile T;
+    ContractTile<NJ> T;
     T.setup(J.E, J.nCB, m0 >> 5, J.X, J.ldx, n0, g.N, g.B, tid);
-    // The unguarded loads of a stage take 32 whole rows of X and 256 columns from n0 on.  They stay inside the matrix
+    // The unguarded loads of a stage take 32 whole rows of X and W columns from n0 on.   They stay inside the matrix
     // (B rows of ldx elements, the last one of N) for the stages below `safe`: rows beyond B never, and where the tile
-    // is wider than what is left of a row (n0 + 256 > N) the words past the row's end are the next rows' - they exist
+    // is wider than what is left of a row (n0 + W > N)  the words past the row's end are the next rows' - they exist
     // except behind the last rows, and what they put into the columns from N on reaches no output.  Those stages run
     // through the ring; the few that are left at the ragged end go one at a time with guards.
     int64_t rows_ok = g.B;
-    if (n0 + 256 > g.N) rows_ok -= (n0 + 256 - g.N + J.ldx - 1) / J.ldx;
+    if (n0 + W > g.N) rows_ok -= (n0 + W - g.N + J.ldx - 1) / J.ldx;
     const int safe = rows_ok > 0 ? (int)(rows_ok / BK) : 0;
     const int S_ring = s0 + S <= safe ? S : (safe > s0 ? safe - s0 : 0);
     if (S_ring > 0) {
@@ -790,21 +846,21 @@ __global__ void __launch_bounds__(256) k_contract_bf16(ContractArgs g) {
     }
     if (S_ring < S) guarded_mainloop(acc, T, ring, s0 + S_ring, S - S_ring, tid);
   }
-  // The partial result leaves as whole tiles of [64 groups of 4 rows][256 columns][4 rows]: a lane holds C[m][n] for
-  // n = n0 + wn 128 + tj 32 + lr and the rows m = m0 + wm 128 + ti 32 + 8 q + 4 hk + t, t = 0..3, so its four values of one
+  // The partial result leaves as whole tiles of [64 groups of 4 rows][W columns][4 rows]: a lane holds C[m][n] for
+  // n = n0 + wn W/2 + tj 32 + lr and the rows m = m0 + wm 128 + ti 32 + 8 q + 4 hk + t, t = 0..3, so its four values of one
   // q are one 16-byte word of that layout and a wave store covers two runs of 512 consecutive bytes.  The buffer holds
   // whole tiles, so nothing is guarded here; k_finalize_bf16 reads four rows at a time in the same order.
   const int lr = lane & 31, hk = lane >> 5;
-  float* __restrict__ C = J.C + (size_t)split * J.split_stride + (size_t)tile * kPartialTileFloats +
-                          ((wm * 32 + hk) * 256 + wn * 128 + lr) * 4;
+  float* __restrict__ C = J.C + (size_t)split * J.split_stride + (size_t)tile * (256 * W) +
+                          ((wm * 32 + hk) * W + wn * (W / 2) + lr) * 4;
 #pragma unroll
   for (int ti = 0; ti < 4; ++ti)
 #pragma unroll
-    for (int tj = 0; tj < 4; ++tj)
+    for (int tj = 0; tj < NJ; ++tj)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const f32x4 v = {acc[ti][tj][4 * q], acc[ti][tj][4 * q + 1], acc[ti][tj][4 * q + 2], acc[ti][tj][4 * q + 3]};
-        *(f32x4*)(C + ((ti * 8 + q * 2) * 256 + tj * 32) * 4) = v;
+        *(f32x4*)(C + ((ti * 8 + q * 2) * W + tj * 32) * 4) = v;
       }
 }
 
@@ -819,7 +875,7 @@ void launch_contract_bf16(const StepCtx& c) {
     J.X = (const bf16_t*)(s == 0 ? c.buf.txt_glob : c.buf.img_glob);
     J.ldx = s == 0 ? c.cfg.ld_txt : c.cfg.ld_img;
     J.C = (float*)(c.ws + L.Opart[s]);
-    J.split_stride = partial_split_floats(L.b, L.d);
+    J.split_stride = partial_split_floats(L.b, L.d, L.out_cols);
     J.nCB = L.ldE / 16;
     J.stages = (int)(L.ldE / BK);
     J.slice = (int)L.kslice;
@@ -827,9 +883,10 @@ void launch_contract_bf16(const StepCtx& c) {
   g.M = L.b; g.N = L.d; g.B = L.B;
   g.nsplit = L.nsplit;
   g.tiles_m = (int)((L.b + 255) / 256);
-  g.tiles_n = (int)((L.d + 255) / 256);
+  g.tiles_n = (int)((L.d + L.out_cols - 1) / L.out_cols);
   const unsigned grid = (unsigned)njobs * (unsigned)(g.nsplit * g.tiles_m * g.tiles_n);
-  hipLaunchKernelGGL(k_contract_bf16, dim3(grid), dim3(256), 0, c.s, g);
+  auto* kernel = L.out_cols == 192 ? k_contract_bf16<3> : k_contract_bf16<4>;
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, c.s, g);
 }
 
 }  // namespace fc

@@ -81,7 +81,7 @@ struct PrepArgs {
 
 template <typename T, bool GATHERED>
 __global__ void __launch_bounds__(256) k_prep(PrepArgs<T> a) {
-  warm_arguments<sizeof(PrepArgs<T>)>();
+  if constexpr (GATHERED) warm_arguments<sizeof(PrepArgs<T>)>();   // else few of them: 0.4 us more
   const int lane = threadIdx.x & 63;
   const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < a.narrived; i += (int)(gridDim.x * 256)) a.arrived[i] = 0u;
@@ -536,9 +536,9 @@ __global__ void k_scalars(const double* red, int nblocks, int64_t b, int version
 // ------------------------------------------------------------------------------------------
 // MFMA path, last phase.  d_img[r] = c1_r * (sum over splits of the contraction)[r] - dcoef_r txt_p, and the mirror
 // image (the contraction already carries the contrast-side terms divided by c_r); block (0,0,0) also writes the
-// scalars.  The split partials are whole 256 x 256 tiles of [64 groups of 4 rows][256 columns][4 rows] (the order in
-// which k_contract_bf16's accumulators leave in 16-byte words), so a block of one wavefront takes four rows and the 256
-// columns of one tile, 4 KiB of consecutive addresses per split, and a thread four columns.  A block is four
+// scalars.  The split partials are whole tiles of [64 groups of 4 rows][cols columns][4 rows] (the order in
+// which k_contract_bf16's accumulators leave in 16-byte words), so a block of one wavefront takes four rows and 256
+// columns, 4 KiB of addresses per split (consecutive ones inside a tile), and a thread four columns.  A block is four
 // wavefronts: four groups of rows (SHARE_SPLITS false), or, when that would leave most of the chip idle, one group
 // of rows whose splits the four wavefronts share (wave w sums the splits w, w + 4, ..; the four sums meet in LDS and
 // are added in the order of the waves).
@@ -546,7 +546,7 @@ template <bool SHARE_SPLITS>
 __global__ void __launch_bounds__(256) k_finalize_bf16(const bf16_t* __restrict__ img, const bf16_t* __restrict__ txt,
                                                        int64_t ld_img, int64_t ld_txt, int64_t off, int64_t b, int64_t d,
                                                        const float* __restrict__ O1, const float* __restrict__ O2,
-                                                       int nsplit, const float* __restrict__ c1,
+                                                       int nsplit, int cols, const float* __restrict__ c1,
                                                        const float* __restrict__ c2, const float* __restrict__ dcoef,
                                                        float* __restrict__ d_img, float* __restrict__ d_txt,
                                                        const double* __restrict__ red, int nblocks, int version,
@@ -575,10 +575,11 @@ __global__ void __launch_bounds__(256) k_finalize_bf16(const bf16_t* __restrict_
       }
     }
     const float* O = side == 0 ? O1 : O2;
-    const size_t split_stride = partial_split_floats(b, d);
+    const size_t split_stride = partial_split_floats(b, d, cols);
     const int64_t tiles_m = (b + 255) / 256;
-    const size_t at = (size_t)((n0 >> 8) * tiles_m + (r0 >> 8)) * kPartialTileFloats +
-                      (size_t)((((r0 & 255) >> 2) * 256 + (n0 & 255)) * 4);
+    const int n = (int)n0, tile_n = cols == 256 ? n >> 8 : n / 192;      // d < 2^24; four columns never straddle tiles
+    const size_t at = (size_t)(tile_n * tiles_m + (r0 >> 8)) * (size_t)(256 * cols) +
+                      (size_t)((((r0 & 255) >> 2) * cols + (n - tile_n * cols)) * 4);
 #pragma unroll 4
     for (int s = SHARE_SPLITS ? wave : 0; s < nsplit; s += SHARE_SPLITS ? 4 : 1) {
 #pragma unroll
@@ -654,8 +655,8 @@ void launch_finalize_bf16(const StepCtx& c) {
   auto* kernel = share ? k_finalize_bf16<true> : k_finalize_bf16<false>;
   hipLaunchKernelGGL(kernel, grid, block, 0, c.s, (const bf16_t*)c.buf.img_glob, (const bf16_t*)c.buf.txt_glob,
                      c.cfg.ld_img, c.cfg.ld_txt, L.off, L.b, L.d, (const float*)(c.ws + L.Opart[0]),
-                     (const float*)(c.ws + L.Opart[1]), L.nsplit, (const float*)(c.ws + L.c1), (const float*)(c.ws + L.c2),
-                     (const float*)(c.ws + L.dcoef), c.buf.d_img, c.buf.d_txt, (const double*)(c.ws + L.red),
+                     (const float*)(c.ws + L.Opart[1]), L.nsplit, L.out_cols, (const float*)(c.ws + L.c1),
+                     (const float*)(c.ws + L.c2), (const float*)(c.ws + L.dcoef), c.buf.d_img, c.buf.d_txt, (const double*)(c.ws + L.red),
                      L.nstate_blocks, c.cfg.version, c.buf.tau, c.cfg.rho, c.buf.loss, c.buf.d_tau);
 }
 

@@ -23,9 +23,12 @@ constexpr int kRingBytes = 5 * kStageBytes;  // 160 KiB: all of the LDS of a com
 #define FC_FENCE() do { FC_PIN(); asm volatile("" ::: "memory"); FC_PIN(); } while (0)
 #define FC_WAIT_VMCNT0() __builtin_amdgcn_s_waitcnt(0x0f70)
 #define FC_WAIT_VMCNT8() __builtin_amdgcn_s_waitcnt(0x0f78)
-#define FC_WAIT_VMCNT16() __builtin_amdgcn_s_waitcnt(0x4f70)
-#define FC_WAIT_VMCNT20() __builtin_amdgcn_s_waitcnt(0x4f74)
-#define FC_WAIT_VMCNT24() __builtin_amdgcn_s_waitcnt(0x4f78)
+// at most N of the wave's vector memory operations may stay in flight
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  static_assert(N >= 0 && N < 64, "six bits");
+  __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14));
+}
 
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
@@ -123,11 +126,12 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   p[1] = (__bf16)hi;
   return __builtin_bit_cast(uint32_t, p);
 }
-__device__ __forceinline__ void zero_acc(f32x16 (&acc)[4][4]) {
+template <int NJ>
+__device__ __forceinline__ void zero_acc(f32x16 (&acc)[4][NJ]) {
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 }

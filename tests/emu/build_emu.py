@@ -70,6 +70,10 @@ PLAN_RULES = [
      "L->own_prep = " + _forced("(tiles + 255) / 256 * rows * cfg.d <= 200000", "EMU_OWN_PREP") + ";"),
     ("fc_internal.hpp", "return 2 * ((L.b + 63) / 64) * (int64_t)L.nparts <= 256;",
      "return " + _forced("2 * ((L.b + 63) / 64) * (int64_t)L.nparts <= 256", "EMU_NARROW") + ";"),
+    # large tiles: columns of an output tile of the contraction
+    ("fastclip_api.hip", "    for (int cols = 256; cols >= 192; cols -= 64) {",
+     '    for (int cols = 256; cols >= 192; cols -= 64) {\n'
+     '      if (getenv("EMU_OUT_COLS") && atoi(getenv("EMU_OUT_COLS")) != cols) { most = SIZE_MAX; continue; }'),
     # fp32 path: tile sizes, plain loops, what is left of a plan that has to fit the static array
     ("fastclip_api.hip", "((cfg.B + 63) / 64) >= 256 ? 64 : 32;", "((cfg.B + 63) / 64) >= " + _forced("256", "EMU_F32_TILES") + " ? 64 : 32;"),
     ("fastclip_api.hip", "  for (int T = 32; T <= 64; T += 32) {",

@@ -439,6 +439,16 @@ def test_bf16_small_tile_plans(B, b, off, d):
     test_bf16_tiles_128(B, b, off, d, V2 if d % 3 else V3)
 
 
+@pytest.mark.parametrize("B,b,off,d", [
+    (256, 200, 56, 8), (1056, 300, 700, 192), (1040, 257, 100, 200), (1056, 256, 800, 256),     # one or two tiles of columns,
+    (2056, 300, 0, 384), (1100, 600, 500, 392), (1300, 260, 1040, 512), (900, 900, 0, 520),      # whole ones and the first words
+    (700, 513, 100, 768)])                                                                       # of another; ragged depths
+def test_bf16_large_tile_output_columns(B, b, off, d):
+    """Output tiles of 192 and of 256 columns in the contraction of the large tiles, as in test_bf16_tiles_128 (which runs the
+    batch on the large tiles too)."""
+    test_bf16_tiles_128(B, b, off, d, V2 if d % 3 else V3)
+
+
 @pytest.mark.parametrize("B,b,off,d", BF16_SMALL[:-1] + [(1024, 128, 128, 512), (2560, 320, 320, 512), (5120, 640, 640, 512)])
 @pytest.mark.parametrize("version", [V0, V1, V2, V3])
 def test_bf16_fine_tiles(B, b, off, d, version):

@@ -186,6 +186,9 @@ FORCED = [
     dict(plan=dict(OUT_ROWS=64, NSPLIT=3, OWN_PREP=0), B=200, b=70, off=129, d=136, version=V0),
     dict(plan=dict(OUT_ROWS=128, NSPLIT=2), B=200, b=140, off=33, d=72, version=V3),
     dict(plan=dict(OUT_ROWS=64, NSPLIT=2, NARROW=0), B=200, b=140, off=33, d=72, version=V3, gathered=True),
+    # large tiles: output tiles of the contraction of either width, a whole one and one cut short, on the ring and behind it
+    dict(plan=dict(OUT_COLS=256), B=520, b=200, off=112, d=264, version=V1, flags=fc.TILES_256, ld_txt=272),
+    dict(plan=dict(OUT_COLS=192), B=520, b=200, off=112, d=264, version=V2, flags=fc.TILES_256, ld_txt=272),
     # fp32 path: 64 x 64 tiles of strips and gradients, splits, the single pass on them; splits with gathered state; one partial
     # sum over several tiles, as where the strips alone fill the static array
     dict(plan=dict(F32_TILES=1, GRAD_TILE=64, NSPLIT=2), B=150, b=70, off=33, d=68, ld_img=72, version=V3, dtype="f32"),
