@@ -336,6 +336,8 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
     // round unused.  Steps with 256 / with the chosen 192 columns, us: 4096 of 4096 at 768 131 / 129, at 640 125 / 123, at 576
     // 122 / 112, at 384 105 / 97, at 128 86 / 81; 1024 of 8192 at 768 87.4 / 82.5, at 192 59.5 / 55.1; 512 of 32768 at 768
     // 148 / 126; 2048 of 16384 at 576 196 / 177; 3000 of 3000 at 768 143 / 139; 2560 of 2560 at 960 106 / 95.
+    // Gathered state: the strips are twice as much whatever the columns, so a stage of 192 takes as long; stages come in pairs
+    // there (remote_mainloop), a last odd one takes as long as four.
     const int64_t stages = L->ldE / 32;
     int64_t max_split = stages / 8;
     if (max_split > kMaxSplit) max_split = kMaxSplit;
@@ -343,10 +345,11 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
     double best_cost = 0.0;
     size_t most = 0;
     for (int cols = 256; cols >= 192; cols -= 64) {
-      const double width = cols == 256 ? 1.0 : 0.80;
+      const double width = cols == 256 || L->gathered ? 1.0 : 0.80;
       const int64_t tiles = ((cfg.b + 255) / 256) * ((cfg.d + cols - 1) / cols) * 2;
       for (int64_t ns = 1; ns <= max_split; ++ns) {
-        const int64_t slice = (stages + ns - 1) / ns;
+        int64_t slice = (stages + ns - 1) / ns;
+        if (L->gathered) slice += slice & 1;
         const int64_t used = (stages + slice - 1) / slice;          // splits that really get stages
         const size_t partial = (size_t)used * partial_split_floats(cfg.b, cfg.d, cols);
         if (cols < 256 && partial > most) break;                    // no more workspace than on whole tiles

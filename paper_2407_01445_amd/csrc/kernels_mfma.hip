@@ -102,7 +102,8 @@ struct StripTile {
 // LDS image of the B operand: rows of 64 NJ columns, 16-byte piece p of row k at piece position p ^ nswz(k), so that the
 // 4 rows x 64 bytes of a transposing read cover all 64 banks.  256 columns (512 bytes a row): nt_swz.  192 columns: rows are
 // 384 bytes apart, every other one half the banks further, and rows 2 and 3 of four take the other quarter.
-template <int NJ_>
+// REMOTE (gathered state): the A operand is E + F / c_own, formed between the loads of both strips and the LDS image.
+template <int NJ_, bool REMOTE>
 struct ContractTile {
   static constexpr int NJ = NJ_;
   static constexpr int kCols = 64 * NJ, kPieces = 8 * NJ;
@@ -113,6 +114,8 @@ struct ContractTile {
   uint32_t la[4], lb[NJ];
   int wm, wn, lane;
   int64_t n0, N, B;   // guarded path
+  const bf16_t* Ffr;  // REMOTE: the second strip as Efr, and 1 / c_own of the lane's row in the two anchor blocks that the
+  float inv[2];       // wave brings in (fragments 0, 1 and 2, 3)
 
   static __device__ __forceinline__ int nswz(int k) { return NJ == 4 ? nt_swz(k) : ((k >> 1) & 1) << 2; }
   // row of the stage and logical piece that lane `lane` of wave load f (0 .. 4 NJ - 1) fetches
@@ -142,6 +145,27 @@ struct ContractTile {
       lb[i] = (uint32_t)(kOpBytes + f * 1024);
     }
   }
+  __device__ __forceinline__ void setup_remote(const bf16_t* F, int64_t nCB, int64_t ab0, const float* c_own, int64_t b, int tid) {
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    Ffr = F + ab0 * nCB * 512;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int64_t r = (ab0 + wave * 2 + i) * 32 + (lane & 31);
+      inv[i] = r < b ? 1.0f / c_own[r] : 0.f;
+    }
+  }
+  // chunk i of a stage of either strip, and two of its elements put together
+  __device__ __forceinline__ u32x4 load_e(int i, int stage) const {
+    return *(const u32x4*)((const char*)(Efr + (int64_t)stage * 1024) + oa[i]);
+  }
+  __device__ __forceinline__ u32x4 load_f(int i, int stage) const {
+    return *(const u32x4*)((const char*)(Ffr + (int64_t)stage * 1024) + oa[i]);
+  }
+  __device__ __forceinline__ uint32_t combine(int i, uint32_t e, uint32_t f) const {
+    const float lo = fmaf(__uint_as_float(f << 16), inv[i >> 1], __uint_as_float(e << 16));
+    const float hi = fmaf(__uint_as_float(f & 0xffff0000u), inv[i >> 1], __uint_as_float(e & 0xffff0000u));
+    return pack_bf16x2(lo, hi);
+  }
   __device__ __forceinline__ const bf16_t* stage_rows(int stage) const {   // X row of stage row 0, plus n0
     return Xn + (int64_t)stage * BK * ldx;
   }
@@ -154,7 +178,13 @@ struct ContractTile {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int f = wave * 4 + i;
-      *(u32x4*)(slot + f * 1024 + lane * 16) = *(const u32x4*)((const char*)(Efr + (int64_t)stage * 1024) + oa[i]);
+      u32x4 v = load_e(i, stage);
+      if constexpr (REMOTE) {
+        const u32x4 w = load_f(i, stage);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = combine(i, v[q], w[q]);
+      }
+      *(u32x4*)(slot + f * 1024 + lane * 16) = v;
     }
 #pragma unroll
     for (int i = 0; i < NJ; ++i) {
@@ -310,6 +340,145 @@ __device__ __forceinline__ void ring_mainloop(f32x16 (&acc)[4][Tile::NJ], const 
   while (s + 2 < S) FC_STAGE(T, true, false, false, L)
   while (s + 1 < S) FC_STAGE(T, true, false, false, 0)
   FC_STAGE(T, false, false, false, 0)
+  __syncthreads();
+}
+
+// The contraction's loop with gathered state (ContractTile<NJ, true>): the B operand comes as above, the A operand through
+// registers.  Stage s forms the A operand of stage s + 3 from chunks of both strips that were requested two stages before, writes
+// it into its slot and requests those of stage s + 5 into the registers just freed: two sets, taken in turn, so S is even (and
+// at least 8, for the stages at the end).  A pair of elements (seven VALU instructions) goes behind every other MFMA.
+// LDS: what a stage writes is complete before the barrier of the one after the next: later reads of this wave, which LDS serves
+// in order, have been waited for by then.
+// Why not a pass over both strips ahead of the contraction: it reads and writes 384 MiB for 1024 of 32768 pairs
+// at width 1024, 63 us; the loop takes 160 us instead of 115, bound by the strips' way from memory (pairs in the second half
+// stage only or spread over both make no difference).  Steps, pass / here, us: 1024 of 32768 at 1024 387 / 364, 512 of 32768 at
+// 512 159 / 140, 1024 of 16384 at 384 140 / 110, 1024 of 5120 at 1024 102 / 96.
+struct RemoteSet {
+  u32x4 e[4], f[4];
+};
+template <typename Tile>
+__device__ __forceinline__ void remote_request(const Tile& T, RemoteSet& r, int stage) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { r.e[i] = T.load_e(i, stage); r.f[i] = T.load_f(i, stage); }
+}
+// Pair w of the set's 16; a chunk that is complete goes to its place in the slot and its registers to the stage `next`.
+template <typename Tile>
+__device__ __forceinline__ void remote_pair(const Tile& T, RemoteSet& r, int w, char* slot, bool request, int next) {
+  const int i = w >> 2;
+  r.e[i][w & 3] = T.combine(i, r.e[i][w & 3], r.f[i][w & 3]);
+  if ((w & 3) == 3) {
+    *(u32x4*)(slot + T.la[i] + T.lane * 16) = r.e[i];
+    if (request) { r.e[i] = T.load_e(i, next); r.f[i] = T.load_f(i, next); }
+  }
+}
+// The half stages with a pair of elements behind every other MFMA (of three: behind two): P(0) .. P(7).
+#define FC_HALF_P(AP, BLP, BHP, AQ, BLQ, BHQ, src, KQ, RD, D0, D1, D2, D3, P)                                       \
+    FC_SLOT(0, 0, AP, BLP, BHP, if (RD) BLQ[0] = T.read_b_half(src, 0, KQ, 0); P(0))                                \
+    FC_SLOT(0, 1, AP, BLP, BHP, if (RD) BHQ[0] = T.read_b_half(src, 0, KQ, 1))                                      \
+    FC_SLOT(0, 2, AP, BLP, BHP, if (RD) AQ[0] = T.read_a(src, 0, KQ); P(1))                                         \
+    FC_SLOT(0, 3, AP, BLP, BHP, D0)                                                                                 \
+    FC_SLOT(1, 0, AP, BLP, BHP, if (RD) BLQ[1] = T.read_b_half(src, 1, KQ, 0); P(2))                                \
+    FC_SLOT(1, 1, AP, BLP, BHP, if (RD) BHQ[1] = T.read_b_half(src, 1, KQ, 1))                                      \
+    FC_SLOT(1, 2, AP, BLP, BHP, if (RD) BLQ[2] = T.read_b_half(src, 2, KQ, 0); P(3))                                \
+    FC_SLOT(1, 3, AP, BLP, BHP, D1)                                                                                 \
+    FC_SLOT(2, 0, AP, BLP, BHP, if (RD) BHQ[2] = T.read_b_half(src, 2, KQ, 1); P(4))                                \
+    FC_SLOT(2, 1, AP, BLP, BHP, if (RD) BLQ[3] = T.read_b_half(src, 3, KQ, 0))                                      \
+    FC_SLOT(2, 2, AP, BLP, BHP, if (RD) BHQ[3] = T.read_b_half(src, 3, KQ, 1); P(5))                                \
+    FC_SLOT(2, 3, AP, BLP, BHP, D2)                                                                                 \
+    FC_SLOT(3, 0, AP, BLP, BHP, if (RD) AQ[1] = T.read_a(src, 1, KQ); P(6))                                         \
+    FC_SLOT(3, 1, AP, BLP, BHP, if (RD) AQ[2] = T.read_a(src, 2, KQ))                                               \
+    FC_SLOT(3, 2, AP, BLP, BHP, if (RD) AQ[3] = T.read_a(src, 3, KQ); P(7))                                         \
+    FC_SLOT(3, 3, AP, BLP, BHP, D3)
+#define FC_HALF3_P(AP, BLP, BHP, AQ, BLQ, BHQ, src, KQ, RD, D0, D1, D2, D3, P)                                      \
+    FC_SLOT(0, 0, AP, BLP, BHP, if (RD) BLQ[0] = T.read_b_half(src, 0, KQ, 0); P(0))                                \
+    FC_SLOT(0, 1, AP, BLP, BHP, if (RD) BHQ[0] = T.read_b_half(src, 0, KQ, 1); P(1))                                \
+    FC_SLOT(0, 2, AP, BLP, BHP, if (RD) AQ[0] = T.read_a(src, 0, KQ))                                               \
+    FC_SLOT(1, 0, AP, BLP, BHP, if (RD) BLQ[1] = T.read_b_half(src, 1, KQ, 0); P(2))                                \
+    FC_SLOT(1, 1, AP, BLP, BHP, if (RD) BHQ[1] = T.read_b_half(src, 1, KQ, 1); P(3))                                \
+    FC_SLOT(1, 2, AP, BLP, BHP, if (RD) BLQ[2] = T.read_b_half(src, 2, KQ, 0); D0)                                  \
+    FC_SLOT(2, 0, AP, BLP, BHP, if (RD) BHQ[2] = T.read_b_half(src, 2, KQ, 1); P(4))                                \
+    FC_SLOT(2, 1, AP, BLP, BHP, if (RD) AQ[1] = T.read_a(src, 1, KQ); P(5))                                         \
+    FC_SLOT(2, 2, AP, BLP, BHP, D1)                                                                                 \
+    FC_SLOT(3, 0, AP, BLP, BHP, if (RD) AQ[2] = T.read_a(src, 2, KQ); P(6))                                         \
+    FC_SLOT(3, 1, AP, BLP, BHP, if (RD) AQ[3] = T.read_a(src, 3, KQ); P(7))                                         \
+    FC_SLOT(3, 2, AP, BLP, BHP, D2)
+// Stage s: SET holds the chunks of stage s + 3 (STORE: there is such a stage; MOREREQ: stage s + 5 too), of which the first
+// half stage takes the first eight pairs and the second half the others.  WAIT: loads that may stay in flight at the barrier:
+// those younger than the B operand of stage s + 1, at least four per half stage since then that requests chunks and NJ per
+// stage with a B operand.
+#define FC_PAIR(k, SET, STORE, MOREREQ) if (STORE) remote_pair(T, SET, k, ring + wslot, MOREREQ, s0 + s + 5)
+#define FC_STAGE_REMOTE(SET, MORE, STORE, MOREREQ, WAIT)                                                            \
+  {                                                                                                                 \
+    const char* sl = ring + cur;                                                                                    \
+    const uint32_t bslot = ring_addr + pp, wslot = pp;                                                              \
+    auto first = [&](int k) __attribute__((always_inline)) { FC_PAIR(k, SET, STORE, MOREREQ); };                    \
+    auto second = [&](int k) __attribute__((always_inline)) { FC_PAIR(8 + k, SET, STORE, MOREREQ); };               \
+    if constexpr (NJ == 4) {                                                                                        \
+      FC_HALF_P(a0, bl0, bh0, a1, bl1, bh1, sl, 1, true, if (STORE) T.dma(4, s0 + s + 3, bslot),                    \
+                if (STORE) T.dma(5, s0 + s + 3, bslot), if (STORE) T.dma(6, s0 + s + 3, bslot),                     \
+                if (STORE) T.dma(7, s0 + s + 3, bslot), first)                                                      \
+    } else {                                                                                                        \
+      FC_HALF3_P(a0, bl0, bh0, a1, bl1, bh1, sl, 1, true, if (STORE) T.dma(4, s0 + s + 3, bslot),                   \
+                 if (STORE) T.dma(5, s0 + s + 3, bslot), if (STORE) T.dma(6, s0 + s + 3, bslot), , first)           \
+    }                                                                                                               \
+    wait_vmcnt<WAIT>();                                                                                             \
+    __builtin_amdgcn_s_barrier();                                                                                   \
+    FC_PIN();                                                                                                       \
+    const char* nx = ring + nxt;                                                                                    \
+    if constexpr (NJ == 4) {                                                                                        \
+      FC_HALF_P(a1, bl1, bh1, a0, bl0, bh0, nx, 0, MORE, , , , , second)                                            \
+    } else {                                                                                                        \
+      FC_HALF3_P(a1, bl1, bh1, a0, bl0, bh0, nx, 0, MORE, , , , , second)                                           \
+    }                                                                                                               \
+    pp = prv; prv = cur; cur = nxt;                                                                                 \
+    nxt = (nxt + (uint32_t)kStageBytes == (uint32_t)kRingBytes) ? 0u : nxt + (uint32_t)kStageBytes;                 \
+    ++s;                                                                                                            \
+  }
+template <typename Tile>
+__device__ __forceinline__ void remote_mainloop(f32x16 (&acc)[4][Tile::NJ], const Tile& T, char* ring, uint32_t ring_addr,
+                                                int s0, int S) {
+  constexpr int NJ = Tile::NJ;
+  RemoteSet x, y;            // even stages, odd stages
+  remote_request(T, x, s0);
+  remote_request(T, y, s0 + 1);
+  FC_FENCE();
+#pragma unroll
+  for (int p = 0; p < 3; ++p)
+#pragma unroll
+    for (int i = 4; i < 4 + NJ; ++i) T.dma(i, s0 + p, ring_addr + p * kStageBytes);
+#pragma unroll
+  for (int w = 0; w < 16; ++w) remote_pair(T, x, w, ring, true, s0 + 2);
+  FC_FENCE();
+#pragma unroll
+  for (int w = 0; w < 16; ++w) remote_pair(T, y, w, ring + kStageBytes, true, s0 + 3);
+  FC_FENCE();
+#pragma unroll
+  for (int w = 0; w < 16; ++w) remote_pair(T, x, w, ring + 2 * kStageBytes, true, s0 + 4);
+  FC_FENCE();
+  wait_vmcnt<8>();           // the B operands of stages 0 .. 2 have landed: 16 loads of the two sets are younger
+  __syncthreads();
+  bf16x8 a0[4], a1[4];
+  u32x2 bl0[NJ], bh0[NJ], bl1[NJ], bh1[NJ];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) a0[t] = T.read_a(ring, t, 0);
+#pragma unroll
+  for (int t = 0; t < NJ; ++t) {
+    bl0[t] = T.read_b_half(ring, t, 0, 0);
+    bh0[t] = T.read_b_half(ring, t, 0, 1);
+  }
+  uint32_t cur = 0u, nxt = (uint32_t)kStageBytes, prv = 4u * (uint32_t)kStageBytes, pp = 3u * (uint32_t)kStageBytes;
+  int s = 0;
+  // at the barrier of stage s: two sets and the B operands of stages s + 2 and s + 3 are younger than that of s + 1
+  while (s + 6 < S) {
+    FC_STAGE_REMOTE(y, true, true, true, 16 + 2 * NJ)
+    FC_STAGE_REMOTE(x, true, true, true, 16 + 2 * NJ)
+  }
+  FC_STAGE_REMOTE(y, true, true, true, 16 + 2 * NJ)      // S - 6: the last request
+  FC_STAGE_REMOTE(x, true, true, false, 12 + 2 * NJ)
+  FC_STAGE_REMOTE(y, true, true, false, 4 + 2 * NJ)      // S - 4: the last B operand
+  FC_STAGE_REMOTE(x, true, false, false, NJ)
+  FC_STAGE_REMOTE(x, true, false, false, 0)
+  FC_STAGE_REMOTE(x, false, false, false, 0)
   __syncthreads();
 }
 
@@ -743,36 +912,6 @@ __global__ void __launch_bounds__(256) k_fold_square_bf16(bf16_t* __restrict__ E
   }
 }
 
-// Gathered state: the weights c_j l(j, p_r) of the remote anchors (strip F, stored by the strip kernel in the layout of
-// E) multiply the same rows of X as l(r, j) does, so E[r][j] += F[r][j] / c_own[r] lets one contraction per side
-// produce both sums (its result is multiplied by c_own[r] afterwards).  F is 0 at the local rows' columns, which
-// k_fold_bf16 handles, so the two folds touch E independently.  One 16-byte fragment chunk per thread.
-__global__ void __launch_bounds__(256) k_fold_remote_bf16(bf16_t* __restrict__ E0, const bf16_t* __restrict__ F0,
-                                                          bf16_t* __restrict__ E1, const bf16_t* __restrict__ F1,
-                                                          const float* __restrict__ c1, const float* __restrict__ c2,
-                                                          int64_t chunks_per_row_block, int64_t b) {
-  const int side = blockIdx.y;
-  bf16_t* __restrict__ E = side == 0 ? E0 : E1;
-  const bf16_t* __restrict__ F = side == 0 ? F0 : F1;
-  const float* __restrict__ c_own = side == 0 ? c1 : c2;
-  const int64_t chunk = (int64_t)blockIdx.x * 256 + threadIdx.x;      // (anchor block, column block, lane)
-  const int64_t ab = chunk / chunks_per_row_block;
-  const int64_t r = ab * 32 + (chunk & 31);
-  if (r >= b) return;
-  const float inv = 1.0f / c_own[r];
-  const uint4 e = *(const uint4*)(E + chunk * 8), f = *(const uint4*)(F + chunk * 8);
-  const uint32_t ew[4] = {e.x, e.y, e.z, e.w}, fw[4] = {f.x, f.y, f.z, f.w};
-  uint32_t o[4];
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const float lo = fmaf(__uint_as_float(fw[w] << 16), inv, __uint_as_float(ew[w] << 16));
-    const float hi = fmaf(__uint_as_float(fw[w] & 0xffff0000u), inv, __uint_as_float(ew[w] & 0xffff0000u));
-    o[w] = pack_bf16x2(lo, hi);
-  }
-  const u32x4 ov = {o[0], o[1], o[2], o[3]};
-  *(u32x4*)(E + chunk * 8) = ov;
-}
-
 void launch_fold_bf16(const StepCtx& c) {
   const Layout& L = c.L;
   const unsigned nb = (unsigned)((L.b + 63) / 64);
@@ -783,19 +922,13 @@ void launch_fold_bf16(const StepCtx& c) {
   else
     hipLaunchKernelGGL(k_fold_bf16, dim3(nb, nb), dim3(256), 0, c.s, (bf16_t*)(c.ws + L.E[0]), (bf16_t*)(c.ws + L.E[1]),
                        L.ldE / 16, st, L.off);
-  if (L.gathered) {   // after the kernel above: it leaves the coefficients of all local rows
-    const int64_t per_block = (L.ldE / 16) * 64;                       // chunks per block of 32 anchors
-    const int64_t chunks = (int64_t)((L.b + 31) / 32) * per_block;
-    hipLaunchKernelGGL(k_fold_remote_bf16, dim3((unsigned)((chunks + 255) / 256), 2), dim3(256), 0, c.s,
-                       (bf16_t*)(c.ws + L.E[0]), (const bf16_t*)(c.ws + L.F[0]), (bf16_t*)(c.ws + L.E[1]),
-                       (const bf16_t*)(c.ws + L.F[1]), (const float*)(c.ws + L.c1), (const float*)(c.ws + L.c2),
-                       per_block, L.b);
-  }
 }
 
 // ----------------------------------------------------------------------------------------------------------------
 struct ContractJob {
   const bf16_t* E;    // fragment-ordered strip: l of the local anchors with the contrast-side weights folded in
+  const bf16_t* F;    // gathered state: the second strip, fragment-ordered as E, and the coefficients of the local anchors
+  const float* c_own;
   const bf16_t* X;    // the matrix whose rows the strip weights: texts for strip 0, images for strip 1
   float* C;           // [nsplit][tile][64 groups of 4 rows][64 NJ columns][4 rows]: whole tiles
   int64_t ldx;
@@ -809,7 +942,7 @@ struct ContractArgs {
   int nsplit, tiles_m, tiles_n;
 };
 
-template <int NJ>
+template <int NJ, bool REMOTE>
 __global__ void __launch_bounds__(256) k_contract_bf16(ContractArgs g) {
   constexpr int W = 64 * NJ;       // columns of an output tile
   __shared__ __attribute__((aligned(1024))) char ring[kRingBytes];
@@ -829,8 +962,9 @@ __global__ void __launch_bounds__(256) k_contract_bf16(ContractArgs g) {
   f32x16 acc[4][NJ];
   zero_acc(acc);
   if (S > 0) {
-    ContractTile<NJ> T;
+    ContractTile<NJ, REMOTE> T;
     T.setup(J.E, J.nCB, m0 >> 5, J.X, J.ldx, n0, g.N, g.B, tid);
+    if constexpr (REMOTE) T.setup_remote(J.F, J.nCB, m0 >> 5, J.c_own, g.M, tid);
     // The unguarded loads of a stage take 32 whole rows of X and W columns from n0 on.   They stay inside the matrix
     // (B rows of ldx elements, the last one of N) for the stages below `safe`: rows beyond B never, and where the tile
     // is wider than what is left of a row (n0 + W > N)  the words past the row's end are the next rows' - they exist
@@ -839,8 +973,11 @@ __global__ void __launch_bounds__(256) k_contract_bf16(ContractArgs g) {
     int64_t rows_ok = g.B;
     if (n0 + W > g.N) rows_ok -= (n0 + W - g.N + J.ldx - 1) / J.ldx;
     const int safe = rows_ok > 0 ? (int)(rows_ok / BK) : 0;
-    const int S_ring = s0 + S <= safe ? S : (safe > s0 ? safe - s0 : 0);
-    if (S_ring > 0) {
+    int S_ring = s0 + S <= safe ? S : (safe > s0 ? safe - s0 : 0);
+    if constexpr (REMOTE) {
+      S_ring = S_ring < 8 ? 0 : S_ring & ~1;
+      if (S_ring > 0) remote_mainloop(acc, T, ring, ring_addr, s0, S_ring);
+    } else if (S_ring > 0) {
       ring_prologue(T, ring_addr, s0, S_ring);
       ring_mainloop(acc, T, ring, ring_addr, s0, S_ring);
     }
@@ -851,17 +988,20 @@ __global__ void __launch_bounds__(256) k_contract_bf16(ContractArgs g) {
   // q are one 16-byte word of that layout and a wave store covers two runs of 512 consecutive bytes.  The buffer holds
   // whole tiles, so nothing is guarded here; k_finalize_bf16 reads four rows at a time in the same order.
   const int lr = lane & 31, hk = lane >> 5;
-  float* __restrict__ C = J.C + (size_t)split * J.split_stride + (size_t)tile * (256 * W) +
-                          ((wm * 32 + hk) * W + wn * (W / 2) + lr) * 4;
+  float* C = J.C + (size_t)split * J.split_stride + (size_t)tile * (256 * W);     // wave-uniform
+  const uint32_t at = (uint32_t)(((wm * 32 + hk) * W + wn * (W / 2) + lr) * 4);
 #pragma unroll
   for (int ti = 0; ti < 4; ++ti)
 #pragma unroll
-    for (int tj = 0; tj < NJ; ++tj)
+    for (int q = 0; q < 4; ++q) {
+      float* row = C + (ti * 8 + q * 2) * (W * 4);
+      asm volatile("" : "+s"(row));            // one scalar address per four rows, not one per store in vector registers
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+      for (int tj = 0; tj < NJ; ++tj) {
         const f32x4 v = {acc[ti][tj][4 * q], acc[ti][tj][4 * q + 1], acc[ti][tj][4 * q + 2], acc[ti][tj][4 * q + 3]};
-        *(f32x4*)(C + ((ti * 8 + q * 2) * W + tj * 32) * 4) = v;
+        *(f32x4*)(row + at + tj * 128) = v;
       }
+    }
 }
 
 void launch_contract_bf16(const StepCtx& c) {
@@ -872,6 +1012,8 @@ void launch_contract_bf16(const StepCtx& c) {
     const int s = j & 1;
     ContractJob& J = g.job[j];
     J.E = (const bf16_t*)(c.ws + L.E[s]);
+    J.F = L.gathered ? (const bf16_t*)(c.ws + L.F[s]) : nullptr;
+    J.c_own = (const float*)(c.ws + (s == 0 ? L.c1 : L.c2));
     J.X = (const bf16_t*)(s == 0 ? c.buf.txt_glob : c.buf.img_glob);
     J.ldx = s == 0 ? c.cfg.ld_txt : c.cfg.ld_img;
     J.C = (float*)(c.ws + L.Opart[s]);
@@ -885,7 +1027,8 @@ void launch_contract_bf16(const StepCtx& c) {
   g.tiles_m = (int)((L.b + 255) / 256);
   g.tiles_n = (int)((L.d + L.out_cols - 1) / L.out_cols);
   const unsigned grid = (unsigned)njobs * (unsigned)(g.nsplit * g.tiles_m * g.tiles_n);
-  auto* kernel = L.out_cols == 192 ? k_contract_bf16<3> : k_contract_bf16<4>;
+  auto* kernel = L.gathered ? (L.out_cols == 192 ? k_contract_bf16<3, true> : k_contract_bf16<4, true>)
+                            : (L.out_cols == 192 ? k_contract_bf16<3, false> : k_contract_bf16<4, false>);
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, c.s, g);
 }
 

@@ -638,6 +638,16 @@ def test_normalize_rows_alignment(b, d, ld, at):
     assert (t_unit[:, d:] == 7.5).all()
 
 
+@pytest.mark.parametrize("B,b,off,d", [
+    (200, 90, 100, 72),                           # no stage on the loop that forms the operand from both strips
+    (256, 128, 0, 200), (288, 100, 150, 256),     # its eight stages; one more behind it; output tiles of either width
+    (520, 300, 217, 520), (700, 257, 443, 264), (1100, 513, 300, 768),      # several splits, odd ones, ragged rows and columns
+    (2304, 300, 77, 392)])
+def test_bf16_gathered_state_large_tiles_edges(B, b, off, d):
+    """Contraction of the large tiles with gathered state at the depths and widths where its loop begins and ends."""
+    run_gathered(B, b, off, d, V2 if d % 3 else V3, "bf16", TOL_BF16, ld_pad=8)
+
+
 def test_gathered_state_with_whole_batch_is_the_plain_step():
     """b == B: no remote anchors; the flag changes nothing and the gathered arrays are not read."""
     B, d, N = 520, 64, 5000

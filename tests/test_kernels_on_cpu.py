@@ -189,6 +189,9 @@ FORCED = [
     # large tiles: output tiles of the contraction of either width, a whole one and one cut short, on the ring and behind it
     dict(plan=dict(OUT_COLS=256), B=520, b=200, off=112, d=264, version=V1, flags=fc.TILES_256, ld_txt=272),
     dict(plan=dict(OUT_COLS=192), B=520, b=200, off=112, d=264, version=V2, flags=fc.TILES_256, ld_txt=272),
+    # ... with gathered state, where the loop over whole stages forms its operand from both strips
+    dict(plan=dict(OUT_COLS=256), B=700, b=40, off=300, d=40, version=V2, flags=fc.TILES_256, gathered=True),
+    dict(plan=dict(OUT_COLS=192), B=520, b=200, off=112, d=264, version=V3, flags=fc.TILES_256, gathered=True, ld_txt=272),
     # fp32 path: 64 x 64 tiles of strips and gradients, splits, the single pass on them; splits with gathered state; one partial
     # sum over several tiles, as where the strips alone fill the static array
     dict(plan=dict(F32_TILES=1, GRAD_TILE=64, NSPLIT=2), B=150, b=70, off=33, d=68, ld_img=72, version=V3, dtype="f32"),
