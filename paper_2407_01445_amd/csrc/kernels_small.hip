@@ -70,7 +70,7 @@ struct PrepArgs {
   int version;
   float *diag, *tau1, *tau2, *k1, *k2, *uold1, *uold2;
   unsigned* arrived;
-  int narrived;
+  int narrived, threads;         // threads of the launch
   // gathered state
   const float *tau_glob_img, *tau_glob_txt, *u_glob_img, *u_glob_txt;
   float eps, bm;
@@ -81,10 +81,10 @@ struct PrepArgs {
 
 template <typename T, bool GATHERED>
 __global__ void __launch_bounds__(256) k_prep(PrepArgs<T> a) {
-  if constexpr (GATHERED) warm_arguments<sizeof(PrepArgs<T>)>();   // else few of them: 0.4 us more
+  if constexpr (GATHERED) warm_arguments<sizeof(PrepArgs<T>)>();
   const int lane = threadIdx.x & 63;
   const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < a.narrived; i += (int)(gridDim.x * 256)) a.arrived[i] = 0u;
+  for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < a.narrived; i += a.threads) a.arrived[i] = 0u;
   if (w >= (GATHERED ? a.ncol : a.b)) return;
   const int64_t j = GATHERED ? w : a.off + w, r = j - a.off;      // global row; local anchor
   const bool local = !GATHERED || (r >= 0 && r < a.b);            // wave-uniform
@@ -150,6 +150,7 @@ static void launch_prep_rows(const StepCtx& c) {
   a.arrived = (unsigned*)(c.ws + L.arrived); a.narrived = L.narrived;
   const int64_t rows = L.gathered ? L.ncol : L.b;
   const dim3 grid((unsigned)((rows + 3) / 4)), block(256);
+  a.threads = (int)(grid.x * 256);
   if (!L.gathered) {
     hipLaunchKernelGGL((k_prep<T, false>), grid, block, 0, c.s, a);
     return;

@@ -49,6 +49,13 @@ struct StateArgs {
   int fused;           // fold kernels: 1 = form the coefficients and finish the anchors there, 0 = k_state has run
   int64_t bstride, b;
   int64_t stride;      // elements between consecutive samples in u_img / u_txt (and the temperature arrays)
+  // k_state only.  gather: the kernel reads u^t and the temperatures from the state arrays itself (uold / tau1 / tau2
+  // are not used; tau_glob is the global temperature of V0, V1, V3 for that case).  records: the per-sample arrays are
+  // the fields {u_1, tau_1, m_1, v_1, u_2, tau_2, m_2, v_2} of 32-byte aligned records (state_records_are_canonical):
+  // a lane moves its side's four fields as one 16-byte word.  lanes: threads per anchor side over the partial sums.
+  // (Beside the counts above: what the kernel needs first, in one line of its arguments.)
+  int gather, records, lanes;
+  int64_t ntiles;     // tiles of 128 / lanes anchors; a block takes the tiles blockIdx.x, blockIdx.x + gridDim.x, ..
   float M, gamma, eps, rho, tau_scale;
   float inv_M, bM;    // 1 / M; b M: each rounded once, on the host
   int version;
@@ -58,13 +65,7 @@ struct StateArgs {
   // V2 with the temperature update in the same pass (optimizer != 0): the temperatures and their moments at idx
   TauUpd tau_upd;
   float *tau_img, *tau_txt, *m_img, *v_img, *m_txt, *v_txt;
-  // k_state only.  gather: the kernel reads u^t and the temperatures from the state arrays itself (uold / tau1 / tau2
-  // are not used; tau_glob is the global temperature of V0, V1, V3 for that case).  records: the per-sample arrays are
-  // the fields {u_1, tau_1, m_1, v_1, u_2, tau_2, m_2, v_2} of 32-byte aligned records (state_records_are_canonical):
-  // a lane moves its side's four fields as one 16-byte word.  lanes: threads per anchor side over the partial sums.
-  int gather, records, lanes;
-  int64_t ntiles;     // tiles of 128 / lanes anchors; a block takes the tiles blockIdx.x, blockIdx.x + gridDim.x, ..
-  const float* tau_glob;
+  const float* tau_glob;        // k_state with gather
 };
 StateArgs make_state_args(const StepCtx& c);
 
