@@ -343,7 +343,20 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
     if (max_split > kMaxSplit) max_split = kMaxSplit;
     if (max_split < 1) max_split = 1;
     double best_cost = 0.0;
+    // No plan takes more workspace for partial results than whole tiles and runs of any length would: `most`.
     size_t most = 0;
+    if (L->gathered) {
+      const int64_t tiles = ((cfg.b + 255) / 256) * ((cfg.d + 255) / 256) * 2;
+      for (int64_t ns = 1; ns <= max_split; ++ns) {
+        const int64_t slice = (stages + ns - 1) / ns, used = (stages + slice - 1) / slice;
+        const double cost = (double)((tiles * used + 255) / 256) * (double)(slice + 12) + 0.05 * (double)tiles * (double)used;
+        if (best_cost == 0.0 || cost < best_cost) {
+          best_cost = cost;
+          most = (size_t)used * partial_split_floats(cfg.b, cfg.d, 256);
+        }
+      }
+      best_cost = 0.0;
+    }
     for (int cols = 256; cols >= 192; cols -= 64) {
       const double width = cols == 256 || L->gathered ? 1.0 : 0.80;
       const int64_t tiles = ((cfg.b + 255) / 256) * ((cfg.d + cols - 1) / cols) * 2;
@@ -352,7 +365,7 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
         if (L->gathered) slice += slice & 1;
         const int64_t used = (stages + slice - 1) / slice;          // splits that really get stages
         const size_t partial = (size_t)used * partial_split_floats(cfg.b, cfg.d, cols);
-        if (cols < 256 && partial > most) break;                    // no more workspace than on whole tiles
+        if (most && partial > most) break;
         const int64_t rounds = (tiles * used + 255) / 256;
         const double cost = (double)rounds * width * (double)(slice + 12) + 0.05 * (double)tiles * (double)used * (double)cols / 256.0;
         if (best_cost == 0.0 || cost < best_cost) {
@@ -360,7 +373,7 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
           L->out_cols = cols; L->nsplit = (int)used; L->kslice = slice;
         }
       }
-      if (cols == 256) most = (size_t)L->nsplit * partial_split_floats(cfg.b, cfg.d, 256);
+      if (cols == 256 && !L->gathered) most = (size_t)L->nsplit * partial_split_floats(cfg.b, cfg.d, 256);
     }
   } else {
     L->ldE = room.partial_sums ? (int64_t)round_up((size_t)cfg.B, 4) : cfg.B;

@@ -475,3 +475,12 @@ def test_few_fp32_pairs_take_no_tiles():
                          (dict(B=17, b=17, d=136), 0), (dict(B=25, b=25, d=8), 0)):
         plan = fc.fastclip_describe(good_cfg(emb_dtype=fc.F32, off=0, N=100, **shape))
         assert plan["single_pass"] == 1 - plain and plan["nparts"] == plan["nsplit"] == 1, (shape, plan)
+
+
+@pytest.mark.parametrize("B,b,d", [(963, 741, 2336), (2461, 309, 2008), (2388, 965, 648), (2418, 1189, 448)])
+def test_gathered_state_on_large_tiles_keeps_to_the_static_array(B, b, d):
+    """The contraction's stages come in pairs with gathered state; the splits that suit them take no more workspace than the
+    others would, so what fits the array of fastclip_step_static goes on fitting it."""
+    cfg = fc.make_config(version=fc.V3, emb_dtype=fc.BF16, B=B, b=b, off=0, d=d, N=1 << 20, gamma=0.5, eps=1e-6, rho=1.0,
+                         ld_img=d, ld_txt=d, flags=fc.TILES_256 | fc.GATHERED_STATE)
+    assert 0 < fc.fastclip_workspace_bytes(cfg) <= 64 << 20
