@@ -548,8 +548,7 @@ __device__ __forceinline__ bool t128_finish(const T128Args& g, const StateArgs& 
     float m = 0.f, v = 0.f;
     if (a.version == FASTCLIP_V2 && a.tau_upd.optimizer) {
       m = (side ? a.m_txt : a.m_img)[n];
-      const float* pv = side ? a.v_txt : a.v_img;
-      if (pv) v = pv[n];
+      if (keeps_second_moment(a.tau_upd)) v = (side ? a.v_txt : a.v_img)[n];
     }
     const float* e = a.sums + (size_t)(2 * side) * a.nparts * a.bstride + r;
     const float* x = e + (size_t)a.nparts * a.bstride;
@@ -793,8 +792,7 @@ __device__ __forceinline__ bool t128_tile(const T128Args& g, const StateArgs& a,
       const StateArgs& la = late_argument<kStateAt>(a);
       if (la.version == FASTCLIP_V2 && la.tau_upd.optimizer) {      // the temperature's moments, by now addressable
         fm = (fside ? la.m_txt : la.m_img)[fn * la.stride];
-        const float* pv = fside ? la.v_txt : la.v_img;
-        if (pv) fv = pv[fn * la.stride];
+        if (keeps_second_moment(la.tau_upd)) fv = (fside ? la.v_txt : la.v_img)[fn * la.stride];
       }
     }
     request_more();

@@ -25,9 +25,13 @@ __device__ inline void tau_step_values(const TauUpd& u, float& tau, float& m, fl
   }
   tau = fmaxf(next, u.tau_min);
 }
-// The same on memory (pv may be NULL for SGDM / LION).
+// Whether the optimizer has a second moment.  Where it does not, nothing reads or writes the v arrays, whatever they are.
+__device__ inline bool keeps_second_moment(const TauUpd& u) {
+  return u.optimizer == FASTCLIP_TAU_ADAMW || u.optimizer == FASTCLIP_TAU_LAMB;
+}
+// A step on memory (pv may be NULL for SGDM / LION).
 __device__ inline void tau_step(const TauUpd& u, float* ptau, float* pm, float* pv, float g) {
-  const bool two = u.optimizer == FASTCLIP_TAU_ADAMW || u.optimizer == FASTCLIP_TAU_LAMB;
+  const bool two = keeps_second_moment(u);
   float tau = *ptau, m = *pm, v = two ? *pv : 0.f;
   tau_step_values(u, tau, m, v, g);
   if (two) *pv = v;
@@ -241,9 +245,8 @@ __device__ inline void state_finish_side(const StateArgs& a, int side, int64_t r
   if (a.version == FASTCLIP_V2) {
     (side ? a.d_tau_txt : a.d_tau_img)[r] = o.gt;
     if (a.tau_upd.optimizer) {
-      const bool two = a.tau_upd.optimizer == FASTCLIP_TAU_ADAMW || a.tau_upd.optimizer == FASTCLIP_TAU_LAMB;
       tau_step_values(a.tau_upd, tau, m, v, o.gt);
-      if (two) (side ? a.v_txt : a.v_img)[n] = v;
+      if (keeps_second_moment(a.tau_upd)) (side ? a.v_txt : a.v_img)[n] = v;
       (side ? a.m_txt : a.m_img)[n] = m;
       (side ? a.tau_txt : a.tau_img)[n] = tau;
     }

@@ -70,6 +70,11 @@ PLAN_RULES = [
      "L->own_prep = " + _forced("(tiles + 255) / 256 * rows * cfg.d <= 200000", "EMU_OWN_PREP") + ";"),
     ("fc_internal.hpp", "return 2 * ((L.b + 63) / 64) * (int64_t)L.nparts <= 256;",
      "return " + _forced("2 * ((L.b + 63) / 64) * (int64_t)L.nparts <= 256", "EMU_NARROW") + ";"),
+    # ... the state phase: inside the contraction or on its own; by workgroups of its own there or by those of the output tiles
+    ("fastclip_api.hip", "const bool fused = r == 1 || (rows == 64 && nq <= 256 && L->nparts <= 64);",
+     "const bool fused = " + _forced("r == 1 || (rows == 64 && nq <= 256 && L->nparts <= 64)", "EMU_FUSED") + ";"),
+    ("kernels_tiles128.hip", "g.finishers = L.fused_state && groups + finishers <= 256 ? (int)finishers : 0;",
+     "g.finishers = L.fused_state && " + _forced("groups + finishers <= 256", "EMU_FINISHERS") + " ? (int)finishers : 0;"),
     # large tiles: columns of an output tile of the contraction
     ("fastclip_api.hip", "    for (int cols = 256; cols >= 192; cols -= 64) {",
      '    for (int cols = 256; cols >= 192; cols -= 64) {\n'

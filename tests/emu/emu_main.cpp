@@ -208,7 +208,14 @@ int main(int argc, char** argv) {
   void* ws = nullptr;
   if (posix_memalign(&ws, 256, need)) return 2;
   if (!getenv("EMU_UNINIT")) memset(ws, 0xff, need);
-  const fastclip_status st = with_tau ? fastclip_step_update_tau(&cfg, &b, &upd, &tst, ws, need, nullptr)
+  // an optimizer without a second moment touches none: one byte stands for each dense array, any access is outside
+  fastclip_tau_state given = tst;
+  const bool second = upd.optimizer == FASTCLIP_TAU_ADAMW || upd.optimizer == FASTCLIP_TAU_LAMB;
+  if (with_tau && v2_ && !second && S == 1) {
+    given.v_img = (float*)malloc(1);
+    given.v_txt = (float*)malloc(1);
+  }
+  const fastclip_status st = with_tau ? fastclip_step_update_tau(&cfg, &b, &upd, &given, ws, need, nullptr)
                                       : fastclip_step(&cfg, &b, ws, need, nullptr);
   if (st != FASTCLIP_OK) { fprintf(stderr, "fastclip_step: %d\n", (int)st); return 4; }
   FILE* o = fopen(argv[2], "wb");

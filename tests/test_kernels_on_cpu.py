@@ -19,7 +19,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, os.path.join(ROOT, "tests", "emu"))
 import build_emu  # noqa: E402
 
-from oracle import ADAMW, LION, V0, V1, V2, V3, ema_update, fcco_step, normalize_rows, temperature_update  # noqa: E402
+from oracle import ADAMW, LION, SGDM, V0, V1, V2, V3, ema_update, fcco_step, normalize_rows, temperature_update  # noqa: E402
 from paper_2407_01445_amd import binding as fc  # noqa: E402
 from paper_2407_01445_amd.workloads import draw_indices, make_embeddings  # noqa: E402
 
@@ -238,14 +238,20 @@ UPD = dict(lr=2e-3, step=3, beta1=0.9, beta2=0.98, eps=1e-8, tau_min=0.02, lr_dr
     dict(B=300, b=140, off=100, d=72, version=V2, optimizer=ADAMW, stride=8, flags=fc.TILES_256),
     # ... records with four floats of padding that must stay untouched; the state phase inside the fold (small tiles)
     dict(B=300, b=140, off=100, d=72, version=V2, optimizer=ADAMW, stride=12),
-    # dense arrays, field by field
+    # dense arrays, field by field; without a second moment, whose arrays nothing may touch then (emu_main.cpp): anchors finished
+    # by workgroups of their own, by those of the output tiles, by k_state and by the fold
     dict(B=40, b=40, off=0, d=16, version=V2, optimizer=LION, stride=1),
+    dict(plan=dict(OUT_ROWS=32, FINISHERS=0), B=140, b=70, off=33, d=40, version=V2, optimizer=LION, stride=1),
+    dict(plan=dict(FUSED=0), B=140, b=70, off=33, d=40, version=V2, optimizer=SGDM, stride=1),
+    dict(B=140, b=70, off=33, d=40, version=V2, optimizer=SGDM, stride=1, flags=fc.TILES_256),
     # the global temperature stepped by a kernel of its own once its gradient is complete
     dict(B=300, b=140, off=100, d=72, version=V3, optimizer=ADAMW, stride=1),
 ], ids=lambda c: "-".join("%s%s" % (k, v) for k, v in c.items()))
-def test_step_with_temperature_update_of_the_host_built_kernels(emu_step, tmp_path, case):
+def test_step_with_temperature_update_of_the_host_built_kernels(emu_step, tmp_path, monkeypatch, case):
     """fastclip_step_update_tau: every output of the step, the state, and the temperatures with their moments after
     Proc. temperature_update, against the oracle's step followed by its temperature update."""
+    for k, v in case.get("plan", {}).items():
+        monkeypatch.setenv("EMU_" + k, str(v))
     B, b, off, d, version, S = case["B"], case["b"], case["off"], case["d"], case["version"], case["stride"]
     N, gamma, eps, rho, tau = max(700, b + 100), 0.6, 1e-6, 6.5, 0.07
     rng = np.random.default_rng(5)
@@ -303,8 +309,8 @@ def test_step_with_temperature_update_of_the_host_built_kernels(emu_step, tmp_pa
         temperature_update(V2, want, optimizer=case["optimizer"], tau_img=w["tau_img"], tau_txt=w["tau_txt"], idx=idx,
                            m_img=w["m_img"], v_img=w["v_img"], m_txt=w["m_txt"], v_txt=w["v_txt"], **kw)
         for k in ("tau_img", "tau_txt", "m_img", "v_img", "m_txt", "v_txt"):
-            if case["optimizer"] == LION and k.startswith("v_"):
-                assert np.array_equal(got[k], st[k].astype(np.float64))          # Lion keeps no second moment
+            if case["optimizer"] in (LION, SGDM) and k.startswith("v_"):
+                assert np.array_equal(got[k], st[k].astype(np.float64))          # they keep no second moment
                 continue
             scale = np.max(np.abs(w[k]))
             assert np.max(np.abs(got[k] - w[k])) <= 2e-2 * scale, k
