@@ -120,9 +120,9 @@ struct ContractTile {
   static __device__ __forceinline__ int nswz(int k) { return NJ == 4 ? nt_swz(k) : ((k >> 1) & 1) << 2; }
   // row of the stage and logical piece that lane `lane` of wave load f (0 .. 4 NJ - 1) fetches
   __device__ __forceinline__ void b_piece(int f, int* k, int* piece) const {
-    const int at = f * 64 + lane;
-    *k = at / kPieces;
-    *piece = (at - *k * kPieces) ^ nswz(*k);
+    const unsigned at = (unsigned)(f * 64 + lane);
+    *k = (int)(at / kPieces);
+    *piece = (int)(at % kPieces) ^ nswz(*k);
   }
   __device__ __forceinline__ void setup(const bf16_t* E, int64_t nCB, int64_t ab0, const bf16_t* X_, int64_t ldx_,
                                         int64_t n0_, int64_t N_, int64_t B_, int tid) {
@@ -326,11 +326,12 @@ __device__ __forceinline__ void ring_mainloop(f32x16 (&acc)[4][Tile::NJ], const 
   bf16x8 a0[4], a1[4];
   u32x2 bl0[NJ], bh0[NJ], bl1[NJ], bh1[NJ];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) a0[t] = T.read_a(ring, t, 0);
-#pragma unroll
-  for (int t = 0; t < NJ; ++t) {
-    bl0[t] = T.read_b_half(ring, t, 0, 0);
-    bh0[t] = T.read_b_half(ring, t, 0, 1);
+  for (int t = 0; t < 4; ++t) {
+    a0[t] = T.read_a(ring, t, 0);
+    if (t < NJ) {
+      bl0[t] = T.read_b_half(ring, t, 0, 0);
+      bh0[t] = T.read_b_half(ring, t, 0, 1);
+    }
   }
   uint32_t cur = 0u, nxt = (uint32_t)kStageBytes, prv = 4u * (uint32_t)kStageBytes, pp = 3u * (uint32_t)kStageBytes;
   int s = 0;
@@ -494,9 +495,10 @@ __device__ __forceinline__ void guarded_mainloop(f32x16 (&acc)[4][Tile::NJ], con
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) a[t] = T.read_a(ring, t, kk);
-#pragma unroll
-      for (int t = 0; t < Tile::NJ; ++t) bq[t] = T.read_b(ring, t, kk);
+      for (int t = 0; t < 4; ++t) {
+        a[t] = T.read_a(ring, t, kk);
+        if (t < Tile::NJ) bq[t] = T.read_b(ring, t, kk);
+      }
 #pragma unroll
       for (int ti = 0; ti < 4; ++ti)
 #pragma unroll
@@ -925,10 +927,10 @@ void launch_fold_bf16(const StepCtx& c) {
 }
 
 // ----------------------------------------------------------------------------------------------------------------
+typedef __attribute__((address_space(1))) float global_f32;      // known to be global memory
+typedef __attribute__((address_space(1))) f32x4 global_f32x4;
 struct ContractJob {
   const bf16_t* E;    // fragment-ordered strip: l of the local anchors with the contrast-side weights folded in
-  const bf16_t* F;    // gathered state: the second strip, fragment-ordered as E, and the coefficients of the local anchors
-  const float* c_own;
   const bf16_t* X;    // the matrix whose rows the strip weights: texts for strip 0, images for strip 1
   float* C;           // [nsplit][tile][64 groups of 4 rows][64 NJ columns][4 rows]: whole tiles
   int64_t ldx;
@@ -940,6 +942,9 @@ struct ContractArgs {
   ContractJob job[2];   // the two strips
   int64_t M, N, B;
   int nsplit, tiles_m, tiles_n;
+  // gathered state: the second strip, fragment-ordered as E, and the coefficients of the local anchors
+  const bf16_t* F[2];
+  const float* c_own[2];
 };
 
 template <int NJ, bool REMOTE>
@@ -964,10 +969,10 @@ __global__ void __launch_bounds__(256) k_contract_bf16(ContractArgs g) {
   if (S > 0) {
     ContractTile<NJ, REMOTE> T;
     T.setup(J.E, J.nCB, m0 >> 5, J.X, J.ldx, n0, g.N, g.B, tid);
-    if constexpr (REMOTE) T.setup_remote(J.F, J.nCB, m0 >> 5, J.c_own, g.M, tid);
-    // The unguarded loads of a stage take 32 whole rows of X and W columns from n0 on.   They stay inside the matrix
+    if constexpr (REMOTE) T.setup_remote(g.F[ji], J.nCB, m0 >> 5, g.c_own[ji], g.M, tid);
+    // The unguarded loads of a stage take 32 whole rows of X and W columns from n0 on.  They stay inside the matrix
     // (B rows of ldx elements, the last one of N) for the stages below `safe`: rows beyond B never, and where the tile
-    // is wider than what is left of a row (n0 + W > N)  the words past the row's end are the next rows' - they exist
+    // is wider than what is left of a row (n0 + W > N) the words past the row's end are the next rows' - they exist
     // except behind the last rows, and what they put into the columns from N on reaches no output.  Those stages run
     // through the ring; the few that are left at the ragged end go one at a time with guards.
     int64_t rows_ok = g.B;
@@ -986,7 +991,9 @@ __global__ void __launch_bounds__(256) k_contract_bf16(ContractArgs g) {
   // The partial result leaves as whole tiles of [64 groups of 4 rows][W columns][4 rows]: a lane holds C[m][n] for
   // n = n0 + wn W/2 + tj 32 + lr and the rows m = m0 + wm 128 + ti 32 + 8 q + 4 hk + t, t = 0..3, so its four values of one
   // q are one 16-byte word of that layout and a wave store covers two runs of 512 consecutive bytes.  The buffer holds
-  // whole tiles, so nothing is guarded here; k_finalize_bf16 reads four rows at a time in the same order.
+  // whole tiles, so nothing is guarded here; k_finalize_bf16 reads four rows at a time in the same order.  The scalar base
+  // keeps its address space through the asm statement: as flat stores the kernel takes 0.5 - 1.5 us longer (832 of 13312 at
+  // 240: 27.0 / 25.5, 1024 of 32768 at 1024: 117.5 / 116).
   const int lr = lane & 31, hk = lane >> 5;
   float* C = J.C + (size_t)split * J.split_stride + (size_t)tile * (256 * W);     // wave-uniform
   const uint32_t at = (uint32_t)(((wm * 32 + hk) * W + wn * (W / 2) + lr) * 4);
@@ -994,12 +1001,12 @@ __global__ void __launch_bounds__(256) k_contract_bf16(ContractArgs g) {
   for (int ti = 0; ti < 4; ++ti)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      float* row = C + (ti * 8 + q * 2) * (W * 4);
+      global_f32* row = (global_f32*)C + (ti * 8 + q * 2) * (W * 4);
       asm volatile("" : "+s"(row));            // one scalar address per four rows, not one per store in vector registers
 #pragma unroll
       for (int tj = 0; tj < NJ; ++tj) {
         const f32x4 v = {acc[ti][tj][4 * q], acc[ti][tj][4 * q + 1], acc[ti][tj][4 * q + 2], acc[ti][tj][4 * q + 3]};
-        *(f32x4*)(row + at + tj * 128) = v;
+        *(global_f32x4*)(row + at + tj * 128) = v;
       }
     }
 }
@@ -1007,13 +1014,11 @@ __global__ void __launch_bounds__(256) k_contract_bf16(ContractArgs g) {
 void launch_contract_bf16(const StepCtx& c) {
   const Layout& L = c.L;
   ContractArgs g;
-  const int njobs = 2;
-  for (int j = 0; j < njobs; ++j) {
-    const int s = j & 1;
-    ContractJob& J = g.job[j];
+  for (int s = 0; s < 2; ++s) {
+    ContractJob& J = g.job[s];
     J.E = (const bf16_t*)(c.ws + L.E[s]);
-    J.F = L.gathered ? (const bf16_t*)(c.ws + L.F[s]) : nullptr;
-    J.c_own = (const float*)(c.ws + (s == 0 ? L.c1 : L.c2));
+    g.F[s] = L.gathered ? (const bf16_t*)(c.ws + L.F[s]) : nullptr;
+    g.c_own[s] = (const float*)(c.ws + (s == 0 ? L.c1 : L.c2));
     J.X = (const bf16_t*)(s == 0 ? c.buf.txt_glob : c.buf.img_glob);
     J.ldx = s == 0 ? c.cfg.ld_txt : c.cfg.ld_img;
     J.C = (float*)(c.ws + L.Opart[s]);
@@ -1026,7 +1031,7 @@ void launch_contract_bf16(const StepCtx& c) {
   g.nsplit = L.nsplit;
   g.tiles_m = (int)((L.b + 255) / 256);
   g.tiles_n = (int)((L.d + L.out_cols - 1) / L.out_cols);
-  const unsigned grid = (unsigned)njobs * (unsigned)(g.nsplit * g.tiles_m * g.tiles_n);
+  const unsigned grid = 2u * (unsigned)(g.nsplit * g.tiles_m * g.tiles_n);
   auto* kernel = L.gathered ? (L.out_cols == 192 ? k_contract_bf16<3, true> : k_contract_bf16<4, true>)
                             : (L.out_cols == 192 ? k_contract_bf16<3, false> : k_contract_bf16<4, false>);
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, c.s, g);

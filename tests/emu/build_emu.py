@@ -2,7 +2,7 @@
 hip/hip_runtime.h of this folder, linked with emu_main.cpp into _build/emu/emu_step, AddressSanitizer on.
 
 The sources are copied with the few constructs a host compiler cannot take replaced by calls into the stand-in: inline
-assembly (direct-to-LDS loads, accumulator reads) and the LDS address-space attribute.  Indexing, guards, barriers and the
+assembly (direct-to-LDS loads, accumulator reads) and the address-space attributes.  Indexing, guards, barriers and the
 order of operations are the product's.  So that a small shape can run what the library's plans keep for large ones, the rules
 in PLAN_RULES also listen to environment variables (EMU_...): unset, they decide as in the product."""
 from __future__ import annotations
@@ -97,7 +97,7 @@ def generate():
             if not n.endswith((".hip", ".hpp", ".h")):
                 continue
             s = open(os.path.join(d, n)).read()
-            s = s.replace("__attribute__((address_space(3)))", "")
+            s = s.replace("__attribute__((address_space(3)))", "").replace("__attribute__((address_space(1)))", "")
             s = re.sub(r'asm volatile\((?:[^;]|\n)*?\);', _asm_replacement, s)
             for name, text, instead in PLAN_RULES:
                 if name == n:

@@ -150,3 +150,39 @@ def test_no_kernel_uses_scratch_memory_and_lds_fits_a_compute_unit(assembly):
             assert lds <= 160 * 1024, (name, lds)
             assert scratch == 0 and spills == 0, (name, scratch, spills)
     assert n >= 30
+
+
+def kernel_lines(asm: str, part: str):
+    """(name, instructions and labels) of every kernel whose mangled name holds `part`"""
+    for m in re.finditer(r"^(_ZN2fc\w+):.*?(?=^\s*\.section)", asm, re.S | re.M):
+        if part in m.group(1):
+            yield m.group(1), [ln.strip() for ln in m.group(0).split("\n") if ln.strip() and not ln.lstrip().startswith(";")]
+
+
+def test_large_tile_contraction_stores_to_global_memory(assembly):
+    """Its partial tiles leave as global stores: a flat one waits for LDS traffic as well, 0.5 - 1.7 us of the kernel."""
+    kernels = list(kernel_lines(assembly["kernels_mfma.hip"], "k_contract_bf16"))
+    assert len(kernels) == 4
+    for name, lines in kernels:
+        assert sum(ln.startswith("global_store_dwordx4") for ln in lines) >= 48, name
+        assert not [ln for ln in lines if ln.startswith("flat_")], name
+
+
+def test_ring_stages_of_the_large_tiles_hold_their_addresses(assembly):
+    """The loops of ring_mainloop (24 or 32 products and one barrier a stage): the LDS addresses of the operand reads stay in
+    registers from stage to stage.  Up to 12 vector instructions beside products and reads are the wave loads' and the
+    ring's; formed again in every stage the addresses take another 20."""
+    seen = 0
+    for part in ("k_strips_edge_bf16", "k_contract_bf16ILi3ELb0", "k_contract_bf16ILi4ELb0"):
+        for name, lines in kernel_lines(assembly["kernels_mfma.hip"], part):
+            labels = {ln.split(":")[0]: i for i, ln in enumerate(lines) if re.match(r"^\S+:", ln)}
+            for i, ln in enumerate(lines):
+                op = ln.split()
+                start = labels.get(op[1], i) if op[0].startswith("s_cbranch") else i
+                body = lines[start:i]
+                if sum(x.startswith("v_mfma") for x in body) not in (24, 32) or sum(x.startswith("s_barrier") for x in body) != 1:
+                    continue
+                seen += 1
+                other = [x for x in body if x.startswith("v_") and not x.startswith("v_mfma")]
+                assert len(other) <= 16, (name, len(other), other)
+    assert seen >= 12
