@@ -954,12 +954,16 @@ __global__ void __launch_bounds__(256) k_contract_bf16(ContractArgs g) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   const uint32_t ring_addr = lds_addr(ring);
-  const int per_job = g.nsplit * g.tiles_m * g.tiles_n;
-  const int ji = (int)blockIdx.x / per_job;
-  const int local = (int)blockIdx.x % per_job;
+  // Workgroups that share an XCD (id mod 8) take neighbours in the order split, side, column tile, row tile: the same slice of the
+  // depth, whose rows of X and fragments of the strips its L2 then fetches once.  With the splits going round the ids every
+  // XCD fetched every slice where their number is no multiple of eight: 1792 of 7168 at 1024 (3 splits) 83 us, now 54; 1408 of
+  // 22528 at 512 (10) 77 / 66; gathered state 768 of 24576 at 1024 (10) 144 / 94, 2160 of 8640 at 952 (3) 140 / 96.
+  const int tiles = g.tiles_m * g.tiles_n;
+  const int p = ((int)blockIdx.x & 7) * ((int)gridDim.x >> 3) + ((int)blockIdx.x >> 3);
+  if (p >= 2 * tiles * g.nsplit) return;
+  const int split = p / (2 * tiles), of_split = p - split * 2 * tiles;
+  const int ji = of_split >= tiles, tile = of_split - ji * tiles;
   const ContractJob& J = g.job[ji];
-  const int split = local % g.nsplit;            // consecutive ids -> different XCDs -> different column slices
-  const int tile = local / g.nsplit;
   const int64_t m0 = (int64_t)(tile % g.tiles_m) * 256, n0 = (int64_t)(tile / g.tiles_m) * W;
   const int s0 = split * J.slice;
   const int S = (s0 + J.slice <= J.stages ? J.slice : J.stages - s0);
@@ -1031,7 +1035,7 @@ void launch_contract_bf16(const StepCtx& c) {
   g.nsplit = L.nsplit;
   g.tiles_m = (int)((L.b + 255) / 256);
   g.tiles_n = (int)((L.d + L.out_cols - 1) / L.out_cols);
-  const unsigned grid = 2u * (unsigned)(g.nsplit * g.tiles_m * g.tiles_n);
+  const unsigned grid = (2u * (unsigned)(g.nsplit * g.tiles_m * g.tiles_n) + 7) / 8 * 8;
   auto* kernel = L.gathered ? (L.out_cols == 192 ? k_contract_bf16<3, true> : k_contract_bf16<4, true>)
                             : (L.out_cols == 192 ? k_contract_bf16<3, false> : k_contract_bf16<4, false>);
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, c.s, g);

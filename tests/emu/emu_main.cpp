@@ -2,6 +2,7 @@
 // its own exact-size allocation, so that AddressSanitizer sees any access outside it; the matrices end with the last
 // row's d elements.  Test infrastructure (see hip/hip_runtime.h).
 #include <hip/hip_runtime.h>
+#include <unordered_set>
 #include "fastclip.h"
 
 thread_local dim3 threadIdx, blockIdx;
@@ -51,6 +52,25 @@ struct Pool {
 };
 static Pool g_pool;
 
+// Direct-to-LDS loads of a launch (one per lane), and the 128-byte lines that they touch, counted once per XCD: workgroups
+// go to the eight XCDs in turn, and each has an L2 of its own.
+bool g_count = getenv("EMU_FETCHES") != nullptr;
+static std::mutex g_count_mutex;
+static size_t g_loads;
+static std::unordered_set<uintptr_t> g_lines[8];
+void note_fetch(const void* p) {
+  const unsigned wg = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+  std::lock_guard<std::mutex> lock(g_count_mutex);
+  ++g_loads;
+  g_lines[wg % 8].insert((uintptr_t)p / 128);
+}
+static void report_fetches(dim3 grid, dim3 block) {
+  size_t lines = 0;
+  for (auto& l : g_lines) { lines += l.size(); l.clear(); }
+  fprintf(stderr, "fetches: workgroups %u threads %u loads %zu lines %zu\n", grid.x * grid.y * grid.z, block.x, g_loads, lines);
+  g_loads = 0;
+}
+
 void launch(dim3 grid, dim3 block, const std::function<void()>& body) {
   gridDim = grid; blockDim = block;
   const int nthreads = (int)(block.x * block.y * block.z), nwaves = (nthreads + 63) / 64;
@@ -70,6 +90,7 @@ void launch(dim3 grid, dim3 block, const std::function<void()>& body) {
           t_block->bar.leave();
         });
       }
+  if (g_count) report_fetches(grid, block);
 }
 }  // namespace emu
 

@@ -74,6 +74,8 @@ extern thread_local Block* t_block;
 extern thread_local Wave* t_wave;
 extern thread_local int t_lane;
 extern uintptr_t g_lds_hi;      // upper 32 bits shared by every static (LDS) object of the image
+extern bool g_count;            // EMU_FETCHES: every launch reports its direct-to-LDS loads
+void note_fetch(const void* p);
 }  // namespace emu
 
 extern thread_local dim3 threadIdx, blockIdx;
@@ -139,6 +141,7 @@ static inline T __shfl(T v, int from) {
 static inline void emu_dma(const void* base, uint32_t off, uint32_t lds32, int bytes) {
   char* dst = (char*)(emu::g_lds_hi | (uintptr_t)lds32) + (size_t)bytes * emu::t_lane;
   memcpy(dst, (const char*)base + off, bytes);
+  if (emu::g_count) emu::note_fetch((const char*)base + off);
 }
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 emu_bf16x8;

@@ -9,6 +9,7 @@ runs as long as it is kept off the GPU."""
 from __future__ import annotations
 
 import os
+import re
 import subprocess
 import sys
 
@@ -82,7 +83,7 @@ def run_case(exe, tmp_path, *, B, b, off, d, version, dtype="bf16", flags=0, ld_
             if version == V2:
                 glob["tau_img"].tofile(f)
                 glob["tau_txt"].tofile(f)
-    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0", TSAN_OPTIONS="report_thread_leaks=0")
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0", TSAN_OPTIONS="report_thread_leaks=0", EMU_FETCHES="1")
     if SANITIZER == "memory":
         env["EMU_UNINIT"] = "1"
     r = subprocess.run([exe, fin, fout], capture_output=True, text=True, timeout=600, env=env)
@@ -130,6 +131,8 @@ def run_case(exe, tmp_path, *, B, b, off, d, version, dtype="bf16", flags=0, ld_
     errs["u_txt"] = np.max(np.abs(got["u_txt"][idx] - ut[idx]) / ut[idx])
     bad = {k: v for k, v in errs.items() if not v <= tol}
     assert not bad, bad
+    # per launch with direct-to-LDS loads: loads (one per lane) and the lines of memory that the XCDs' L2 caches fetch for them
+    return [(int(n), int(m)) for n, m in re.findall(r"loads (\d+) lines (\d+)", r.stderr) if int(n)]
 
 
 CASES = [
@@ -206,6 +209,16 @@ def test_plans_of_larger_shapes_on_the_host_built_kernels(emu_step, tmp_path, mo
     for k, v in case["plan"].items():
         monkeypatch.setenv("EMU_" + k, str(v))
     run_case(emu_step, tmp_path, **{k: v for k, v in case.items() if k != "plan"})
+
+
+def test_large_tile_contraction_shares_its_operands_inside_an_xcd(emu_step, tmp_path):
+    """Three splits of two row tiles and two sides: the workgroups of an XCD read the same slice of the depth, so that the
+    eight L2 caches together fetch little more than every line of the strips and the matrices once."""
+    b, B, d = 260, 768, 72
+    launches = run_case(emu_step, tmp_path, B=B, b=b, off=300, d=d, version=V3, flags=fc.TILES_256)
+    assert len(launches) == 2                                      # strips, contraction
+    strips, matrices = 2 * 512 * B * 2 // 128, 2 * B * d * 2 // 128
+    assert launches[1][1] <= strips + matrices, (launches, strips, matrices)
 
 
 @pytest.mark.parametrize("seed", range(8))
