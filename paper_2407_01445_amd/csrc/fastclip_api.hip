@@ -336,33 +336,18 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
     // round unused.  Steps with 256 / with the chosen 192 columns, us: 4096 of 4096 at 768 131 / 129, at 640 125 / 123, at 576
     // 122 / 112, at 384 105 / 97, at 128 86 / 81; 1024 of 8192 at 768 87.4 / 82.5, at 192 59.5 / 55.1; 512 of 32768 at 768
     // 148 / 126; 2048 of 16384 at 576 196 / 177; 3000 of 3000 at 768 143 / 139; 2560 of 2560 at 960 106 / 95.
-    // Gathered state: the strips are twice as much whatever the columns, so a stage of 192 takes as long; stages come in pairs
-    // there (remote_mainloop), a last odd one takes as long as four.
+    // Gathered state: the strips are twice as much whatever the columns, so a stage of 192 takes as long.
     const int64_t stages = L->ldE / 32;
     int64_t max_split = stages / 8;
     if (max_split > kMaxSplit) max_split = kMaxSplit;
     if (max_split < 1) max_split = 1;
     double best_cost = 0.0;
-    // No plan takes more workspace for partial results than whole tiles and runs of any length would: `most`.
-    size_t most = 0;
-    if (L->gathered) {
-      const int64_t tiles = ((cfg.b + 255) / 256) * ((cfg.d + 255) / 256) * 2;
-      for (int64_t ns = 1; ns <= max_split; ++ns) {
-        const int64_t slice = (stages + ns - 1) / ns, used = (stages + slice - 1) / slice;
-        const double cost = (double)((tiles * used + 255) / 256) * (double)(slice + 12) + 0.05 * (double)tiles * (double)used;
-        if (best_cost == 0.0 || cost < best_cost) {
-          best_cost = cost;
-          most = (size_t)used * partial_split_floats(cfg.b, cfg.d, 256);
-        }
-      }
-      best_cost = 0.0;
-    }
+    size_t most = 0;      // 192 columns take no more workspace for partial results than the plan of 256 would
     for (int cols = 256; cols >= 192; cols -= 64) {
       const double width = cols == 256 || L->gathered ? 1.0 : 0.80;
       const int64_t tiles = ((cfg.b + 255) / 256) * ((cfg.d + cols - 1) / cols) * 2;
       for (int64_t ns = 1; ns <= max_split; ++ns) {
-        int64_t slice = (stages + ns - 1) / ns;
-        if (L->gathered) slice += slice & 1;
+        const int64_t slice = (stages + ns - 1) / ns;
         const int64_t used = (stages + slice - 1) / slice;          // splits that really get stages
         const size_t partial = (size_t)used * partial_split_floats(cfg.b, cfg.d, cols);
         if (most && partial > most) break;
@@ -373,7 +358,7 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
           L->out_cols = cols; L->nsplit = (int)used; L->kslice = slice;
         }
       }
-      if (cols == 256 && !L->gathered) most = (size_t)L->nsplit * partial_split_floats(cfg.b, cfg.d, 256);
+      if (cols == 256) most = (size_t)L->nsplit * partial_split_floats(cfg.b, cfg.d, 256);
     }
   } else {
     L->ldE = room.partial_sums ? (int64_t)round_up((size_t)cfg.B, 4) : cfg.B;

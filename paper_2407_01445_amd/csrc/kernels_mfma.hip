@@ -346,14 +346,20 @@ __device__ __forceinline__ void ring_mainloop(f32x16 (&acc)[4][Tile::NJ], const 
 
 // The contraction's loop with gathered state (ContractTile<NJ, true>): the B operand comes as above, the A operand through
 // registers.  Stage s forms the A operand of stage s + 3 from chunks of both strips that were requested two stages before, writes
-// it into its slot and requests those of stage s + 5 into the registers just freed: two sets, taken in turn, so S is even (and
-// at least 8, for the stages at the end).  A pair of elements (seven VALU instructions) goes behind every other MFMA.
+// it into its slot and requests those of stage s + 5 into the registers just freed: two sets, taken in turn.  A pair of
+// elements (seven VALU instructions) goes behind every other MFMA.
+// Any run of stages, S >= 1: an odd one begins with a stage of zeros (A operand) ahead of its first, and what lies behind the last
+// stage is requested as that one, into registers and slots that nobody reads.  One body, for which the wait counts are
+// constant.  With the stages at the end peeled, and their requests left out, runs of 14 stages took 22.4 us instead of 23.1, of 32
+// 36.2 instead of 36.7, of 128 155 instead of 154; with the short runs in a loop of their own beside them the kernel spills.
+// Runs below eight stages and last odd ones one at a time through guarded_mainloop take as long as four stages each: 1536 of 3072
+// at 200 36.6 us, here 20.1; 704 of 5632 at 448, steps, 80 / 69.
 // LDS: what a stage writes is complete before the barrier of the one after the next: later reads of this wave, which LDS serves
 // in order, have been waited for by then.
 // Why not a pass over both strips ahead of the contraction: it reads and writes 384 MiB for 1024 of 32768 pairs
-// at width 1024, 63 us; the loop takes 160 us instead of 115, bound by the strips' way from memory (pairs in the second half
-// stage only or spread over both make no difference).  Steps, pass / here, us: 1024 of 32768 at 1024 387 / 364, 512 of 32768 at
-// 512 159 / 140, 1024 of 16384 at 384 140 / 110, 1024 of 5120 at 1024 102 / 96.
+// at width 1024, 63 us; the loop takes 155 us instead of 116, bound by the strips' way from memory (pairs in the second half
+// stage only or spread over both make no difference).  Steps, pass / here, us: 1024 of 32768 at 1024 376 / 347, 512 of 32768 at
+// 512 162 / 143, 1024 of 16384 at 384 140 / 110, 1024 of 5120 at 1024 101 / 94.
 struct RemoteSet {
   u32x4 e[4], f[4];
 };
@@ -364,12 +370,12 @@ __device__ __forceinline__ void remote_request(const Tile& T, RemoteSet& r, int 
 }
 // Pair w of the set's 16; a chunk that is complete goes to its place in the slot and its registers to the stage `next`.
 template <typename Tile>
-__device__ __forceinline__ void remote_pair(const Tile& T, RemoteSet& r, int w, char* slot, bool request, int next) {
+__device__ __forceinline__ void remote_pair(const Tile& T, RemoteSet& r, int w, char* slot, int next, bool zero = false) {
   const int i = w >> 2;
   r.e[i][w & 3] = T.combine(i, r.e[i][w & 3], r.f[i][w & 3]);
   if ((w & 3) == 3) {
-    *(u32x4*)(slot + T.la[i] + T.lane * 16) = r.e[i];
-    if (request) { r.e[i] = T.load_e(i, next); r.f[i] = T.load_f(i, next); }
+    *(u32x4*)(slot + T.la[i] + T.lane * 16) = zero ? u32x4{0u, 0u, 0u, 0u} : r.e[i];
+    r.e[i] = T.load_e(i, next); r.f[i] = T.load_f(i, next);
   }
 }
 // The half stages with a pair of elements behind every other MFMA (of three: behind two): P(0) .. P(7).
@@ -403,33 +409,31 @@ __device__ __forceinline__ void remote_pair(const Tile& T, RemoteSet& r, int w, 
     FC_SLOT(3, 0, AP, BLP, BHP, if (RD) AQ[2] = T.read_a(src, 2, KQ); P(6))                                         \
     FC_SLOT(3, 1, AP, BLP, BHP, if (RD) AQ[3] = T.read_a(src, 3, KQ); P(7))                                         \
     FC_SLOT(3, 2, AP, BLP, BHP, D2)
-// Stage s: SET holds the chunks of stage s + 3 (STORE: there is such a stage; MOREREQ: stage s + 5 too), of which the first
-// half stage takes the first eight pairs and the second half the others.  WAIT: loads that may stay in flight at the barrier:
-// those younger than the B operand of stage s + 1, at least four per half stage since then that requests chunks and NJ per
-// stage with a B operand.
-#define FC_PAIR(k, SET, STORE, MOREREQ) if (STORE) remote_pair(T, SET, k, ring + wslot, MOREREQ, s0 + s + 5)
-#define FC_STAGE_REMOTE(SET, MORE, STORE, MOREREQ, WAIT)                                                            \
+// Stage s: SET holds the chunks of stage s + 3, of which the first half stage takes the first eight pairs and the second half
+// the others.  At the barrier those loads may stay in flight that are younger than the B operand of stage s + 1: two sets' and
+// the B operands of stages s + 2 and s + 3.
+#define FC_PAIR(k, SET) remote_pair(T, SET, k, ring + wslot, later(5))
+#define FC_STAGE_REMOTE(SET)                                                                                        \
   {                                                                                                                 \
     const char* sl = ring + cur;                                                                                    \
     const uint32_t bslot = ring_addr + pp, wslot = pp;                                                              \
-    auto first = [&](int k) __attribute__((always_inline)) { FC_PAIR(k, SET, STORE, MOREREQ); };                    \
-    auto second = [&](int k) __attribute__((always_inline)) { FC_PAIR(8 + k, SET, STORE, MOREREQ); };               \
+    auto first = [&](int k) __attribute__((always_inline)) { FC_PAIR(k, SET); };                                    \
+    auto second = [&](int k) __attribute__((always_inline)) { FC_PAIR(8 + k, SET); };                               \
     if constexpr (NJ == 4) {                                                                                        \
-      FC_HALF_P(a0, bl0, bh0, a1, bl1, bh1, sl, 1, true, if (STORE) T.dma(4, s0 + s + 3, bslot),                    \
-                if (STORE) T.dma(5, s0 + s + 3, bslot), if (STORE) T.dma(6, s0 + s + 3, bslot),                     \
-                if (STORE) T.dma(7, s0 + s + 3, bslot), first)                                                      \
+      FC_HALF_P(a0, bl0, bh0, a1, bl1, bh1, sl, 1, true, T.dma(4, later(3), bslot), T.dma(5, later(3), bslot),      \
+                T.dma(6, later(3), bslot), T.dma(7, later(3), bslot), first)                                        \
     } else {                                                                                                        \
-      FC_HALF3_P(a0, bl0, bh0, a1, bl1, bh1, sl, 1, true, if (STORE) T.dma(4, s0 + s + 3, bslot),                   \
-                 if (STORE) T.dma(5, s0 + s + 3, bslot), if (STORE) T.dma(6, s0 + s + 3, bslot), , first)           \
+      FC_HALF3_P(a0, bl0, bh0, a1, bl1, bh1, sl, 1, true, T.dma(4, later(3), bslot), T.dma(5, later(3), bslot),     \
+                 T.dma(6, later(3), bslot), , first)                                                                \
     }                                                                                                               \
-    wait_vmcnt<WAIT>();                                                                                             \
+    wait_vmcnt<16 + 2 * NJ>();                                                                                      \
     __builtin_amdgcn_s_barrier();                                                                                   \
     FC_PIN();                                                                                                       \
     const char* nx = ring + nxt;                                                                                    \
     if constexpr (NJ == 4) {                                                                                        \
-      FC_HALF_P(a1, bl1, bh1, a0, bl0, bh0, nx, 0, MORE, , , , , second)                                            \
+      FC_HALF_P(a1, bl1, bh1, a0, bl0, bh0, nx, 0, true, , , , , second)                                            \
     } else {                                                                                                        \
-      FC_HALF3_P(a1, bl1, bh1, a0, bl0, bh0, nx, 0, MORE, , , , , second)                                           \
+      FC_HALF3_P(a1, bl1, bh1, a0, bl0, bh0, nx, 0, true, , , , , second)                                           \
     }                                                                                                               \
     pp = prv; prv = cur; cur = nxt;                                                                                 \
     nxt = (nxt + (uint32_t)kStageBytes == (uint32_t)kRingBytes) ? 0u : nxt + (uint32_t)kStageBytes;                 \
@@ -439,22 +443,25 @@ template <typename Tile>
 __device__ __forceinline__ void remote_mainloop(f32x16 (&acc)[4][Tile::NJ], const Tile& T, char* ring, uint32_t ring_addr,
                                                 int s0, int S) {
   constexpr int NJ = Tile::NJ;
+  const int pad = S & 1, last = S - 1;
+  int s = -pad;
+  auto later = [&](int n) __attribute__((always_inline)) { return s0 + (s + n < 0 ? 0 : (s + n < last ? s + n : last)); };
   RemoteSet x, y;            // even stages, odd stages
-  remote_request(T, x, s0);
-  remote_request(T, y, s0 + 1);
+  remote_request(T, x, later(0));
+  remote_request(T, y, later(1));
   FC_FENCE();
 #pragma unroll
   for (int p = 0; p < 3; ++p)
 #pragma unroll
-    for (int i = 4; i < 4 + NJ; ++i) T.dma(i, s0 + p, ring_addr + p * kStageBytes);
+    for (int i = 4; i < 4 + NJ; ++i) T.dma(i, later(p), ring_addr + p * kStageBytes);
 #pragma unroll
-  for (int w = 0; w < 16; ++w) remote_pair(T, x, w, ring, true, s0 + 2);
+  for (int w = 0; w < 16; ++w) remote_pair(T, x, w, ring, later(2), pad);
   FC_FENCE();
 #pragma unroll
-  for (int w = 0; w < 16; ++w) remote_pair(T, y, w, ring + kStageBytes, true, s0 + 3);
+  for (int w = 0; w < 16; ++w) remote_pair(T, y, w, ring + kStageBytes, later(3));
   FC_FENCE();
 #pragma unroll
-  for (int w = 0; w < 16; ++w) remote_pair(T, x, w, ring + 2 * kStageBytes, true, s0 + 4);
+  for (int w = 0; w < 16; ++w) remote_pair(T, x, w, ring + 2 * kStageBytes, later(4));
   FC_FENCE();
   wait_vmcnt<8>();           // the B operands of stages 0 .. 2 have landed: 16 loads of the two sets are younger
   __syncthreads();
@@ -468,18 +475,11 @@ __device__ __forceinline__ void remote_mainloop(f32x16 (&acc)[4][Tile::NJ], cons
     bh0[t] = T.read_b_half(ring, t, 0, 1);
   }
   uint32_t cur = 0u, nxt = (uint32_t)kStageBytes, prv = 4u * (uint32_t)kStageBytes, pp = 3u * (uint32_t)kStageBytes;
-  int s = 0;
-  // at the barrier of stage s: two sets and the B operands of stages s + 2 and s + 3 are younger than that of s + 1
-  while (s + 6 < S) {
-    FC_STAGE_REMOTE(y, true, true, true, 16 + 2 * NJ)
-    FC_STAGE_REMOTE(x, true, true, true, 16 + 2 * NJ)
+  while (s < S) {
+    FC_STAGE_REMOTE(y)
+    FC_STAGE_REMOTE(x)
   }
-  FC_STAGE_REMOTE(y, true, true, true, 16 + 2 * NJ)      // S - 6: the last request
-  FC_STAGE_REMOTE(x, true, true, false, 12 + 2 * NJ)
-  FC_STAGE_REMOTE(y, true, true, false, 4 + 2 * NJ)      // S - 4: the last B operand
-  FC_STAGE_REMOTE(x, true, false, false, NJ)
-  FC_STAGE_REMOTE(x, true, false, false, 0)
-  FC_STAGE_REMOTE(x, false, false, false, 0)
+  wait_vmcnt<0>();           // into slots that nobody has read
   __syncthreads();
 }
 
@@ -982,13 +982,14 @@ __global__ void __launch_bounds__(256) k_contract_bf16(ContractArgs g) {
     int64_t rows_ok = g.B;
     if (n0 + W > g.N) rows_ok -= (n0 + W - g.N + J.ldx - 1) / J.ldx;
     const int safe = rows_ok > 0 ? (int)(rows_ok / BK) : 0;
-    int S_ring = s0 + S <= safe ? S : (safe > s0 ? safe - s0 : 0);
-    if constexpr (REMOTE) {
-      S_ring = S_ring < 8 ? 0 : S_ring & ~1;
-      if (S_ring > 0) remote_mainloop(acc, T, ring, ring_addr, s0, S_ring);
-    } else if (S_ring > 0) {
-      ring_prologue(T, ring_addr, s0, S_ring);
-      ring_mainloop(acc, T, ring, ring_addr, s0, S_ring);
+    const int S_ring = s0 + S <= safe ? S : (safe > s0 ? safe - s0 : 0);
+    if (S_ring > 0) {
+      if constexpr (REMOTE) {
+        remote_mainloop(acc, T, ring, ring_addr, s0, S_ring);
+      } else {
+        ring_prologue(T, ring_addr, s0, S_ring);
+        ring_mainloop(acc, T, ring, ring_addr, s0, S_ring);
+      }
     }
     if (S_ring < S) guarded_mainloop(acc, T, ring, s0 + S_ring, S - S_ring, tid);
   }

@@ -639,13 +639,20 @@ def test_normalize_rows_alignment(b, d, ld, at):
 
 
 @pytest.mark.parametrize("B,b,off,d", [
-    (200, 90, 100, 72),                           # no stage on the loop that forms the operand from both strips
-    (256, 128, 0, 200), (288, 100, 150, 256),     # its eight stages; one more behind it; output tiles of either width
+    (200, 90, 100, 72),                           # six stages on the loop that forms the operand from both strips
+    (256, 128, 0, 200), (288, 100, 150, 256),     # eight; nine, an odd run; output tiles of either width
     (520, 300, 217, 520), (700, 257, 443, 264), (1100, 513, 300, 768),      # several splits, odd ones, ragged rows and columns
     (2304, 300, 77, 392)])
 def test_bf16_gathered_state_large_tiles_edges(B, b, off, d):
     """Contraction of the large tiles with gathered state at the depths and widths where its loop begins and ends."""
     run_gathered(B, b, off, d, V2 if d % 3 else V3, "bf16", TOL_BF16, ld_pad=8)
+
+
+@pytest.mark.parametrize("stages", [1, 2, 3, 4, 5, 7, 11])
+@pytest.mark.parametrize("d", [192, 256])
+def test_bf16_gathered_state_large_tiles_runs_of_stages(stages, d):
+    """... and where the whole stages of a split are few or an odd number; a row behind them is left to the guarded loop."""
+    run_gathered(32 * stages + 1, 20, 9, d, V2 if stages % 2 else V3, "bf16", TOL_BF16, ld_pad=8)
 
 
 def test_gathered_state_with_whole_batch_is_the_plain_step():
