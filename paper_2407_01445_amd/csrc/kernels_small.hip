@@ -2,6 +2,8 @@
 // the per-anchor coefficients, the finishing kernels of the MFMA path, the scalar outputs, and the index checker.
 #include <string.h>
 
+#include <type_traits>
+
 #include "fc_internal.hpp"
 #include "mfma_common.hpp"
 #include "state_common.hpp"
@@ -60,53 +62,68 @@ __device__ inline double row_dot(const bf16_t* pi, const bf16_t* pt, int64_t d, 
 // What bounds it: the launch and two dependent gathers for a small batch, reading both matrices (5.7 TB/s) for a large one.
 // Local and remote rows are one launch, in which either's latency hides behind the other's; as two launches 640 of 5120 at
 // width 512 took 4.7 + 4.0 us, 1024 of 32768 at 1024 4.8 + 23.7.
+// Arguments: what only gathered state needs is in a struct of its own behind the rest, so that the plain kernel's are three lines,
+// which come at once.  fp32, 64 pairs at width 32: 3.22 us with all fields in one struct, 3.14 so without the early touch of the
+// three lines, 3.01 with it.
 template <typename T>
 struct PrepArgs {
   const T *img, *txt;
-  int64_t ld_img, ld_txt, B, off, b, d;
+  int64_t ld_img, ld_txt, off, b, d;
   const int64_t* idx;
   const float *tau, *tau_img, *tau_txt, *u_img, *u_txt;
   int64_t stride;
-  int version;
+  int version, narrived, threads;        // threads of the launch
   float *diag, *tau1, *tau2, *k1, *k2, *uold1, *uold2;
   unsigned* arrived;
-  int narrived, threads;         // threads of the launch
-  // gathered state
+};
+template <typename T>
+struct PrepGatheredArgs : PrepArgs<T> {
+  int64_t B;
   const float *tau_glob_img, *tau_glob_txt, *u_glob_img, *u_glob_txt;
   float eps, bm;
-  int from_own;
   int64_t ncol;
   float* colp;
+  int from_own;
 };
+static_assert(sizeof(PrepArgs<float>) <= 192, "three lines");
 
-template <typename T, bool GATHERED>
-__global__ void __launch_bounds__(256) k_prep(PrepArgs<T> a) {
-  if constexpr (GATHERED) warm_arguments<sizeof(PrepArgs<T>)>();
+template <typename T, typename Args>
+__global__ void __launch_bounds__(256) k_prep(Args a) {
+  constexpr bool GATHERED = std::is_same<Args, PrepGatheredArgs<T>>::value;
+  warm_arguments<sizeof(Args)>();
   const int lane = threadIdx.x & 63;
   const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < a.narrived; i += a.threads) a.arrived[i] = 0u;
-  if (w >= (GATHERED ? a.ncol : a.b)) return;
-  const int64_t j = GATHERED ? w : a.off + w, r = j - a.off;      // global row; local anchor
+  int64_t rows = a.b, j = a.off + w;                              // global row
+  if constexpr (GATHERED) { rows = a.ncol; j = w; }
+  if (w >= rows) return;
+  const int64_t r = j - a.off;                                    // local anchor
   const bool local = !GATHERED || (r >= 0 && r < a.b);            // wave-uniform
+  bool exists = true;
+  if constexpr (GATHERED) exists = j < a.B;
   float t1 = 0.f, t2 = 0.f, u1 = 0.f, u2 = 0.f;
-  if (lane == 0 && (local || j < a.B)) {
+  if (lane == 0 && exists) {
     // issue the gathers before the dot product so that the latencies overlap: by dataset index the temperatures, and u^t of
     // Eq. 1 for the state phase (nothing writes u before that phase); of a remote anchor what its worker has sent
-    const int64_t n = local ? a.idx[r] * a.stride : j;
-    u1 = (local ? a.u_img : a.u_glob_img)[n];
-    u2 = (local ? a.u_txt : a.u_glob_txt)[n];
+    const float *u_img = a.u_img, *u_txt = a.u_txt, *tau_img = a.tau_img, *tau_txt = a.tau_txt;
+    if constexpr (GATHERED) {
+      if (!local) { u_img = a.u_glob_img; u_txt = a.u_glob_txt; tau_img = a.tau_glob_img; tau_txt = a.tau_glob_txt; }
+    }
+    const int64_t at = local ? a.idx[r] : 0;
+    if (a.version != FASTCLIP_V2) t1 = t2 = a.tau[0];       // on its way together with the index
+    const int64_t n = local ? at * a.stride : j;
+    u1 = u_img[n];
+    u2 = u_txt[n];
     if (a.version == FASTCLIP_V2) {
-      t1 = (local ? a.tau_img : a.tau_glob_img)[n];
-      t2 = (local ? a.tau_txt : a.tau_glob_txt)[n];
-    } else {
-      t1 = t2 = a.tau[0];
+      t1 = tau_img[n];
+      t2 = tau_txt[n];
     }
   }
   double s_jj = 0.0;
-  if (!GATHERED || j < a.B) s_jj = wave_sum(row_dot(a.img + j * a.ld_img, a.txt + j * a.ld_txt, a.d, lane));
+  if (exists) s_jj = wave_sum(row_dot(a.img + j * a.ld_img, a.txt + j * a.ld_txt, a.d, lane));
   if (lane != 0) return;
   float k1 = 0.f, k2 = 0.f;
-  if (local || j < a.B) { k1 = kLog2e / t1; k2 = kLog2e / t2; }
+  if (exists) { k1 = kLog2e / t1; k2 = kLog2e / t2; }
   if (local) {
     a.diag[r] = (float)s_jj;
     a.tau1[r] = t1;
@@ -119,13 +136,13 @@ __global__ void __launch_bounds__(256) k_prep(PrepArgs<T> a) {
   if constexpr (GATHERED) {
     float c1 = 0.f, c2 = 0.f;
     if (local) k1 = k2 = 0.f;
-    else if (j < a.B) {
+    else if (exists) {
       c1 = 1.0f / (a.bm * (a.eps + u1));
       c2 = 1.0f / (a.bm * (a.eps + u2));
       if (a.version == FASTCLIP_V0) { c1 /= t1; c2 /= t2; }
     }
     // column of row j: its number, or (from_own) counted from the worker's own rows on
-    const int64_t col = !a.from_own || j >= a.B ? j : (j >= a.off ? j - a.off : j - a.off + a.B);
+    const int64_t col = !a.from_own || !exists ? j : (j >= a.off ? j - a.off : j - a.off + a.B);
     const int64_t ntile = a.ncol >> 8, tile = col >> 8, in = col & 255;
     float* p0 = a.colp + ((0 * ntile + tile) * 4) * 256 + in;   // side 0: text anchors (tau_2, u_2)
     float* p1 = a.colp + ((1 * ntile + tile) * 4) * 256 + in;   // side 1: image anchors (tau_1, u_1)
@@ -134,13 +151,11 @@ __global__ void __launch_bounds__(256) k_prep(PrepArgs<T> a) {
   }
 }
 
-template <typename T>
-static void launch_prep_rows(const StepCtx& c) {
+template <typename T, typename Args>
+static void launch_prep_rows(const StepCtx& c, Args& a, int64_t rows) {
   const Layout& L = c.L;
-  PrepArgs<T> a;
-  memset(&a, 0, sizeof(a));
   a.img = (const T*)c.buf.img_glob; a.txt = (const T*)c.buf.txt_glob;
-  a.ld_img = c.cfg.ld_img; a.ld_txt = c.cfg.ld_txt; a.B = L.B; a.off = L.off; a.b = L.b; a.d = L.d;
+  a.ld_img = c.cfg.ld_img; a.ld_txt = c.cfg.ld_txt; a.off = L.off; a.b = L.b; a.d = L.d;
   a.idx = c.buf.idx; a.tau = c.buf.tau; a.tau_img = c.buf.tau_img; a.tau_txt = c.buf.tau_txt;
   a.u_img = c.buf.u_img; a.u_txt = c.buf.u_txt; a.stride = c.cfg.state_stride; a.version = c.cfg.version;
   a.diag = (float*)(c.ws + L.diag);
@@ -148,24 +163,32 @@ static void launch_prep_rows(const StepCtx& c) {
   a.k1 = (float*)(c.ws + L.k1); a.k2 = (float*)(c.ws + L.k2);
   a.uold1 = (float*)(c.ws + L.uold1); a.uold2 = (float*)(c.ws + L.uold2);
   a.arrived = (unsigned*)(c.ws + L.arrived); a.narrived = L.narrived;
-  const int64_t rows = L.gathered ? L.ncol : L.b;
   const dim3 grid((unsigned)((rows + 3) / 4)), block(256);
   a.threads = (int)(grid.x * 256);
+  hipLaunchKernelGGL((k_prep<T, Args>), grid, block, 0, c.s, a);
+}
+
+template <typename T>
+static void launch_prep_of(const StepCtx& c) {
+  const Layout& L = c.L;
   if (!L.gathered) {
-    hipLaunchKernelGGL((k_prep<T, false>), grid, block, 0, c.s, a);
+    PrepArgs<T> a;
+    launch_prep_rows<T>(c, a, L.b);
     return;
   }
+  PrepGatheredArgs<T> a;
+  a.B = L.B;
   a.tau_glob_img = c.buf.tau_glob_img; a.tau_glob_txt = c.buf.tau_glob_txt;
   a.u_glob_img = c.buf.u_glob_img; a.u_glob_txt = c.buf.u_glob_txt;
   a.eps = c.cfg.eps; a.bm = (float)L.b * (float)(L.B - 1);
   a.from_own = L.t128; a.ncol = L.ncol;
   a.colp = (float*)(c.ws + L.colp);
-  hipLaunchKernelGGL((k_prep<T, true>), grid, block, 0, c.s, a);
+  launch_prep_rows<T>(c, a, L.ncol);
 }
 
 void launch_prep(const StepCtx& c) {
-  if (c.L.bf16) launch_prep_rows<bf16_t>(c);
-  else launch_prep_rows<float>(c);
+  if (c.L.bf16) launch_prep_of<bf16_t>(c);
+  else launch_prep_of<float>(c);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -64,9 +64,14 @@ __device__ __forceinline__ void dma4(const void* uniform_base, uint32_t lane_byt
 // them.  By hand: values that the compiler knows it keeps, and spills.
 template <size_t BYTES>
 __device__ __forceinline__ void warm_arguments() {
-  static_assert((BYTES >= 0x104 && BYTES <= 0x140) || (BYTES >= 0x204 && BYTES <= 0x280), "the words below cover the arguments");
+  static_assert((BYTES > 0x80 && BYTES <= 0xc0) || (BYTES > 0x100 && BYTES <= 0x140) || (BYTES > 0x200 && BYTES <= 0x240),
+                "the words below cover the arguments, and lie in them");
   uint32_t w0, w1, w2, w3, w4, w5, w6, w7, w8;
-  if constexpr (BYTES <= 0x140) {
+  if constexpr (BYTES <= 0xc0) {
+    asm volatile("s_load_dword %0, %3, 0x0\n\ts_load_dword %1, %3, 0x40\n\ts_load_dword %2, %3, 0x80\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&s"(w0), "=&s"(w1), "=&s"(w2)
+                 : "s"(__builtin_amdgcn_kernarg_segment_ptr()));
+  } else if constexpr (BYTES <= 0x140) {
     asm volatile("s_load_dword %0, %5, 0x0\n\ts_load_dword %1, %5, 0x40\n\ts_load_dword %2, %5, 0x80\n\t"
                  "s_load_dword %3, %5, 0xc0\n\ts_load_dword %4, %5, 0x100\n\ts_waitcnt lgkmcnt(0)"
                  : "=&s"(w0), "=&s"(w1), "=&s"(w2), "=&s"(w3), "=&s"(w4)

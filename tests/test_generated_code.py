@@ -186,3 +186,17 @@ def test_ring_stages_of_the_large_tiles_hold_their_addresses(assembly):
                 other = [x for x in body if x.startswith("v_") and not x.startswith("v_mfma")]
                 assert len(other) <= 16, (name, len(other), other)
     assert seen >= 12
+
+
+def test_prep_kernel_waits_once_for_its_arguments_and_once_for_index_and_temperature(assembly):
+    """k_prep without gathered state, which is nothing but a chain of waits: its three lines of arguments are all requested ahead of
+    the first wait, and the global temperature ahead of the wait for the dataset index."""
+    kernels = [k for k in kernel_lines(assembly["kernels_small.hip"], "k_prep") if "Gathered" not in k[0]]
+    assert len(kernels) == 2
+    for name, lines in kernels:
+        head = lines[:next(i for i, ln in enumerate(lines) if ln.startswith("s_waitcnt"))]
+        at = [int(ln.rsplit(",", 1)[1], 16) // 64 for ln in head if ln.startswith("s_load")]
+        assert set(at) == {0, 1, 2}, (name, head)
+        index = next(i for i, ln in enumerate(lines) if ln.startswith("global_load_dwordx2"))
+        wait = next(i for i in range(index, len(lines)) if lines[i].startswith("s_waitcnt") and "vmcnt" in lines[i])
+        assert [ln for ln in lines[index + 1:wait] if ln.startswith(("global_load_dword ", "s_load_dword "))], (name, lines[index:wait])
