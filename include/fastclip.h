@@ -185,8 +185,8 @@ fastclip_status fastclip_step(const fastclip_config* cfg, const fastclip_buffers
  * call on a device it looks the array's device address up (hipGetSymbolAddress) and keeps it.
  *   - A configuration whose fastclip_workspace_bytes() exceeds FASTCLIP_STATIC_SCRATCH_BYTES is refused with
  *     FASTCLIP_ERR_WORKSPACE before anything is launched, except that bf16 batches on the small tiles run here without
- *     splits of the contraction if that makes them fit, those with gathered state on the small tiles however wide their
- *     rows (same results up to summation order, more time) (64 MiB holds the paper's own shapes: up to 640 local
+ *     splits of the contraction if that makes them fit, and those with gathered state on the small tiles however wide
+ *     their rows or on the large ones with somewhat fewer splits (same results up to summation order, more time) (64 MiB holds the paper's own shapes: up to 640 local
  *     anchors of a global batch of 5120 at width 512, and 1024 x 1024 x 512 or 256 of 8192 x 512).
  *   - All calls on one GPU share that GPU's array, whatever their stream: calls that overlap in time on one GPU race
  *     on it.  Calls that follow each other on one stream, or are ordered by events, are safe.  The array keeps the

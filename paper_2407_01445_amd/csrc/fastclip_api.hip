@@ -342,12 +342,14 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
     if (max_split > kMaxSplit) max_split = kMaxSplit;
     if (max_split < 1) max_split = 1;
     double best_cost = 0.0;
-    size_t most = 0;      // 192 columns take no more workspace for partial results than the plan of 256 would
-    for (int cols = 256; cols >= 192; cols -= 64) {
+    // Plans of `cols` columns whose partial results take at most `most` floats (0: any); even: whose splits are all of an even
+    // number of stages.
+    auto consider = [&](int cols, size_t most, bool even) {
       const double width = cols == 256 || L->gathered ? 1.0 : 0.80;
       const int64_t tiles = ((cfg.b + 255) / 256) * ((cfg.d + cols - 1) / cols) * 2;
       for (int64_t ns = 1; ns <= max_split; ++ns) {
-        const int64_t slice = (stages + ns - 1) / ns;
+        int64_t slice = (stages + ns - 1) / ns;
+        if (even) slice += slice & 1;
         const int64_t used = (stages + slice - 1) / slice;          // splits that really get stages
         const size_t partial = (size_t)used * partial_split_floats(cfg.b, cfg.d, cols);
         if (most && partial > most) break;
@@ -358,8 +360,16 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
           L->out_cols = cols; L->nsplit = (int)used; L->kslice = slice;
         }
       }
-      if (cols == 256) most = (size_t)L->nsplit * partial_split_floats(cfg.b, cfg.d, 256);
+    };
+    consider(256, 0, false);
+    const size_t most = (size_t)L->nsplit * partial_split_floats(cfg.b, cfg.d, 256);   // 192 columns take no more workspace
+    // Gathered state that does not fit the array of fastclip_step_static: longer runs, which some batches fit it with.
+    const bool even = L->gathered && room.split_bytes == 0;
+    if (even) {
+      best_cost = 0.0;
+      consider(256, most, true);
     }
+    consider(192, most, even);
   } else {
     L->ldE = room.partial_sums ? (int64_t)round_up((size_t)cfg.B, 4) : cfg.B;
     if (L->few) L->nparts = L->nsplit = 1;
@@ -578,7 +588,8 @@ fastclip_status fastclip_step_static(const fastclip_config* cfg, const fastclip_
   if (st != FASTCLIP_OK) return st;
   fc::Layout L;
   fc::make_layout(*cfg, &L);
-  // the small tiles without partial results, also for gathered state that is on the 256 x 256 tiles for the time they take
+  // the small tiles without partial results, also for gathered state that is on the 256 x 256 tiles for the time they take; or
+  // the longer runs that gathered state on the latter can do with
   if (L.total > (size_t)FASTCLIP_STATIC_SCRATCH_BYTES) fc::make_layout(*cfg, fc::Room{0, true}, &L);
   if (L.total > (size_t)FASTCLIP_STATIC_SCRATCH_BYTES) return FASTCLIP_ERR_WORKSPACE;
   void* ws = nullptr;

@@ -76,9 +76,9 @@ PLAN_RULES = [
     ("kernels_tiles128.hip", "g.finishers = L.fused_state && groups + finishers <= 256 ? (int)finishers : 0;",
      "g.finishers = L.fused_state && " + _forced("groups + finishers <= 256", "EMU_FINISHERS") + " ? (int)finishers : 0;"),
     # large tiles: columns of an output tile of the contraction
-    ("fastclip_api.hip", "    for (int cols = 256; cols >= 192; cols -= 64) {",
-     '    for (int cols = 256; cols >= 192; cols -= 64) {\n'
-     '      if (getenv("EMU_OUT_COLS") && atoi(getenv("EMU_OUT_COLS")) != cols) { most = SIZE_MAX; continue; }'),
+    ("fastclip_api.hip", "      const double width = cols == 256 || L->gathered ? 1.0 : 0.80;",
+     '      if (getenv("EMU_OUT_COLS") && atoi(getenv("EMU_OUT_COLS")) != cols) return;\n'
+     '      const double width = cols == 256 || L->gathered ? 1.0 : 0.80;'),
     # fp32 path: tile sizes, plain loops, what is left of a plan that has to fit the static array
     ("fastclip_api.hip", "((cfg.B + 63) / 64) >= 256 ? 64 : 32;", "((cfg.B + 63) / 64) >= " + _forced("256", "EMU_F32_TILES") + " ? 64 : 32;"),
     ("fastclip_api.hip", "  for (int T = 32; T <= 64; T += 32) {",

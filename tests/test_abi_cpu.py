@@ -479,8 +479,8 @@ def test_few_fp32_pairs_take_no_tiles():
 
 @pytest.mark.parametrize("B,b,d", [(963, 741, 2336), (2461, 309, 2008), (2388, 965, 648), (2418, 1189, 448)])
 def test_gathered_state_on_large_tiles_keeps_to_the_static_array(B, b, d):
-    """The contraction's stages come in pairs with gathered state; the splits that suit them take no more workspace than the
-    others would, so what fits the array of fastclip_step_static goes on fitting it."""
+    """Splits of the contraction over tiles of 192 columns take no more workspace than those over 256 would, so what fits the
+    array of fastclip_step_static with the one fits it with the other."""
     cfg = fc.make_config(version=fc.V3, emb_dtype=fc.BF16, B=B, b=b, off=0, d=d, N=1 << 20, gamma=0.5, eps=1e-6, rho=1.0,
                          ld_img=d, ld_txt=d, flags=fc.TILES_256 | fc.GATHERED_STATE)
     assert 0 < fc.fastclip_workspace_bytes(cfg) <= 64 << 20

@@ -72,12 +72,15 @@ def test_static_scratch_takes_what_fits_without_the_extras(shape, version):
     same_bits(plain, static)
 
 
-@pytest.mark.parametrize("shape,gathered", [((4096, 1024, 1024, 2048), True), ((2048, 2048, 0, 2264), False)])
+@pytest.mark.parametrize("shape,gathered", [
+    ((4096, 1024, 1024, 2048), True), ((2048, 2048, 0, 2264), False),
+    ((8722, 272, 2118, 248), True)])          # too many large tiles for the small ones: longer runs of the contraction
 def test_static_scratch_takes_small_tiles_without_splits(shape, gathered):
     """A step with gathered state and wide rows runs on the large tiles, one on the small tiles with many splits of the
-    contraction, and the partial results of either do not fit the array; on the small tiles without splits they do, and the
-    outputs agree up to rounding: the weights of the contraction are rounded to bf16 on either path (gradients within the
-    2e-2 of the bf16 path), sums of 4096 positive numbers are added up in fp32 (4096 x 2^-24)."""
+    contraction, and the partial results of either do not fit the array; on the small tiles without splits (or on the large
+    ones with fewer) they do, and the outputs agree up to rounding: the weights of the contraction are rounded to bf16 on either path (gradients within the
+    2e-2 of the bf16 path), sums of 4096 positive numbers are added up in fp32
+    (4096 x 2^-24; of 8722 in partial sums of 256 first)."""
     (B, b, off, d), N = shape, 6000
     rng = np.random.default_rng(21)
     img, txt = make_embeddings(22, B, d, 0.5, "bf16")
