@@ -186,8 +186,9 @@ fastclip_status fastclip_step(const fastclip_config* cfg, const fastclip_buffers
  *   - A configuration whose fastclip_workspace_bytes() exceeds FASTCLIP_STATIC_SCRATCH_BYTES is refused with
  *     FASTCLIP_ERR_WORKSPACE before anything is launched, except that bf16 batches on the small tiles run here without
  *     splits of the contraction if that makes them fit, and those with gathered state on the small tiles however wide
- *     their rows or on the large ones with somewhat fewer splits (same results up to summation order, more time) (64 MiB holds the paper's own shapes: up to 640 local
- *     anchors of a global batch of 5120 at width 512, and 1024 x 1024 x 512 or 256 of 8192 x 512).
+ *     their rows or on the large ones with somewhat fewer splits (same results up to summation order, more time).
+ *     64 MiB holds the paper's own shapes: up to 640 local anchors of a global batch of 5120 at width 512, and
+ *     1024 x 1024 x 512 or 256 of 8192 x 512.
  *   - All calls on one GPU share that GPU's array, whatever their stream: calls that overlap in time on one GPU race
  *     on it.  Calls that follow each other on one stream, or are ordered by events, are safe.  The array keeps the
  *     last call's contents; the step reads nothing from its workspace that it has not written in the same call, so
@@ -214,7 +215,7 @@ fastclip_status fastclip_normalize_rows(const void* raw, int32_t raw_dtype, int6
  * (host memory; phases that a path does not run are reported as 0).  Measurement aid:
  * it creates and destroys events and blocks the calling thread. */
 #define FASTCLIP_N_PHASES 8
-#define FASTCLIP_PHASE_PREP 0      /* s_ii and temperature gather */
+#define FASTCLIP_PHASE_PREP 0      /* s_ii and temperature gather (0 where small batches prepare their anchors in the strips) */
 #define FASTCLIP_PHASE_STRIPS 1    /* similarity strips + exp + row sums (Proc. 1) */
 #define FASTCLIP_PHASE_STATE 2     /* Eq. 1 update / scatter, coefficients, scalars (0 where the bf16 path runs it inside a later phase) */
 #define FASTCLIP_PHASE_LOCAL 3     /* bf16 path: contrast-side weights of Eqs. 3/5/7 folded into the stored strips (+ the state phase for small batches); 0 where the small

@@ -74,7 +74,7 @@ struct Layout {
   size_t uold1, uold2;               // float[bstride]: u^t of the batch's samples (gathered with the temperatures)
   size_t sums;                       // float[4][nparts][bstride]: sum e1, sum x1 e1, sum e2, sum x2 e2
                                      // (fp32 path with nparts > 1: double)
-  size_t arrived;                    // unsigned[narrived]: arrival counters of the output tiles, zeroed by k_prep
+  size_t arrived;                    // unsigned[narrived]: arrival counters of the output tiles, zeroed by k_prep or (own_prep) the strips
   int narrived;
   size_t c1, c2, dcoef;              // float[bstride]
   size_t red;                        // double[nstate_blocks][2]
@@ -87,9 +87,8 @@ struct Layout {
   // [s][tile][4][256]: log2(e)/tau_j, s_jj log2(e)/tau_j, c_j (0 for local rows and beyond B), unused.
   // Side 0 describes the text anchors j (l2(j, .), weights of d_img), side 1 the image anchors (l1(j, .), d_txt).
   size_t colp;
-  size_t F[2];                       // gathered: the second stored strip c_j l(j, p_r), same form as E, folded into E after
-                                     // the state phase (256 x 256 tiles), added in the contraction (t128) or summed
-                                     // directly (fp32 path)
+  size_t F[2];                       // gathered: the second stored strip c_j l(j, p_r), same form as E, added where the
+                                     // contraction stages its operand (MFMA path) or summed directly (fp32 path)
   size_t total;
 };
 

@@ -1,11 +1,13 @@
 // MFMA kernels of the FCCO step for batches whose 256 x 256 tiles would leave most of the chip idle (the shapes the paper
 // trains at: 128 - 640 anchors per worker of a global batch of 1024 - 5120, width 512):
 //
-//  k_strips_t128_bf16    the similarity strips of Proc. 1 on 128 x 128 tiles: l = exp((s - s_ii) / tau), the per-anchor
-//                        sums of l and (s - s_ii) l, l stored in the fragment order of the contraction; any ragged edge;
-//  k_contract_t128_bf16  everything behind them on 64 x 64 output tiles: the state phase (Eq. 1, coefficients, Eq. 9,
-//                        loss), the gradient contractions of Eqs. 2 - 7 with the contrast-side term of the local anchors
-//                        as further contraction depth, the outputs and the scalars.
+//  k_strips_t128_bf16    the similarity strips of Proc. 1 on tiles of 64 or 128 anchors by 128 contrasts: l = exp((s - s_ii) /
+//                        tau), the per-anchor sums of l and (s - s_ii) l, l stored in the fragment order of the contraction;
+//                        any ragged edge; where the anchors' rows are few, s_ii and the gathers by dataset index too;
+//  k_contract_t128_bf16  everything behind them on output tiles of 32 x 32, 64 x 64 or 128 x 64: the state phase (Eq. 1,
+//                        coefficients, Eq. 9, loss) where there is one round of workgroups, the gradient contractions of
+//                        Eqs. 2 - 7 with the contrast-side term of the local anchors as further contraction depth, the
+//                        outputs and the scalars.
 //
 // What bounds these batches is not bytes or flops but the chain of dependent launches and, inside a launch, the chain of
 // dependent instructions: a launch costs about 3 us, and so does a kernel that waits for memory twice.  So the whole
@@ -511,22 +513,25 @@ struct T128Args {
   float *loss, *d_tau;
 };
 
-// Output tile (m0 .. + 63, n0 .. + 63) of one side: C = sum_c c_own E[r][c] X[c] + sum_q c_other[q] E_other[q][r] X[q] over
+// Output tile (rows from m0, columns from n0) of one side: C = sum_c c_own E[r][c] X[c] + sum_q c_other[q] E_other[q][r] X[q] over
 // the contrasts c and the local anchors q (Eq. 2 / 4 / 6 and the local part of Eqs. 3 / 5 / 7; column q is the row X[q] in
 // both sums), minus the diagonal term.  The depth is cut into nsplit x 8 slices, one per wave of every workgroup of the
 // tile; a wave adds up its part of the first sum, multiplies by the rows' coefficients and goes on with its part of the
 // second.  Its operands go through LDS of its own, four 16-deep stages in flight, and nothing but its own waits is in the
 // loop.  Then the eight waves' tiles are added up through LDS, and with several splits by the last workgroup to arrive.
 //
-// The state phase rides along: every workgroup forms the coefficients that it needs from the partial sums (same
-// instructions, same order, hence the same bits everywhere) while its first stages are on their way.  The anchors are finished
+// The state phase rides along: every workgroup forms the coefficients that it needs from the partial sums while its first
+// stages are on their way.  The order of the sums is fixed but not the same everywhere (an output tile's rows as eight
+// interleaved runs, local anchors as eight, four, two or one, the finishing workgroups one after the other), so the
+// coefficient of an anchor in two workgroups, and the u^{t+1} behind it and the one that is stored, are equal up to the
+// rounding of fp32 sums in another order; two steps on the same inputs give the same bits.  The anchors are finished
 // (scatter, Eq. 9, loss) by workgroups of their own where compute units are left for them, else by the last waves of the
 // workgroups of side 0, split 0 and the first columns, which are late by that (4 us in the chain of one of 12 us).  When there
 // is more than one round of workgroups (plan_t128), k_state has run before and the coefficients are read.
 //
 // What bounds it: operands come at 64 bytes per clock and compute unit, so eight 16-deep stages of 64 x 64 tiles (32 KiB) take
 // 512 cycles against 256 of products (650 - 880 measured), and about 5 us go into the start, the coefficients, the sum over
-// the waves and the outputs.  128-row tiles (MB = 2) move a quarter less per product and are taken where 64-row ones need
+// the waves and the outputs.  128-row tiles (RB = 4) move a quarter less per product and are taken where 64-row ones need
 // a second round of workgroups; the cost model is in plan_t128.  Steps before and after (fold + contraction + finalize
 // kernels before; strips of 64 anchors included): 128 of 1024 pairs, d = 512: 34.7 -> 20.7 us, 256 of 8192: 47.8 -> 31.2,
 // 1024 of 1024: 37.9 -> 30.1, 1000 of 4000, d = 760, rows of 768 (128-row tiles): 71.5 -> 61.9; 640 of 5120 with gathered state

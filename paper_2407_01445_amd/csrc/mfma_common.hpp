@@ -111,7 +111,6 @@ __device__ __forceinline__ int rt_off(int row, int chunk) { return row * 64 + ((
 // piece position p ^ ((k & 3) << 2), so that the 4 rows x 64 bytes which a transposing read touches per cycle cover
 // a whole bank window.
 __device__ __forceinline__ int nt_swz(int k) { return (k & 3) << 2; }
-__device__ __forceinline__ int nt_off(int k, int piece) { return k * 512 + ((piece ^ nt_swz(k)) << 4); }
 
 // One accumulator element out of its AGPR at the point of use.  Left to itself the register allocator copies large
 // parts of the accumulator block into VGPRs right after the main loop, which costs more VGPRs than there are.

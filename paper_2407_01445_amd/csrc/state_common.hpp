@@ -82,7 +82,7 @@ __device__ __forceinline__ double load_agent(const double* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // Called by every thread of `n` workgroups after their store_agent's; true in the threads of the last one to arrive, which
-// may then load_agent what all of them stored.  *counter is 0 before the launch (k_prep); nobody waits for anybody: the
+// may then load_agent what all of them stored.  *counter is 0 before the launch (k_prep or the strips); nobody waits for anybody: the
 // others go on and leave.  The wait is for this wave's own stores to be acknowledged at agent scope, the barrier for the
 // workgroup's other waves, and only then is the arrival counted.
 __device__ __forceinline__ bool last_to_arrive(unsigned* counter, unsigned n, int* lds_flag) {
