@@ -414,9 +414,9 @@ def test_bf16_tiles_128(B, b, off, d, version):
 @pytest.mark.parametrize("B,b,off,d", [
     # fewer rows than a stage is deep, the columns' numbering wrapping inside it; one stage more or less; a last row block of one
     (7, 3, 2, 8), (16, 16, 0, 64), (17, 9, 8, 72), (129, 65, 64, 520),
-    # more local anchors than the contraction holds sums for (state phase on its own), 64-row and 128-row output tiles
+    # four groups of 256 local anchors, of three splits or one, on 128-row output tiles too
     (2048, 2048, 0, 64), (4000, 1000, 3000, 760), (1030, 1023, 7, 1016),
-    # the depth split over sixteen workgroups
+    # the depth split over eight workgroups
     (8192, 64, 8128, 64),
     # contraction on 128 x 128 output tiles behind the fold: ragged everywhere, one split; rows that are not the first, a
     # last row block of one; two splits, strips of two workgroups per compute unit with a guarded last stage
@@ -426,16 +426,23 @@ def test_bf16_tiles_128_edges(B, b, off, d):
     test_bf16_tiles_128(B, b, off, d, V2 if B % 2 else V3)
 
 
-@pytest.mark.parametrize("B,b,off,d", [
-    (33, 33, 0, 8), (40, 1, 39, 40), (65, 31, 34, 24),       # 32 x 32 output tiles: one stage, one row, widths inside a tile
-    (300, 256, 40, 512), (257, 255, 2, 504),                 # ... on every compute unit: the anchors finished by the first columns
-    (1100, 130, 700, 200),                                   # ... several stages per wave, rows that wrap around the batch
-    (700, 600, 60, 256), (1300, 1030, 270, 128),             # coefficients of several groups of 256 local anchors: 3, 5 and, with a
-    (2400, 2310, 90, 64),                                    # second pass, 10; eight partial sums and more per wave
-    (2304, 1000, 1200, 760), (3000, 520, 100, 72)])          # 128-row tiles; anchors of several finishing workgroups, splits
-def test_bf16_small_tile_plans(B, b, off, d):
+@pytest.mark.parametrize("B,b,off,d,fused,nsplit", [
+    # 32 x 32 output tiles: one stage, one row, widths inside a tile
+    (33, 33, 0, 8, 1, 1), (40, 1, 39, 40, 1, 1), (65, 31, 34, 24, 1, 1),
+    (300, 256, 40, 512, 1, 1), (257, 255, 2, 504, 1, 1),     # ... on every compute unit: the anchors finished by the first columns
+    (1100, 130, 700, 200, 1, 1),                             # ... several stages per wave, rows that wrap around the batch
+    # coefficients of several groups of 256 local anchors, which the waves share out: three groups; five, of two in a split;
+    # five and eight in one workgroup (64-row tiles), six (128-row tiles) and, with a second pass, nine
+    (700, 600, 60, 256, 1, 1), (1300, 1030, 270, 128, 1, 3), (1300, 1270, 30, 256, 1, 1), (2048, 2000, 40, 192, 1, 1),
+    (1600, 1500, 33, 512, 1, 1), (2300, 2250, 30, 448, 1, 1),
+    (2304, 1000, 1200, 760, 1, 1), (3000, 520, 100, 72, 1, 6),   # 128-row tiles; anchors of several finishing workgroups, splits
+    (300, 300, 0, 4104, 0, 1)])                              # several rounds of workgroups: the state phase on its own
+def test_bf16_small_tile_plans(B, b, off, d, fused, nsplit):
     """The plans of the small tiles at the sizes where they change what they do (tile size, who forms the coefficients and who
     finishes the anchors, groups and slices of the partial sums), as in test_bf16_tiles_128."""
+    plan = fc.fastclip_describe(fc.make_config(version=V3, emb_dtype=fc.BF16, B=B, b=b, off=off, d=d, N=5000, gamma=0.6,
+                                               eps=1e-6, rho=6.5, ld_img=d + 8, ld_txt=d, flags=fc.TILES_128))
+    assert (plan["tile"], plan["fused_state"], plan["nsplit"]) == (128, fused, nsplit)
     test_bf16_tiles_128(B, b, off, d, V2 if d % 3 else V3)
 
 
@@ -569,16 +576,21 @@ def test_bf16_gathered_state(B, b, off, d, version):
 @pytest.mark.parametrize("B,b,off,d", [
     # one contrast tile of a pair, a second one that is short, columns wrapping inside a tile and inside a stage
     (100, 9, 91, 64), (300, 130, 57, 72), (257, 65, 3, 136), (1000, 64, 936, 520),
-    # several splits; the state phase on its own
-    (2048, 256, 768, 512), (5120, 640, 3200, 512)])
+    # several splits; three groups of 256 local anchors; two rounds of output tiles, hence the state phase on its own
+    (2048, 256, 768, 512), (5120, 640, 3200, 512), (1000, 520, 300, 1024)])
 @pytest.mark.parametrize("version", [V0, V1, V2, V3])
 def test_bf16_gathered_state_on_small_tiles(B, b, off, d, version):
+    plan = fc.fastclip_describe(fc.make_config(version=version, emb_dtype=fc.BF16, B=B, b=b, off=off, d=d, N=5000, gamma=0.6,
+                                               eps=1e-6, rho=6.5, ld_img=d + 8, ld_txt=d, flags=fc.GATHERED_STATE))
+    assert plan["tile"] == 128 and plan["fused_state"] == (d < 1024) and (plan["nsplit"] > 1) == (B == 2048)
     run_gathered(B, b, off, d, version, "bf16", TOL_BF16, ld_pad=8, tiles=None)
 
 
-@pytest.mark.parametrize("B,b,off,d", [(300, 130, 57, 72), (1000, 600, 200, 72)])    # state phase in the contraction; on its own
+@pytest.mark.parametrize("B,b,off,d,inside", [
+    # state phase in the contraction, of one group of 256 local anchors and of three; on its own
+    (300, 130, 57, 72, 1), (1000, 600, 200, 72, 1), (1000, 520, 300, 1024, 0)])
 @pytest.mark.parametrize("version", [V2, V3])
-def test_gathered_state_on_small_tiles_with_temperature_update(B, b, off, d, version):
+def test_gathered_state_on_small_tiles_with_temperature_update(B, b, off, d, inside, version):
     """fastclip_step_update_tau with gathered state is fastclip_step followed by fastclip_temperature_update: the same bits
     in every output and in the state (one set of kernels), the temperatures and moments to a few units in the last place
     (the same arithmetic in another kernel, whose multiply-adds may be contracted differently)."""
@@ -595,7 +607,8 @@ def test_gathered_state_on_small_tiles_with_temperature_update(B, b, off, d, ver
         g = GpuStep(B=B, b=b, off=off, d=d, N=N, dtype="bf16", version=version, eps=1e-6, rho=6.5, tau=0.07, u_img0=u0i,
                     u_txt0=u0t, tau_img0=t_img, tau_txt0=t_txt, gathered=dict(u_img=ug1, u_txt=ug2, tau_img=tg1, tau_txt=tg2),
                     tiles=None)
-        assert fc.fastclip_describe(g.config(0.6))["tile"] == 128
+        plan = fc.fastclip_describe(g.config(0.6))
+        assert plan["tile"] == 128 and plan["fused_state"] == inside
         g.set_inputs(img, txt, idx)
         z = lambda n: torch.full((n,), 0.01, dtype=torch.float32, device=DEV)
         moments = {k: z(N) for k in ("m_img", "v_img", "m_txt", "v_txt")} if version == V2 else dict(m=z(1), v=z(1))
@@ -795,7 +808,8 @@ def test_temperature_update_alone(opt, hp, stride):
 @pytest.mark.parametrize("tiles", [256, None])   # the large-tile kernels; the library's choice (small tiles here)
 @pytest.mark.parametrize("stride", [1, 8, "canonical 8", "canonical 16"])
 @pytest.mark.parametrize("dtype,tol,shape", [("f32", TOL_F32, (64, 64, 0, 32)), ("bf16", TOL_BF16, (700, 300, 133, 72)),
-                                             # enough anchors that the state phase is a kernel of its own on the MFMA path
+                                             # enough anchors that the state phase is a kernel of its own on the large tiles
+                                             # (on the small ones it rides along with four splits of the contraction)
                                              ("bf16", TOL_BF16, (2048, 1536, 256, 64))])
 @pytest.mark.parametrize("version", [V2, V3, V0])
 def test_step_with_temperature_update_three_iterations(dtype, tol, shape, version, stride, tiles):

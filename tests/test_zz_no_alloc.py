@@ -56,7 +56,7 @@ def test_static_scratch_step_equals_the_step_twice_in_a_row_second_input_smaller
     same_bits(*both_ways((1024, 320, 704, 128), fc.V2, "bf16", 11))
     same_bits(*both_ways((700, 300, 133, 72), fc.V3, "bf16", 12))
     same_bits(*both_ways((37, 11, 13, 19), fc.V2, "f32", 13))
-    same_bits(*both_ways((2048, 1536, 256, 64), fc.V0, "bf16", 14))     # larger again: the state phase is its own kernel
+    same_bits(*both_ways((2048, 1536, 256, 64), fc.V0, "bf16", 14))     # larger again: on the large tiles the state phase is its own kernel
 
 
 @pytest.mark.parametrize("shape,version", [
