@@ -377,6 +377,8 @@ def main():
     # tiles than compute units (one similarity pass), two contractions over the padded column range.  Small tiles: 64 anchors
     # by 128 contrasts (128 anchors pad the same at the workloads' sizes), output tiles of 64 columns, and the local
     # anchors' contrast-side term as further depth of the contraction instead of a pass over the strips before it.
+    # Output tiles of the large tiles have 256 or 192 columns, whichever the plan takes: products of a last one beyond the
+    # width in whole 64s are not counted (none where the columns divide the width).
     up = lambda x, m: (x + m - 1) // m * m
     tile = plan["tile"]
     if tile == 128:
@@ -384,7 +386,7 @@ def main():
                     "contract": 2 * 2.0 * up(b, 64) * (up(B, 16) + up(b, 16)) * up(d, 64)}
     else:
         executed = {"strips": (1 if plan["single_pass"] else 2) * 2.0 * up(b, tile) * up(B, tile) * d,
-                    "contract": 2 * 2.0 * up(b, tile) * up(B, 64) * up(d, tile)}
+                    "contract": 2 * 2.0 * up(b, tile) * up(B, 64) * up(d, 64)}
     gemm_ms = phase_ms["strips"] + phase_ms["contract"]
     gemm_phases = {"algorithmic_tflops": round((alg["strips"] + alg["contract"]) / (gemm_ms * 1e-3) / 1e12, 2),
                    "frac_of_bf16_peak": round((alg["strips"] + alg["contract"]) / (gemm_ms * 1e-3) / PEAK_BF16_FLOPS, 4),
