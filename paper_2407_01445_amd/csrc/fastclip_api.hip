@@ -393,7 +393,19 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
     out_blocks = 8 * ((cfg.b + 255) / 256);
     out_blocks = of_tiles > out_blocks ? of_tiles : out_blocks;
   }
-  L->nstate_blocks = L->fused_state ? (int)(out_blocks ? out_blocks : (cfg.b + 63) / 64) : state_blocks(cfg.b, L->nparts);
+  if (!L->bf16 && !L->few) {
+    // The state phase inside the gradients: on 32 x 32 tiles, two workgroups of which fit a compute unit, where that leaves room for
+    // those that finish the anchors (behind 512 others they would come last), and where a workgroup forms the coefficients of at
+    // most 1024 of the other side's anchors, those of its slice, from at most 25000 partial sums.  Steps with k_state / so, us: 64 pairs at width 32 18.5 / 15.2,
+    // 128 of 128 at 512 26.5 / 22.8, 448 of 448 at 512 (462 workgroups) 37.6 / 33.5, 1024 of 1024 at 64 37.1 / 35.0, 128 of 1024 at
+    // 512 34.1 / 30.0; with more than 512 workgroups 512 of 512 at 512 37.2 / 38.5, 768 of 768 at 512 69.1 / 72.4; with 35000 and 67000 partial
+    // sums (800 of 800 at 96, 21600: 44.3 / 42.6) 1024 of 2048 at 64 68.2 / 69.6, 1000 of 4000 at 128 153 / 158.
+    const int64_t of_slice = L->square ? L->kslice * 64 : (L->kslice * 64 < cfg.b + 63 ? L->kslice * 64 : (cfg.b + 63) / 64 * 64);
+    const int64_t tiles = 2 * ((cfg.b + 31) / 32) * ((cfg.d + 31) / 32), finishers = 2 * ((cfg.b + 63) / 64);
+    L->grad_state = L->grad_tile == 32 && of_slice <= kGradAnchors && (of_slice + 64) * L->nparts <= 25000 &&
+                    tiles * L->nsplit + finishers <= 512;
+  }
+  L->nstate_blocks = L->grad_state ? (int)(2 * ((cfg.b + 63) / 64)) : L->fused_state ? (int)(out_blocks ? out_blocks : (cfg.b + 63) / 64) : state_blocks(cfg.b, L->nparts);
   L->diag = take(fb); L->tau1 = take(fb); L->tau2 = take(fb); L->k1 = take(fb); L->k2 = take(fb);
   L->uold1 = take(fb); L->uold2 = take(fb);
   L->sums = take(fb * 4 * (size_t)L->nparts * (!L->bf16 && L->nparts > 1 ? 2 : 1));
@@ -426,9 +438,12 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
     if (L->nsplit > 1) {
       const int64_t T = L->grad_tile, tiles = 2 * ((cfg.b + T - 1) / T) * ((cfg.d + T - 1) / T);
       L->narrived = (int)tiles;
-      L->arrived = take(sizeof(unsigned) * (size_t)tiles);
       L->Opart[0] = take(sizeof(double) * (size_t)L->nsplit * (size_t)tiles * (size_t)(T * T));
     }
+  }
+  if (!L->bf16) {
+    L->narrived += L->grad_state;
+    if (L->narrived) L->arrived = take(sizeof(unsigned) * (size_t)L->narrived);
   }
   if (L->square && L->bf16) L->F[0] = take(esz * round_up((size_t)cfg.b, 256) * (size_t)L->ldE);
   if (L->gathered) {
@@ -538,7 +553,7 @@ static fastclip_status run_step(const fastclip_config* cfg, const fastclip_buffe
     launch_grad_f32_few(c);
   } else {
     launch_strips_f32(c);                 mark(FASTCLIP_PHASE_STRIPS);
-    launch_state(c);                      mark(FASTCLIP_PHASE_STATE);
+    if (!c.L.grad_state) { launch_state(c); mark(FASTCLIP_PHASE_STATE); }
     launch_grad_f32(c);
     launch_norm_backward(c);
   }

@@ -14,6 +14,7 @@ constexpr int kTileContrasts = 256;  // contrast rows per workgroup tile of the 
 constexpr int kMaxSplit = 64;
 constexpr int kFewPairs = 16;        // fp32 path: up to this many pairs in plain loops (kernels_f32.hip),
 constexpr int kFewNarrowPairs = 24;  // ... up to this many of width 128 or less
+constexpr int kGradAnchors = 1024;   // fp32 path: anchors of the other side whose coefficients a workgroup of the gradients forms
 constexpr int kMaxLocalQ = 2560;     // 128 x 128-tile path: local anchors whose coefficients a workgroup of the contraction holds
 
 // State kernel: threads per anchor side that share the work of adding up that side's partial sums (a power of two up to
@@ -45,6 +46,7 @@ struct Layout {
   int64_t bstride;   // anchors padded to whole tiles of 256 (stride of the per-anchor arrays)
   int few;           // 1: fp32 path in plain loops (few pairs)
   int per_part;      // fp32 path: contrast tiles behind one partial sum
+  int grad_state;              // fp32 path: 1: k_grad_f64 runs the state phase itself
   int strip_tile, grad_tile;   // fp32 path: tile sizes of k_strips_f64 / k_grad_f64 (32 or 64)
   int64_t ldE;       // contrast columns of the stored exp strips (MFMA path: multiple of 64; fp32 path: of 4, or B
                      // itself where the strips alone fill the static array)

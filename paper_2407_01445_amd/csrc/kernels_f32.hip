@@ -358,7 +358,108 @@ struct GradF32Args {
   unsigned* arrived;                       // nsplit > 1: [2][tiles], zeroed by the prep kernel
   const float* dcoef;
   const double* red; int nred; int version; const float* tau; float rho; float* loss; float* d_tau;
+  unsigned* scalars_arrived;               // STATE: 0 before the launch
+  int finishers;                           // STATE: workgroups behind the tiles' that finish the anchors
 };
+constexpr size_t kGradStateAt = (sizeof(GradF32Args) + 7) / 8 * 8;      // the kernel's second argument
+
+// A side's partial sums of anchor r and one quantity, `step` of them from `first` on, in fp64.
+__device__ __forceinline__ double add_partials(const StateArgs& a, int quantity, int64_t r, int first, int step) {
+  double s = 0.0;
+  auto add = [&](const auto* p) {
+    for (int p0 = first; p0 < a.nparts; p0 += 8 * step) {         // eight in flight at once
+      double v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = (double)p[(size_t)(p0 + i * step < a.nparts ? p0 + i * step : p0) * a.bstride];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) s += p0 + i * step < a.nparts ? v[i] : 0.0;
+    }
+  };
+  const size_t at = (size_t)quantity * a.nparts * a.bstride + r;
+  if (a.sums64) add(a.sums64 + at);
+  else add(a.sums + at);
+  return s;
+}
+
+// STATE.  The coefficients that a workgroup's tile and slice need: own[T] and drow[T] of its rows, other[nk] of the anchors k0 ..
+// of the other side, zeros where there is no anchor.  Up to 512 at a time: a power of two of threads share an anchor's sum.
+template <int T>
+__device__ __forceinline__ void grad_coefficients(const StateArgs& a, int side, int64_t m0, int64_t k0, int nk, float* own, float* drow,
+                                                  float* other, double* work) {
+  const int items = 2 * T + nk, tid = threadIdx.x;
+  int per = 2 * T;                                  // threads of a lane: the least power of two that holds the items, or all
+  while (per < items && per < 512) per *= 2;
+  const int lane = tid / per, lanes = 512 / per;
+  // (the side differs between lanes: chosen among pointers that are there, not by a load from the arguments)
+  const float *u1 = wave_uniform(a.uold1), *u2 = wave_uniform(a.uold2), *t1 = wave_uniform(a.tau1), *t2 = wave_uniform(a.tau2);
+  for (int i0 = 0; i0 < items; i0 += 512) {
+    const int i = i0 + (tid & (per - 1));
+    const int s = i < T ? side : 1 - side;
+    const int64_t r = i < 2 * T ? m0 + (i & (T - 1)) : k0 + i - 2 * T;
+    const bool live = i < items && r < a.b;
+    float u = 0.f, tau = 1.f;
+    if (live && lane == 0) {
+      u = (s ? u2 : u1)[r];
+      tau = (s ? t2 : t1)[r];
+    }
+    double se = 0.0;
+    if (live) se = add_partials(a, 2 * s, r, lane, lanes);
+    if (lane > 0) work[tid] = se;
+    __syncthreads();
+    if (lane == 0) {
+      float c = 0.f, ce = 0.f;
+      if (live) {
+        for (int q = 1; q < lanes; ++q) se += work[q * per + i];
+        c = anchor_coefficient(a, (float)se, u, tau, &u);
+        ce = __fmul_rn(c, (float)se);
+      }
+      if (i < T) own[i] = c;
+      else if (i >= 2 * T && i < items) other[i - 2 * T] = c;
+      // c1 M g1 + c2 M g2: a row's two sides are 32 lanes apart
+      static_assert(T == 32, "one wave holds both sides of the rows");
+      const float both = ce + __shfl_xor(ce, 32);
+      if (i < T) drow[i] = both;
+    }
+    __syncthreads();
+  }
+}
+
+// STATE.  The state phase of one side of 64 anchors by a workgroup of its own, eight threads per anchor; true in the wave that is
+// to form the scalars.
+__device__ __forceinline__ bool grad_finish(const GradF32Args& g, const StateArgs& a, int f, double* work, int* flag) {
+  const int side = f & 1, tid = threadIdx.x, col = tid & 63, lane = tid >> 6;
+  const int64_t r = (int64_t)(f >> 1) * 64 + col;
+  const bool live = r < g.b, finisher = live && lane == 0;
+  int64_t n = 0;
+  float u_old = 0.f, tau = 1.f, m = 0.f, v = 0.f;
+  if (finisher) {
+    n = a.idx[r] * a.stride;
+    u_old = (side ? a.uold2 : a.uold1)[r];
+    tau = (side ? a.tau2 : a.tau1)[r];
+    if (a.version == FASTCLIP_V2 && a.tau_upd.optimizer) {
+      m = (side ? a.m_txt : a.m_img)[n];
+      if (keeps_second_moment(a.tau_upd)) v = (side ? a.v_txt : a.v_img)[n];
+    }
+  }
+  double se = live ? add_partials(a, 2 * side, r, lane, 8) : 0.0, sx = live ? add_partials(a, 2 * side + 1, r, lane, 8) : 0.0;
+  work[tid] = se;
+  work[512 + tid] = sx;
+  __syncthreads();
+  double lterm = 0.0, hterm = 0.0;
+  if (finisher) {
+#pragma unroll
+    for (int q = 1; q < 8; ++q) { se += work[q * 64 + col]; sx += work[512 + q * 64 + col]; }
+    state_finish_side<true>(a, side, r, n, (float)se, (float)sx, u_old, tau, m, v, &lterm, &hterm);
+  }
+  lterm = wave_sum_f64(lterm);
+  hterm = wave_sum_f64(hterm);
+  if (tid == 0) {
+    double* red = a.red + 2 * f;
+    store_agent(red, lterm);
+    store_agent(red + 1, hterm);
+  }
+  return last_to_arrive(g.scalars_arrived, (unsigned)g.finishers, flag) && tid < 64;
+}
 
 // T x T output tile, stages of KD of the depth; per thread and stage U words of four weights and of four elements of X.
 // The weights are formed in fp64 on the way into LDS, [k][m]; X stays fp32, [k][n].  The pitches put the four k rows that
@@ -374,6 +475,9 @@ struct GradTile {
   float (*Xs)[KD][T + 16];      // [2]
   int tid, kg, row0, col0, lr, gk;
   int64_t m0, n0, ldE, ldx, b, d;
+  // STATE: the coefficients in LDS, of the tile's rows (this side) and of the slice's anchors k (the other side, from k0 on)
+  const float *own, *other;
+  int64_t k0;
 
   // columns of a weight's LDS row k: m ^ swz(k); whole groups of four columns change places
   static __device__ __forceinline__ int swz(int k) { return ((k >> 2) & (T / 4 - 1)) * 4; }
@@ -437,7 +541,7 @@ struct GradTile {
   // compiler then counts outstanding loads; behind a branch it waits for all of them, which made the kernel wait for
   // memory in every stage: 61 us instead of 49 us on the 1024 x 1024 x 512 step).  Rows and columns of the tile that do not exist are taken from
   // the last ones that do: what they yield is never stored.
-  template <bool TRANS, bool HAS_F, bool HAS_CC>
+  template <bool STATE, bool TRANS, bool HAS_F, bool HAS_CC>
   __device__ __forceinline__ void run(f64x4 (&acc)[W][W], const GradRange& R, int s0, int s1) const {
     const int whole = d % 4 == 0 ? (int)(R.K / KD) : 0;       // d % 4: a word of X would end behind the matrix
     const int p1 = s1 < whole ? s1 : whole;
@@ -456,9 +560,15 @@ struct GradTile {
         pe[i] = R.E + at;
         pf[i] = HAS_F ? R.F + at : nullptr;
         px[i] = R.X + ((int64_t)s0 * KD + u / MC) * ldx + n;
-        pc[i] = (TRANS ? R.c_row : R.c_col) + k;
-        c_fix[i] = TRANS ? 0.f : R.c_row[m];
-        if (TRANS && HAS_CC) cc_fix[i] = load4(R.c_col + m);
+        if constexpr (STATE) {
+          pc[i] = other + (k - k0);
+          c_fix[i] = TRANS ? 0.f : own[m - m0];
+          if (TRANS && HAS_CC) cc_fix[i] = load4(own + (m_own - m0));
+        } else {
+          pc[i] = (TRANS ? R.c_row : R.c_col) + k;
+          c_fix[i] = TRANS ? 0.f : R.c_row[m];
+          if (TRANS && HAS_CC) cc_fix[i] = load4(R.c_col + m);
+        }
       }
       const int64_t de = TRANS ? (int64_t)KD * ldE : KD, dx = (int64_t)KD * ldx;
       auto load = [&](Words& w, int s) {        // the last stage again once the stages have run out
@@ -497,9 +607,14 @@ struct GradTile {
         const int64_t have = TRANS ? (k < R.K ? b - m : 0) : (m < b ? R.K - k : 0);
         const int64_t at = TRANS ? k * ldE + m : m * ldE + k;
         w.e[i] = load4_guarded(R.E + at, have);
-        w.cr[i] = TRANS ? (k < R.K ? R.c_row[k] : 0.f) : (m < b ? R.c_row[m] : 0.f);
         if (HAS_F) w.f[i] = load4_guarded(R.F + at, have);
-        if (HAS_CC) w.cc[i] = TRANS ? load4_guarded(R.c_col + m, b - m) : load4_guarded(R.c_col + k, R.K - k);
+        if constexpr (STATE) {                                // zeros behind the last row and the last anchor
+          w.cr[i] = TRANS ? other[k - k0] : own[m - m0];
+          if (HAS_CC) w.cc[i] = load4(TRANS ? own + (m - m0) : other + (k - k0));
+        } else {
+          w.cr[i] = TRANS ? (k < R.K ? R.c_row[k] : 0.f) : (m < b ? R.c_row[m] : 0.f);
+          if (HAS_CC) w.cc[i] = TRANS ? load4_guarded(R.c_col + m, b - m) : load4_guarded(R.c_col + k, R.K - k);
+        }
         w.x[i] = load4_guarded(R.X + kx * ldx + n, kx < R.K ? d - n : 0);
       }
       store<TRANS, HAS_F, HAS_CC>(w, 0);
@@ -512,19 +627,31 @@ struct GradTile {
 
 // With several splits of the depth the last workgroup of an output tile to arrive adds the partial tiles up in the order of
 // the splits, so the result does not depend on who was last.  One more workgroup forms the step's scalars.
-template <int T, int KD>
-__global__ void __launch_bounds__(512, 2) k_grad_f64(GradF32Args g) {
+//
+// STATE (where make_layout says so): the state phase rides along.  Every workgroup forms the coefficients that it needs, a trip to
+// memory of some 1.5 us, and workgroups of their own, for which there is room beside the tiles' on a compute unit, finish the
+// anchors and the scalars while the products run: a launch of 4 us less (64 pairs at width 32: 18.3 -> 14.8 us a step, 128 of
+// 1024 at 512 34.8 -> 31.2).  (By the last workgroup of a row of strip tiles instead the step took longer, 19.5 and 36.1: store,
+// count, gather, sums and logarithm come one after the other there.)  The order of the sums differs between the coefficients
+// here and the anchors' own, in fp64.
+template <int T, int KD, bool STATE>
+__global__ void __launch_bounds__(512, 2) k_grad_f64(GradF32Args g, StateArgs state) {
   using Tile = GradTile<T, KD>;
   constexpr int W = Tile::W;
   __shared__ __attribute__((aligned(16))) double As[2][KD][T + 16];
   __shared__ __attribute__((aligned(16))) float Xs[2][KD][T + 16];
   __shared__ int last_flag;
+  __shared__ __attribute__((aligned(16))) float own[STATE ? T : 1], drow[STATE ? T : 1], other[STATE ? kGradAnchors : 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  if (blockIdx.x == gridDim.x - 1) {
-    if (tid < 64) write_scalars(g.red, g.nred, g.b, g.version, g.tau, g.rho, g.loss, g.d_tau);
+  const int tiles = g.tiles_m * g.tiles_n;
+  if ((int)blockIdx.x >= 2 * tiles * g.nsplit) {
+    bool scalars = tid < 64;
+    if constexpr (STATE)
+      scalars = grad_finish(late_argument<0>(g), late_argument<kGradStateAt>(state), (int)blockIdx.x - 2 * tiles * g.nsplit, &As[0][0][0],
+                            &last_flag);
+    if (scalars) write_scalars<STATE>(g.red, g.nred, g.b, g.version, g.tau, g.rho, g.loss, g.d_tau);
     return;
   }
-  const int tiles = g.tiles_m * g.tiles_n;
   const int split = (int)blockIdx.x % g.nsplit, tile = ((int)blockIdx.x / g.nsplit) % tiles;
   const int side = (int)blockIdx.x / (g.nsplit * tiles);
   const GradSide& Sd = g.side[side];
@@ -546,7 +673,7 @@ __global__ void __launch_bounds__(512, 2) k_grad_f64(GradF32Args g) {
     for (int v = 0; v < 4; ++v) {
       const int64_t m = t.m0 + t.row0 + p * 16 + 4 * v + t.gk;
       const bool mine = t.kg == 0 && m < g.b;
-      dc[p][v] = mine ? g.dcoef[m] : 0.f;
+      dc[p][v] = mine && !STATE ? g.dcoef[m] : 0.f;
 #pragma unroll
       for (int q = 0; q < W; ++q) {
         const int64_t n = t.n0 + t.col0 + q * 16 + t.lr;
@@ -558,15 +685,27 @@ __global__ void __launch_bounds__(512, 2) k_grad_f64(GradF32Args g) {
   for (int i = 0; i < W; ++i)
 #pragma unroll
     for (int j = 0; j < W; ++j) acc[i][j] = (f64x4){0.0, 0.0, 0.0, 0.0};
+  const int q_begin = s_begin > n_first ? s_begin - n_first : 0;               // stages over the other side's strip
+  if constexpr (STATE) {
+    const bool square = Sd.nrange == 1;
+    const int first = square ? s_begin : q_begin, last = square ? s_end : (s_end > n_first ? s_end - n_first : 0);
+    t.own = own; t.other = other; t.k0 = (int64_t)first * KD;
+    grad_coefficients<T>(late_argument<kGradStateAt>(state), side, t.m0, t.k0, last > first ? (last - first) * KD : 0, own, drow, other,
+                         &As[0][0][0]);
+#pragma unroll
+    for (int p = 0; p < W; ++p)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) dc[p][v] = drow[t.row0 + p * 16 + 4 * v + t.gk];
+  }
   if (s_begin < n_first) {
     const GradRange& R = Sd.range[0];
     const int e = s_end < n_first ? s_end : n_first;
-    if (R.trans) t.template run<true, true, true>(acc, R, s_begin, e);            // square, text side
-    else if (R.c_col) t.template run<false, true, true>(acc, R, s_begin, e);      // square, image side
-    else if (R.F) t.template run<false, true, false>(acc, R, s_begin, e);         // gathered state
-    else t.template run<false, false, false>(acc, R, s_begin, e);
+    if (R.trans) t.template run<STATE, true, true, true>(acc, R, s_begin, e);            // square, text side
+    else if (Sd.nrange == 1) t.template run<STATE, false, true, true>(acc, R, s_begin, e);      // square, image side
+    else if (R.F) t.template run<STATE, false, true, false>(acc, R, s_begin, e);         // gathered state
+    else t.template run<STATE, false, false, false>(acc, R, s_begin, e);
   }
-  if (s_end > n_first) t.template run<true, false, false>(acc, Sd.range[1], s_begin > n_first ? s_begin - n_first : 0, s_end - n_first);
+  if (s_end > n_first) t.template run<STATE, true, false, false>(acc, Sd.range[1], q_begin, s_end - n_first);
   // the second group's accumulators join the first's (the staging buffers are free)
   double* meet = &As[0][0][0];
   if (t.kg == 1) {
@@ -672,9 +811,11 @@ void launch_grad_f32(const StepCtx& c) {
   g.dcoef = (const float*)(c.ws + L.dcoef);
   g.red = (const double*)(c.ws + L.red); g.nred = L.nstate_blocks; g.version = c.cfg.version;
   g.tau = c.buf.tau; g.rho = c.cfg.rho; g.loss = c.buf.loss; g.d_tau = c.buf.d_tau;
-  const dim3 grid((unsigned)(2 * g.tiles_m * g.tiles_n * g.nsplit + 1));
-  if (T == 64) hipLaunchKernelGGL((k_grad_f64<64, 32>), grid, dim3(512), 0, c.s, g);
-  else hipLaunchKernelGGL((k_grad_f64<32, 64>), grid, dim3(512), 0, c.s, g);
+  g.finishers = L.grad_state ? L.nstate_blocks : 0;
+  g.scalars_arrived = L.grad_state ? g.arrived + L.narrived - 1 : nullptr;
+  const dim3 grid((unsigned)(2 * g.tiles_m * g.tiles_n * g.nsplit + (L.grad_state ? g.finishers : 1)));
+  auto* kernel = L.grad_state ? k_grad_f64<32, 64, true> : (T == 64 ? k_grad_f64<64, 32, false> : k_grad_f64<32, 64, false>);
+  hipLaunchKernelGGL(kernel, grid, dim3(512), 0, c.s, g, make_state_args(c));
 }
 
 // ------------------------------------------------------------------------------------------
