@@ -66,7 +66,7 @@ struct Layout {
   int out_rows;      // t128 without wide: rows of an output tile of the contraction, 32, 64 or 128
   int out_cols;      // MFMA path, 256-row tiles: columns of an output tile of the contraction, 256 or 192
   int wide_strips;   // wide: the strips are k_strips_wide128_bf16
-  int own_prep;      // t128: k_strips_t128_bf16 prepares its anchors itself, k_prep is not launched
+  int own_prep;      // t128: k_strips_t128_bf16 prepares its anchors itself, k_prep is not launched; fp32 path: so does k_strips_f64
   int wide;          // t128: the contraction is k_contract_wide128_bf16 (kernels_wide128.hip) behind the fold; nsplit /
                      //    kslice count 32-deep stages
   int square;        // 1: b == B and the similarity matrix is formed once.  MFMA path: F[0] holds l2(j, p) in the

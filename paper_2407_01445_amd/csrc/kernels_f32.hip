@@ -64,6 +64,13 @@ struct F32StripArgs {
   int nparts, per_part;         // partial sums per anchor and quantity; contrast tiles behind each
   int64_t bstride, b, B, d, off;
   int nAT, nCT, square;
+  // PREP: what k_prep reads and leaves for the state phase
+  const int64_t* idx;
+  int64_t stride;
+  const float *tau_glob, *tau_in[2], *u_in[2];     // tau_glob: nullptr with one temperature per sample (V2)
+  float *tau_out[2], *u_out[2];
+  unsigned* arrived;            // counters of the gradients, zeroed here
+  int narrived;
 };
 
 constexpr int kFD = 32;                        // depth of a stage: 128 bytes per row
@@ -77,7 +84,11 @@ __device__ __forceinline__ int fd_off(int row, int chunk) { return row * 128 + (
 // Eight waves, two per SIMD, so that one wave's LDS reads, conversions and barrier waits hide behind the other's products:
 // two groups of 2 x 2 waves of T/2 x T/2, which take every other stage and add their accumulators up through the
 // similarity tile.  A step of the loop is two stages; the ring holds four steps (T = 32: 64 KiB, T = 64: 128 KiB).
-template <int T>
+//
+// PREP: the workgroup prepares its anchors itself and k_prep is not launched: s_ii of its rows (and, whole batch local, columns),
+// 16 threads per row over 16-byte words;
+// temperature and u^t by dataset index.
+template <int T, bool PREP>
 __global__ void __launch_bounds__(512, 2) k_strips_f64(F32StripArgs a) {
   constexpr int W = T / 32;                    // 16 x 16 blocks of a wave in either direction
   constexpr int kSlot = 2 * T * 128, kSteps = 4, kAhead = kSteps - 1, kSlots = 2 * kSteps;
@@ -100,7 +111,8 @@ __global__ void __launch_bounds__(512, 2) k_strips_f64(F32StripArgs a) {
   const int prow = tid / TPR, pcol = (tid % TPR) * CPT;
   const int64_t r = a0 + prow;
   const bool live = r < a.b;
-  const double s_pp = live ? (double)a.diag[r] : 0.0, inv_tau = live ? 1.0 / (double)a.tau[strip][r] : 0.0;
+  double s_pp = 0.0, inv_tau = 0.0;
+  if (!PREP && live) { s_pp = (double)a.diag[r]; inv_tau = 1.0 / (double)a.tau[strip][r]; }
   double sum_e = 0.0, sum_xe = 0.0;
   const int64_t lda = a.ld_anchor[strip], ldx = a.ld_contrast[strip];
   const float* A0 = a.anchors[strip] + a0 * lda;
@@ -116,6 +128,52 @@ __global__ void __launch_bounds__(512, 2) k_strips_f64(F32StripArgs a) {
     }
   }
   const int ct_end = (part + 1) * a.per_part < a.nCT ? (part + 1) * a.per_part : a.nCT;
+  // PREP: [rows, columns][s_ii, 1 / tau][T]; threads < 64 gather, of a row (tid < 32) or column tid % 32
+  __shared__ double anchor[PREP ? 2 : 1][2][PREP ? T : 1];
+  float my_tau = 1.f, my_u = 0.f;
+  const int my_set = tid >> 5;                     // 0: the rows' side; 1 (whole batch local): the columns', side 1
+  const int64_t my_r = (my_set ? (int64_t)part * T : a0) + (tid & 31);
+  const bool gathers = PREP && tid < (a.square ? 64 : 32) && my_r < a.b, keeper = gathers && (my_set ? at : part) == 0;
+  if constexpr (PREP) {
+    static_assert(T == 32, "16 threads per row");
+    if (gathers) {
+      const int side = my_set ? 1 : strip;
+      my_tau = a.tau_glob ? a.tau_glob[0] : 1.f;
+      const int64_t n = a.idx[my_r] * a.stride;
+      if (!a.tau_glob) my_tau = a.tau_in[side][n];
+      if (keeper) my_u = a.u_in[side][n];
+    }
+    for (int i = (int)blockIdx.x * 512 + tid; i < a.narrived; i += (int)gridDim.x * 512) a.arrived[i] = 0u;
+  }
+  if constexpr (PREP) {
+    for (int set = 0; set < (a.square ? 2 : 1); ++set) {
+      const int row = tid >> 4, sub = tid & 15;
+      const int64_t q = (set ? (int64_t)part * T : a0) + row;
+      double dot = 0.0;
+      if (q < a.b) {
+        const float *pa = a.anchors[strip] + q * lda, *px = a.contrasts[strip] + (a.off + q) * ldx;
+        for (int64_t k0 = 4 * sub; k0 < a.d; k0 += 512) {         // eight words of either row in flight at once
+          f32x4 x[8], y[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const int64_t k = k0 + 64 * i;
+            x[i] = y[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            if (k + 4 <= a.d) { x[i] = load4(pa + k); y[i] = load4(px + k); }
+            else if (k < a.d) { x[i] = load4_guarded(pa + k, a.d - k); y[i] = load4_guarded(px + k, a.d - k); }
+          }
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            if (k0 + 64 * i < a.d) {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) dot += (double)x[i][e] * (double)y[i][e];
+            }
+        }
+      }
+#pragma unroll
+      for (int o = 1; o < 16; o <<= 1) dot += __shfl_xor(dot, o);
+      if (sub == 0) anchor[set][0][row] = (double)(float)dot;
+    }
+  }
   for (int ct = part * a.per_part; ct < ct_end; ++ct) {
     const int64_t c0 = (int64_t)ct * T;
     const float* X0 = a.contrasts[strip] + c0 * ldx;
@@ -192,7 +250,12 @@ __global__ void __launch_bounds__(512, 2) k_strips_f64(F32StripArgs a) {
       __syncthreads();
       if (kg == 0) compute(ring);
     }
+    if (gathers) anchor[my_set][1][tid & 31] = 1.0 / (double)my_tau;
     __syncthreads();
+    if constexpr (PREP) {
+      s_pp = anchor[0][0][prow];
+      inv_tau = anchor[0][1][prow];
+    }
     for (int half = 0; half < 2; ++half) {
       if (kg == half) {
 #pragma unroll
@@ -238,7 +301,8 @@ __global__ void __launch_bounds__(512, 2) k_strips_f64(F32StripArgs a) {
       const int64_t j = c0 + col;
       if (a.square) {                               // l2(j, p) of text anchor j, and its sums over the images
         const bool there = j < a.B;
-        const double s_jj = there ? (double)a.diag[j] : 0.0, inv = there ? 1.0 / (double)a.tau[1][j] : 0.0;
+        const double s_jj = PREP ? anchor[PREP][0][PREP ? col : 0] : (there ? (double)a.diag[j] : 0.0);
+        const double inv = PREP ? anchor[PREP][1][PREP ? col : 0] : (there ? 1.0 / (double)a.tau[1][j] : 0.0);
         double se = 0.0, sx = 0.0;
 #pragma unroll
         for (int i = 0; i < T / TPR; ++i) {
@@ -275,6 +339,11 @@ __global__ void __launch_bounds__(512, 2) k_strips_f64(F32StripArgs a) {
       else a.sums64[((size_t)(2 + q) * a.nparts + at) * a.bstride + c0 + col] = s;
     }
     __syncthreads();
+  }
+  if (keeper) {
+    const int side = my_set ? 1 : strip;
+    a.tau_out[side][my_r] = my_tau;
+    a.u_out[side][my_r] = my_u;
   }
 #pragma unroll
   for (int o = 1; o < TPR; o <<= 1) {
@@ -329,8 +398,17 @@ void launch_strips_f32(const StepCtx& c) {
   a.nCT = (int)((L.B + T - 1) / T);
   a.square = L.square;
   const dim3 grid((unsigned)((L.square ? 1 : 2) * a.nAT * a.nparts));
-  if (T == 64) hipLaunchKernelGGL(k_strips_f64<64>, grid, dim3(512), 0, c.s, a);
-  else hipLaunchKernelGGL(k_strips_f64<32>, grid, dim3(512), 0, c.s, a);
+  if (L.own_prep) {
+    a.idx = c.buf.idx; a.stride = c.cfg.state_stride;
+    a.tau_glob = c.cfg.version == FASTCLIP_V2 ? nullptr : c.buf.tau;
+    a.tau_in[0] = c.buf.tau_img; a.tau_in[1] = c.buf.tau_txt;
+    a.u_in[0] = c.buf.u_img; a.u_in[1] = c.buf.u_txt;
+    a.tau_out[0] = (float*)(c.ws + L.tau1); a.tau_out[1] = (float*)(c.ws + L.tau2);
+    a.u_out[0] = (float*)(c.ws + L.uold1); a.u_out[1] = (float*)(c.ws + L.uold2);
+    a.arrived = (unsigned*)(c.ws + L.arrived); a.narrived = L.narrived;
+  }
+  auto* kernel = T == 64 ? k_strips_f64<64, false> : (L.own_prep ? k_strips_f64<32, true> : k_strips_f64<32, false>);
+  hipLaunchKernelGGL(kernel, grid, dim3(512), 0, c.s, a);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -147,9 +147,11 @@ def test_f32_tiles_at_their_edges(B, b, off, d, pad, version):
 
 @pytest.mark.parametrize("B,b,off,d,pad", [
     # coefficients of 512 anchors in one pass and of more in two, the most that a workgroup forms, more than that; several
-    # workgroups that finish anchors, the last one a single anchor; one anchor in all; 512 workgroups and more without them
+    # workgroups that finish anchors, the last one a single anchor; one anchor in all; 512 workgroups and more without them;
+    # strips that prepare their anchors, of the widest rows with the whole batch local and of wide ragged ones without
     (448, 448, 0, 40, 0), (449, 449, 0, 40, 0), (900, 448, 450, 68, 4), (1024, 1024, 0, 20, 0), (1040, 1030, 5, 20, 4),
-    (700, 257, 100, 300, 0), (65, 65, 0, 520, 0), (40, 1, 39, 36, 0), (520, 520, 0, 484, 0)])
+    (700, 257, 100, 300, 0), (65, 65, 0, 520, 0), (40, 1, 39, 36, 0), (520, 520, 0, 484, 0), (70, 70, 0, 512, 4),
+    (140, 70, 31, 1030, 0)])
 @pytest.mark.parametrize("version", [V0, V2, V3])
 def test_f32_state_phase_inside_the_gradients(B, b, off, d, pad, version):
     test_f32_tiles_at_their_edges(B, b, off, d, pad, version)
