@@ -398,7 +398,10 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
     // as many where the whole batch is local.  Steps without / so, us: 128 of 1024 at width 128 20.6 / 19.4, at 512 29.6 / 28.4, at
     // 1024 44.9 / 41.3, at 4096 125 / 119, 200 of 2000 at 1536 158 / 158; whole batches 64 at 32 14.7 / 14.4, 448 at 128 23.3 /
     // 22.7, 128 at 512 22.3 / 21.8, 512 at 512 36.6 / 36.5, but 128 at 768 25.9 / 26.5, 256 at 1024 37.6 / 38.4.
-    L->own_prep = L->strip_tile == 32 && !L->gathered && (!L->square || cfg.d <= 512);
+    // Two workgroups fit a compute unit; with more than 512, where they would prepare in rounds, it does not pay: 800 of 800 at 96
+    // 42.6 / 43.8, 768 of 768 at 512 68.9 / 69.3.
+    const int64_t strip_wgs = (L->square ? 1 : 2) * ((cfg.b + 31) / 32) * L->nparts;
+    L->own_prep = L->strip_tile == 32 && !L->gathered && (!L->square || cfg.d <= 512) && strip_wgs <= 512;
     // The state phase inside the gradients: on 32 x 32 tiles, two workgroups of which fit a compute unit, where that leaves room for
     // those that finish the anchors (behind 512 others they would come last), and where a workgroup forms the coefficients of at
     // most 1024 of the other side's anchors, those of its slice, from at most 25000 partial sums.  Steps with k_state / so, us: 64 pairs at width 32 18.5 / 15.2,

@@ -64,7 +64,7 @@ __device__ __forceinline__ void dma4(const void* uniform_base, uint32_t lane_byt
 // them.  By hand: values that the compiler knows it keeps, and spills.
 template <size_t BYTES>
 __device__ __forceinline__ void warm_arguments() {
-  static_assert((BYTES > 0x80 && BYTES <= 0xc0) || (BYTES > 0x100 && BYTES <= 0x140) || (BYTES > 0x200 && BYTES <= 0x240),
+  static_assert((BYTES > 0x80 && BYTES <= 0xc0) || (BYTES > 0x100 && BYTES <= 0x1c0) || (BYTES > 0x200 && BYTES <= 0x240),
                 "the words below cover the arguments, and lie in them");
   uint32_t w0, w1, w2, w3, w4, w5, w6, w7, w8;
   if constexpr (BYTES <= 0xc0) {
@@ -75,6 +75,17 @@ __device__ __forceinline__ void warm_arguments() {
     asm volatile("s_load_dword %0, %5, 0x0\n\ts_load_dword %1, %5, 0x40\n\ts_load_dword %2, %5, 0x80\n\t"
                  "s_load_dword %3, %5, 0xc0\n\ts_load_dword %4, %5, 0x100\n\ts_waitcnt lgkmcnt(0)"
                  : "=&s"(w0), "=&s"(w1), "=&s"(w2), "=&s"(w3), "=&s"(w4)
+                 : "s"(__builtin_amdgcn_kernarg_segment_ptr()));
+  } else if constexpr (BYTES <= 0x180) {
+    asm volatile("s_load_dword %0, %6, 0x0\n\ts_load_dword %1, %6, 0x40\n\ts_load_dword %2, %6, 0x80\n\t"
+                 "s_load_dword %3, %6, 0xc0\n\ts_load_dword %4, %6, 0x100\n\ts_load_dword %5, %6, 0x140\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&s"(w0), "=&s"(w1), "=&s"(w2), "=&s"(w3), "=&s"(w4), "=&s"(w5)
+                 : "s"(__builtin_amdgcn_kernarg_segment_ptr()));
+  } else if constexpr (BYTES <= 0x1c0) {
+    asm volatile("s_load_dword %0, %7, 0x0\n\ts_load_dword %1, %7, 0x40\n\ts_load_dword %2, %7, 0x80\n\t"
+                 "s_load_dword %3, %7, 0xc0\n\ts_load_dword %4, %7, 0x100\n\ts_load_dword %5, %7, 0x140\n\t"
+                 "s_load_dword %6, %7, 0x180\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&s"(w0), "=&s"(w1), "=&s"(w2), "=&s"(w3), "=&s"(w4), "=&s"(w5), "=&s"(w6)
                  : "s"(__builtin_amdgcn_kernarg_segment_ptr()));
   } else {
     asm volatile("s_load_dword %0, %9, 0x0\n\ts_load_dword %1, %9, 0x40\n\ts_load_dword %2, %9, 0x80\n\t"
