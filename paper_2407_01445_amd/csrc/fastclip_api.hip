@@ -378,12 +378,13 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
   if (L->t128 && !L->gathered && !L->wide_strips) {
     // Strips that prepare their anchors save the launch, about 3 us, and take longer by two or four 16-byte loads and LDS reads a
     // lane for every 128 of width, in every round of workgroups.  What that saves of a step, us, by width:
-    // 64 anchors a tile, 128 of 1024 2.6 (256), 2.3 (512), 0.9 (1024), 0.5 (1152), 0.0 (1280), -0.9 (1536), -2.2 (2048), -5.2
+    // 32 anchors a tile, 128 of 1024 1.3 (512), 0.3 (1024), 0.2 (1152), -0.2 (1280), -0.7 (1536), -2.0 (2048), 512 of 512 0.7 (1024),
+    // 0.0 (1280), -0.4 (1536); 64 anchors a tile, 128 of 1024 2.6 (256), 2.3 (512), 0.9 (1024), 0.5 (1152), 0.0 (1280), -0.9 (1536), -2.2 (2048), -5.2
     // (3072), 512 of 2048 2.3, 1.8, 0.5, 0.2, -0.3, -1.2, -2.5, -4.8; 128 anchors, 256 of 8192 1.6 (256), 1.4 (768), 0.7 (1152), 0.2
     // (1280), 0.1 (1536), -0.3 (2048), 384 of 4096 1.2 (512), 0.6 (1152), 0.5 (1280), -0.4 (1536); two rounds, 1000 of 4000 1.1
     // (256), 0.2 (448), -0.3 (512), -2.4 (768), 1280 of 2560 1.8, 0.0, 0.0, -0.4 (640); more rounds, no difference up to 384.
-    const int64_t rows = strips_t128_narrow(*L) ? 64 : 128, tiles = 2 * ((cfg.b + rows - 1) / rows) * L->nparts;
-    L->own_prep = cfg.d <= (tiles <= 256 ? (rows == 64 ? 1200 : 1400) : (tiles <= 512 ? 480 : 0));
+    const int64_t rows = strips_t128_anchors(*L), tiles = 2 * ((cfg.b + rows - 1) / rows) * L->nparts;
+    L->own_prep = cfg.d <= (tiles <= 256 ? (rows <= 64 ? 1200 : 1400) : (tiles <= 512 ? 480 : 0));
   }
   if (!L->t128) L->fused_state = L->bf16 && fold_forms_state(cfg.b, L->nparts);
   // scalar partials: t128 without the fold leaves those of its finishing waves, eight of a workgroup of 256 anchors or the tiles'

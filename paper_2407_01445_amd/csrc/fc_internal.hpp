@@ -99,6 +99,14 @@ struct Layout {
 // 1024 30.7 -> 30.1), else 128: beyond one round two tiles of 64 take longer than one of 128 (3.5 us of either are its start
 // and end).
 static inline bool strips_t128_narrow(const Layout& L) { return 2 * ((L.b + 63) / 64) * (int64_t)L.nparts <= 256; }
+// ... and 32 where even that is one round: a tile fetches three quarters of the bytes of one of 64 and finishes half of the
+// elements.  Steps with 64 / with 32, us: 128 of 1024 at width 512 13.8 / 12.7, at 1024 18.6 / 17.3, 256 of 2048 at 512 27.4 / 26.4
+// (V2 from records, raw rows), 512 of 512 17.5 / 16.4, 128 of 4096 21.2 / 20.3, 64 of 64 at 64 10.3 / 9.6; two of them on a compute
+// unit: 1024 of 1024 26.4 / 28.5, 512 of 2048 23.6 / 25.1, 300 of 2048 21.0 / 22.5.
+static inline bool strips_t128_few(const Layout& L) { return 2 * ((L.b + 31) / 32) * (int64_t)L.nparts <= 256; }
+static inline int strips_t128_anchors(const Layout& L) {
+  return !strips_t128_narrow(L) ? 128 : (strips_t128_few(L) && !L.gathered ? 32 : 64);
+}
 
 // Waves of k_contract_t128_bf16 that finish the anchors of an output tile where no workgroup of its own does.
 static inline int t128_finishing_waves(int out_rows) { return out_rows == 32 ? 2 : out_rows / 32; }

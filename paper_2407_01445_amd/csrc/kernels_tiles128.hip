@@ -74,8 +74,8 @@ struct T128StripArgs {
 // One workgroup per tile (AT = 128: 128 anchors against 128 contrasts of one strip), eight waves = two groups of 2 x 2 waves of
 // 64 x 64: either group takes every other 64-deep stage, so that a SIMD always has a second wave to issue from, an operand
 // read serves two products, and the loop has half the barriers; afterwards the groups exchange halves of their
-// accumulators and each finishes half of the tile's columns.  AT = 64: the four waves of a group take 32 contrasts each.
-// Measured with AT = 128 at 128 anchors of 1024 pairs, d = 512 (a shape that takes AT = 64 now, see the launch), against four
+// accumulators and each finishes half of the tile's columns.  AT = 64, 32: the four waves of a group take 32 contrasts each.
+// Measured with AT = 128 at 128 anchors of 1024 pairs, d = 512 (a shape that takes AT = 32 now, strips_t128_anchors), against four
 // waves on 32-deep stages through a ring of five (k_strips_wide128_bf16): 12.0 -> 8.5 us, of which (in-kernel counters, 2.4
 // GHz) 0.4 set-up, 1.1 until the first step is there, 2.6 in the four steps (1.7 of products), 0.7 exchange, 1.5
 // exponentials, 0.5 sums.
@@ -92,12 +92,13 @@ struct T128StripArgs {
 template <int AT, bool GATHERED, bool PREP>
 __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
   static_assert(!(GATHERED && PREP), "gathered state is prepared by k_prep");
-  constexpr int NP = AT / 64;                     // PREP: anchors per group of eight lanes
-  constexpr int WC = AT / 64, NI = WC;            // waves across the anchors; 32-row blocks of contrasts per wave
+  constexpr int NP = AT > 64 ? AT / 64 : 1;       // PREP: anchors per group of eight lanes
+  constexpr int NJ = AT == 32 ? 1 : 2;            // 32-row blocks of anchors per wave
+  constexpr int WC = AT / (32 * NJ), NI = WC;     // waves across the anchors; 32-row blocks of contrasts per wave
   constexpr int kStage = kPanel + AT * kD * 2, kStep = 2 * kStage;   // a step = one stage for either group of waves
-  constexpr int NL = 4 + 2 * WC;                  // wave loads per step: 4 of the contrasts, 2 or 4 of the anchors
+  constexpr int NA = AT / 32, NL = 4 + NA;        // wave loads per step: 4 of the contrasts, 1, 2 or 4 of the anchors
   constexpr int CW = 32 * NI;                     // contrasts of a wave
-  __shared__ __attribute__((aligned(1024))) char ring[2 * kStep];    // 96 / 128 KiB
+  __shared__ __attribute__((aligned(1024))) char ring[2 * kStep];    // 80 / 96 / 128 KiB
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kg = wave >> 2, q4 = wave & 3, wr = q4 / WC, wc = q4 % WC, lr = lane & 31, hk = lane >> 5;
   const int ct = blockIdx.x, at = blockIdx.y, strip = blockIdx.z;    // no divisions: they are serial instructions at the start
@@ -116,7 +117,7 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
   uint32_t ox[NL];
 #pragma unroll
   for (int i = 0; i < NL; ++i) {
-    const int row = (i < 4 ? 8 * (4 * q4 + i) : 8 * (2 * WC * q4 + i - 4)) + (lane >> 3);
+    const int row = (i < 4 ? 8 * (4 * q4 + i) : 8 * (NA * q4 + i - 4)) + (lane >> 3);
     int g = first + (c0 + row < B ? c0 + row : B - 1);
     g -= g >= B ? B : 0;
     const int m = a0 + row < b ? a0 + row : b - 1;
@@ -124,16 +125,17 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
   }
   const int S = (d + kD - 1) / kD, steps = (S + 1) / 2;
   const int tail = (d % kD) / 8;                  // 16-byte chunks of the last stage that exist (0: all eight)
-  // the epilogue's per-anchor scalars (a lane's anchors are a0 + 64 wc + 32 tj + lr), requested ahead of everything else
-  float kk[2], dk[2];
+  // the epilogue's per-anchor scalars (a lane's anchors are a0 + 32 (NJ wc + tj) + lr), requested ahead of everything else
+  float kk[NJ], dk[NJ];
 #pragma unroll
-  for (int tj = 0; tj < 2; ++tj) {
-    const int m = a0 + wc * 64 + tj * 32 + lr;
+  for (int tj = 0; tj < NJ; ++tj) {
+    const int m = a0 + (wc * NJ + tj) * 32 + lr;
     kk[tj] = !PREP && m < b ? J.kscale[m] : 0.f;
     dk[tj] = !PREP && m < b ? a.diag[m] : 0.f;
   }
-  // PREP: anchors 64 i + 8 wave + lane / 8 of the tile, chunk lane % 8 of every stage
-  const int prow = 8 * wave + (lane >> 3), pch = lane & 7;
+  // PREP: anchors 64 i + 8 wave + lane / 8 of the tile (AT = 32: the last four waves do the last anchor's again), chunk lane % 8 of
+  // every stage
+  const int prow = 8 * wave + (lane >> 3) < AT ? 8 * wave + (lane >> 3) : AT - 1, pch = lane & 7;
   uint32_t po[NP];
   u32x4 partner[2][NP], mine[2][NP];              // [stage of the step][anchor]
   double dot[NP];
@@ -207,7 +209,7 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
   auto request = [&](auto edge, int step, int i) {
     int st = step * 2 + kg;
     uint32_t o = ox[i];
-    const int row8 = i < 4 ? 4 * q4 + i : 2 * WC * q4 + i - 4;        // its rows: 8 row8 .. + 7 of the panel
+    const int row8 = i < 4 ? 4 * q4 + i : NA * q4 + i - 4;            // its rows: 8 row8 .. + 7 of the panel
     if constexpr (decltype(edge)::value) {
       st = st < S ? st : S - 1;
       if (tail && st == S - 1) {                  // a chunk beyond the row is fetched as the stage's first one, and not used
@@ -223,22 +225,21 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
 #pragma unroll
     for (int i = 0; i < NL; ++i) request(std::true_type{}, 1, i);
   }
-  f32x16 acc[NI][2];
+  f32x16 acc[NI][NJ];
 #pragma unroll
   for (int i = 0; i < NI; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
   if (steps == 1) FC_WAIT_VMCNT0();
-  else if (NL == 8) FC_WAIT_VMCNT8();
-  else __builtin_amdgcn_s_waitcnt(0x0f76);      // vmcnt(6)
+  else wait_vmcnt<NL>();
   __syncthreads();
   FC_FENCE();
-  const int rx = wr * CW + lr, ra = wc * 64 + lr;     // rows 32 further on share the swizzle
+  const int rx = wr * CW + lr, ra = wc * NJ * 32 + lr;     // rows 32 further on share the swizzle
   // EDGE: the step holds the last stage (which may end inside, or not exist for group 1)
-  auto read = [&](auto edge, int s, int kq, bf16x8 (&x)[NI], bf16x8 (&y)[2]) {
+  auto read = [&](auto edge, int s, int kq, bf16x8 (&x)[NI], bf16x8 (&y)[NJ]) {
     const char* px = ring + (s & 1) * kStep + kg * kStage + rx * 128;
     const char* pa = ring + (s & 1) * kStep + kg * kStage + kPanel + ra * 128;
     const int c = 2 * kq + hk, st = s * 2 + kg;
@@ -251,7 +252,7 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
       x[i] = __builtin_bit_cast(bf16x8, v);
     }
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < NJ; ++i) {
       u32x4 v = *(const u32x4*)(pa + i * 4096 + ((c ^ p_swz(ra)) << 4));
       if constexpr (decltype(edge)::value) v = c < valid ? v : z;
       y[i] = __builtin_bit_cast(bf16x8, v);
@@ -259,13 +260,13 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
   };
   // The products on (x, y); loads r, r + 1 of step `next` are dealt out between them: a direct-to-LDS load holds its wave for
   // about a hundred cycles when all eight waves issue, which the SIMD's other wave fills with its products.
-  auto multiply = [&](auto edge, const bf16x8 (&x)[NI], const bf16x8 (&y)[2], bool more, int next, int r) {
+  auto multiply = [&](auto edge, const bf16x8 (&x)[NI], const bf16x8 (&y)[NJ], bool more, int next, int r) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
 #pragma unroll
       for (int p = 0; p < NI; ++p) {              // NI products, then a load
         const int ti = NI == 2 ? h : 0, tj = NI == 2 ? p : h;
-        acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[ti], y[tj], acc[ti][tj], 0, 0, 0);
+        if (tj < NJ) acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[ti], y[tj], acc[ti][tj], 0, 0, 0);
       }
       FC_PIN();
       if (more && r + h < NL) request(edge, next, r + h);
@@ -275,7 +276,7 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
   // Step s: the loads from 2 on of step s + 1 go out between its first products (0 and 1 went out behind the barrier of step s - 1);
   // three quarters in, the step's panels have been read and the next step's have landed.
   auto step = [&](auto edge_here, auto edge_next, int s) {
-    bf16x8 x0[NI], y0[2], x1[NI], y1[2];
+    bf16x8 x0[NI], y0[NJ], x1[NI], y1[NJ];
     const bool fill = s > 0 && s + 1 < steps;
     read(edge_here, s, 0, x0, y0);
     read(edge_here, s, 1, x1, y1);
@@ -309,12 +310,12 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
 #pragma unroll
     for (int ti = 0; ti < NI; ++ti)
 #pragma unroll
-      for (int tj = 0; tj < 2; ++tj)
+      for (int tj = 0; tj < NJ; ++tj)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           const f32x4 w = {acc[ti][tj][FROM + 4 * h], acc[ti][tj][FROM + 4 * h + 1], acc[ti][tj][FROM + 4 * h + 2],
                            acc[ti][tj][FROM + 4 * h + 3]};
-          *(f32x4*)(mine + ((ti * 2 + tj) * 2 + h) * 256) = w;
+          *(f32x4*)(mine + ((ti * NJ + tj) * 2 + h) * 256) = w;
         }
   };
   if (kg) give(std::true_type{}); else give(std::false_type{});
@@ -333,9 +334,9 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
   __syncthreads();
   if constexpr (PREP) {
 #pragma unroll
-    for (int tj = 0; tj < 2; ++tj) {
-      kk[tj] = scol[wc * 64 + tj * 32 + lr];
-      dk[tj] = scol[AT + wc * 64 + tj * 32 + lr];
+    for (int tj = 0; tj < NJ; ++tj) {
+      kk[tj] = scol[(wc * NJ + tj) * 32 + lr];
+      dk[tj] = scol[AT + (wc * NJ + tj) * 32 + lr];
     }
   }
   const float* other = (const float*)(ring + (wave ^ 4) * 8192);
@@ -347,8 +348,8 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
     constexpr bool MASK = decltype(masked)::value;
     constexpr int OWN = decltype(group)::value ? 8 : 0;
 #pragma unroll
-    for (int tj = 0; tj < 2; ++tj) {
-      const int al = wc * 64 + tj * 32 + lr, anchor = a0 + al;
+    for (int tj = 0; tj < NJ; ++tj) {
+      const int al = (wc * NJ + tj) * 32 + lr, anchor = a0 + al;
       const float k = kk[tj], dkk = dk[tj] * k;
       float sg[4] = {0.f, 0.f, 0.f, 0.f}, sx[4] = {0.f, 0.f, 0.f, 0.f};   // independent chains
 #pragma unroll
@@ -363,7 +364,7 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
             ck = *(const f32x4*)cp; cd = *(const f32x4*)(cp + kT); cc = *(const f32x4*)(cp + 2 * kT);
           }
           float f[4];
-          const f32x4 o = *(const f32x4*)(other + ((ti * 2 + tj) * 2 + h) * 256 + lane * 4);
+          const f32x4 o = *(const f32x4*)(other + ((ti * NJ + tj) * 2 + h) * 256 + lane * 4);
           float e[4];
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
@@ -387,7 +388,7 @@ __global__ void __launch_bounds__(512, 2) k_strips_t128_bf16(T128StripArgs a) {
         }
         const int cb = ((c0 + wr * CW) >> 4) + 2 * ti + kg;
         const u32x4 w = {pk[0], pk[1], pk[2], pk[3]};
-        const int64_t word = (((int64_t)((a0 + wc * 64) / 32 + tj) * a.nCB + cb) * 64 + lane) * 8;
+        const int64_t word = (((int64_t)(a0 / 32 + wc * NJ + tj) * a.nCB + cb) * 64 + lane) * 8;
         if (!MASK || 16 * cb < a.ldE) {
           *(u32x4*)(E + word) = w;
           if constexpr (GATHERED) { const u32x4 wf = {pf[0], pf[1], pf[2], pf[3]}; *(u32x4*)(F + word) = wf; }
@@ -449,7 +450,7 @@ void launch_strips_t128_bf16(const StepCtx& c) {
   a.nCB = (int)(L.ldE / 16); a.ldE = (int)L.ldE; a.nparts = L.nparts; a.bstride = (int)L.bstride;
   a.b = (int)L.b; a.B = (int)L.B; a.d = (int)L.d;
   a.first = L.wide ? 0 : (int)L.off; a.own = L.wide ? (int)L.off : 0;
-  const bool narrow = strips_t128_narrow(L);
+  const int rows = strips_t128_anchors(L);
   if (L.own_prep) {
     a.idx = c.buf.idx; a.stride = c.cfg.state_stride;
     a.tau_glob = c.cfg.version == FASTCLIP_V2 ? nullptr : c.buf.tau;
@@ -461,11 +462,12 @@ void launch_strips_t128_bf16(const StepCtx& c) {
       a.job[i].u_out = (float*)(c.ws + (i == 0 ? L.uold1 : L.uold2));
     }
   }
-  auto* kernel = L.gathered ? (narrow ? k_strips_t128_bf16<64, true, false> : k_strips_t128_bf16<128, true, false>)
-                 : L.own_prep ? (narrow ? k_strips_t128_bf16<64, false, true> : k_strips_t128_bf16<128, false, true>)
-                              : (narrow ? k_strips_t128_bf16<64, false, false> : k_strips_t128_bf16<128, false, false>);
-  const int64_t at_rows = narrow ? 64 : 128;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)L.nparts, (unsigned)((L.b + at_rows - 1) / at_rows), 2), dim3(512), 0, c.s, a);
+  auto* kernel = L.gathered ? (rows == 64 ? k_strips_t128_bf16<64, true, false> : k_strips_t128_bf16<128, true, false>)
+                 : L.own_prep ? (rows == 32 ? k_strips_t128_bf16<32, false, true>
+                                            : rows == 64 ? k_strips_t128_bf16<64, false, true> : k_strips_t128_bf16<128, false, true>)
+                              : (rows == 32 ? k_strips_t128_bf16<32, false, false>
+                                            : rows == 64 ? k_strips_t128_bf16<64, false, false> : k_strips_t128_bf16<128, false, false>);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)L.nparts, (unsigned)((L.b + rows - 1) / rows), 2), dim3(512), 0, c.s, a);
 }
 
 // ----------------------------------------------------------------------------------------------------------------

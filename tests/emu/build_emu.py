@@ -66,10 +66,12 @@ PLAN_RULES = [
     ("fastclip_api.hip", "  if (wgs >= (cfg.b > 512 ? 256 : 257) &&", '  if (getenv("EMU_WIDE") || wgs >= (cfg.b > 512 ? 256 : 257) &&'),
     ("fastclip_api.hip", "L->wide_strips = tiles > 256 && tiles < 512 && (4 * cfg.b > 3 * cfg.B || L->nparts % 2);",
      "L->wide_strips = " + _forced("tiles > 256 && tiles < 512 && (4 * cfg.b > 3 * cfg.B || L->nparts % 2)", "EMU_WIDE_STRIPS") + ";"),
-    ("fastclip_api.hip", "L->own_prep = cfg.d <= (tiles <= 256 ? (rows == 64 ? 1200 : 1400) : (tiles <= 512 ? 480 : 0));",
-     "L->own_prep = " + _forced("cfg.d <= (tiles <= 256 ? (rows == 64 ? 1200 : 1400) : (tiles <= 512 ? 480 : 0))", "EMU_OWN_PREP") + ";"),
+    ("fastclip_api.hip", "L->own_prep = cfg.d <= (tiles <= 256 ? (rows <= 64 ? 1200 : 1400) : (tiles <= 512 ? 480 : 0));",
+     "L->own_prep = " + _forced("cfg.d <= (tiles <= 256 ? (rows <= 64 ? 1200 : 1400) : (tiles <= 512 ? 480 : 0))", "EMU_OWN_PREP") + ";"),
     ("fc_internal.hpp", "return 2 * ((L.b + 63) / 64) * (int64_t)L.nparts <= 256;",
      "return " + _forced("2 * ((L.b + 63) / 64) * (int64_t)L.nparts <= 256", "EMU_NARROW") + ";"),
+    ("fc_internal.hpp", "return 2 * ((L.b + 31) / 32) * (int64_t)L.nparts <= 256;",
+     "return " + _forced("2 * ((L.b + 31) / 32) * (int64_t)L.nparts <= 256", "EMU_FEW") + ";"),
     # ... the state phase: inside the contraction or on its own; by workgroups of its own there or by those of the output tiles
     ("fastclip_api.hip", "const bool fused = r == 1 || (rows == 64 && nq <= 256 && L->nparts <= 64);",
      "const bool fused = " + _forced("r == 1 || (rows == 64 && nq <= 256 && L->nparts <= 64)", "EMU_FUSED") + ";"),

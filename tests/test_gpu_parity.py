@@ -438,6 +438,15 @@ def test_bf16_tiles_128_edges(B, b, off, d):
     test_bf16_tiles_128(B, b, off, d, V2 if B % 2 else V3)
 
 
+@pytest.mark.parametrize("B,b,off,d", [
+    # strip tiles of 32 anchors up to one round of them, then of 64 and of 128; with a last anchor alone in its tile; one step and
+    # a half; rows that the strips prepare and, wider, the launch before them
+    (2048, 256, 768, 512), (2048, 257, 700, 512), (2049, 256, 1000, 264), (1000, 97, 500, 192), (1100, 33, 1000, 136),
+    (600, 290, 10, 1200), (600, 290, 10, 1208)])
+def test_bf16_small_tiles_of_32_anchors(B, b, off, d):
+    test_bf16_tiles_128(B, b, off, d, V2 if d % 3 else V3)
+
+
 @pytest.mark.parametrize("B,b,off,d,fused,nsplit", [
     # 32 x 32 output tiles: one stage, one row, widths inside a tile
     (33, 33, 0, 8, 1, 1), (40, 1, 39, 40, 1, 1), (65, 31, 34, 24, 1, 1),

@@ -185,6 +185,9 @@ FORCED = [
     dict(plan=dict(WIDE=1, WIDE_STRIPS=1), B=300, b=140, off=100, d=72, version=V0, ld_txt=80),
     dict(plan=dict(OUT_ROWS=128, NARROW=0), B=200, b=140, off=33, d=72, version=V2),
     dict(plan=dict(OUT_ROWS=32), B=200, b=140, off=33, d=72, version=V2, ld_img=80),
+    dict(plan=dict(FEW=0), B=200, b=140, off=33, d=200, version=V2, ld_img=208),              # strips of 64 anchors
+    dict(plan=dict(FEW=0, OWN_PREP=0), B=200, b=140, off=33, d=72, version=V3),
+    dict(plan=dict(OWN_PREP=0), B=200, b=140, off=33, d=200, version=V0),                     # of 32, prepared by the launch before
     dict(plan=dict(OUT_ROWS=64), B=600, b=530, off=70, d=24, version=V3),
     dict(plan=dict(OUT_ROWS=64, NSPLIT=3, OWN_PREP=0), B=200, b=70, off=129, d=136, version=V0),
     dict(plan=dict(OUT_ROWS=128, NSPLIT=2), B=200, b=140, off=33, d=72, version=V3),
