@@ -355,6 +355,14 @@ def test_bf16_single_similarity_pass_on_any_shape(B, b, d, version):
         assert rel_each(outs[0][k], outs[1][k]) < 1e-4, k
 
 
+@pytest.mark.parametrize("B,b,d", [
+    # one strip of weights read by rows and by columns: columns of a tile of rows that the strip does not have, a last stage of one
+    # row, several splits, output tiles of either width
+    (257, 257, 8), (320, 320, 200), (449, 449, 264), (1217, 1217, 136), (2300, 2300, 72)])
+def test_bf16_single_similarity_pass_contracts_one_strip_both_ways(B, b, d):
+    test_bf16_single_similarity_pass_on_any_shape(B, b, d, V2 if B % 2 else V3)
+
+
 def test_bf16_single_similarity_pass_chosen_by_the_library_on_a_ragged_batch():
     """3000 x 3000 pairs: more 256 x 256 tiles than compute units, so the library forms the similarity matrix once without
     being asked; 11 x 11 whole tiles go to the persistent kernel, the ragged last row and column to the guarded one."""
