@@ -341,6 +341,7 @@ __global__ void __launch_bounds__(256) k_state(StateArgs a) {
   using sum_t = typename SumType<PRECISE>::type;
   __shared__ sum_t part[2][256];
   __shared__ double scal[2][4];
+  warm_arguments<sizeof(StateArgs)>();
   const int SA = 256 / a.lanes;                       // anchor sides per tile of a block
   const int sa = threadIdx.x % SA, pl = threadIdx.x / SA;
   const int side = sa & 1;
@@ -368,10 +369,23 @@ __global__ void __launch_bounds__(256) k_state(StateArgs a) {
     }
     sum_t se_t = 0, sx_t = 0;
     if (r < a.b) {
-      // four partial sums of each quantity per round, so that eight loads are in flight instead of two
+      // eight partial sums of each quantity per round (sixteen loads in flight), or four
       auto add_up = [&](const auto* s0) {
         const auto* s1 = s0 + (size_t)a.nparts * a.bstride;
         int pt = pl;
+        for (; pt + 7 * a.lanes < a.nparts; pt += 8 * a.lanes) {
+          sum_t e[8], x[8];
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            e[q] = s0[(size_t)(pt + q * a.lanes) * a.bstride];
+            x[q] = s1[(size_t)(pt + q * a.lanes) * a.bstride];
+          }
+#pragma unroll
+          for (int q = 0; q < 8; q += 4) {
+            se_t += (e[q] + e[q + 1]) + (e[q + 2] + e[q + 3]);
+            sx_t += (x[q] + x[q + 1]) + (x[q + 2] + x[q + 3]);
+          }
+        }
         for (; pt + 3 * a.lanes < a.nparts; pt += 4 * a.lanes) {
           sum_t e[4], x[4];
 #pragma unroll
