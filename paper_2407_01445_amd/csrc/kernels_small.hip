@@ -292,16 +292,19 @@ __global__ void k_tau_scalar(TauUpd u, float* tau, float* m, float* v, const flo
   if (threadIdx.x == 0 && blockIdx.x == 0) tau_step(u, tau, m, v, d_tau[0]);
 }
 
-// Individual temperatures (V2): one thread per local anchor, both sides; gathers and scatters by dataset index.
+// Individual temperatures (V2): one thread per side (blockIdx.y) of a local anchor; gathers and scatters by dataset index.  What
+// bounds it for a batch is the chain index - gathers - scatters; both sides by one thread were two of them.
 __global__ void __launch_bounds__(256) k_tau_sparse(TauUpd u, const int64_t* __restrict__ idx, int64_t b,
                                                     const float* __restrict__ g_img, const float* __restrict__ g_txt,
                                                     float* tau_img, float* tau_txt, float* m_img, float* v_img,
                                                     float* m_txt, float* v_txt) {
   const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (r >= b) return;
+  const int side = blockIdx.y;
+  const float g = (side ? g_txt : g_img)[r];
   const int64_t n = idx[r] * u.stride;
-  tau_step(u, tau_img + n, m_img + n, v_img ? v_img + n : nullptr, g_img[r]);
-  tau_step(u, tau_txt + n, m_txt + n, v_txt ? v_txt + n : nullptr, g_txt[r]);
+  float* v = side ? v_txt : v_img;
+  tau_step(u, (side ? tau_txt : tau_img) + n, (side ? m_txt : m_img) + n, v ? v + n : nullptr, g);
 }
 
 void launch_tau_scalar(const TauUpd& u, const fastclip_tau_state& st, const float* d_tau, hipStream_t s) {
@@ -310,7 +313,7 @@ void launch_tau_scalar(const TauUpd& u, const fastclip_tau_state& st, const floa
 
 void launch_tau_sparse(const TauUpd& u, const fastclip_tau_state& st, const int64_t* idx, int64_t b,
                        const float* d_tau_img, const float* d_tau_txt, hipStream_t s) {
-  hipLaunchKernelGGL(k_tau_sparse, dim3((unsigned)((b + 255) / 256)), dim3(256), 0, s, u, idx, b, d_tau_img,
+  hipLaunchKernelGGL(k_tau_sparse, dim3((unsigned)((b + 255) / 256), 2), dim3(256), 0, s, u, idx, b, d_tau_img,
                      d_tau_txt, st.tau_img, st.tau_txt, st.m_img, st.v_img, st.m_txt, st.v_txt);
 }
 
@@ -683,6 +686,42 @@ __global__ void __launch_bounds__(256) k_norm_backward(const T* __restrict__ img
   for (int64_t n = threadIdx.x; n < d; n += 256) out[n] = (float)(((A)out[n] - dot * (A)load_elem(ep + n)) * inv);
 }
 
+// The same where rows are whole groups of four elements, aligned, and at most 1024 wide: a wavefront per anchor and side, whose
+// lanes hold the row (k_normalize_rows_quads).  What bounds it is the chain load - sum - store: with the norm and the row a
+// second time behind the sum it was three trips to memory (256 rows of width 512: 4.0 -> 3.4 us a launch).
+template <typename T, typename A>
+__global__ void __launch_bounds__(256) k_norm_backward_quads(const T* __restrict__ img, const T* __restrict__ txt, int64_t ld_img,
+                                                             int64_t ld_txt, int64_t off, int64_t b, int d,
+                                                             float* __restrict__ d_img, float* __restrict__ d_txt,
+                                                             const float* __restrict__ norm_img, const float* __restrict__ norm_txt) {
+  const int lane = threadIdx.x & 63, side = blockIdx.y;
+  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r >= b) return;
+  const T* ep = side == 0 ? img + (off + r) * ld_img : txt + (off + r) * ld_txt;
+  float* out = (side == 0 ? d_img : d_txt) + r * d;
+  const float norm = (side == 0 ? norm_img : norm_txt)[r];
+  float4 o[kNormQuads], e[kNormQuads];
+#pragma unroll
+  for (int i = 0; i < kNormQuads; ++i) {
+    const int k = 4 * (lane + 64 * i);
+    o[i] = k < d ? load_quad((const float*)out + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+    e[i] = k < d ? load_quad(ep + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  A dot = 0;
+#pragma unroll
+  for (int i = 0; i < kNormQuads; ++i)
+    dot += ((A)o[i].x * (A)e[i].x + (A)o[i].y * (A)e[i].y) + ((A)o[i].z * (A)e[i].z + (A)o[i].w * (A)e[i].w);
+  dot = wave_sum(dot);
+  const A inv = (A)1 / (A)norm;
+#pragma unroll
+  for (int i = 0; i < kNormQuads; ++i) {
+    const int k = 4 * (lane + 64 * i);
+    if (k < d)
+      store_quad(out + k, make_float4((float)(((A)o[i].x - dot * (A)e[i].x) * inv), (float)(((A)o[i].y - dot * (A)e[i].y) * inv),
+                                      (float)(((A)o[i].z - dot * (A)e[i].z) * inv), (float)(((A)o[i].w - dot * (A)e[i].w) * inv)));
+  }
+}
+
 void launch_finalize_bf16(const StepCtx& c) {
   const Layout& L = c.L;
   const dim3 block(256);
@@ -701,8 +740,19 @@ void launch_finalize_bf16(const StepCtx& c) {
 void launch_norm_backward(const StepCtx& c) {
   const Layout& L = c.L;
   if (!c.buf.norm_img) return;
-  const dim3 grid((unsigned)L.b, 2), block(256);
-  if (L.bf16)
+  const dim3 grid((unsigned)L.b, 2), block(256), of_quads((unsigned)((L.b + 3) / 4), 2);
+  const size_t quad = 4 * (L.bf16 ? sizeof(bf16_t) : sizeof(float));
+  const bool quads = L.d % 4 == 0 && L.d <= 256 * kNormQuads && c.cfg.ld_img % 4 == 0 && c.cfg.ld_txt % 4 == 0 &&
+                     (uintptr_t)c.buf.img_glob % quad == 0 && (uintptr_t)c.buf.txt_glob % quad == 0;   // (d_img, d_txt: 16 bytes)
+  if (quads && L.bf16)
+    hipLaunchKernelGGL((k_norm_backward_quads<bf16_t, float>), of_quads, block, 0, c.s, (const bf16_t*)c.buf.img_glob,
+                       (const bf16_t*)c.buf.txt_glob, c.cfg.ld_img, c.cfg.ld_txt, L.off, L.b, (int)L.d, c.buf.d_img, c.buf.d_txt,
+                       c.buf.norm_img, c.buf.norm_txt);
+  else if (quads)
+    hipLaunchKernelGGL((k_norm_backward_quads<float, double>), of_quads, block, 0, c.s, (const float*)c.buf.img_glob,
+                       (const float*)c.buf.txt_glob, c.cfg.ld_img, c.cfg.ld_txt, L.off, L.b, (int)L.d, c.buf.d_img, c.buf.d_txt,
+                       c.buf.norm_img, c.buf.norm_txt);
+  else if (L.bf16)
     hipLaunchKernelGGL((k_norm_backward<bf16_t, float>), grid, block, 0, c.s, (const bf16_t*)c.buf.img_glob,
                        (const bf16_t*)c.buf.txt_glob, c.cfg.ld_img, c.cfg.ld_txt, L.off, L.d, c.buf.d_img, c.buf.d_txt,
                        c.buf.norm_img, c.buf.norm_txt);
