@@ -446,6 +446,16 @@ def test_bf16_tiles_128_edges(B, b, off, d):
     test_bf16_tiles_128(B, b, off, d, V2 if B % 2 else V3)
 
 
+def test_calls_without_a_stream_take_the_current_one():
+    """On torch's default stream, on a stream of the program's own and back, as torch.cuda.current_stream() names them."""
+    side = torch.cuda.Stream()
+    for context in (None, side, None):
+        with torch.cuda.stream(context):
+            assert fc._stream(None) == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert fc._stream(None) == side.cuda_stream and fc._stream(torch.cuda.default_stream()) == torch.cuda.default_stream().cuda_stream
+
+
 @pytest.mark.parametrize("B,b,off,d", [
     # strip tiles of 32 anchors up to one round of them, then of 64 and of 128; with a last anchor alone in its tile; one step and
     # a half; rows that the strips prepare and, wider, the launch before them
