@@ -112,6 +112,7 @@ TauUpd make_tau_upd(const fastclip_tau_update& upd) {
 struct Room {
   int64_t split_bytes;     // partial results of splits
   bool partial_sums;       // fp32 path: partial sums of the strips, which its single pass needs too
+  bool state_rides;        // fp32 path: the state phase inside the gradients, which has a counter and scalar partials of its own
 };
 
 // fp32 path: tile sizes, partial sums and the split of the gradients' depth.
@@ -411,7 +412,7 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
     // sums (800 of 800 at 96, 21600: 44.3 / 42.6) 1024 of 2048 at 64 68.2 / 69.6, 1000 of 4000 at 128 153 / 158.
     const int64_t of_slice = L->square ? L->kslice * 64 : (L->kslice * 64 < cfg.b + 63 ? L->kslice * 64 : (cfg.b + 63) / 64 * 64);
     const int64_t tiles = 2 * ((cfg.b + 31) / 32) * ((cfg.d + 31) / 32), finishers = 2 * ((cfg.b + 63) / 64);
-    L->grad_state = L->grad_tile == 32 && of_slice <= kGradAnchors && (of_slice + 64) * L->nparts <= 25000 &&
+    L->grad_state = room.state_rides && L->grad_tile == 32 && of_slice <= kGradAnchors && (of_slice + 64) * L->nparts <= 25000 &&
                     tiles * L->nsplit + finishers <= 512;
   }
   L->nstate_blocks = L->grad_state ? (int)(2 * ((cfg.b + 63) / 64)) : L->fused_state ? (int)(out_blocks ? out_blocks : (cfg.b + 63) / 64) : state_blocks(cfg.b, L->nparts);
@@ -469,23 +470,25 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
 
 // A configuration of the fp32 path whose stored strips fit the array of fastclip_step_static fits it whole, so that every such
 // configuration is taken there, and with the same layout whichever entry point runs it.  What the step has in its workspace
-// for speed alone gives way in this order: splits as far as their partial results do not fit (a few per cent mostly, at worst
+// for speed alone gives way in this order: the state phase inside the gradients (3 us, by less than 3 KiB), splits as far as their partial results do not fit (a few per cent mostly, at worst
 // a quarter: 1000 of 8000 pairs at width 64 take 227 us, 177 with two splits; 2600 of 2600 at width 512 keep their single pass
 // and take 577, with three splits 537, without the single pass 1460), then, where the strips alone leave less than the partial
 // sums take (the last 5 % below the array's size), the partial sums and the single pass, at two to three times the time.
 void make_layout(const fastclip_config& cfg, Layout* L) {
   constexpr int64_t kLimit = FASTCLIP_STATIC_SCRATCH_BYTES;
-  make_layout(cfg, Room{INT64_MAX, true}, L);
+  make_layout(cfg, Room{INT64_MAX, true, true}, L);
   if (L->bf16 || (int64_t)L->total <= kLimit) return;
   Layout small;
-  make_layout(cfg, Room{0, true}, &small);
+  make_layout(cfg, Room{INT64_MAX, true, false}, &small);
+  if ((int64_t)small.total <= kLimit) { *L = small; return; }
+  make_layout(cfg, Room{0, true, false}, &small);
   if ((int64_t)small.total <= kLimit) {
     // beside the partial results a split plan has an arrival counter for each of its at most 1024 tiles
-    make_layout(cfg, Room{kLimit - (int64_t)small.total - 4096, true}, L);
+    make_layout(cfg, Room{kLimit - (int64_t)small.total - 4096, true, false}, L);
     if ((int64_t)L->total > kLimit) *L = small;
     return;
   }
-  make_layout(cfg, Room{0, false}, &small);
+  make_layout(cfg, Room{0, false, false}, &small);
   if ((int64_t)small.total <= kLimit) *L = small;
 }
 
@@ -620,7 +623,7 @@ fastclip_status fastclip_step_static(const fastclip_config* cfg, const fastclip_
   fc::make_layout(*cfg, &L);
   // the small tiles without partial results, also for gathered state that is on the 256 x 256 tiles for the time they take; or
   // the longer runs that gathered state on the latter can do with
-  if (L.total > (size_t)FASTCLIP_STATIC_SCRATCH_BYTES) fc::make_layout(*cfg, fc::Room{0, true}, &L);
+  if (L.total > (size_t)FASTCLIP_STATIC_SCRATCH_BYTES) fc::make_layout(*cfg, fc::Room{0, true, false}, &L);
   if (L.total > (size_t)FASTCLIP_STATIC_SCRATCH_BYTES) return FASTCLIP_ERR_WORKSPACE;
   void* ws = nullptr;
   const fastclip_status sp = fc::static_scratch(&ws);

@@ -469,6 +469,14 @@ def test_f32_workspace_takes_no_more_than_the_strips_where_the_static_array_asks
     assert fc.fastclip_describe(good_cfg(emb_dtype=fc.F32, B=8192, b=512, off=0, d=64, N=5000))["nparts"] > 1
 
 
+def test_f32_state_phase_inside_the_gradients_takes_no_room_of_the_static_array():
+    """Strips that fill the static array but for one block of 256 bytes, beside what the step cannot do without."""
+    for B, b, d in ((12917, 649, 20), (11468, 731, 128), (14404, 582, 32), (15582, 538, 20), (8964, 935, 64)):
+        plan = good_cfg(emb_dtype=fc.F32, B=B, b=b, off=0, d=d, N=90000)
+        assert fc.fastclip_workspace_bytes(plan) == fc.STATIC_SCRATCH_BYTES - 256
+        assert fc.fastclip_describe(plan)["nparts"] == 1
+
+
 def test_few_fp32_pairs_take_no_tiles():
     """Few fp32 pairs run in plain loops: two strips, one partial sum, one split whatever the tiled path would take."""
     for shape, plain in ((dict(B=2, b=2, d=1024), 1), (dict(B=16, b=16, d=512), 1), (dict(B=24, b=24, d=128), 1),
