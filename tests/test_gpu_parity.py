@@ -947,6 +947,28 @@ def test_gradients_through_normalisation(dtype, tol, shape, version, tiles):
     compare(g.outputs(), want, version, tol, "normalised %s %s v%d" % (dtype, shape, version))
 
 
+@pytest.mark.parametrize("dtype,tol,shape,pad", [
+    # whole groups of four elements, a wavefront per row: one group, a lane's last word short of the row, the widest; wider rows and
+    # a stride that is no multiple of four elements, a workgroup per row; a last workgroup of one anchor
+    ("f32", TOL_F32, (40, 9, 7, 4), 0), ("f32", TOL_F32, (40, 21, 7, 260), 4), ("f32", TOL_F32, (40, 17, 3, 1024), 0),
+    ("f32", TOL_F32, (40, 17, 3, 1028), 0), ("f32", TOL_F32, (40, 9, 7, 260), 3),
+    ("bf16", TOL_BF16, (140, 65, 33, 8), 0), ("bf16", TOL_BF16, (140, 65, 33, 1024), 8), ("bf16", TOL_BF16, (140, 65, 33, 1032), 0)])
+def test_gradients_through_normalisation_of_rows_of_any_width(dtype, tol, shape, pad):
+    B, b, off, d = shape
+    rng = np.random.default_rng(B + d)
+    img, txt = make_embeddings(B + 5, B, d, 0.5, dtype)
+    idx = draw_indices(B + 6, b, 3000)
+    norms = [rng.uniform(0.3, 20.0, b).astype(np.float32) for _ in range(2)]
+    g = GpuStep(B=B, b=b, off=off, d=d, N=3000, dtype=dtype, version=V3, eps=1e-6, rho=6.5, tau=0.07, norms=norms,
+                ld_img=d + pad, ld_txt=d + pad)
+    g.set_inputs(img, txt, idx)
+    g.step(0.6)
+    want = fcco_step(img.astype(np.float64), txt.astype(np.float64), off, b, idx, np.zeros(3000), np.zeros(3000), version=V3,
+                     gamma=0.6, eps=g.eps, rho=g.rho, tau=float(np.float32(0.07)), tau_grad_scale=g.scale,
+                     norm_img=norms[0].astype(np.float64), norm_txt=norms[1].astype(np.float64))
+    compare(g.outputs(), want, V3, tol, "normalised %s %s" % (dtype, shape))
+
+
 def raw_rows(rng, b, d, dtype):
     """Encoder outputs before normalisation: rows of very different lengths (values bf16-representable if dtype is bf16)."""
     raw = (rng.standard_normal((b, d)) * np.exp(rng.uniform(np.log(0.05), np.log(30.0), (b, 1)))).astype(np.float32)
