@@ -70,7 +70,7 @@ struct Layout {
   int wide;          // t128: the contraction is k_contract_wide128_bf16 (kernels_wide128.hip) behind the fold; nsplit /
                      //    kslice count 32-deep stages
   int square;        // 1: b == B and the similarity matrix is formed once.  MFMA path: F[0] holds l2(j, p) in the
-                     //    layout of E[0] until the fold adds it there (E[1], which the workspace has all the same, is nobody's); fp32 path: E[1] holds it as [p][j]
+                     //    layout of E[0] until the fold transposes it into E[1]; fp32 path: E[1] holds it as [p][j]
   int64_t ncol;      // gathered: entries per column-parameter array (B rounded up to whole 256-column tiles)
   size_t diag, tau1, tau2, k1, k2;   // float[bstride]
   size_t uold1, uold2;               // float[bstride]: u^t of the batch's samples (gathered with the temperatures)

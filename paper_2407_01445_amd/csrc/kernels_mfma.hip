@@ -103,10 +103,7 @@ struct StripTile {
 // 4 rows x 64 bytes of a transposing read cover all 64 banks.  256 columns (512 bytes a row): nt_swz.  192 columns: rows are
 // 384 bytes apart, every other one half the banks further, and rows 2 and 3 of four take the other quarter.
 // REMOTE (gathered state): the A operand is E + F / c_own, formed between the loads of both strips and the LDS image.
-// TRANS (whole batch local): the A operand's rows are the strip's columns.  A stage is 32 of its rows by 256 columns, sixteen
-// consecutive fragments, read with transposing reads; 16-byte chunk (half h, row q) of column block cb sits at row position q ^
-// 4 h ^ 8 (cb & 1), so that the 4 rows x 64 bytes of such a read cover all banks.
-template <int NJ_, bool REMOTE, bool TRANS = false>
+template <int NJ_, bool REMOTE>
 struct ContractTile {
   static constexpr int NJ = NJ_;
   static constexpr int kCols = 64 * NJ, kPieces = 8 * NJ;
@@ -117,7 +114,6 @@ struct ContractTile {
   uint32_t la[4], lb[NJ];
   int wm, wn, lane;
   int64_t n0, N, B;   // guarded path
-  int64_t e_stage;    // elements of the strip between stages
   const bf16_t* Ffr;  // REMOTE: the second strip as Efr, and 1 / c_own of the lane's row in the two anchor blocks that the
   float inv[2];       // wave brings in (fragments 0, 1 and 2, 3)
 
@@ -132,18 +128,12 @@ struct ContractTile {
                                         int64_t n0_, int64_t N_, int64_t B_, int tid) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, kept in SGPRs
     lane = tid & 63; wm = wave >> 1; wn = wave & 1;
-    Efr = E + (TRANS ? 2 * ab0 : ab0 * nCB) * 512; Xn = X_ + n0_; ldx = ldx_;
-    e_stage = TRANS ? nCB * 512 : 1024;
+    Efr = E + ab0 * nCB * 512; Xn = X_ + n0_; ldx = ldx_;
     n0 = n0_; N = N_; B = B_;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int f = wave * 4 + i;                       // fragment f = 2 * (anchor block) + (column block in stage)
-      if constexpr (TRANS) {                            // ... = column block of the tile
-        const int h = lane >> 5, q = (lane & 31) ^ (4 * h) ^ (8 * (f & 1));
-        oa[i] = (uint32_t)(f * 64 + q + 32 * h) * 16u;
-      } else {
-        oa[i] = (uint32_t)(((f >> 1) * (int)nCB + (f & 1)) * 512 + lane * 8) * 2u;
-      }
+      oa[i] = (uint32_t)(((f >> 1) * (int)nCB + (f & 1)) * 512 + lane * 8) * 2u;
       la[i] = (uint32_t)(f * 1024);
     }
 #pragma unroll
@@ -166,7 +156,7 @@ struct ContractTile {
   }
   // chunk i of a stage of either strip, and two of its elements put together
   __device__ __forceinline__ u32x4 load_e(int i, int stage) const {
-    return *(const u32x4*)((const char*)(Efr + stage * (TRANS ? e_stage : 1024)) + oa[i]);
+    return *(const u32x4*)((const char*)(Efr + (int64_t)stage * 1024) + oa[i]);
   }
   __device__ __forceinline__ u32x4 load_f(int i, int stage) const {
     return *(const u32x4*)((const char*)(Ffr + (int64_t)stage * 1024) + oa[i]);
@@ -180,7 +170,7 @@ struct ContractTile {
     return Xn + (int64_t)stage * BK * ldx;
   }
   __device__ __forceinline__ void dma(int i, int stage, uint32_t slot) const {
-    if (i < 4) dma16(Efr + stage * (TRANS ? e_stage : 1024), oa[i], slot + la[i]);
+    if (i < 4) dma16(Efr + (int64_t)stage * 1024, oa[i], slot + la[i]);
     else dma16(stage_rows(stage), ob[i - 4], slot + lb[i - 4]);
   }
   __device__ __forceinline__ void fill_guarded(int stage, char* slot, int tid) const {
@@ -209,20 +199,7 @@ struct ContractTile {
     }
   }
   __device__ __forceinline__ bf16x8 read_a(const char* slot, int t, int kk) const {
-    if constexpr (TRANS) {
-      // columns 4 r4 .. + 3 of a block of 16: half r4 & 1 of the row's chunks, their first or second eight bytes
-      const int s = lane & 15, cb = ((lane >> 4) & 1), r4 = s & 3, hh = r4 & 1, k0 = 4 * (lane >> 5) + (s >> 2);
-      u32x2 part[2];
-#pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        const char* p = slot + (((cb * 2 + hh) * 32 + ((8 * half + k0) ^ (4 * hh) ^ (8 * cb))) * 16 + (r4 >> 1) * 8);
-        part[half] = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                                                   (lds_v4s*)(uintptr_t)lds_addr(p + (wm * 4 + t) * 2048 + kk * 256)));
-      }
-      return join_halves(part[0], part[1]);
-    } else {
-      return *(const bf16x8*)(slot + (((wm * 4 + t) * 2 + kk) * 1024 + lane * 16));
-    }
+    return *(const bf16x8*)(slot + (((wm * 4 + t) * 2 + kk) * 1024 + lane * 16));
   }
   // slots e = 0..3 <-> rows 16 kk + 4 h + e, slots 4..7 <-> rows 16 kk + 8 + 4 h + (e - 4): two transposing reads
   // (half 0 / 1), each taking 4 rows x 16 columns per group of 16 lanes (source lane s: row s / 4, columns 4 (s % 4) ..).
@@ -889,14 +866,17 @@ __global__ void __launch_bounds__(256) k_fold_bf16(bf16_t* __restrict__ E0, bf16
 }
 
 // The same when the whole batch is local and the similarity matrix was formed once: F0[r][q] holds l2(q, p_r) in the
-// layout of E0 (off == 0), and w = c1_r E0[r][q] + c2_q F0[r][q] weights text q in the gradient of image r as well as image r in
-// that of text q: it goes back to E0[r][q], which the contraction reads by rows for the one side and by columns for the
-// other.  A thread forms w from the two chunks that it loads and stores it from its registers.  Rows and columns of the blocks
-// that reach beyond the batch become zeros, as depth of either side's contraction.
-// What bounds it: memory, two strips read and one written: 96 MiB for 4096 pairs, 16.7 us.  (With w / c1 and, transposed
-// through LDS, w / c2 as strips of their own, 128 MiB, it took 21.8.)
-__global__ void __launch_bounds__(256) k_fold_square_bf16(bf16_t* __restrict__ E0, const bf16_t* __restrict__ F0, int64_t nCB,
-                                                          StateArgs a) {
+// layout of E0 (off == 0), so w = c1_r E0[r][q] + c2_q F0[r][q]; w / c1_r goes back to E0[r][q] and w / c2_q, transposed,
+// to E1[q][r], which nothing has written before: a block writes all 64 columns of its rows of E1, zeros beyond the
+// batch, so that every column of E1 up to its padded width holds a number for the contraction.
+// What bounds it: memory, two strips read and two written (128 MiB for 4096 pairs).  off == 0, so a window is whole chunks:
+// a thread forms w from the two chunks it loads (wave w: column block w of the window, two anchor blocks), stores the
+// first result from its registers and passes only the second through LDS, as the bf16 that it stores.  With both windows
+// laid out in LDS as fp32, element by element, a step of 4096 pairs at width 768 took 148.2 us; now 137.1.
+// (Rows of the LDS window are 36 words apart: the writes of a wave's two halves, four rows apart, go to different banks.)
+__global__ void __launch_bounds__(256) k_fold_square_bf16(bf16_t* __restrict__ E0, const bf16_t* __restrict__ F0,
+                                                          bf16_t* __restrict__ E1, int64_t nCB, StateArgs a) {
+  __shared__ __attribute__((aligned(16))) bf16_t t1[64][72];     // [q][r]: w / c2_q
   __shared__ __attribute__((aligned(16))) float sc[4][64];
   __shared__ FoldState fs;
   const int64_t b = a.b;
@@ -920,24 +900,35 @@ __global__ void __launch_bounds__(256) k_fold_square_bf16(bf16_t* __restrict__ E
   for (int i = 0; i < 2; ++i) {
     const int rl = 32 * i + (lane & 31);
     const bool row_ok = r0 + rl < b;
-    const float cr = sc[0][rl];
+    const float cr = sc[0][rl], icr = sc[2][rl];
     uint32_t out[4];
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
-      const float4 cq4 = *(const float4*)&sc[1][ql + 8 * half];
-      const float cq[4] = {cq4.x, cq4.y, cq4.z, cq4.w};
-      float w[4];
+      const float4 cq4 = *(const float4*)&sc[1][ql + 8 * half], icq4 = *(const float4*)&sc[3][ql + 8 * half];
+      const float cq[4] = {cq4.x, cq4.y, cq4.z, cq4.w}, icq[4] = {icq4.x, icq4.y, icq4.z, icq4.w};
+      float w0[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const uint32_t ew = ev[i][2 * half + (e >> 1)], fw = fv[i][2 * half + (e >> 1)];
         const float l1 = __uint_as_float((e & 1) ? (ew & 0xffff0000u) : (ew << 16));
         const float l2 = __uint_as_float((e & 1) ? (fw & 0xffff0000u) : (fw << 16));
-        w[e] = row_ok && q0 + ql + 8 * half + e < b ? fmaf(cr, l1, cq[e] * l2) : 0.f;
+        const int q = ql + 8 * half + e;
+        const float w = row_ok && q0 + q < b ? fmaf(cr, l1, cq[e] * l2) : 0.f;
+        w0[e] = w * icr;
+        t1[q][rl] = f2bf(w * icq[e]);
       }
-      out[2 * half] = pack_bf16x2(w[0], w[1]);
-      out[2 * half + 1] = pack_bf16x2(w[2], w[3]);
+      out[2 * half] = pack_bf16x2(w0[0], w0[1]);
+      out[2 * half + 1] = pack_bf16x2(w0[2], w0[3]);
     }
-    *(u32x4*)(E0 + ((((r0 >> 5) + i) * nCB + (q0 >> 4) + wave) * 64 + lane) * 8) = u32x4{out[0], out[1], out[2], out[3]};
+    if (row_ok) *(u32x4*)(E0 + ((((r0 >> 5) + i) * nCB + (q0 >> 4) + wave) * 64 + lane) * 8) = u32x4{out[0], out[1], out[2], out[3]};
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {       // E1: rows q, columns r = 16 wave + 4 h + 0..3, 8..11 of the window
+    const int q = 32 * i + (lane & 31);
+    if (q0 + q >= b) continue;
+    const u32x2 lo = *(const u32x2*)&t1[q][ql], hi = *(const u32x2*)&t1[q][ql + 8];
+    *(u32x4*)(E1 + ((((q0 >> 5) + i) * nCB + (r0 >> 4) + wave) * 64 + lane) * 8) = u32x4{lo[0], lo[1], hi[0], hi[1]};
   }
 }
 
@@ -947,7 +938,7 @@ void launch_fold_bf16(const StepCtx& c) {
   const StateArgs st = make_state_args(c);
   if (L.square)
     hipLaunchKernelGGL(k_fold_square_bf16, dim3(nb, nb), dim3(256), 0, c.s, (bf16_t*)(c.ws + L.E[0]),
-                       (const bf16_t*)(c.ws + L.F[0]), L.ldE / 16, st);
+                       (const bf16_t*)(c.ws + L.F[0]), (bf16_t*)(c.ws + L.E[1]), L.ldE / 16, st);
   else
     hipLaunchKernelGGL(k_fold_bf16, dim3(nb, nb), dim3(256), 0, c.s, (bf16_t*)(c.ws + L.E[0]), (bf16_t*)(c.ws + L.E[1]),
                        L.ldE / 16, st, L.off);
@@ -974,12 +965,10 @@ struct ContractArgs {
   const float* c_own[2];
 };
 
-// SQUARE: both sides from one strip of weights (k_fold_square_bf16), the texts' by its columns (A operand in two transposing
-// reads instead of one plain one: no difference in time, 49.5 us for 4096 pairs at width 768).  Steps with two strips / one, us:
-// 4096 pairs at 768 135 / 126, at 64 95 / 89, 3000 at 768 137 / 134, 4000 at 512 148 / 143.
-template <int NJ, bool REMOTE, bool SQUARE>
-__device__ __forceinline__ void contract_tile(const ContractArgs& g, char* ring) {
+template <int NJ, bool REMOTE>
+__global__ void __launch_bounds__(256) k_contract_bf16(ContractArgs g) {
   constexpr int W = 64 * NJ;       // columns of an output tile
+  __shared__ __attribute__((aligned(1024))) char ring[kRingBytes];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   const uint32_t ring_addr = lds_addr(ring);
@@ -1000,6 +989,9 @@ __device__ __forceinline__ void contract_tile(const ContractArgs& g, char* ring)
   f32x16 acc[4][NJ];
   zero_acc(acc);
   if (S > 0) {
+    ContractTile<NJ, REMOTE> T;
+    T.setup(J.E, J.nCB, m0 >> 5, J.X, J.ldx, n0, g.N, g.B, tid);
+    if constexpr (REMOTE) T.setup_remote(g.F[ji], J.nCB, m0 >> 5, g.c_own[ji], g.M, tid);
     // The unguarded loads of a stage take 32 whole rows of X and W columns from n0 on.  They stay inside the matrix
     // (B rows of ldx elements, the last one of N) for the stages below `safe`: rows beyond B never, and where the tile
     // is wider than what is left of a row (n0 + W > N) the words past the row's end are the next rows' - they exist
@@ -1009,26 +1001,15 @@ __device__ __forceinline__ void contract_tile(const ContractArgs& g, char* ring)
     if (n0 + W > g.N) rows_ok -= (n0 + W - g.N + J.ldx - 1) / J.ldx;
     const int safe = rows_ok > 0 ? (int)(rows_ok / BK) : 0;
     const int S_ring = s0 + S <= safe ? S : (safe > s0 ? safe - s0 : 0);
-    auto run = [&](auto& T) {
-      T.setup(J.E, J.nCB, m0 >> 5, J.X, J.ldx, n0, g.N, g.B, tid);
-      if constexpr (REMOTE) T.setup_remote(g.F[ji], J.nCB, m0 >> 5, g.c_own[ji], g.M, tid);
-      if (S_ring > 0) {
-        if constexpr (REMOTE) {
-          remote_mainloop(acc, T, ring, ring_addr, s0, S_ring);
-        } else {
-          ring_prologue(T, ring_addr, s0, S_ring);
-          ring_mainloop(acc, T, ring, ring_addr, s0, S_ring);
-        }
+    if (S_ring > 0) {
+      if constexpr (REMOTE) {
+        remote_mainloop(acc, T, ring, ring_addr, s0, S_ring);
+      } else {
+        ring_prologue(T, ring_addr, s0, S_ring);
+        ring_mainloop(acc, T, ring, ring_addr, s0, S_ring);
       }
-      if (S_ring < S) guarded_mainloop(acc, T, ring, s0 + S_ring, S - S_ring, tid);
-    };
-    if (SQUARE && ji == 1) {
-      ContractTile<NJ, false, true> T;
-      run(T);
-    } else {
-      ContractTile<NJ, REMOTE> T;
-      run(T);
     }
+    if (S_ring < S) guarded_mainloop(acc, T, ring, s0 + S_ring, S - S_ring, tid);
   }
   // The partial result leaves as whole tiles of [64 groups of 4 rows][W columns][4 rows]: a lane holds C[m][n] for
   // n = n0 + wn W/2 + tj 32 + lr and the rows m = m0 + wm 128 + ti 32 + 8 q + 4 hk + t, t = 0..3, so its four values of one
@@ -1053,23 +1034,12 @@ __device__ __forceinline__ void contract_tile(const ContractArgs& g, char* ring)
     }
 }
 
-template <int NJ, bool REMOTE>
-__global__ void __launch_bounds__(256) k_contract_bf16(ContractArgs g) {
-  __shared__ __attribute__((aligned(1024))) char ring[kRingBytes];
-  contract_tile<NJ, REMOTE, false>(g, ring);
-}
-template <int NJ>
-__global__ void __launch_bounds__(256) k_contract_square_bf16(ContractArgs g) {
-  __shared__ __attribute__((aligned(1024))) char ring[kRingBytes];
-  contract_tile<NJ, false, true>(g, ring);
-}
-
 void launch_contract_bf16(const StepCtx& c) {
   const Layout& L = c.L;
   ContractArgs g;
   for (int s = 0; s < 2; ++s) {
     ContractJob& J = g.job[s];
-    J.E = (const bf16_t*)(c.ws + L.E[L.square ? 0 : s]);
+    J.E = (const bf16_t*)(c.ws + L.E[s]);
     g.F[s] = L.gathered ? (const bf16_t*)(c.ws + L.F[s]) : nullptr;
     g.c_own[s] = (const float*)(c.ws + (s == 0 ? L.c1 : L.c2));
     J.X = (const bf16_t*)(s == 0 ? c.buf.txt_glob : c.buf.img_glob);
@@ -1085,8 +1055,7 @@ void launch_contract_bf16(const StepCtx& c) {
   g.tiles_m = (int)((L.b + 255) / 256);
   g.tiles_n = (int)((L.d + L.out_cols - 1) / L.out_cols);
   const unsigned grid = (2u * (unsigned)(g.nsplit * g.tiles_m * g.tiles_n) + 7) / 8 * 8;
-  auto* kernel = L.square ? (L.out_cols == 192 ? k_contract_square_bf16<3> : k_contract_square_bf16<4>)
-                 : L.gathered ? (L.out_cols == 192 ? k_contract_bf16<3, true> : k_contract_bf16<4, true>)
+  auto* kernel = L.gathered ? (L.out_cols == 192 ? k_contract_bf16<3, true> : k_contract_bf16<4, true>)
                             : (L.out_cols == 192 ? k_contract_bf16<3, false> : k_contract_bf16<4, false>);
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, c.s, g);
 }

@@ -576,8 +576,8 @@ __global__ void k_scalars(const double* red, int nblocks, int64_t b, int version
 
 // ------------------------------------------------------------------------------------------
 // MFMA path, last phase.  d_img[r] = c1_r * (sum over splits of the contraction)[r] - dcoef_r txt_p, and the mirror
-// image (the contraction already carries the contrast-side terms divided by c_r; c1 == nullptr: it carries the weights
-// themselves, whole batch local); block (0,0,0) also writes the scalars.  The split partials are whole tiles of [64 groups of 4 rows][cols columns][4 rows] (the order in
+// image (the contraction already carries the contrast-side terms divided by c_r); block (0,0,0) also writes the
+// scalars.  The split partials are whole tiles of [64 groups of 4 rows][cols columns][4 rows] (the order in
 // which k_contract_bf16's accumulators leave in 16-byte words), so a block of one wavefront takes four rows and 256
 // columns, 4 KiB of addresses per split (consecutive ones inside a tile), and a thread four columns.  A block is four
 // wavefronts: four groups of rows (SHARE_SPLITS false), or, when that would leave most of the chip idle, one group
@@ -610,7 +610,7 @@ __global__ void __launch_bounds__(256) k_finalize_bf16(const bf16_t* __restrict_
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         const int64_t r = r0 + (t < nr ? t : 0);
-        cown[t] = c1 ? (side == 0 ? c1 : c2)[r] : 1.f;
+        cown[t] = (side == 0 ? c1 : c2)[r];
         dc[t] = dcoef[r];
         xr[t] = *(const uint2*)(X + (off + r) * ldx + n0);
       }
@@ -732,7 +732,7 @@ void launch_finalize_bf16(const StepCtx& c) {
   auto* kernel = share ? k_finalize_bf16<true> : k_finalize_bf16<false>;
   hipLaunchKernelGGL(kernel, grid, block, 0, c.s, (const bf16_t*)c.buf.img_glob, (const bf16_t*)c.buf.txt_glob,
                      c.cfg.ld_img, c.cfg.ld_txt, L.off, L.b, L.d, (const float*)(c.ws + L.Opart[0]),
-                     (const float*)(c.ws + L.Opart[1]), L.nsplit, L.out_cols, L.square ? nullptr : (const float*)(c.ws + L.c1),
+                     (const float*)(c.ws + L.Opart[1]), L.nsplit, L.out_cols, (const float*)(c.ws + L.c1),
                      (const float*)(c.ws + L.c2), (const float*)(c.ws + L.dcoef), c.buf.d_img, c.buf.d_txt, (const double*)(c.ws + L.red),
                      L.nstate_blocks, c.cfg.version, c.buf.tau, c.cfg.rho, c.buf.loss, c.buf.d_tau);
 }

@@ -401,3 +401,50 @@ def test_small_entry_points_of_the_host_built_kernels(emu_step, tmp_path, b, d, 
         new = ema_update(want, idx, s_.astype(np.float64) / float(M), float(gamma))
         assert np.max(np.abs(got - want) / np.maximum(want, 1e-30)) <= 1e-6
         assert np.max(np.abs(got_new - new) / new) <= 1e-6
+
+
+# ------------------------------------------------------------------ what the single pass rounds
+def bf16_round(x):
+    """Nearest bf16, ties to even, as fp64."""
+    u = np.ascontiguousarray(x, np.float32).view(np.uint32)
+    return (((u + 0x7fff + ((u >> 16) & 1)) & 0xffff0000).astype(np.uint32)).view(np.float32).astype(np.float64)
+
+
+@pytest.mark.parametrize("b,d", [(300, 72), (512, 64)])
+def test_single_pass_rounds_each_side_s_weights_divided_by_its_own_coefficient(emu_step, tmp_path, b, d):
+    """The whole batch local, similarity matrix formed once: either side's contraction takes w / c_own as bf16, w = c1_r l1 + c2_q l2,
+    and multiplies by c_own in fp32, as the two-strip form does.  Taken as bf16 themselves, the weights w would be rounded
+    elsewhere and the gradients would move by 1.6e-3 of an operand's size per product.
+
+    Tolerance: a fourth of the distance between those two forms here.  What is left between this model in fp64 and the kernels
+    are single elements that the fp32 evaluation rounds to the other bf16 neighbour: the exponentials are off by some 3e-6 (an
+    exponent of up to 60 in fp32), so one in a thousand of them and of the weights, 4e-3 each: 1.3e-4 per product against 1.6e-3."""
+    run_case(emu_step, tmp_path, B=b, b=b, off=0, d=d, version=V2, flags=fc.SINGLE_PASS)
+    raw, n_state = open(tmp_path / "case.in", "rb").read(), 900
+    eps = float(np.frombuffer(raw, np.float32, 5, 96)[1])
+    at, rows = 96 + 20, []
+    for _ in range(2):
+        bits = np.frombuffer(raw, np.uint16, b * d, at).reshape(b, d).astype(np.uint32)
+        rows.append((bits << 16).view(np.float32).astype(np.float64))
+        at += 2 * b * d
+    idx = np.frombuffer(raw, np.int64, b, at)
+    at += 8 * b + 8 * n_state                                                # u_img, u_txt
+    tau = [np.frombuffer(raw, np.float32, n_state, at + 4 * n_state * k)[idx].astype(np.float64) for k in range(2)]
+    out = np.fromfile(tmp_path / "case.out", np.float32).astype(np.float64)
+    got = [out[:b * d].reshape(b, d), out[b * d:2 * b * d].reshape(b, d)]
+    at = 2 * b * d + 1 + 2 * b                                               # loss, d_tau_img, d_tau_txt
+    g, u = [out[at + k * b:at + (k + 1) * b] for k in (0, 1)], [out[at + k * b:at + (k + 1) * b] for k in (2, 3)]
+
+    M = b - 1.0
+    c = [1.0 / (b * M * (eps + u[k])) for k in (0, 1)]
+    s = rows[0] @ rows[1].T                                                  # [image][text]
+    off_diagonal = ~np.eye(b, dtype=bool)
+    l1 = bf16_round(np.exp((s - np.diag(s)[:, None]) / tau[0][:, None]) * off_diagonal)
+    l2 = bf16_round(np.exp((s - np.diag(s)[None, :]) / tau[1][None, :]) * off_diagonal)      # of text q against image r, at [r][q]
+    w = c[0][:, None] * l1 + c[1][None, :] * l2
+    diagonal = (c[0] * M * g[0] + c[1] * M * g[1])[:, None]
+    one = bf16_round(w)
+    for side, (weights, other, whole) in enumerate(((w / c[0][:, None], rows[1], one), ((w / c[1][None, :]).T, rows[0], one.T))):
+        want = c[side][:, None] * (bf16_round(weights) @ other) - diagonal * other
+        distance = np.linalg.norm(whole @ other - diagonal * other - want)
+        assert np.linalg.norm(got[side] - want) <= distance / 4, (side, np.linalg.norm(got[side] - want), distance)
