@@ -300,8 +300,9 @@ typedef struct {             /* DEVICE memory owned by the caller, updated in pl
 
 /* The update alone, from gradients that a previous fastclip_step wrote (a caller with several workers averages
  * d_tau over the workers in between; d_tau_img / d_tau_txt need no averaging).  d_tau: [1] device (V0, V3);
- * d_tau_img, d_tau_txt: [b] device, batch order, with idx [b] (V2).  Asynchronous on `stream`; V1 returns
- * FASTCLIP_OK and does nothing. */
+ * d_tau_img, d_tau_txt: [b] device, batch order, with idx [b] (V2).  An array of *state may be passed for both sides
+ * (one temperature for both, say): a sample's image step comes first then, and its text step goes on from there.
+ * Asynchronous on `stream`; V1 returns FASTCLIP_OK and does nothing. */
 fastclip_status fastclip_temperature_update(int32_t version, const fastclip_tau_update* upd,
                                             const fastclip_tau_state* state, const int64_t* idx, int64_t b,
                                             int64_t N, const float* d_tau, const float* d_tau_img,
@@ -311,7 +312,8 @@ fastclip_status fastclip_temperature_update(int32_t version, const fastclip_tau_
  * d_tau in between).  For V2 the update is part of the state phase: the kernel that gathers u by idx and scatters
  * u^{t+1} also steps tau_1, tau_2 and their moments at the same indices.  bufs->tau (V0, V3) must be state->tau,
  * bufs->tau_img / tau_txt (V2) must be state->tau_img / tau_txt; the step itself uses the temperatures as they were
- * before the call, and every output of fastclip_step is produced as usual. */
+ * before the call, and every output of fastclip_step is produced as usual.  V2: the arrays of *state are distinct
+ * (different threads step a sample's two sides). */
 fastclip_status fastclip_step_update_tau(const fastclip_config* cfg, const fastclip_buffers* bufs,
                                          const fastclip_tau_update* upd, const fastclip_tau_state* state,
                                          void* workspace, size_t workspace_bytes, void* stream);

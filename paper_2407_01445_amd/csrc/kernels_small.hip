@@ -293,18 +293,22 @@ __global__ void k_tau_scalar(TauUpd u, float* tau, float* m, float* v, const flo
 }
 
 // Individual temperatures (V2): one thread per side (blockIdx.y) of a local anchor; gathers and scatters by dataset index.  What
-// bounds it for a batch is the chain index - gathers - scatters; both sides by one thread were two of them.
+// bounds it for a batch is the chain index - gathers - scatters; both sides by one thread are two of them.  So they are (one row
+// of workgroups, sides == 1) where the sides share an array: the text's step goes on from what the image's has left there.
 __global__ void __launch_bounds__(256) k_tau_sparse(TauUpd u, const int64_t* __restrict__ idx, int64_t b,
                                                     const float* __restrict__ g_img, const float* __restrict__ g_txt,
                                                     float* tau_img, float* tau_txt, float* m_img, float* v_img,
-                                                    float* m_txt, float* v_txt) {
+                                                    float* m_txt, float* v_txt, int sides) {
   const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (r >= b) return;
-  const int side = blockIdx.y;
-  const float g = (side ? g_txt : g_img)[r];
-  const int64_t n = idx[r] * u.stride;
-  float* v = side ? v_txt : v_img;
-  tau_step(u, (side ? tau_txt : tau_img) + n, (side ? m_txt : m_img) + n, v ? v + n : nullptr, g);
+  int side = blockIdx.y;
+  do {
+    const float g = (side ? g_txt : g_img)[r];
+    const int64_t n = idx[r] * u.stride;
+    float* v = side ? v_txt : v_img;
+    tau_step(u, (side ? tau_txt : tau_img) + n, (side ? m_txt : m_img) + n, v ? v + n : nullptr, g);
+    side += sides;
+  } while (side < 2);
 }
 
 void launch_tau_scalar(const TauUpd& u, const fastclip_tau_state& st, const float* d_tau, hipStream_t s) {
@@ -313,8 +317,13 @@ void launch_tau_scalar(const TauUpd& u, const fastclip_tau_state& st, const floa
 
 void launch_tau_sparse(const TauUpd& u, const fastclip_tau_state& st, const int64_t* idx, int64_t b,
                        const float* d_tau_img, const float* d_tau_txt, hipStream_t s) {
-  hipLaunchKernelGGL(k_tau_sparse, dim3((unsigned)((b + 255) / 256), 2), dim3(256), 0, s, u, idx, b, d_tau_img,
-                     d_tau_txt, st.tau_img, st.tau_txt, st.m_img, st.v_img, st.m_txt, st.v_txt);
+  const float *img[3] = {st.tau_img, st.m_img, st.v_img}, *txt[3] = {st.tau_txt, st.m_txt, st.v_txt};
+  int sides = 2;
+  for (const float* p : img)
+    for (const float* q : txt)
+      if (p && p == q) sides = 1;
+  hipLaunchKernelGGL(k_tau_sparse, dim3((unsigned)((b + 255) / 256), (unsigned)sides), dim3(256), 0, s, u, idx, b, d_tau_img,
+                     d_tau_txt, st.tau_img, st.tau_txt, st.m_img, st.v_img, st.m_txt, st.v_txt, sides);
 }
 
 // ------------------------------------------------------------------------------------------

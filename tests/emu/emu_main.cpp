@@ -74,9 +74,11 @@ static void report_fetches(dim3 grid, dim3 block) {
 void launch(dim3 grid, dim3 block, const std::function<void()>& body) {
   gridDim = grid; blockDim = block;
   const int nthreads = (int)(block.x * block.y * block.z), nwaves = (nthreads + 63) / 64;
-  for (unsigned bz = 0; bz < grid.z; ++bz)
-    for (unsigned by = 0; by < grid.y; ++by)
-      for (unsigned bx = 0; bx < grid.x; ++bx) {
+  const bool backwards = getenv("EMU_BACKWARDS") != nullptr;      // no order of the workgroups is promised: the last one first
+  for (unsigned iz = 0; iz < grid.z; ++iz)
+    for (unsigned iy = 0; iy < grid.y; ++iy)
+      for (unsigned ix = 0; ix < grid.x; ++ix) {
+        const unsigned bx = backwards ? grid.x - 1 - ix : ix, by = backwards ? grid.y - 1 - iy : iy, bz = backwards ? grid.z - 1 - iz : iz;
         Block blk;
         blk.waves = std::vector<Wave>(nwaves);
         blk.bar.reset(nthreads);
@@ -154,9 +156,44 @@ static int run_misc(const char* fin, const char* fout) {
   return 0;
 }
 
+// fastclip_temperature_update of V2 on one file: "temperatures" <in> <out>.  In: 5 int64 {b, N, optimizer, step, shared}, 4 float {lr,
+// beta1, beta2, eps}, idx [b], d_tau_img, d_tau_txt [b], tau, m, v [N] of the images, tau, m, v [N] of the texts.  Bits of `shared`: the
+// images' tau (1), m (2), v (4) are passed for the texts as well.  Out: the six arrays that were passed, as they are then.
+static int run_temperatures(const char* fin, const char* fout) {
+  FILE* f = fopen(fin, "rb");
+  if (!f) return 2;
+  int64_t h[5];
+  float p[4];
+  if (fread(h, 8, 5, f) != 5 || fread(p, 4, 4, f) != 4) return 2;
+  const int64_t b = h[0], N = h[1];
+  int64_t* idx = rd<int64_t>(f, b);
+  float *g_img = rd<float>(f, b), *g_txt = rd<float>(f, b), *a[2][3];
+  for (int side = 0; side < 2; ++side)
+    for (int k = 0; k < 3; ++k) a[side][k] = rd<float>(f, N);
+  fclose(f);
+  for (int k = 0; k < 3; ++k)
+    if (h[4] >> k & 1) a[1][k] = a[0][k];
+  fastclip_tau_update upd;
+  memset(&upd, 0, sizeof(upd));
+  upd.struct_size = sizeof(upd); upd.optimizer = (int32_t)h[2]; upd.step = h[3];
+  upd.lr = p[0]; upd.beta1 = p[1]; upd.beta2 = p[2]; upd.eps = p[3];
+  fastclip_tau_state st;
+  memset(&st, 0, sizeof(st));
+  st.tau_img = a[0][0]; st.m_img = a[0][1]; st.v_img = a[0][2];
+  st.tau_txt = a[1][0]; st.m_txt = a[1][1]; st.v_txt = a[1][2];
+  if (fastclip_temperature_update(FASTCLIP_V2, &upd, &st, idx, b, N, nullptr, g_img, g_txt, nullptr) != FASTCLIP_OK) return 4;
+  FILE* o = fopen(fout, "wb");
+  if (!o) return 2;
+  for (int side = 0; side < 2; ++side)
+    for (int k = 0; k < 3; ++k) fwrite(a[side][k], 4, N, o);
+  fclose(o);
+  return 0;
+}
+
 int main(int argc, char** argv) {
   emu::g_lds_hi = (uintptr_t)&emu::g_marker & ~(uintptr_t)0xffffffffull;
   if (argc == 4 && !strcmp(argv[1], "misc")) return run_misc(argv[2], argv[3]);
+  if (argc == 4 && !strcmp(argv[1], "temperatures")) return run_temperatures(argv[2], argv[3]);
   if (argc < 3) return 2;
   FILE* f = fopen(argv[1], "rb");
   if (!f) return 2;

@@ -844,6 +844,28 @@ def test_temperature_update_alone(opt, hp, stride):
             assert v.item() == pytest.approx(wv, rel=1e-5)
 
 
+@pytest.mark.parametrize("b", [1, 300])
+def test_temperature_update_with_one_array_for_both_sides(b):
+    """One temperature and one set of moments for both sides of a sample (V2): the image's step, then the text's from there."""
+    N, step = 900, 4
+    rng = np.random.default_rng(b)
+    f32 = lambda lo, hi, n: rng.uniform(lo, hi, n).astype(np.float32)
+    idx, g = draw_indices(56, b, N), [f32(-1, 1, b) for _ in range(2)]
+    host = dict(tau=f32(0.05, 0.1, N), m=f32(-0.1, 0.1, N), v=f32(0.01, 0.05, N))
+    dev = {k: torch.from_numpy(x.copy()).to(DEV) for k, x in host.items()}
+    hp = {k: float(np.float32(x)) for k, x in dict(lr=2e-3, beta1=0.9, beta2=0.98, eps=1e-6).items()}
+    upd = fc.make_tau_update(optimizer=ADAMW, step=step, **hp)
+    both = lambda arrays: {k + side: x for k, x in arrays.items() for side in ("_img", "_txt")}
+    t_idx, t_g = torch.from_numpy(idx).to(DEV), [torch.from_numpy(x).to(DEV) for x in g]
+    fc.fastclip_temperature_update(V2, upd, fc.make_tau_state(**both(dev)), t_idx, b, N, None, t_g[0], t_g[1])
+    torch.cuda.synchronize()
+    want = {k: x.astype(np.float64) for k, x in host.items()}
+    temperature_update(V2, dict(d_tau_img=g[0].astype(np.float64), d_tau_txt=g[1].astype(np.float64)), optimizer=ADAMW, step=step,
+                       idx=idx, **hp, **both(want))
+    for k in want:       # a dozen fp32 operations a step, each rounded once: 2^-24 of what they add up to, which is below 1
+        assert np.max(np.abs(dev[k].cpu().numpy().astype(np.float64) - want[k])) <= 16 * 2.0 ** -24, k
+
+
 @pytest.mark.parametrize("tiles", [256, None])   # the large-tile kernels; the library's choice (small tiles here)
 @pytest.mark.parametrize("stride", [1, 8, "canonical 8", "canonical 16"])
 @pytest.mark.parametrize("dtype,tol,shape", [("f32", TOL_F32, (64, 64, 0, 32)), ("bf16", TOL_BF16, (700, 300, 133, 72)),

@@ -448,3 +448,43 @@ def test_single_pass_rounds_each_side_s_weights_divided_by_its_own_coefficient(e
         want = c[side][:, None] * (bf16_round(weights) @ other) - diagonal * other
         distance = np.linalg.norm(whole @ other - diagonal * other - want)
         assert np.linalg.norm(got[side] - want) <= distance / 4, (side, np.linalg.norm(got[side] - want), distance)
+
+
+# ------------------------------------------------------------------ one array for both sides' temperatures
+@pytest.mark.parametrize("b,optimizer,shared", [
+    # nothing shared; one temperature for both sides with its moments; a moment shared alone; a second moment that is not kept
+    (70, ADAMW, 0), (70, ADAMW, 7), (300, SGDM, 3), (70, SGDM, 2), (70, ADAMW, 4), (70, LION, 4)])
+def test_temperature_update_with_arrays_that_both_sides_share(emu_step, tmp_path, monkeypatch, b, optimizer, shared):
+    """fastclip_temperature_update (V2) where an array is passed for both sides: an anchor's image step comes first and its text
+    step goes on from there, in whatever order the workgroups run (last first here)."""
+    monkeypatch.setenv("EMU_BACKWARDS", "1")
+    N, step = 2 * b, 3
+    rng = np.random.default_rng(b + shared)
+    f32 = lambda lo, hi, n: rng.uniform(lo, hi, n).astype(np.float32)
+    idx = draw_indices(60, b, N)
+    g = [f32(-1, 1, b) for _ in range(2)]
+    given = [[f32(0.05, 0.1, N), f32(-0.1, 0.1, N), f32(0.01, 0.05, N)] for _ in range(2)]        # tau, m, v of either side
+    hp = [float(np.float32(x)) for x in (2e-3, 0.9, 0.98, 1e-6)]
+    fin, fout = str(tmp_path / "tau.in"), str(tmp_path / "tau.out")
+    with open(fin, "wb") as f:
+        np.array([b, N, optimizer, step, shared], np.int64).tofile(f)
+        np.array(hp, np.float32).tofile(f)
+        for a in [idx.astype(np.int64)] + g + given[0] + given[1]:
+            a.tofile(f)
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0", TSAN_OPTIONS="report_thread_leaks=0")
+    r = subprocess.run([emu_step, "temperatures", fin, fout], capture_output=True, text=True, timeout=600, env=env)
+    assert r.returncode == 0 and "Sanitizer" not in r.stderr, r.stderr[:6000]
+    got = np.fromfile(fout, np.float32).astype(np.float64).reshape(2, 3, N)
+    want = [[a.astype(np.float64) for a in side] for side in given]
+    for k in range(3):
+        if shared >> k & 1:
+            want[1][k] = want[0][k]
+    keeps_v = optimizer == ADAMW
+    temperature_update(V2, dict(d_tau_img=g[0].astype(np.float64), d_tau_txt=g[1].astype(np.float64)), optimizer=optimizer, lr=hp[0],
+                       step=step, beta1=hp[1], beta2=hp[2], eps=hp[3], idx=idx,
+                       **{n + s: (want[i][k] if n != "v_" or keeps_v else want[i][k].copy())
+                          for i, s in ((0, "img"), (1, "txt")) for k, n in enumerate(("tau_", "m_", "v_"))})
+    # a dozen fp32 operations a step, each rounded once: 2^-24 of what they add up to, which is about 2 at most
+    for side in range(2):
+        for k in range(3):
+            assert np.max(np.abs(got[side][k] - want[side][k])) <= 16 * 2.0 ** -24, (side, k)
