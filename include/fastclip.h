@@ -158,7 +158,8 @@ typedef struct {
                             tiles 64 x 64); 0 on the fp32 path */
   int32_t single_pass;   /* 1: b == B and the similarity matrix is formed once */
   int32_t gathered;      /* 1: the contrast side runs over every global anchor (flag set and b < B) */
-  int32_t fused_state;   /* 1: the state phase runs inside the fold kernel or, with tile 128, the contraction */
+  int32_t fused_state;   /* 1: the state phase runs inside the fold kernel, with tile 128 inside the contraction, on the fp32
+                            path inside the gradients */
   int32_t nsplit;        /* splits of the contraction's column range over workgroups */
   int32_t nparts;        /* partial sums per anchor and quantity that the strip phase leaves to the state phase (one per
                             contrast tile; with tile 128 and gathered state one per two of them) */
@@ -217,7 +218,7 @@ fastclip_status fastclip_normalize_rows(const void* raw, int32_t raw_dtype, int6
 #define FASTCLIP_N_PHASES 8
 #define FASTCLIP_PHASE_PREP 0      /* s_ii and temperature gather (0 where small batches prepare their anchors in the strips) */
 #define FASTCLIP_PHASE_STRIPS 1    /* similarity strips + exp + row sums (Proc. 1) */
-#define FASTCLIP_PHASE_STATE 2     /* Eq. 1 update / scatter, coefficients, scalars (0 where the bf16 path runs it inside a later phase) */
+#define FASTCLIP_PHASE_STATE 2     /* Eq. 1 update / scatter, coefficients, scalars (0 where it runs inside a later phase: on the fp32 path FINALIZE) */
 #define FASTCLIP_PHASE_LOCAL 3     /* bf16 path: contrast-side weights of Eqs. 3/5/7 folded into the stored strips (+ the state phase for small batches); 0 where the small
                                       tiles' contraction takes them as further depth */
 #define FASTCLIP_PHASE_CONTRACT 4  /* gradient contractions of Eqs. 2-7; on the small tiles everything behind the strips that is

@@ -647,7 +647,7 @@ fastclip_status fastclip_describe(const fastclip_config* cfg, fastclip_plan* pla
   plan->tile = !L.bf16 ? 0 : (L.t128 ? 128 : (L.fine ? 64 : 256));
   plan->single_pass = L.square;
   plan->gathered = L.gathered;
-  plan->fused_state = L.fused_state;
+  plan->fused_state = L.fused_state || L.grad_state;
   plan->nsplit = L.nsplit;
   plan->nparts = L.nparts;
   return FASTCLIP_OK;

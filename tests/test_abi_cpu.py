@@ -492,3 +492,22 @@ def test_gathered_state_on_large_tiles_keeps_to_the_static_array(B, b, d):
     cfg = fc.make_config(version=fc.V3, emb_dtype=fc.BF16, B=B, b=b, off=0, d=d, N=1 << 20, gamma=0.5, eps=1e-6, rho=1.0,
                          ld_img=d, ld_txt=d, flags=fc.TILES_256 | fc.GATHERED_STATE)
     assert 0 < fc.fastclip_workspace_bytes(cfg) <= 64 << 20
+
+
+# fp32 batches at the edges of the rule that puts the state phase inside the gradients: (B, b, d, splits, inside)
+F32_STATE_PHASE = [
+    (64, 64, 32, 1, 1), (1024, 128, 512, 2, 1),
+    (448, 448, 132, 1, 1), (449, 449, 132, 1, 1),         # coefficients of a workgroup: 512, one pass of its threads; 576, two
+    (1024, 1024, 72, 1, 1), (1030, 1030, 68, 1, 0),       # of 1024 anchors of the other side, the most; of 1088
+    (576, 576, 404, 1, 1), (577, 577, 404, 1, 0),         # 486 workgroups with those that finish anchors; 514
+    (1896, 948, 20, 4, 1), (1930, 948, 20, 4, 0),         # 24960 partial sums a workgroup; 25792
+    (1024, 1024, 512, 1, 0), (16, 16, 32, 1, 0),          # 64 x 64 tiles; plain loops
+]
+
+
+@pytest.mark.parametrize("B,b,d,nsplit,inside", F32_STATE_PHASE)
+def test_the_plan_says_where_the_fp32_path_runs_its_state_phase(B, b, d, nsplit, inside):
+    """fused_state is 1 where no launch of its own runs the state phase, on the fp32 path inside the gradients."""
+    off = (B - b) // 2
+    p = fc.fastclip_describe(good_cfg(emb_dtype=fc.F32, B=B, b=b, off=off, d=d, ld_img=d, ld_txt=d, N=9000))
+    assert (p["tile"], p["nsplit"], p["fused_state"]) == (0, nsplit, inside), p
