@@ -85,6 +85,11 @@ PLAN_RULES = [
     ("fastclip_api.hip", "((cfg.B + 63) / 64) >= 256 ? 64 : 32;", "((cfg.B + 63) / 64) >= " + _forced("256", "EMU_F32_TILES") + " ? 64 : 32;"),
     ("fastclip_api.hip", "  for (int T = 32; T <= 64; T += 32) {",
      '  for (int T = 32; T <= 64; T += 32) {\n    if (getenv("EMU_GRAD_TILE") && atoi(getenv("EMU_GRAD_TILE")) != T) continue;'),
+    # ... whether its strips prepare the anchors and its gradients run the state phase
+    ("fastclip_api.hip", "L->own_prep = L->strip_tile == 32 && !L->gathered && (!L->square || cfg.d <= 512) && strip_wgs <= 512;",
+     "L->own_prep = L->strip_tile == 32 && !L->gathered && " + _forced("(!L->square || cfg.d <= 512) && strip_wgs <= 512", "EMU_F32_OWN_PREP") + ";"),
+    ("fastclip_api.hip", "    L->grad_state = room.state_rides && L->grad_tile == 32 &&",
+     "    L->grad_state = " + _forced("1", "EMU_GRAD_STATE") + " && room.state_rides && L->grad_tile == 32 &&"),
     ("fastclip_api.hip", "  constexpr int64_t kLimit = FASTCLIP_STATIC_SCRATCH_BYTES;",
      "  const int64_t kLimit = " + _forced("FASTCLIP_STATIC_SCRATCH_BYTES", "EMU_STATIC_BYTES") + ";"),
 ]

@@ -157,6 +157,31 @@ def test_f32_state_phase_inside_the_gradients(B, b, off, d, pad, version):
     test_f32_tiles_at_their_edges(B, b, off, d, pad, version)
 
 
+@pytest.mark.parametrize("B,b,off,d,pad,nsplit,inside,prepares", [
+    # a workgroup's coefficients: those of 512 anchors, one pass of its threads; of 576, two; of 1024 of the other side, the most; of
+    # 1088, too many
+    (448, 448, 0, 132, 0, 1, 1, 1), (449, 449, 0, 132, 4, 1, 1, 1), (1024, 1024, 0, 72, 0, 1, 1, 0), (1030, 1030, 0, 68, 4, 1, 0, 0),
+    # 486 workgroups of the gradients with those that finish anchors, and 514
+    (576, 576, 0, 404, 0, 1, 1, 1), (577, 577, 0, 404, 0, 1, 0, 1),
+    # 24960 partial sums a workgroup, and 25792
+    (1896, 948, 500, 20, 0, 4, 1, 0), (1930, 948, 500, 20, 0, 4, 0, 0),
+    # strips that prepare: rows of 512 with the whole batch local, and wider; 512 workgroups, and with the whole batch local 529;
+    # several contrast tiles behind one partial sum
+    (96, 96, 0, 512, 0, 1, 1, 1), (96, 96, 0, 516, 0, 1, 1, 0), (2048, 128, 900, 36, 0, 9, 1, 1), (736, 736, 0, 40, 0, 2, 1, 0),
+    (2100, 130, 1970, 36, 3, 9, 1, 1)])
+def test_f32_launches_at_the_edges_of_their_rules(B, b, off, d, pad, nsplit, inside, prepares):
+    """The plan, the launches that a timed step saw (a phase that no launch ran takes exactly 0), and the outputs."""
+    version = V2 if B % 4 else V3
+    g = GpuStep(B=B, b=b, off=off, d=d, N=6000, dtype="f32", version=version, eps=1e-6, rho=6.5, tau=0.07, ld_img=d + pad)
+    plan = fc.fastclip_describe(g.config(0.6))
+    assert (plan["tile"], plan["nsplit"], plan["fused_state"]) == (0, nsplit, inside)
+    test_f32_tiles_at_their_edges(B, b, off, d, pad, version)
+    img, txt = make_embeddings(B + 3, B, d, 0.5, "f32")
+    g.set_inputs(img, txt, draw_indices(B + 4, b, 6000))
+    phases = g.step(0.6, timed=True)
+    assert [phases[k] > 0.0 for k in ("prep", "strips", "state", "finalize")] == [not prepares, True, not inside, True], phases
+
+
 @pytest.mark.parametrize("version", [V0, V2])
 def test_f32_gathered_state_on_several_tiles(version):
     run_gathered(300, 130, 170, 72, version, "f32", TOL_F32)

@@ -87,6 +87,7 @@ def run_case(exe, tmp_path, *, B, b, off, d, version, dtype="bf16", flags=0, ld_
     if SANITIZER == "memory":
         env["EMU_UNINIT"] = "1"
     r = subprocess.run([exe, fin, fout], capture_output=True, text=True, timeout=600, env=env)
+    (tmp_path / "case.err").write_text(r.stderr)
     assert r.returncode == 0 and "Sanitizer" not in r.stderr, \
         "the CPU build of the kernels failed (sanitizer report below)\n" + r.stderr[:6000]
     out = np.fromfile(fout, np.float32)
@@ -488,3 +489,45 @@ def test_temperature_update_with_arrays_that_both_sides_share(emu_step, tmp_path
     for side in range(2):
         for k in range(3):
             assert np.max(np.abs(got[side][k] - want[side][k])) <= 16 * 2.0 ** -24, (side, k)
+
+
+# ------------------------------------------------------------------ which kernels a plan launches
+def launches_of(tmp_path):
+    """(workgroups, threads) of every launch of the step that run_case has run."""
+    return [(int(w), int(t)) for w, t in re.findall(r"workgroups (\d+) threads (\d+)", (tmp_path / "case.err").read_text())]
+
+
+@pytest.mark.parametrize("case,prep,state", [
+    # the whole batch local, ragged tiles; two strips, rows that begin inside the batch, several splits of the gradients
+    (dict(B=40, b=40, off=0, d=20, version=V3), 0, 0),
+    (dict(plan=dict(F32_OWN_PREP=0), B=40, b=40, off=0, d=20, version=V3), 1, 0),
+    (dict(plan=dict(GRAD_STATE=0), B=40, b=40, off=0, d=20, version=V2), 0, 1),
+    (dict(plan=dict(F32_OWN_PREP=0, GRAD_STATE=0), B=40, b=40, off=0, d=20, version=V0), 1, 1),
+    (dict(plan=dict(NSPLIT=2, F32_OWN_PREP=0), B=70, b=36, off=33, d=20, version=V0), 1, 0),
+    (dict(plan=dict(NSPLIT=2, GRAD_STATE=0), B=70, b=36, off=33, d=20, ld_img=23, version=V3), 0, 1),
+    # wide rows of a whole local batch, which the rule leaves to the launch before the strips
+    (dict(B=28, b=28, off=0, d=516, version=V2), 1, 0),
+    (dict(plan=dict(F32_OWN_PREP=1), B=28, b=28, off=0, d=516, ld_img=519, version=V2), 0, 0),
+    # gathered state is prepared by the launch before, whose gradients run the state phase all the same
+    (dict(B=60, b=20, off=11, d=20, version=V2, gathered=True), 1, 0),
+    (dict(plan=dict(GRAD_STATE=0), B=60, b=20, off=11, d=20, version=V2, gathered=True), 1, 1),
+], ids=lambda c: "-".join("%s%s" % (k, v) for k, v in c.items()) if isinstance(c, dict) else "")
+def test_f32_launches_with_and_without_prep_and_state_phase(emu_step, tmp_path, monkeypatch, case, prep, state):
+    """The fp32 path's strips prepare their anchors and its gradients run the state phase, or launches of 256 threads before and
+    between them do: the launches are those that the plan promises, and the outputs the oracle's either way."""
+    for k, v in case.get("plan", {}).items():
+        monkeypatch.setenv("EMU_" + k, str(v))
+    run_case(emu_step, tmp_path, dtype="f32", **{k: v for k, v in case.items() if k != "plan"})
+    threads = [t for _, t in launches_of(tmp_path)]
+    assert threads == [256] * prep + [512] + [256] * state + [512], threads
+
+
+@pytest.mark.parametrize("plan,anchors", [({}, 32), (dict(FEW=0), 64), (dict(FEW=0, NARROW=0), 128)])
+def test_anchors_of_a_small_strip_tile(emu_step, tmp_path, monkeypatch, plan, anchors):
+    """Strips of the small tiles, the launch before the contraction: two contrast tiles, 130 anchors in tiles of 32 (one round of
+    workgroups, the library's own choice here), 64 and 128, two strips."""
+    for k, v in plan.items():
+        monkeypatch.setenv("EMU_" + k, str(v))
+    run_case(emu_step, tmp_path, B=200, b=130, off=33, d=40, version=V3)
+    launches = launches_of(tmp_path)
+    assert launches[0] == (2 * 2 * -(-130 // anchors), 512), launches
