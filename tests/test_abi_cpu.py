@@ -511,3 +511,23 @@ def test_the_plan_says_where_the_fp32_path_runs_its_state_phase(B, b, d, nsplit,
     off = (B - b) // 2
     p = fc.fastclip_describe(good_cfg(emb_dtype=fc.F32, B=B, b=b, off=off, d=d, ld_img=d, ld_txt=d, N=9000))
     assert (p["tile"], p["nsplit"], p["fused_state"]) == (0, nsplit, inside), p
+
+
+def test_current_stream_by_the_raw_lookup_and_without_it(monkeypatch):
+    """A call without a stream takes torch's current one: by torch's raw lookup where the GPU is in use and torch has it, else as
+    torch.cuda.current_stream() gives it, which also initialises the GPU."""
+    torch = pytest.importorskip("torch")
+    asked = []
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: asked.append(device) or 0x1230, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("Stream", (), {"cuda_stream": 0x4560})())
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    assert fc._stream(None) == 0x1230 and asked == [3]
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: False)
+    assert fc._stream(None) == 0x4560
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    for name in ("_cuda_getDevice", "_cuda_getCurrentRawStream"):
+        with monkeypatch.context() as without:
+            without.delattr(torch._C, name)
+            assert fc._stream(None) == 0x4560
+    assert asked == [3] and fc._stream(0) == 0 and fc._stream(None) == 0x1230
