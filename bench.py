@@ -375,7 +375,7 @@ def main():
                                 "kind": "k_mfma_ceiling: independent 32x32x16 bf16 MFMAs on pseudo-random register operands"}
     # what the two MFMA kernels execute: whole tiles, two strips unless the whole batch is local in whole tiles on more
     # tiles than compute units (one similarity pass), two contractions over the padded column range.  Small tiles: 64 anchors
-    # by 128 contrasts (128 anchors pad the same at the workloads' sizes), output tiles of 64 columns, and the local
+    # by 128 contrasts (32 and 128 anchors pad the same at the workloads' sizes), output tiles of 64 columns, and the local
     # anchors' contrast-side term as further depth of the contraction instead of a pass over the strips before it.
     # Output tiles of the large tiles have 256 or 192 columns, whichever the plan takes: products of a last one beyond the
     # width in whole 64s are not counted (none where the columns divide the width).

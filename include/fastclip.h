@@ -81,9 +81,9 @@ typedef enum { FASTCLIP_F32 = 0, FASTCLIP_BF16 = 1 } fastclip_dtype;
 #define FASTCLIP_SINGLE_PASS 4
 /* Tile size of the bf16 path.  By default the library chooses: batches whose 256 x 256 strip tiles would occupy at most
  * half of the compute units (2 ceil(b/256) ceil(B/256) <= 128; not in the single-pass form) run the strip phase on tiles
- * of 64 or 128 anchors by 128 contrasts (with gathered state pairs of them, 256 contrasts) and everything behind it in one
- * kernel on 64 x 64 or 128 x 64 output tiles or, where those would need a second round of workgroups (wide rows), the
- * contraction on 128 x 128 output tiles; everything else runs on 256 x 256 tiles, and so do batches with gathered state
+ * of 32, 64 or 128 anchors by 128 contrasts (with gathered state 64 or 128 by pairs of them, 256 contrasts) and everything
+ * behind it in one kernel on 32 x 32, 64 x 64 or 128 x 64 output tiles or, where those would need a second round of
+ * workgroups (wide rows), the contraction on 128 x 128 output tiles; everything else runs on 256 x 256 tiles, and so do batches with gathered state
  * whose rows are so wide that those take less time.  FASTCLIP_TILES_128 asks for the small tiles wherever they apply (up
  * to 191 large tiles; not those gathered batches), FASTCLIP_TILES_256 for the large ones always; both together are an
  * error.  Same results up to summation order. */
@@ -154,7 +154,7 @@ size_t fastclip_workspace_bytes(const fastclip_config* cfg);
  * benchmark's labels; nothing in it has to be passed back. */
 typedef struct {
   int32_t tile;          /* the kernels of the bf16 path: 256 those of 256 x 256 tiles, 128 those of the small tiles (strip tiles
-                            of 64 or 128 anchors by 128 contrasts), 64 FASTCLIP_FINE_TILES (strip tiles 128 x 128, output
+                            of 32, 64 or 128 anchors by 128 contrasts), 64 FASTCLIP_FINE_TILES (strip tiles 128 x 128, output
                             tiles 64 x 64); 0 on the fp32 path */
   int32_t single_pass;   /* 1: b == B and the similarity matrix is formed once */
   int32_t gathered;      /* 1: the contrast side runs over every global anchor (flag set and b < B) */

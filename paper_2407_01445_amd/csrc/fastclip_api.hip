@@ -408,8 +408,8 @@ static void make_layout(const fastclip_config& cfg, const Room& room, Layout* L)
     // those that finish the anchors (behind 512 others they would come last), and where a workgroup forms the coefficients of at
     // most 1024 of the other side's anchors, those of its slice, from at most 25000 partial sums.  Steps with k_state / so, us: 64 pairs at width 32 18.5 / 15.2,
     // 128 of 128 at 512 26.5 / 22.8, 448 of 448 at 512 (462 workgroups) 37.6 / 33.5, 1024 of 1024 at 64 37.1 / 35.0, 128 of 1024 at
-    // 512 34.1 / 30.0; with more than 512 workgroups 512 of 512 at 512 37.2 / 38.5, 768 of 768 at 512 69.1 / 72.4; with 35000 and 67000 partial
-    // sums (800 of 800 at 96, 21600: 44.3 / 42.6) 1024 of 2048 at 64 68.2 / 69.6, 1000 of 4000 at 128 153 / 158.
+    // 512 34.1 / 30.0; with more than 512 workgroups 512 of 512 at 512 37.2 / 38.5, 768 of 768 at 512 69.1 / 72.4; with 34816 and 68544 partial
+    // sums (800 of 800 at 96, 22400: 44.3 / 42.6) 1024 of 2048 at 64 68.2 / 69.6, 1000 of 4000 at 128 153 / 158.
     const int64_t of_slice = L->square ? L->kslice * 64 : (L->kslice * 64 < cfg.b + 63 ? L->kslice * 64 : (cfg.b + 63) / 64 * 64);
     const int64_t tiles = 2 * ((cfg.b + 31) / 32) * ((cfg.d + 31) / 32), finishers = 2 * ((cfg.b + 63) / 64);
     L->grad_state = room.state_rides && L->grad_tile == 32 && of_slice <= kGradAnchors && (of_slice + 64) * L->nparts <= 25000 &&

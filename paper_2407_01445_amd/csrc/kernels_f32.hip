@@ -16,6 +16,8 @@
 //                                        strips                gradients
 //   128 of 1024 pairs, d = 512, v3      417 ->  12.3 us       398 ->  14.6 us    (0.27 GFLOP each: 4 us at the fp64 rate)
 //   1024 pairs, d = 512, v2             996 ->  28 us        1757 ->  46.6 us    (1.07 and 2.15 GFLOP: 14 and 28 us)
+// (These two phases alone.  Where the strips prepare their anchors and the gradients run the state phase, as at 128 of 1024, the
+// launches take 13.4 and 16.0 us and are the step's only ones.)
 // When the whole batch is local (b == B) the text strip is the transpose of the image strip, so only one is formed and
 // both sides' weights come from it.
 //
@@ -440,7 +442,7 @@ struct GradF32Args {
   int64_t ldE, b, d, off;
   int tiles_m, tiles_n, nsplit, slice;     // stages per split
   double* part;                            // nsplit > 1: [nsplit][2][tiles][T * T]
-  unsigned* arrived;                       // nsplit > 1: [2][tiles], zeroed by the prep kernel
+  unsigned* arrived;                       // nsplit > 1: [2][tiles], zeroed by the prep kernel or the strips that take its place
   const float* dcoef;
   const double* red; int nred; int version; const float* tau; float rho; float* loss; float* d_tau;
   unsigned* scalars_arrived;               // STATE: 0 before the launch

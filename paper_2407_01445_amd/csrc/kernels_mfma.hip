@@ -707,8 +707,8 @@ static void make_strip_args(const StepCtx& c, StripArgs* out, bool* any_interior
 // A 64 x 64 window of a strip (rows row0 .., columns col0 ..) is read as whole 16-byte fragment chunks and laid out
 // as tile[row][column] in LDS; col0 need not be a multiple of 16, so up to 5 column blocks are touched, ten chunks a row,
 // of which a thread takes two or three.  All of them, of both windows, are requested before the first is used: what bounds this
-// kernel on a small batch is latency, and one after the other they were six trips to memory (1024 local anchors: 9.2 us a
-// launch, now 7.6).  A chunk that does not exist is fetched as one that does.
+// kernel on a small batch is latency, and one after the other they were six trips to memory (1024 local anchors: 8.6 us a
+// launch, now 7.3).  A chunk that does not exist is fetched as one that does.
 struct FoldChunks { uint4 raw[3]; };
 __device__ __forceinline__ void fold_load(const bf16_t* __restrict__ E, int64_t nCB, int64_t row0, int64_t col0, int64_t rows,
                                           FoldChunks& c) {
