@@ -381,6 +381,8 @@ def test_bf16_single_similarity_pass_on_any_shape(B, b, d, version):
 
 
 @pytest.mark.parametrize("B,b,d", [
+    # (The weights are two strips, w / c of either side, and each is read by rows.  The shapes are those at which one strip read both
+    # ways could go wrong:)
     # one strip of weights read by rows and by columns: columns of a tile of rows that the strip does not have, a last stage of one
     # row, several splits, output tiles of either width
     (257, 257, 8), (320, 320, 200), (449, 449, 264), (1217, 1217, 136), (2300, 2300, 72)])
